@@ -1741,6 +1741,7 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, int *
         nq->nbr[i].v = (int8_t)pr.nbr[i].v;
         nq->nbr[i].dir = (int8_t)pr.nbr[i].dir;
         nq->nbr[i].mode = (int8_t)pr.nbr[i].mode;
+        nq->nbr[i].e = (int8_t)pr.nbr[i].e;
         nq->nbr[i].rel = pr.nbr[i].rel;
     }
     *pl_out = pl;

@@ -24,7 +24,7 @@ struct NNbr {
     int8_t v;     // the other query vertex
     int8_t dir;   // 0: out-edges of the candidate, 1: in-edges
     int8_t mode;  // 0: test v's bitmap; 1: test v's predicate
-    int8_t pad;
+    int8_t e;     // the query edge tested
     int32_t rel;  // -1: any
 };
 

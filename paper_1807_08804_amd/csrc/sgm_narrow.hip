@@ -82,6 +82,13 @@ struct Smem {
     int8_t qsrc[SGM_MAX_QE], qdst[SGM_MAX_QE];  // the query's edges, staged for join_order
     uint64_t revmask;
     NNbr nbl[SGM_MAX_QE];  // neighbours a step still tests per candidate
+    // What filtering has established so far. ver[v] counts the changes of
+    // C(v); okv[2 e + s] is the version of one endpoint's candidates for
+    // which every candidate of the other (s = 0: the source of query edge e,
+    // 1: its destination) is known to have a matching neighbour, or -1.
+    int32_t ver[SGM_MAX_QV];
+    int32_t okv[2 * SGM_MAX_QE];
+    int32_t skippar;  // the step's test against its parent is known to hold
     int32_t removed;
     int32_t ctr;
     int32_t empty;
@@ -1159,15 +1166,28 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
     // The step's neighbour tests go to LDS. In prune-only steps over many
     // candidates, a neighbour with few candidates whose rows together are
     // shorter than u's list is instead checked from its side (prune_reverse).
+    // A test known to hold is left out: every candidate of u was found (or
+    // pushed) with a matching neighbour in C(v), C(v) has not changed since
+    // and C(u) only shrinks. Refinement repeats the tree edges that the
+    // exploration has just established, so a query whose candidates are down
+    // to a few runs hardly any of its refine steps. An explore step's test
+    // against a parent with a single candidate goes too: what it would push
+    // is that candidate, as long as any candidate of u survives.
     const bool try_rev = !st.push && n_items >= kRevMin;
     if (threadIdx.x < 64) {
         const NNbr *src = c.Q->nbr + st.first;
         int k = 0;
         uint64_t rm = 0;
+        bool skippar = false;
         for (int j = 0; j < st.count; ++j) {
-            const int v = src[j].v, dir = src[j].dir, mode = src[j].mode;
+            const int v = src[j].v, dir = src[j].dir, mode = src[j].mode, e = src[j].e;
             const int32_t rel = src[j].rel;
             bool rev = false;
+            if (mode == 0 && c.s->okv[2 * e + dir] == c.s->ver[v] &&
+                (!st.push || c.s->cnt[v] == 1)) {
+                skippar |= st.push != 0;
+                continue;
+            }
             const int32_t nv = c.s->cnt[v];
             if (try_rev && mode == 0 && nv <= kRevMaxCand && nv < n_items) {
                 // reverse cost: v's list plus its rows, against at least one
@@ -1203,11 +1223,13 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         if (threadIdx.x == 0) {
             c.s->revmask = rm;
             c.s->nnbl = k;
+            c.s->skippar = skippar;
         }
     }
     __syncthreads();
     const NNbr *nb = c.s->nbl;
     const int ncount = c.s->nnbl;
+    const int par = c.s->skippar ? -1 : st.parent;  // parent this step's marks intersect
     const uint64_t rm = c.s->revmask;
     const bool revd = rm != 0;
     for (int j = 0; j < st.count && revd; ++j)
@@ -1216,7 +1238,7 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
             prune_reverse(c, u, d->v, d->dir, d->rel, fb);
         }
     if (ncount == 0) {
-        // every test was done from the other side
+        // every test was known to hold or done from the other side
     } else if (n_items <= NW) {
         int32_t *def = defer_list(c, st);
         for (int32_t it = 0; it < n_items; ++it) item_wg(c, st, nb, ncount, ul[it], ub, fb, def);
@@ -1285,16 +1307,23 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
     }
     add_bytes_wave(c, fb);
     __syncthreads();
-    if (c.s->removed) compact_list(c, u);
-    if (st.parent >= 0 && 4 * c.s->nmarks < c.s->cnt[st.parent]) {
+    const bool shrunk = c.s->removed != 0;
+    if (shrunk) compact_list(c, u);
+    bool pshrunk = false;  // the parent lost candidates
+    if (par >= 0 && c.s->nmarks == c.s->cnt[par]) {
+        // every candidate of the parent was pushed: only the marks go
+        const int32_t nm = c.s->nmarks;
+        for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[c.marks[i] >> 6] = 0ull;
+        if (threadIdx.x == 0) add_bytes(c, 12ull * nm);
+        __syncthreads();
+    } else if (par >= 0 && 4 * c.s->nmarks < c.s->cnt[par]) {
         // Intersect the parent's candidates with the pushed marks. The marks
         // are parent candidates, so the intersection is the marks
         // themselves: with few of them, clear the parent's old words and
         // rebuild its bitmap and list from the marks.
-        const int p = st.parent;
-        uint64_t *pb = c.B(p);
-        int32_t *pl = c.L(p);
-        const int32_t n = c.s->cnt[p], nm = c.s->nmarks;
+        uint64_t *pb = c.B(par);
+        int32_t *pl = c.L(par);
+        const int32_t n = c.s->cnt[par], nm = c.s->nmarks;
         for (int32_t i = threadIdx.x; i < n; i += NT) pb[pl[i] >> 6] = 0ull;
         __syncthreads();
         for (int32_t i = threadIdx.x; i < nm; i += NT) {
@@ -1305,16 +1334,16 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         __syncthreads();
         for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[pl[i] >> 6] = 0ull;
         if (threadIdx.x == 0) {
-            c.s->cnt[p] = nm;
+            c.s->cnt[par] = nm;
             add_bytes(c, 12ull * n + 24ull * nm);
         }
+        pshrunk = true;
         __syncthreads();
-    } else if (st.parent >= 0) {
+    } else if (par >= 0) {
         // intersect the parent's candidates with the pushed scratch bitmap
-        const int p = st.parent;
-        uint64_t *pb = c.B(p);
-        const int32_t *pl = c.L(p);
-        const int32_t n = c.s->cnt[p];
+        uint64_t *pb = c.B(par);
+        const int32_t *pl = c.L(par);
+        const int32_t n = c.s->cnt[par];
         for (int32_t i = threadIdx.x; i < n; i += NT) {
             const int32_t x = pl[i];
             if (!bit_test(c.scratch, x))
@@ -1324,9 +1353,38 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         // scratch only holds parent candidates: zero their words
         for (int32_t i = threadIdx.x; i < n; i += NT) c.scratch[pl[i] >> 6] = 0ull;
         if (threadIdx.x == 0) add_bytes(c, 28ull * n);
+        pshrunk = true;
         __syncthreads();
-        compact_list(c, p);
+        compact_list(c, par);
+    } else if (c.s->skippar && c.s->cnt[u] == 0) {
+        // no candidate left to push the parent's single one
+        const int p = st.parent;
+        if (threadIdx.x == 0) {
+            c.B(p)[c.L(p)[0] >> 6] = 0ull;
+            c.s->cnt[p] = 0;
+        }
+        pshrunk = true;
+        __syncthreads();
     }
+    if (threadIdx.x < 64) {
+        // what the step established: each test for all of C(u), and after an
+        // explore step the other way round too (the children's and the
+        // parent's candidates are the neighbours its survivors pushed)
+        if (threadIdx.x == 0) {
+            if (shrunk) ++c.s->ver[u];
+            if (pshrunk) ++c.s->ver[st.parent];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if ((int)threadIdx.x < st.count) {
+            const NNbr &d = c.Q->nbr[st.first + threadIdx.x];
+            const int e = d.e, dir = d.dir;
+            c.s->okv[2 * e + dir] = c.s->ver[d.v];
+            if (st.push) c.s->okv[2 * e + 1 - dir] = c.s->ver[u];
+        }
+    }
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -2345,6 +2403,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
         s.level_rows[threadIdx.x] = 0;
         s.jorder[threadIdx.x] = -1;
     }
+    if (threadIdx.x < SGM_MAX_QV) s.ver[threadIdx.x] = 0;
+    if (threadIdx.x < 2 * SGM_MAX_QE) s.okv[threadIdx.x] = -1;
     if (threadIdx.x < SGM_MAX_QE) {
         s.ectot[threadIdx.x] = 0;
         s.qsrc[threadIdx.x] = threadIdx.x < Q.m ? (int8_t)Q.esrc[threadIdx.x] : 0;

@@ -199,6 +199,7 @@ void build_program(const QInfo &qi, const Plan &pl, int low_conn_degree, int ref
             d.dir = qi.esrc[e] == u ? 0 : 1;
             d.rel = qi.elabel[e];
             d.mode = initialized[v] ? 0 : 1;
+            d.e = e;
             if (initialized[v]) s.parent = v;
             pr->nbr.push_back(d);
         };
@@ -228,6 +229,7 @@ void build_program(const QInfo &qi, const Plan &pl, int low_conn_degree, int ref
             if (qi.deg[d.v] <= low_conn_degree) continue;
             d.rel = qi.elabel[e];
             d.mode = 0;
+            d.e = e;
             pr->nbr.push_back(d);
         }
         s.count = (int)pr->nbr.size() - s.first;

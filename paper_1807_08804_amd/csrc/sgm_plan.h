@@ -52,7 +52,8 @@ struct PStep {
     int sweep;  // 1: u starts from every vertex its predicate admits (out-only graph)
 };
 struct PNbr {
-    int v, dir, rel, mode;  // dir 0: out-edges of the candidate; mode 0: bitmap test
+    // dir 0: out-edges of the candidate; mode 0: bitmap test; e: query edge
+    int v, dir, rel, mode, e;
 };
 // A vector of at most N elements stored in place (planning allocates no
 // memory, so the entry point that allocates nothing can plan too).
