@@ -233,6 +233,7 @@ struct sgm_graph {
     // device memory owned by the graph
     int32_t *d_out_off = nullptr, *d_in_off = nullptr;
     int2 *d_vinfo = nullptr;
+    int4 *d_vrow = nullptr;
     int2 *d_out_adj = nullptr, *d_in_adj = nullptr;
     int2 *d_out_ta = nullptr, *d_out_tb = nullptr, *d_in_ta = nullptr, *d_in_tb = nullptr;
     int32_t *d_hub_of = nullptr, *d_hub_toff = nullptr;
@@ -429,7 +430,8 @@ void free_graph_mem(sgm_graph *g) {
     void *dp[] = {g->d_out_off, g->d_in_off, g->d_vinfo,  g->d_out_adj, g->d_in_adj,
                   g->d_bits,    g->d_lists,  g->d_prefix, g->d_big,     g->d_desc,
                   g->d_cnt,     g->d_slots,  g->d_out_ta, g->d_out_tb,  g->d_in_ta,
-                  g->d_in_tb,   g->d_hub_of, g->d_hub_toff, g->d_map_off, g->d_map_ids};
+                  g->d_in_tb,   g->d_hub_of, g->d_hub_toff, g->d_map_off, g->d_map_ids,
+                  g->d_vrow};
     for (void *p : dp) {
         bool host = false;
         for (const auto &b : g->host_graph_bufs) host |= b.second == p;
@@ -999,6 +1001,7 @@ struct Query {
         d.key_vertex = t.key;
         d.dir = t.dir;
         d.rel = qi.elabel[e];
+        d.other_label = qi.label[t.other];
         d.keys = list(t.key);
         d.key_count = cand_count_dev(t.key);
         d.other_bits = bits(t.other);
@@ -2453,6 +2456,16 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
     g->n_rels = maxr + 1;
     g->rel_freq.assign((size_t)g->n_rels, 0);
     for (const int2 &e : adj) g->rel_freq[e.y]++;
+    // entries carry the type of their vertex above the relation (DevGraph)
+    g->dg.typed_adj = g->n_types <= (1 << 15) && g->n_rels < (1 << 16);
+    g->dg.rel_mask = g->dg.typed_adj ? 0xffff : -1;
+    if (g->dg.typed_adj)
+        for (std::vector<int2> *a : {&adj, &in_adj}) {
+            int2 *p = a->data();
+            parallel_for((int)a->size(), 1 << 18, [&](int lo, int hi) {
+                for (int i = lo; i < hi; ++i) p[i].y |= type[p[i].x] << 16;
+            });
+        }
     int nbig = 0;
     for (int32_t v = 0; v < n_vertices; ++v) {
         const int32_t od = off[v + 1] - off[v], id = in_off[v + 1] - in_off[v];
@@ -2492,6 +2505,12 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             vi[v] = make_int2(type[v], std::min(od, 255) | std::min(id, 255) << 8);
         }
         g->d_vinfo = dev_upload(vi);
+        {
+            std::vector<int4> vr((size_t)n_vertices);
+            for (int32_t v = 0; v < n_vertices; ++v)
+                vr[v] = make_int4(off[v], off[v + 1], in_off[v], in_off[v + 1]);
+            g->d_vrow = dev_upload(vr);
+        }
         if (g->n_types <= kHubTypesMax) {
             HubIndex hx;
             build_hub_index(n_vertices, off, adj, in_off, in_adj, type, g->n_types, &hx);
@@ -2521,6 +2540,7 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
         g->dg.out_adj = g->d_out_adj;
         g->dg.in_adj = g->d_in_adj;
         g->dg.vinfo = g->d_vinfo;
+        g->dg.vrow = g->d_vrow;
         g->dg.out_ta = g->d_out_ta;
         g->dg.out_tb = g->d_out_tb;
         g->dg.in_ta = g->d_in_ta;

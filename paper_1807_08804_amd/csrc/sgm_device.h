@@ -12,6 +12,15 @@ __device__ __forceinline__ bool bit_test(const uint64_t *bits, int32_t x) {
     return (bits[x >> 6] >> (x & 63)) & 1ull;
 }
 
+// Does an adjacency entry carry relation rel (-1: any), and can its vertex
+// have type `label` (-1: any; without types in the entries: always)?
+__device__ __forceinline__ bool adj_rel_ok(const DevGraph &g, int2 e, int32_t rel) {
+    return rel < 0 || (e.y & g.rel_mask) == rel;
+}
+__device__ __forceinline__ bool adj_type_ok(const DevGraph &g, int2 e, int32_t label) {
+    return !g.typed_adj || label < 0 || (e.y >> 16) == label;
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (1ull << lane) - 1ull; }
 
 // Candidate predicate (Def. 3.3 + pin + incoming degree).

@@ -27,6 +27,17 @@ struct DevGraph {
     const int32_t *in_off;   // [V+1]
     const int2 *out_adj;     // [E]
     const int2 *in_adj;      // [E]
+    // [V] both row extents of a vertex in one 16-byte word (x, y: out_off[v],
+    // out_off[v + 1]; z, w: the same of in_off): a candidate's rows cost one
+    // memory sector instead of two or three
+    const int4 *vrow;
+    // An adjacency entry's second word is its relation (y & rel_mask) and,
+    // with typed_adj, the type of the entry's vertex above it (y >> 16), so
+    // that a test against a typed query vertex reads no memory for the
+    // entries of other types. typed_adj = 0 (rel_mask all ones) for graphs
+    // with more types or relations than 15 and 16 bits hold.
+    int32_t rel_mask;
+    int32_t typed_adj;
     // [V] per-vertex predicate inputs in one 8-byte word: x = type,
     // y = min(out-degree, 255) | min(in-degree, 255) << 8 (a query vertex has
     // at most 15 distinct neighbours per direction, so the clamp is exact)
@@ -88,6 +99,7 @@ struct ECDesc {
     int32_t key_vertex;       // query vertex whose candidates are the keys
     int32_t dir;              // 0: scan out-edges of keys; 1: in-edges
     int32_t rel;              // -1: any relation (distinct pairs)
+    int32_t other_label;      // type of the other endpoint, -1: any
     const int32_t *keys;      // candidate list of key_vertex
     const int32_t *key_count; // device count
     const uint64_t *other_bits;  // candidate bitmap of the other endpoint

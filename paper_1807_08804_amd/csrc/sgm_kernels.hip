@@ -26,7 +26,7 @@ __device__ __forceinline__ void bit_set_atomic(uint64_t *bits, int32_t x) {
 }
 
 __device__ __forceinline__ bool nbr_ok(const DevGraph &g, const NbrDesc &d, int2 e) {
-    if (d.rel >= 0 && e.y != d.rel) return false;
+    if (!adj_rel_ok(g, e, d.rel) || !adj_type_ok(g, e, d.pred.label)) return false;
     return d.mode == 0 ? bit_test(d.test_bits, e.x) : vpred(g, d.pred, e.x);
 }
 
@@ -248,11 +248,12 @@ __global__ __launch_bounds__(kBlock) void k_and(uint64_t *dst, const uint64_t *s
 // offsets), keyed by the candidates of one endpoint (Sec. "Joining Phase")
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool ec_hit(const ECDesc &d, const int2 *adj, int32_t beg, int32_t i,
-                                       int32_t key) {
+__device__ __forceinline__ bool ec_hit(const DevGraph &g, const ECDesc &d, const int2 *adj,
+                                       int32_t beg, int32_t i, int32_t key) {
     const int2 e = adj[i];
+    if (!adj_type_ok(g, e, d.other_label)) return false;
     if (d.rel >= 0) {
-        if (e.y != d.rel) return false;
+        if (!adj_rel_ok(g, e, d.rel)) return false;
     } else if (i > beg && adj[i - 1].x == e.x) {
         return false;  // same neighbour under another relation: one pair
     }
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(kBlock) void k_ec_small(DevGraph g, ECDesc d) {
         int32_t c = WRITE ? d.offs[it] : 0;
         for (int32_t base = beg; base < end; base += G) {
             const int32_t i = base + gl;
-            const bool hit = i < end && ec_hit(d, adj, beg, i, key);
+            const bool hit = i < end && ec_hit(g, d, adj, beg, i, key);
             const uint64_t b = __ballot(hit) & gmask;
             if (WRITE && hit) d.vals[c + __popcll(b & lanemask_lt(lane))] = adj[i].x;
             c += __popcll(b);
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void k_ec_big(DevGraph g, ECDesc d) {
         int32_t c = WRITE ? d.offs[it] : 0;
         for (int32_t base = beg; base < end; base += blockDim.x) {
             const int32_t i = base + threadIdx.x;
-            const bool hit = i < end && ec_hit(d, adj, beg, i, key);
+            const bool hit = i < end && ec_hit(g, d, adj, beg, i, key);
             const uint64_t b = __ballot(hit);
             if (lane == 0) wcnt[wid] = __popcll(b);
             __syncthreads();
@@ -824,7 +825,7 @@ __device__ __forceinline__ bool has_edge(const DevGraph &g, int32_t s, int32_t t
     for (int32_t i = lo; i < g.out_off[s + 1]; ++i) {
         const int2 e = g.out_adj[i];
         if (e.x != t) return false;
-        if (rel < 0 || e.y == rel) return true;
+        if (adj_rel_ok(g, e, rel)) return true;
     }
     return false;
 }

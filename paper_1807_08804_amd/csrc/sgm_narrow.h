@@ -28,6 +28,16 @@ struct NNbr {
     int32_t rel;  // -1: any
 };
 
+// A neighbour test as a filter step holds it: NNbr with the predicate of v.
+// mode 2: the entry's relation and type (and pin) decide alone, since the
+// edge to it already gives the vertex the degree that v asks for.
+struct NTest {
+    int8_t v, dir, mode, e;
+    int32_t rel;
+    int32_t label, pin;  // of v; -1: any, none
+    int32_t qdeg;        // least out-degree | least in-degree << 8
+};
+
 constexpr int kNMaxSteps = 2 * SGM_MAX_QV;
 constexpr int kNMaxNbr = 2 * SGM_MAX_QE + 2 * SGM_MAX_QV;
 
@@ -131,6 +141,7 @@ struct EcJob {
     const uint64_t *ob;
     const int32_t *ol, *items;
     int32_t nk, rel, dir, no, tier;
+    int32_t olabel;  // type of the other endpoint, -1: any
     int32_t homo;  // 1: a key may pair with itself (a compressed graph)
 };
 
@@ -155,7 +166,7 @@ struct HelpJob {
     // up to wg_rows entries (longer ones go on to the workgroup tier)
     int32_t nodefer;
     int32_t cnt[SGM_MAX_QV];
-    NNbr nbl[SGM_MAX_QE];
+    NTest nbl[SGM_MAX_QE];
     // kind 2: chunks of a join level's parent rows; jrows counts the output
     // rows placed so far (kind 3: the table entries written so far)
     unsigned long long jrows;

@@ -81,7 +81,7 @@ struct Smem {
     int32_t hq, hch;            // helper: board entry and chunk claimed (-1: none)
     int8_t qsrc[SGM_MAX_QE], qdst[SGM_MAX_QE];  // the query's edges, staged for join_order
     uint64_t revmask;
-    NNbr nbl[SGM_MAX_QE];  // neighbours a step still tests per candidate
+    NTest nbl[SGM_MAX_QE];  // neighbours a step still tests per candidate
     // What filtering has established so far. ver[v] counts the changes of
     // C(v); okv[2 e + s] is the version of one endpoint's candidates for
     // which every candidate of the other (s = 0: the source of query edge e,
@@ -110,12 +110,12 @@ struct Smem {
     unsigned long long pb[5];  // bytes at the phase boundaries
 };
 
-// Dynamic LDS, 51 KB: with the static part a workgroup stays within 64 KB,
+// Dynamic LDS, 46 KB: with the static part a workgroup stays within 64 KB,
 // and two workgroups per CU remain resident (registers allow no more). List
 // sorting uses [0, 32 KB); the final ordering keeps keys and indices
 // (bitonic) or digit counts (radix) in [0, 24 KB) and stages the candidate
-// lists its keys rank into at [24 KB, 51 KB).
-constexpr size_t kDynLds = 51 << 10;
+// lists its keys rank into at [24 KB, 46 KB).
+constexpr size_t kDynLds = 46 << 10;
 constexpr size_t kStageOff = 24 << 10;
 constexpr int32_t kStageInts = (int32_t)((kDynLds - kStageOff) / sizeof(int32_t));
 static_assert(sizeof(int32_t) * kListSortCap <= kDynLds, "list sort space");
@@ -310,9 +310,14 @@ __device__ __forceinline__ int2 adj_at(const int2 *adj, int32_t i, int32_t end) 
     return i < end ? adj[i] : make_int2(0, -1);
 }
 
-__device__ __forceinline__ bool nbr_hit(const Ctx &c, const NNbr &d, int2 e) {
-    if (d.rel >= 0 && e.y != d.rel) return false;
-    return d.mode == 0 ? bit_test(c.B(d.v), e.x) : vpred(c.g, c.Q->pred[d.v], e.x);
+__device__ __forceinline__ bool nbr_hit(const Ctx &c, const NTest &d, int2 e) {
+    if (!adj_rel_ok(c.g, e, d.rel) || !adj_type_ok(c.g, e, d.label)) return false;
+    if (d.pin >= 0 && e.x != d.pin) return false;
+    if (d.mode == 0) return bit_test(c.B(d.v), e.x);
+    if (d.mode == 2) return true;
+    const int2 vi = c.g.vinfo[e.x];
+    return (d.label < 0 || vi.x == d.label) && (vi.y & 255) >= (d.qdeg & 255) &&
+           (vi.y >> 8) >= (d.qdeg >> 8);
 }
 
 // Keep only the list entries whose bit is still set, preserving order.
@@ -447,9 +452,9 @@ __device__ __forceinline__ void sort_list(Ctx &c, int u) {
 
 __device__ __forceinline__ void row_of(const DevGraph &g, int32_t up, int dir, int32_t *beg,
                                        int32_t *end) {
-    const int32_t *off = dir ? g.in_off : g.out_off;
-    *beg = off[up];
-    *end = off[up + 1];
+    const int4 r = g.vrow[up];
+    *beg = dir ? r.z : r.x;
+    *end = dir ? r.w : r.y;
 }
 
 // Entries of candidate up's row that can pass test d: a hub row (at least
@@ -458,13 +463,13 @@ __device__ __forceinline__ void row_of(const DevGraph &g, int32_t up, int dir, i
 // test), restricted to that type (and relation); any other row in full.
 // Every entry left out fails the test (wrong type or relation), so the
 // outcome is the full row's; the slice keeps the other ends ascending.
-__device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const NNbr &d,
+__device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const NTest &d,
                                                 int32_t *beg, int32_t *end) {
     const DevGraph &g = c.g;
     row_of(g, up, d.dir, beg, end);
     const int2 *adj = d.dir ? g.in_adj : g.out_adj;
     if (g.hub_types == 0 || *end - *beg < kHubRow) return adj;
-    const int32_t t = c.Q->pred[d.v].label;
+    const int32_t t = d.label;
     if (t < 0 || t + 1 >= g.hub_types) return adj;
     const int32_t h = g.hub_of[up];
     const int order = d.rel >= 0 ? 0 : 1;
@@ -476,13 +481,13 @@ __device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const 
         int32_t lo = b, hi = e;
         while (lo < hi) {
             const int32_t mid = (lo + hi) >> 1;
-            if (arr[mid].y < d.rel) lo = mid + 1;
+            if ((arr[mid].y & g.rel_mask) < d.rel) lo = mid + 1;
             else hi = mid;
         }
         int32_t lo2 = lo, hi2 = e;
         while (lo2 < hi2) {
             const int32_t mid = (lo2 + hi2) >> 1;
-            if (arr[mid].y <= d.rel) lo2 = mid + 1;
+            if ((arr[mid].y & g.rel_mask) <= d.rel) lo2 = mid + 1;
             else hi2 = mid;
         }
         b = lo;
@@ -496,10 +501,10 @@ __device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const 
 // Whole workgroup on one candidate (uniform call). Prune: the candidate
 // survives if every listed query edge has a matching neighbour; explore
 // then pushes every matching neighbour.
-__device__ __forceinline__ int32_t max_row(const DevGraph &g, const NNbr *nb, int ncount, int32_t up);
+__device__ __forceinline__ int32_t max_row(const DevGraph &g, const NTest *nb, int ncount, int32_t up);
 
 template <class K>
-__device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, const NNbr *nb,
+__device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, const NTest *nb,
                                           int ncount, int32_t up, uint64_t *ub, uint64_t &fb,
                                           int32_t *defer = nullptr) {
     const DevGraph &g = c.g;
@@ -512,7 +517,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
         __syncthreads();
         uint64_t hits = 0, seen = 0;
         for (int j = 0; j < ncount; ++j) {
-            const NNbr d = nb[j];
+            const NTest d = nb[j];
             const int2 *adj = d.dir ? g.in_adj : g.out_adj;
             int32_t beg, end;
             row_of(g, up, d.dir, &beg, &end);
@@ -542,7 +547,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
             for (int j = 0; j < ncount; ++j) {
                 const uint32_t hj = (uint32_t)(hits >> (4 * j)) & 15u;
                 if (!hj) continue;
-                const NNbr d = nb[j];
+                const NTest d = nb[j];
                 const int2 *adj = d.dir ? g.in_adj : g.out_adj;
                 int32_t beg, end;
                 row_of(g, up, d.dir, &beg, &end);
@@ -558,7 +563,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
     bool alive = true;
     uint64_t seen = 0;
     for (int j = 0; j < ncount && alive; ++j) {
-        const NNbr d = nb[j];
+        const NTest d = nb[j];
         int32_t beg, end;
         const int2 *adj = test_row(c, up, d, &beg, &end);
         bool found = false;
@@ -594,7 +599,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
     }
     if (st.push) {
         for (int j = 0; j < ncount; ++j) {
-            const NNbr d = nb[j];
+            const NTest d = nb[j];
             int32_t beg, end;
             const int2 *adj = test_row(c, up, d, &beg, &end);
             uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -621,14 +626,14 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
     if (threadIdx.x == 0) fb += 20ull + 12ull * seen;
 }
 
-__device__ __forceinline__ void item_wg(Ctx &c, const NStep &st, const NNbr *nb, int ncount, int32_t up,
+__device__ __forceinline__ void item_wg(Ctx &c, const NStep &st, const NTest *nb, int ncount, int32_t up,
                                         uint64_t *ub, uint64_t &fb, int32_t *defer = nullptr) {
     item_wg_k(c, LdsCtr{c.s}, st, nb, ncount, up, ub, fb, defer);
 }
 
 // One wave on one candidate (wave-uniform call, no workgroup barrier), four
 // loads in flight per lane; same outcome as item_wg.
-__device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NNbr *nb, int ncount,
+__device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NTest *nb, int ncount,
                                           int32_t up, uint64_t *ub, uint64_t &fb,
                                           int32_t *defer = nullptr) {
     const DevGraph &g = c.g;
@@ -636,7 +641,7 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NNbr *n
     bool alive = true;
     uint64_t seen = 0;
     for (int j = 0; j < ncount && alive; ++j) {
-        const NNbr d = nb[j];
+        const NTest d = nb[j];
         int32_t beg, end;
         const int2 *adj = test_row(c, up, d, &beg, &end);
         bool found = false;
@@ -674,7 +679,7 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NNbr *n
     }
     if (st.push)
         for (int j = 0; j < ncount; ++j) {
-            const NNbr d = nb[j];
+            const NTest d = nb[j];
             int32_t beg, end;
             const int2 *adj = test_row(c, up, d, &beg, &end);
             uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -696,12 +701,10 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NNbr *n
 }
 
 // longest adjacency row a candidate scans for the listed query edges
-__device__ __forceinline__ int32_t max_row(const DevGraph &g, const NNbr *nb, int ncount, int32_t up) {
+__device__ __forceinline__ int32_t max_row(const DevGraph &g, const NTest *nb, int ncount, int32_t up) {
+    const int4 r = g.vrow[up];
     int32_t m = 0;
-    for (int j = 0; j < ncount; ++j) {
-        const int32_t *off = nb[j].dir ? g.in_off : g.out_off;
-        m = max(m, off[up + 1] - off[up]);
-    }
+    for (int j = 0; j < ncount; ++j) m = max(m, nb[j].dir ? r.w - r.z : r.y - r.x);
     return m;
 }
 
@@ -729,6 +732,7 @@ __device__ __forceinline__ void prune_reverse(Ctx &c, int u, int v, int dir, int
     const int32_t n = c.s->cnt[u];
     const int32_t *vl = c.L(v);
     const int32_t nv = c.s->cnt[v];
+    const int32_t ulabel = c.Q->pred[u].label;
     // a candidate's out-edge (dir 0) is an in-edge of the neighbour, and so on
     const int32_t *off = dir ? g.out_off : g.in_off;
     const int2 *adj = dir ? g.out_adj : g.in_adj;
@@ -739,7 +743,7 @@ __device__ __forceinline__ void prune_reverse(Ctx &c, int u, int v, int dir, int
         const int32_t beg = off[y], end = off[y + 1];
         for (int32_t k = beg + lane; k < end; k += 64) {
             const int2 e = adj[k];
-            if ((rel < 0 || e.y == rel) && bit_test(ub, e.x))
+            if (adj_rel_ok(g, e, rel) && adj_type_ok(g, e, ulabel) && bit_test(ub, e.x))
                 atomicOr((unsigned long long *)&c.scratch[e.x >> 6], 1ull << (e.x & 63));
         }
         if (lane == 0) seen += 12ull + 16ull * (end - beg);
@@ -767,7 +771,7 @@ __device__ __forceinline__ void prune_reverse(Ctx &c, int u, int v, int dir, int
 // pushed. Candidates with a row longer than 64 G entries go to the overflow
 // list at the start of the slab for a wider tier. Counters go to k.
 template <class K>
-__device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, const NNbr *nb,
+__device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, const NTest *nb,
                                              int ncount, const int32_t *ul, uint64_t *ub,
                                              bool revd, int G, int32_t it0, int32_t it1,
                                              uint64_t &fb, bool nodefer = false) {
@@ -789,8 +793,8 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, cons
     int32_t upn = it < it1 ? ul[it] : 0;
     for (; it < it1; it += NGr) {
         const int32_t up = upn;
-        const int32_t ob = g.out_off[up], oe = g.out_off[up + 1];
-        const int32_t ib = g.in_off[up], ie = g.in_off[up + 1];
+        const int4 vr = g.vrow[up];
+        const int32_t ob = vr.x, oe = vr.y, ib = vr.z, ie = vr.w;
         upn = it + NGr < it1 ? ul[it + NGr] : 0;
         if (revd && !bit_test(ub, up)) continue;  // already dropped
         int32_t maxd = 0;
@@ -805,7 +809,7 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, cons
         if (push && ncount == 1) {
             // a single neighbour test: one scan pushes the hits it finds,
             // and a candidate with none is dropped (it pushed nothing)
-            const NNbr d = nb[0];
+            const NTest d = nb[0];
             const int2 *adj = d.dir ? g.in_adj : g.out_adj;
             const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
             uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -833,7 +837,7 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, cons
         bool alive = true;
         uint64_t seen = 0;
         for (int j = 0; j < ncount && alive; ++j) {
-            const NNbr d = nb[j];
+            const NTest d = nb[j];
             const int2 *adj = d.dir ? g.in_adj : g.out_adj;
             const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
             bool found = false;
@@ -865,7 +869,7 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, cons
         }
         if (push)
             for (int j = 0; j < ncount; ++j) {
-                const NNbr d = nb[j];
+                const NTest d = nb[j];
                 const int2 *adj = d.dir ? g.in_adj : g.out_adj;
                 const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
                 uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -925,9 +929,9 @@ constexpr int32_t kSegEntries = 8 * NT;
 // row (whole workgroup). A row's neighbours are distinct, so bits are set
 // without a look first.
 template <class K>
-__device__ __forceinline__ void push_segment(Ctx &c, const K &k, const NNbr *nb, int4 sg,
+__device__ __forceinline__ void push_segment(Ctx &c, const K &k, const NTest *nb, int4 sg,
                                              uint64_t &fb) {
-    const NNbr d = nb[sg.y];
+    const NTest d = nb[sg.y];
     int32_t rb, re;  // the segment indexes the array test_row picks for its row
     const int2 *adj = test_row(c, sg.x, d, &rb, &re);
     uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -948,7 +952,7 @@ __device__ __forceinline__ void push_segment(Ctx &c, const K &k, const NNbr *nb,
 
 // Segments of the rows of the nd deferred candidates into seg (at most cap);
 // the count, or -1 if they do not fit (uniform).
-__device__ __forceinline__ int32_t build_segments(Ctx &c, const NNbr *nb, int ncount,
+__device__ __forceinline__ int32_t build_segments(Ctx &c, const NTest *nb, int ncount,
                                                   const int32_t *def, int32_t nd, int4 *seg,
                                                   int64_t cap) {
     int64_t carry = 0;
@@ -986,7 +990,7 @@ __device__ __forceinline__ void ec_chunk(Ctx &c, const EcJob &E, HelpJob *j, int
 // nch chunks that the owner and its helpers claim (kind 0: K candidates of
 // u's list, G lanes each; kind 1: one row segment each), and the owner waits
 // for the chunks its helpers claimed before taking the counters back.
-__device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, const NNbr *nb,
+__device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, const NTest *nb,
                                            int ncount, const int32_t *ul, uint64_t *ub, bool revd,
                                            int32_t n_items, int32_t K, int G, int32_t nch,
                                            const int4 *seg, uint64_t &fb,
@@ -1011,12 +1015,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         j->ncount = ncount;
         j->revd = revd;
         j->st = st;
-        for (int i = 0; i < ncount; ++i) {
-            j->nbl[i].v = nb[i].v;
-            j->nbl[i].dir = nb[i].dir;
-            j->nbl[i].mode = nb[i].mode;
-            j->nbl[i].rel = nb[i].rel;
-        }
+        for (int i = 0; i < ncount; ++i) j->nbl[i] = nb[i];
         if (ecj) {
             j->ecj = *ecj;
             j->jrows = 0ull;
@@ -1087,7 +1086,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
 }
 
 // Chunks of u's candidate list shared as above.
-__device__ __forceinline__ void shared_items(Ctx &c, const NStep &st, const NNbr *nb, int ncount,
+__device__ __forceinline__ void shared_items(Ctx &c, const NStep &st, const NTest *nb, int ncount,
                                              const int32_t *ul, uint64_t *ub, bool revd,
                                              int32_t n_items, int32_t helpers, uint64_t &fb) {
     const int32_t K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
@@ -1114,7 +1113,7 @@ __device__ __forceinline__ int32_t helpers_now(Ctx &c) {
 
 // The pushes deferred by the wave and workgroup tiers, as shared row
 // segments (or by this workgroup alone when they do not fit the slab).
-__device__ __forceinline__ void push_deferred(Ctx &c, const NStep &st, const NNbr *nb, int ncount,
+__device__ __forceinline__ void push_deferred(Ctx &c, const NStep &st, const NTest *nb, int ncount,
                                               const int32_t *def, uint64_t &fb) {
     __syncthreads();
     const int32_t nd = c.s->ndef;
@@ -1211,11 +1210,19 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
                 rm |= 1ull << j;
             } else {
                 if (threadIdx.x == 0) {
-                    NNbr &t = c.s->nbl[k];
+                    const VPred &p = c.Q->pred[v];
+                    // the edge itself is one in-edge (dir 0) or out-edge of
+                    // the neighbour: often all the degree its vertex asks for
+                    const bool degok = dir ? p.qout <= 1 && p.qin == 0 : p.qin <= 1 && p.qout == 0;
+                    NTest &t = c.s->nbl[k];
                     t.v = (int8_t)v;
                     t.dir = (int8_t)dir;
-                    t.mode = (int8_t)mode;
+                    t.mode = (int8_t)(mode == 1 && degok && g.typed_adj && !c.Q->homo ? 2 : mode);
+                    t.e = (int8_t)e;
                     t.rel = rel;
+                    t.label = p.label;
+                    t.pin = p.pin;
+                    t.qdeg = p.qout | p.qin << 8;
                 }
                 ++k;
             }
@@ -1227,7 +1234,7 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         }
     }
     __syncthreads();
-    const NNbr *nb = c.s->nbl;
+    const NTest *nb = c.s->nbl;
     const int ncount = c.s->nnbl;
     const int par = c.s->skippar ? -1 : st.parent;  // parent this step's marks intersect
     const uint64_t rm = c.s->revmask;
@@ -1394,11 +1401,13 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
 // one pass writes the table: vals[off[i] .. off[i] + num[i]).
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool ec_hit(int32_t rel, const uint64_t *other, const int2 *adj,
-                                       int32_t beg, int32_t i, int32_t key) {
+__device__ __forceinline__ bool ec_hit(const DevGraph &g, int32_t rel, int32_t olabel,
+                                       const uint64_t *other, const int2 *adj, int32_t beg,
+                                       int32_t i, int32_t key) {
     const int2 e = adj[i];
+    if (!adj_type_ok(g, e, olabel)) return false;
     if (rel >= 0) {
-        if (e.y != rel) return false;
+        if (!adj_rel_ok(g, e, rel)) return false;
     } else if (i > beg && adj[i - 1].x == e.x) {
         return false;  // same neighbour under another relation: one pair
     }
@@ -1418,10 +1427,10 @@ __device__ __forceinline__ int32_t row_lower_bound(const int2 *adj, int32_t beg,
 }
 
 // does the row hold neighbour x under relation rel (-1: any relation)?
-__device__ __forceinline__ bool row_has(const int2 *adj, int32_t beg, int32_t end, int32_t x,
-                                        int32_t rel) {
+__device__ __forceinline__ bool row_has(const DevGraph &g, const int2 *adj, int32_t beg,
+                                        int32_t end, int32_t x, int32_t rel) {
     for (int32_t i = row_lower_bound(adj, beg, end, x); i < end && adj[i].x == x; ++i)
-        if (rel < 0 || adj[i].y == rel) return true;
+        if (adj_rel_ok(g, adj[i], rel)) return true;
     return false;
 }
 
@@ -1444,7 +1453,7 @@ __device__ __forceinline__ int64_t ec_probe_wg(Ctx &c, int32_t rel, const int32_
     for (int32_t base = 0; base < no; base += NT) {
         const int32_t i = base + threadIdx.x;
         const int32_t x = i < no ? ol[i] : -1;
-        const bool hit = x >= 0 && x != k && row_has(adj, beg, end, x, rel);
+        const bool hit = x >= 0 && x != k && row_has(c.g, adj, beg, end, x, rel);
         int64_t tot;
         const int64_t p = n + block_excl_scan(hit ? 1 : 0, c.s->sh, &tot);
         if (hit) dst[p] = x;
@@ -1454,7 +1463,7 @@ __device__ __forceinline__ int64_t ec_probe_wg(Ctx &c, int32_t rel, const int32_
 }
 
 // one key, one wave (wave-uniform call): lookup form of ec_key_wave
-__device__ __forceinline__ int64_t ec_probe_wave(int32_t rel, const int32_t *ol, int32_t no,
+__device__ __forceinline__ int64_t ec_probe_wave(const Ctx &c, int32_t rel, const int32_t *ol, int32_t no,
                                                  const int2 *adj, int32_t beg, int32_t end,
                                                  int32_t k, int32_t *dst) {
     const int lane = threadIdx.x & 63;
@@ -1462,7 +1471,7 @@ __device__ __forceinline__ int64_t ec_probe_wave(int32_t rel, const int32_t *ol,
     for (int32_t base = 0; base < no; base += 64) {
         const int32_t i = base + lane;
         const int32_t x = i < no ? ol[i] : -1;
-        const bool hit = x >= 0 && x != k && row_has(adj, beg, end, x, rel);
+        const bool hit = x >= 0 && x != k && row_has(c.g, adj, beg, end, x, rel);
         const uint64_t bm = __ballot(hit);
         if (hit) dst[n + __popcll(bm & lanemask_lt(lane))] = x;
         n += __popcll(bm);
@@ -1471,7 +1480,7 @@ __device__ __forceinline__ int64_t ec_probe_wave(int32_t rel, const int32_t *ol,
 }
 
 // one key, whole workgroup, ordered compaction in chunks of 4*NT entries
-__device__ __forceinline__ int64_t ec_key_wg(Ctx &c, int32_t rel, const uint64_t *ob, const int2 *adj,
+__device__ __forceinline__ int64_t ec_key_wg(Ctx &c, int32_t rel, int32_t olabel, const uint64_t *ob, const int2 *adj,
                              int32_t beg, int32_t end, int32_t k, int32_t *dst) {
     int64_t n = 0;
     for (int32_t base = beg; base < end; base += 4 * NT) {
@@ -1479,7 +1488,7 @@ __device__ __forceinline__ int64_t ec_key_wg(Ctx &c, int32_t rel, const uint64_t
         uint32_t h = 0;  // bit t: entry i0 + t matches
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if (i0 + t < end && ec_hit(rel, ob, adj, beg, i0 + t, k)) h |= 1u << t;
+            if (i0 + t < end && ec_hit(c.g, rel, olabel, ob, adj, beg, i0 + t, k)) h |= 1u << t;
         int64_t tot;
         int64_t p = n + block_excl_scan(__popc(h), c.s->sh, &tot);
 #pragma unroll
@@ -1491,7 +1500,7 @@ __device__ __forceinline__ int64_t ec_key_wg(Ctx &c, int32_t rel, const uint64_t
 }
 
 // one key, one wave (wave-uniform call), same ordered output as ec_key_wg
-__device__ __forceinline__ int64_t ec_key_wave(int32_t rel, const uint64_t *ob, const int2 *adj,
+__device__ __forceinline__ int64_t ec_key_wave(const Ctx &c, int32_t rel, int32_t olabel, const uint64_t *ob, const int2 *adj,
                                                int32_t beg, int32_t end, int32_t k, int32_t *dst) {
     const int lane = threadIdx.x & 63;
     int64_t n = 0;
@@ -1500,7 +1509,7 @@ __device__ __forceinline__ int64_t ec_key_wave(int32_t rel, const uint64_t *ob, 
         uint32_t h = 0;  // bit t: entry i0 + t matches
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if (i0 + t < end && ec_hit(rel, ob, adj, beg, i0 + t, k)) h |= 1u << t;
+            if (i0 + t < end && ec_hit(c.g, rel, olabel, ob, adj, beg, i0 + t, k)) h |= 1u << t;
         const int32_t inc = wave_incl_scan32(__popc(h), lane);
         int64_t p = n + inc - __popc(h);
 #pragma unroll
@@ -1535,7 +1544,7 @@ __device__ __forceinline__ int64_t ec_keys(const Ctx &c, const EcJob &Ej, int32_
         int32_t n = 0;
         for (int32_t base = beg; base < end; base += G) {
             const int32_t i = base + gl;
-            const bool hit = i < end && ec_hit(E.rel, E.ob, adj, beg, i, E.homo ? -1 : k);
+            const bool hit = i < end && ec_hit(c.g, E.rel, E.olabel, E.ob, adj, beg, i, E.homo ? -1 : k);
             const uint64_t bm = __ballot(hit) & gmask;
             if (hit) dst[n + __popcll(bm & lanemask_lt(lane))] = adj[i].x;
             n += __popcll(bm);
@@ -1570,8 +1579,8 @@ __device__ __forceinline__ int64_t ec_long_keys(const Ctx &c, const EcJob &Ej, i
         const bool probe = probe_cheaper(E.no, end - beg);
         int32_t *dst = E.vals + E.degoff[it];
         const int32_t ks = E.homo ? -1 : k;  // -1: the key may pair with itself
-        const int64_t n = probe ? ec_probe_wave(E.rel, E.ol, E.no, adj, beg, end, ks, dst)
-                                : ec_key_wave(E.rel, E.ob, adj, beg, end, ks, dst);
+        const int64_t n = probe ? ec_probe_wave(c, E.rel, E.ol, E.no, adj, beg, end, ks, dst)
+                                : ec_key_wave(c, E.rel, E.olabel, E.ob, adj, beg, end, ks, dst);
         if (lane == 0) {
             E.num[it] = (int32_t)n;
             mytot += n;
@@ -1597,7 +1606,7 @@ __device__ __forceinline__ int64_t ec_giant_keys(Ctx &c, const EcJob &Ej, int32_
         int32_t *dst = E.vals + E.degoff[it];
         const int32_t ks = E.homo ? -1 : k;
         const int64_t n = probe ? ec_probe_wg(c, E.rel, E.ol, E.no, adj, beg, end, ks, dst)
-                                : ec_key_wg(c, E.rel, E.ob, adj, beg, end, ks, dst);
+                                : ec_key_wg(c, E.rel, E.olabel, E.ob, adj, beg, end, ks, dst);
         if (threadIdx.x == 0) {
             E.num[it] = (int32_t)n;
             mytot += n;
@@ -1691,7 +1700,8 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
     uint64_t fb = 0;
     const bool can_share = c.help_items > 0 && c.job;
     const int32_t homo = c.Q->homo;
-    const EcJob E{keys, degoff, num, vals, ovl, ob, ol, nullptr, nk, rel, dir, no, 0, homo};
+    const int32_t olabel = c.Q->pred[other].label;
+    const EcJob E{keys, degoff, num, vals, ovl, ob, ol, nullptr, nk, rel, dir, no, 0, olabel, homo};
     if (nk <= NW) {
         // a handful of keys: one wave each, rows above wg_rows get the
         // whole workgroup
@@ -1704,8 +1714,8 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
             } else {
                 const bool probe = probe_cheaper(no, end - beg);
                 const int32_t ks = homo ? -1 : k;
-                const int64_t n = probe ? ec_probe_wave(rel, ol, no, adj, beg, end, ks, vals + degoff[wave])
-                                        : ec_key_wave(rel, ob, adj, beg, end, ks, vals + degoff[wave]);
+                const int64_t n = probe ? ec_probe_wave(c, rel, ol, no, adj, beg, end, ks, vals + degoff[wave])
+                                        : ec_key_wave(c, rel, olabel, ob, adj, beg, end, ks, vals + degoff[wave]);
                 if (lane == 0) {
                     num[wave] = (int32_t)n;
                     mytot += n;
@@ -1756,8 +1766,8 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
             }
             const bool probe = probe_cheaper(no, end - beg);
             const int32_t ks = homo ? -1 : k;
-            const int64_t n = probe ? ec_probe_wave(rel, ol, no, adj, beg, end, ks, vals + degoff[it])
-                                    : ec_key_wave(rel, ob, adj, beg, end, ks, vals + degoff[it]);
+            const int64_t n = probe ? ec_probe_wave(c, rel, ol, no, adj, beg, end, ks, vals + degoff[it])
+                                    : ec_key_wave(c, rel, olabel, ob, adj, beg, end, ks, vals + degoff[it]);
             if (lane == 0) {
                 num[it] = (int32_t)n;
                 mytot += n;
@@ -1855,8 +1865,8 @@ __device__ __forceinline__ uint64_t ec_build_single(Ctx &c, uint64_t mask, int d
         const int32_t rel = Q.elabel[ed];
         const bool probe = probe_cheaper(no, end - beg);
         const int32_t ks = Q.homo ? -1 : k;
-        const int64_t n = probe ? ec_probe_wave(rel, c.L(other), no, adj, beg, end, ks, vals)
-                                : ec_key_wave(rel, c.B(other), adj, beg, end, ks, vals);
+        const int64_t n = probe ? ec_probe_wave(c, rel, c.L(other), no, adj, beg, end, ks, vals)
+                                : ec_key_wave(c, rel, Q.pred[other].label, c.B(other), adj, beg, end, ks, vals);
         if (lane == 0) {
             degoff[0] = 0;
             degoff[1] = end - beg;
@@ -3003,10 +3013,7 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
     const int32_t *hul = j->ul;
     const bool nodefer = j->nodefer != 0;
     if ((int)threadIdx.x < ncount) {
-        s.nbl[threadIdx.x].v = j->nbl[threadIdx.x].v;
-        s.nbl[threadIdx.x].dir = j->nbl[threadIdx.x].dir;
-        s.nbl[threadIdx.x].mode = j->nbl[threadIdx.x].mode;
-        s.nbl[threadIdx.x].rel = j->nbl[threadIdx.x].rel;
+        s.nbl[threadIdx.x] = j->nbl[threadIdx.x];
     }
     if (kind == 2) {
         const uint64_t *src = (const uint64_t *)&j->jl;

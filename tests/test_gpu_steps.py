@@ -1,0 +1,63 @@
+"""Branches of the kernels' dispatch at the sizes where they change: results
+against the oracle, intermediate counts against the multi-kernel path."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1807_08804_amd as P
+from tests.micro import random_graph, random_query
+
+pytestmark = pytest.mark.gpu
+
+
+def micro(seed, V, E, n_types=3, n_rels=3, nq=8, n_max=7, **kw):
+    rng = np.random.default_rng(seed)
+    mg = random_graph(rng, V, E, n_types=n_types, n_rels=n_rels)
+    qs = [random_query(rng, int(rng.integers(2, n_max)), n_types, n_rels, V, p_pin=0.25, extra=3)
+          for _ in range(nq)]
+    return mg, qs, oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+
+
+@pytest.mark.parametrize("rounds,rev", [(0, 1), (1, 1), (1, 0), (-1, 0)])
+@pytest.mark.parametrize("seed,V,E", [(1, 12, 40), (2, 60, 200), (3, 400, 1600), (4, 3000, 9000)])
+def test_filter_counts_equal_on_both_paths(seed, V, E, rounds, rev):
+    """Tests left out because they are known to hold change no candidate
+    set: counts of candidates and candidate edges equal the multi-kernel
+    path's, which runs every test."""
+    mg, qs, og = micro(900 + seed, V, E)
+    rp, col, rel, typ = mg.csr()
+    gs = [P.Graph(rp, col, rel, typ, path=p, refine_rounds=rounds, refine_reversed=rev)
+          for p in (P.SGM_PATH_NARROW, P.SGM_PATH_WIDE)]
+    for i, q in enumerate(qs):
+        print("case: query", i, flush=True)
+        (rn, sn), (rw, sw) = [g.match_query(q, with_stats=True) for g in gs]
+        assert np.array_equal(rn, rw) and np.array_equal(rn, og.match_query(q))
+        assert sn["cand"] == sw["cand"]
+        if min(sn["cand"]) > 0:
+            assert sn["ec"] == sw["ec"]
+            if min(sn["ec"], default=1) > 0 and len(rn):
+                assert sn["level_rows"] == sw["level_rows"]
+
+
+@pytest.mark.parametrize("n_types,n_rels,tbase,rbase", [
+    (3, 3, 0, 0),                 # types in the adjacency entries
+    (3, 3, 32764, 65531),         # the largest types and relations they hold
+    (3, 3, 32766, 0), (3, 3, 0, 65533),  # one past each: entries without types
+    (3, 3, 70000, 1 << 20),
+])
+def test_types_in_adjacency_entries(n_types, n_rels, tbase, rbase):
+    """Entries that carry their vertex's type and graphs whose types or
+    relations do not fit them give the same matches."""
+    mg, qs, _ = micro(77, 200, 900, n_types, n_rels, nq=12)
+    rp, col, rel, typ = mg.csr()
+    typ, rel = np.asarray(typ) + tbase, np.asarray(rel) + rbase
+    og = oracle.Graph(200, mg.src, mg.dst, np.asarray(mg.rel) + rbase, np.asarray(mg.vtype) + tbase)
+    for path in (P.SGM_PATH_AUTO, P.SGM_PATH_WIDE):
+        g = P.Graph(rp, col, rel, typ, path=path)
+        for i, q in enumerate(qs):
+            print("case: query", i, "path", path, flush=True)
+            q2 = type(q)(**{**q.__dict__})
+            q2.vlabel = np.where(q.vlabel >= 0, q.vlabel + tbase, q.vlabel).astype(np.int32)
+            q2.elabel = np.where(q.elabel >= 0, q.elabel + rbase, q.elabel).astype(np.int32)
+            assert np.array_equal(g.match_query(q2), og.match_query(q2))
+        g.close()
