@@ -32,7 +32,8 @@ struct NNbr {
 // mode 2: the entry's relation and type (and pin) decide alone, since the
 // edge to it already gives the vertex the degree that v asks for.
 struct NTest {
-    int8_t v, dir, mode, e;
+    int8_t v, dir, mode;
+    int8_t known;        // 1: holds already, kept for what it pushes
     int32_t rel;
     int32_t label, pin;  // of v; -1: any, none
     int32_t qdeg;        // least out-degree | least in-degree << 8

@@ -81,6 +81,7 @@ struct Smem {
     int32_t hq, hch;            // helper: board entry and chunk claimed (-1: none)
     int8_t qsrc[SGM_MAX_QE], qdst[SGM_MAX_QE];  // the query's edges, staged for join_order
     uint64_t revmask;
+    NQuery query;           // the descriptor, staged for its many small reads
     NTest nbl[SGM_MAX_QE];  // neighbours a step still tests per candidate
     // What filtering has established so far. ver[v] counts the changes of
     // C(v); okv[2 e + s] is the version of one endpoint's candidates for
@@ -271,13 +272,30 @@ __device__ __forceinline__ bool set_new(uint64_t *tb, int32_t x) {
 
 // push_bit for up to four entries per lane (hk: push xk), appending the
 // newly set ones with one counter update per wave: the lanes that reach
-// this call take consecutive places in the order of their lane index.
+// this call take consecutive places in the order of their lane index. The
+// four reads, then the four atomics, are in flight together.
 template <class K, bool look = true>
 __device__ __forceinline__ void push4(Ctx &c, const K &k, uint64_t *tb, int32_t *tl, int v,
                                       bool h0, int32_t x0, bool h1, int32_t x1, bool h2,
                                       int32_t x2, bool h3, int32_t x3) {
-    const bool n0 = h0 && set_new<look>(tb, x0), n1 = h1 && set_new<look>(tb, x1);
-    const bool n2 = h2 && set_new<look>(tb, x2), n3 = h3 && set_new<look>(tb, x3);
+    bool h[4] = {h0, h1, h2, h3};
+    const int32_t x[4] = {x0, x1, x2, x3};
+    if (look) {
+        uint64_t was[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            was[q] = __atomic_load_n(tb + (h[q] ? x[q] >> 6 : 0), __ATOMIC_RELAXED);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h[q] = h[q] && !((was[q] >> (x[q] & 63)) & 1ull);
+    }
+    unsigned long long old[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        old[q] = ~0ull;
+        if (h[q]) old[q] = atomicOr((unsigned long long *)(tb + (x[q] >> 6)), 1ull << (x[q] & 63));
+    }
+    const bool n0 = !((old[0] >> (x0 & 63)) & 1ull), n1 = !((old[1] >> (x1 & 63)) & 1ull);
+    const bool n2 = !((old[2] >> (x2 & 63)) & 1ull), n3 = !((old[3] >> (x3 & 63)) & 1ull);
     const int cnt = (int)n0 + (int)n1 + (int)n2 + (int)n3;
     const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
     const int tot = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
@@ -564,6 +582,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
     uint64_t seen = 0;
     for (int j = 0; j < ncount && alive; ++j) {
         const NTest d = nb[j];
+        if (d.known) continue;
         int32_t beg, end;
         const int2 *adj = test_row(c, up, d, &beg, &end);
         bool found = false;
@@ -642,6 +661,7 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NTest *
     uint64_t seen = 0;
     for (int j = 0; j < ncount && alive; ++j) {
         const NTest d = nb[j];
+        if (d.known) continue;
         int32_t beg, end;
         const int2 *adj = test_row(c, up, d, &beg, &end);
         bool found = false;
@@ -765,127 +785,309 @@ __device__ __forceinline__ void prune_reverse(Ctx &c, int u, int v, int dir, int
     __syncthreads();
 }
 
-// Candidates [it0, it1) of u's list (ul, bitmap ub), G lanes each: a
+// Flat scan of several adjacency rows by one wave: the entries of up to 64
+// segments (a candidate's row for one test) are laid end to end and dealt to
+// the lanes, so a wave's time follows the sum of its rows, not the longest
+// one. pre: where each segment starts; adr: what turns a position into an
+// index of the adjacency array.
+// Longer rows go to a wider tier: many candidates share a wave's scan, and
+// its few long rows would hold the others back while other waves idle (dense
+// graph, 59 queries: 16.8 ms a call at 512, 14.7 at 96); a wave with one
+// candidate takes more.
+constexpr int kFlatRow = 96;
+constexpr int kFlatRowOne = 512;
+struct FlatLds {
+    int32_t pre[64], adr[64];
+};
+
+// orders this wave's LDS accesses before the call against those after it
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Lane l's segment: len entries from adjacency index beg, positions
+// [*pos, *pos + len). Returns the total.
+__device__ __forceinline__ int32_t flat_begin(FlatLds *w, int32_t beg, int32_t len, int lane,
+                                              int32_t *pos) {
+    const int32_t inc = wave_incl_scan32(len, lane);
+    wave_sync();  // the reads of the scan before
+    w->pre[lane] = inc - len;
+    w->adr[lane] = beg - (inc - len);
+    *pos = inc - len;
+    wave_sync();
+    return __builtin_amdgcn_readlane(inc, 63);
+}
+
+// Do the positions [p, p + 64), lane i's match in bit i of `hits`, hold a
+// match of this lane's segment [pos, pos + len)? (A segment's entries sit on
+// consecutive lanes, so the wave's ballot answers for all 64 segments; one
+// shared word of hit bits took an LDS atomic per matching entry, all on one
+// address.)
+__device__ __forceinline__ bool flat_found(uint64_t hits, int32_t p, int32_t pos, int32_t len) {
+    const int32_t lo = max(pos - p, 0), hi = min(pos + len - p, 64);
+    if (lo >= hi) return false;
+    return (hits >> lo) << (64 - (hi - lo)) != 0ull;
+}
+
+// Segments of positions e[q] (the last one that starts at or before each).
+__device__ __forceinline__ void flat_owner(const FlatLds *w, const int32_t (&e)[4], int (&o)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = 0;
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (w->pre[o[q] + st] <= e[q]) o[q] += st;
+}
+
+__device__ __forceinline__ FlatLds *flat_lds(Ctx &c) {
+    return (FlatLds *)c.dyn + (threadIdx.x >> 6);
+}
+
+// One wave, candidates ul[i0, i1) (at most 64, one per lane), the tests one
+// after the other: a candidate that fails one reads no row for the next.
+template <class K>
+__device__ __forceinline__ void wave_items(Ctx &c, const K &k, bool push, const NTest *nb,
+                                           int ncount, const int32_t *ul, int32_t i0, int32_t i1,
+                                           uint64_t *ub, bool revd, int32_t bigdeg, uint64_t &fb) {
+    const DevGraph &g = c.g;
+    const int lane = threadIdx.x & 63;
+    FlatLds *w = flat_lds(c);
+    bool have = i0 + lane < i1;
+    const int32_t up = have ? ul[i0 + lane] : 0;
+    const int4 vr = g.vrow[up];
+    if (revd) have = have && bit_test(ub, up);  // else already dropped
+    int32_t maxd = 0;
+    for (int j = 0; j < ncount; ++j) maxd = max(maxd, nb[j].dir ? vr.w - vr.z : vr.y - vr.x);
+    if (have && maxd > bigdeg) {
+        // The overflow list sits at the start of the slot's slab, which no
+        // phase uses while filtering (at most lcap entries).
+        ((int32_t *)c.slab)[atomicAdd(k.nbig(), 1)] = up;
+        have = false;
+    }
+    const uint64_t todo = __ballot(have);
+    uint64_t alive = todo;
+    int64_t seen = 0;
+    const bool direct = push && ncount == 1;  // one scan finds and pushes
+    for (int pass = 0; pass < (push && !direct ? 2 : 1); ++pass)
+        for (int j = 0; j < ncount && alive; ++j) {
+            const NTest d = nb[j];
+            if (pass == 0 && d.known && !direct) continue;  // pushes only
+            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
+            const bool on = (alive >> lane) & 1ull;
+            int32_t beg = d.dir ? vr.z : vr.x;
+            int32_t len = on ? (d.dir ? vr.w : vr.y) - beg : 0;
+            const bool pushing = pass == 1 || direct;
+            bool found = false;
+            if (!pushing && d.label < 0 && d.pin < 0) {
+                // a test that most entries pass: each lane's first four
+                // entries first, and only the rest of the others' rows
+                int2 en[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) en[q] = q < len ? adj[beg + q] : make_int2(0, -1);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) found |= q < len && nbr_hit(c, d, en[q]);
+                seen += 4;
+                beg += 4;
+                len = found ? 0 : max(len - 4, 0);
+            }
+            const uint64_t early = __ballot(found);
+            int32_t pos;
+            const int32_t T = flat_begin(w, beg, len, lane, &pos);
+            uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
+            int32_t *tl = d.mode == 0 ? nullptr : c.L(d.v);
+            seen += T;
+            for (int32_t base = 0; base < T; base += 256) {
+                int32_t e[4];
+                int o[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e[q] = base + q * 64 + lane;
+                flat_owner(w, e, o);
+                uint64_t done = 0;
+                if (!pushing && base > 0) {
+                    // candidates found alive need no further entries
+                    done = __ballot(found);
+                    if (((alive & ~early) & ~done) == 0) break;
+                }
+                int2 en[4];
+                bool h[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    h[q] = e[q] < T && !((done >> o[q]) & 1ull);
+                    en[q] = h[q] ? adj[w->adr[o[q]] + e[q]] : make_int2(0, -1);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) h[q] = h[q] && nbr_hit(c, d, en[q]);
+                if (pass == 0)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        found |= flat_found(__ballot(h[q]), base + q * 64, pos, len);
+                if (pushing)
+                    push4(c, k, tb, tl, d.v, h[0], en[0].x, h[1], en[1].x, h[2], en[2].x, h[3],
+                          en[3].x);
+            }
+            if (pass == 0) alive = __ballot(found);
+        }
+    const uint64_t dead = todo & ~alive;
+    if ((dead >> lane) & 1ull)
+        atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
+    if (lane == 0) {
+        if (dead) atomicAdd(k.removed(), __popcll(dead));
+        fb += 20ull * __popcll(todo) + 12ull * seen;
+    }
+}
+
+// One wave, few candidates: every row of every test at once (the candidates
+// times the tests are at most 64 segments), so a step's chain is one read of
+// the row extents, one of the entries and one of what they are tested
+// against. Matches among the first 256 entries are pushed from registers.
+template <class K>
+__device__ __forceinline__ void wave_few(Ctx &c, const K &k, bool push, const NTest *nb, int ncount,
+                                         const int32_t *ul, int32_t i0, int32_t i1, uint64_t *ub,
+                                         bool revd, int32_t bigdeg, uint64_t &fb) {
+    const DevGraph &g = c.g;
+    const int lane = threadIdx.x & 63;
+    FlatLds *w = flat_lds(c);
+    const int n = i1 - i0;
+    // item = lane / ncount by a 16-bit reciprocal (exact for lane < 64)
+    const uint32_t inv = (65536u + (uint32_t)ncount - 1u) / (uint32_t)ncount;
+    const int it = (int)(((uint32_t)lane * inv) >> 16), tj = lane - it * ncount;
+    bool have = it < n;
+    const int32_t up = have ? ul[i0 + it] : 0;
+    const int4 vr = g.vrow[up];
+    if (revd) have = have && bit_test(ub, up);
+    const int dir = nb[tj].dir;
+    const int32_t beg = dir ? vr.z : vr.x, end = dir ? vr.w : vr.y;
+    // this candidate's segments among the wave's, and those that decide
+    const uint64_t mine = (ncount == 64 ? ~0ull : (1ull << ncount) - 1ull) << (it * ncount & 63);
+    const uint64_t need = mine & ~__ballot(nb[tj].known);
+    if (__ballot(have && end - beg > bigdeg) & mine) {
+        if (have && tj == 0) ((int32_t *)c.slab)[atomicAdd(k.nbig(), 1)] = up;
+        have = false;
+    }
+    const bool todo = have;
+    const int32_t len = have ? end - beg : 0;
+    int32_t pos;
+    const int32_t T = flat_begin(w, beg, len, lane, &pos);
+    bool alive = false, found = false;
+    for (int pass = 0; pass < (push && T > 256 ? 2 : 1); ++pass) {
+        uint64_t live = 0;  // segments of surviving candidates
+        if (pass == 1) live = __ballot(alive);
+        for (int32_t base = 0; base < T; base += 256) {
+            int32_t e[4];
+            int o[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) e[q] = base + q * 64 + lane;
+            flat_owner(w, e, o);
+            int2 en[4];
+            bool h[4];
+            NTest d[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int oi = (int)(((uint32_t)o[q] * inv) >> 16);
+                d[q] = nb[o[q] - oi * ncount];
+                h[q] = e[q] < T && (pass == 0 || ((live >> o[q]) & 1ull));
+                const int2 *adj = d[q].dir ? g.in_adj : g.out_adj;
+                en[q] = h[q] ? adj[w->adr[o[q]] + e[q]] : make_int2(0, -1);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) h[q] = h[q] && nbr_hit(c, d[q], en[q]);
+            if (pass == 0)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    found |= flat_found(__ballot(h[q]), base + q * 64, pos, len);
+            if (push && T <= 256) {
+                alive = todo;
+                alive &= (__ballot(found) & need) == need;
+                live = __ballot(alive);
+            }
+            if (push && (pass == 1 || T <= 256)) {
+                // all bits first, then each target's newly set ones take
+                // consecutive places with one counter update
+                unsigned long long old[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    old[q] = ~0ull;
+                    if (h[q] && ((live >> o[q]) & 1ull))
+                        old[q] = atomicOr((unsigned long long *)((d[q].mode == 0 ? c.scratch : c.B(d[q].v)) +
+                                                                 (en[q].x >> 6)),
+                                          1ull << (en[q].x & 63));
+                }
+                int tq[4];  // test of the entry's segment, -1: nothing new
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int oi = (int)(((uint32_t)o[q] * inv) >> 16);
+                    tq[q] = (old[q] >> (en[q].x & 63)) & 1ull ? -1 : o[q] - oi * ncount;
+                }
+                for (int j = 0; j < ncount; ++j) {
+                    uint64_t m[4];
+                    int tot = 0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        m[q] = __ballot(tq[q] == j);
+                        tot += __popcll(m[q]);
+                    }
+                    if (tot == 0) continue;
+                    const int v = nb[j].v;
+                    const bool marks = nb[j].mode == 0;
+                    int32_t p = 0;
+                    if (lane == 0) p = atomicAdd(marks ? k.nmarks() : k.cnt(v), tot);
+                    p = __builtin_amdgcn_readlane(p, 0);
+                    int32_t *tl = marks ? c.marks : c.L(v);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int32_t at = p + __popcll(m[q] & lanemask_lt(lane));
+                        if (tq[q] == j) {
+                            // marks are parent candidates, at most lcap
+                            if (at < c.lcap) tl[at] = en[q].x;
+                            else *k.abort_() = kWhyList;
+                        }
+                        p += __popcll(m[q]);
+                    }
+                }
+            }
+        }
+        if (pass == 0) {
+            alive = todo;
+            alive &= (__ballot(found) & need) == need;
+        }
+    }
+    const bool drop = todo && !alive && tj == 0;
+    if (drop) atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
+    const uint64_t dead = __ballot(drop);
+    if (lane == 0) {
+        if (dead) atomicAdd(k.removed(), __popcll(dead));
+        fb += 20ull * n + 12ull * (uint64_t)T;
+    }
+}
+
+// Candidates [it0, it1) of u's list (ul, bitmap ub), dealt to the waves: a
 // candidate lacking a matching neighbour for one of the ncount tests is
 // dropped; with push, the neighbours of the others that pass a test are
-// pushed. Candidates with a row longer than 64 G entries go to the overflow
-// list at the start of the slab for a wider tier. Counters go to k.
+// pushed. Candidates with a row above kFlatRow entries go to the overflow
+// list at the start of the slab for a wider tier (nodefer: a shared pass
+// over long rows, one wave per row up to wg_rows, which the whole workgroup
+// would take next; longer ones stay with the owner, whose pushes become
+// shared row segments). Counters go to k.
 template <class K>
 __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, const NTest *nb,
                                              int ncount, const int32_t *ul, uint64_t *ub,
-                                             bool revd, int G, int32_t it0, int32_t it1,
-                                             uint64_t &fb, bool nodefer = false) {
-    const DevGraph &g = c.g;
-    const int NGr = NT / G;
-    const int lane = threadIdx.x & 63, gl = lane & (G - 1), gb = lane & ~(G - 1);
-    const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << gb;
-    // more than 64 strides: a wider tier (a shared pass over long rows
-    // keeps the rows up to wg_rows, which the whole workgroup would take
-    // next; longer ones stay with the owner, whose pushes become shared
-    // row segments)
-    const int32_t bigdeg = nodefer ? max(64 * G, c.wg_rows) : 64 * G;
-    // The overflow list sits at the start of the slot's slab, which no phase
-    // uses while filtering (at most lcap entries, far below its size).
-    int32_t *ov = (int32_t *)c.slab;
-    // the next item's vertex is read while this one is tested, and its row
-    // offsets as soon as it has arrived (one dependent read less per item)
-    int32_t it = it0 + threadIdx.x / G;
-    int32_t upn = it < it1 ? ul[it] : 0;
-    for (; it < it1; it += NGr) {
-        const int32_t up = upn;
-        const int4 vr = g.vrow[up];
-        const int32_t ob = vr.x, oe = vr.y, ib = vr.z, ie = vr.w;
-        upn = it + NGr < it1 ? ul[it + NGr] : 0;
-        if (revd && !bit_test(ub, up)) continue;  // already dropped
-        int32_t maxd = 0;
-        for (int j = 0; j < ncount; ++j) maxd = max(maxd, nb[j].dir ? ie - ib : oe - ob);
-        if (maxd > bigdeg) {
-            // long rows: a wider tier after this loop. The overflow list
-            // sits at the start of the slot's slab, which no phase uses
-            // while filtering (at most lcap entries, far below its size).
-            if (gl == 0) ov[atomicAdd(k.nbig(), 1)] = up;
-            continue;
-        }
-        if (push && ncount == 1) {
-            // a single neighbour test: one scan pushes the hits it finds,
-            // and a candidate with none is dropped (it pushed nothing)
-            const NTest d = nb[0];
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
-            const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
-            int32_t *tl = d.mode == 0 ? nullptr : c.L(d.v);
-            bool any = false;
-            for (int32_t i = beg + gl; i < end; i += 4 * G) {
-                const int2 e0 = adj_at(adj, i, end), e1 = adj_at(adj, i + G, end);
-                const int2 e2 = adj_at(adj, i + 2 * G, end), e3 = adj_at(adj, i + 3 * G, end);
-                const bool h0 = (i < end) & nbr_hit(c, d, e0);
-                const bool h1 = (i + G < end) & nbr_hit(c, d, e1);
-                const bool h2 = (i + 2 * G < end) & nbr_hit(c, d, e2);
-                const bool h3 = (i + 3 * G < end) & nbr_hit(c, d, e3);
-                push4(c, k, tb, tl, d.v, h0, e0.x, h1, e1.x, h2, e2.x, h3, e3.x);
-                any |= h0 | h1 | h2 | h3;
-            }
-            if (!(__ballot(any) & gmask)) {
-                if (gl == 0) {
-                    atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
-                    atomicAdd(k.removed(), 1);
-                }
-            }
-            if (gl == 0) fb += 20ull + 12ull * (uint64_t)(end - beg);
-            continue;
-        }
-        bool alive = true;
-        uint64_t seen = 0;
-        for (int j = 0; j < ncount && alive; ++j) {
-            const NTest d = nb[j];
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
-            const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            bool found = false;
-            // four entries per lane in flight; lanes past the row test an
-            // in-range dummy entry and discard the answer
-            for (int32_t base = beg; base < end; base += 4 * G) {
-                const int32_t i = base + gl;
-                const int2 e0 = adj_at(adj, i, end), e1 = adj_at(adj, i + G, end);
-                const int2 e2 = adj_at(adj, i + 2 * G, end), e3 = adj_at(adj, i + 3 * G, end);
-                const bool hit = ((i < end) & nbr_hit(c, d, e0)) |
-                                 ((i + G < end) & nbr_hit(c, d, e1)) |
-                                 ((i + 2 * G < end) & nbr_hit(c, d, e2)) |
-                                 ((i + 3 * G < end) & nbr_hit(c, d, e3));
-                seen += min(4 * G, end - base);
-                if (__ballot(hit) & gmask) {
-                    found = true;
-                    break;
-                }
-            }
-            alive = found;
-        }
-        if (!alive) {
-            if (gl == 0) {
-                atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
-                atomicAdd(k.removed(), 1);
-                fb += 20ull + 12ull * seen;
-            }
-            continue;
-        }
-        if (push)
-            for (int j = 0; j < ncount; ++j) {
-                const NTest d = nb[j];
-                const int2 *adj = d.dir ? g.in_adj : g.out_adj;
-                const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-                uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
-                int32_t *tl = d.mode == 0 ? nullptr : c.L(d.v);
-                seen += end - beg;
-                for (int32_t i = beg + gl; i < end; i += 4 * G) {
-                    const int2 e0 = adj_at(adj, i, end), e1 = adj_at(adj, i + G, end);
-                    const int2 e2 = adj_at(adj, i + 2 * G, end), e3 = adj_at(adj, i + 3 * G, end);
-                    const bool h0 = (i < end) & nbr_hit(c, d, e0);
-                    const bool h1 = (i + G < end) & nbr_hit(c, d, e1);
-                    const bool h2 = (i + 2 * G < end) & nbr_hit(c, d, e2);
-                    const bool h3 = (i + 3 * G < end) & nbr_hit(c, d, e3);
-                    push4(c, k, tb, tl, d.v, h0, e0.x, h1, e1.x, h2, e2.x, h3, e3.x);
-                }
-            }
-        if (gl == 0) fb += 20ull + 12ull * seen;
+                                             bool revd, int32_t it0, int32_t it1, uint64_t &fb,
+                                             bool nodefer = false) {
+    const int wid = threadIdx.x >> 6;
+    const int32_t per = nodefer ? 1 : min(64, (it1 - it0 + NW - 1) / NW);
+    const int32_t bigdeg = nodefer ? max(4096, c.wg_rows) : per == 1 ? kFlatRowOne : kFlatRow;
+    for (int32_t i = it0 + wid * per; i < it1; i += NW * per) {
+        const int32_t e = min(it1, i + per);
+        // few candidates and several tests: all their rows at once; the
+        // rows of long-row passes are read test by test, which stops at the
+        // first match
+        if (!nodefer && ncount > 1 && (e - i) * ncount <= 64)
+            wave_few(c, k, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
+        else
+            wave_items(c, k, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
     }
 }
 
@@ -1039,7 +1241,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         __syncthreads();
         if (ch < 0) break;
         if (kind == 0)
-            filter_items(c, BoardCtr{j}, st.push != 0, nb, ncount, ul, ub, revd, G, ch * K,
+            filter_items(c, BoardCtr{j}, st.push != 0, nb, ncount, ul, ub, revd, ch * K,
                          min(n_items, ch * K + K), fb, nodefer);
         else if (kind == 3)
             ec_chunk(c, *ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
@@ -1091,9 +1293,8 @@ __device__ __forceinline__ void shared_items(Ctx &c, const NStep &st, const NTes
                                              int32_t n_items, int32_t helpers, uint64_t &fb) {
     const int32_t K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
                                            (n_items + kMaxChunks - 1) / kMaxChunks)));
-    const int G = lanes_for(K, c.gmax);
     const int32_t nch = (n_items + K - 1) / K;
-    shared_job(c, 0, st, nb, ncount, ul, ub, revd, n_items, K, G, nch, nullptr, fb);
+    shared_job(c, 0, st, nb, ncount, ul, ub, revd, n_items, K, 64, nch, nullptr, fb);
 }
 
 // Workgroups that can help this slot now: the launch's extra ones and the
@@ -1146,91 +1347,102 @@ __device__ __forceinline__ int32_t *defer_list(Ctx &c, const NStep &st) {
     return (int32_t *)(c.slab + 8 * (int64_t)c.lcap);
 }
 
-__device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
+// One step; returns the number of candidates it removed from C(u) (uniform).
+__device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
     const DevGraph &g = c.g;
     const int u = st.u;
     uint64_t *ub = c.B(u);
     int32_t *ul = c.L(u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        c.s->nbig = 0;
-        c.s->ngiant = 0;
-        c.s->removed = 0;
-        c.s->nmarks = 0;
-        c.s->ndef = 0;
-    }
-    __syncthreads();
     const int32_t n_items = c.s->cnt[u];
     uint64_t fb = 0;  // algorithmic bytes of this thread's work
-    // The step's neighbour tests go to LDS. In prune-only steps over many
-    // candidates, a neighbour with few candidates whose rows together are
-    // shorter than u's list is instead checked from its side (prune_reverse).
     // A test known to hold is left out: every candidate of u was found (or
     // pushed) with a matching neighbour in C(v), C(v) has not changed since
     // and C(u) only shrinks. Refinement repeats the tree edges that the
     // exploration has just established, so a query whose candidates are down
     // to a few runs hardly any of its refine steps. An explore step's test
-    // against a parent with a single candidate goes too: what it would push
-    // is that candidate, as long as any candidate of u survives.
-    const bool try_rev = !st.push && n_items >= kRevMin;
+    // against its parent is kept for what it pushes, except for a parent with
+    // a single candidate: what it would push is that candidate, as long as
+    // any candidate of u survives.
+    const bool in = (int)(threadIdx.x & 63) < st.count;
+    const NNbr td = c.Q->nbr[st.first + (in ? threadIdx.x & 63 : 0)];
+    const bool known = in && td.mode == 0 && c.s->okv[2 * td.e + td.dir] == c.s->ver[td.v];
+    if (!st.push && __popcll(__ballot(known)) == st.count) return 0;  // every wave alike
     if (threadIdx.x < 64) {
-        const NNbr *src = c.Q->nbr + st.first;
-        int k = 0;
+        const int lane = threadIdx.x;
+        if (lane == 0) {
+            c.s->nbig = 0;
+            c.s->ngiant = 0;
+            c.s->removed = 0;
+            c.s->nmarks = 0;
+            c.s->ndef = 0;
+        }
+        const bool spar = known && st.push && c.s->cnt[td.v] == 1;
+        bool keep = in && !spar && (st.push || !known);
+        // In prune-only steps over many candidates, a neighbour with few
+        // candidates whose rows together are shorter than u's list is
+        // checked from its side instead (prune_reverse).
         uint64_t rm = 0;
-        bool skippar = false;
-        for (int j = 0; j < st.count; ++j) {
-            const int v = src[j].v, dir = src[j].dir, mode = src[j].mode, e = src[j].e;
-            const int32_t rel = src[j].rel;
-            bool rev = false;
-            if (mode == 0 && c.s->okv[2 * e + dir] == c.s->ver[v] &&
-                (!st.push || c.s->cnt[v] == 1)) {
-                skippar |= st.push != 0;
-                continue;
-            }
-            const int32_t nv = c.s->cnt[v];
-            if (try_rev && mode == 0 && nv <= kRevMaxCand && nv < n_items) {
+        if (!st.push && n_items >= kRevMin) {
+            const int32_t nvl = c.s->cnt[td.v];
+            uint64_t cand = __ballot(keep && nvl <= kRevMaxCand && nvl < n_items);
+            while (cand) {
+                const int j = __builtin_ctzll(cand);
+                cand &= cand - 1;
+                const int v = __builtin_amdgcn_readlane((int)td.v, j);
+                const int dir = __builtin_amdgcn_readlane((int)td.dir, j);
                 // reverse cost: v's list plus its rows, against at least one
                 // read per candidate of u forward
+                const int32_t nv = c.s->cnt[v];
                 const int32_t *off = dir ? g.out_off : g.in_off;
                 const int32_t *vl = c.L(v);
                 int64_t sum = nv;
                 for (int32_t b = 0; b < nv && sum <= n_items; b += 64) {
                     int32_t len = 0;
-                    if (b + (int32_t)threadIdx.x < nv) {
-                        const int32_t y = vl[b + threadIdx.x];
+                    if (b + lane < nv) {
+                        const int32_t y = vl[b + lane];
                         len = off[y + 1] - off[y];
                     }
 #pragma unroll
                     for (int o = 32; o > 0; o >>= 1) len += __shfl_xor(len, o, 64);
                     sum += len;
                 }
-                rev = sum <= n_items;
+                if (sum <= n_items) rm |= 1ull << j;
             }
-            if (rev) {
-                rm |= 1ull << j;
-            } else {
-                if (threadIdx.x == 0) {
-                    const VPred &p = c.Q->pred[v];
-                    // the edge itself is one in-edge (dir 0) or out-edge of
-                    // the neighbour: often all the degree its vertex asks for
-                    const bool degok = dir ? p.qout <= 1 && p.qin == 0 : p.qin <= 1 && p.qout == 0;
-                    NTest &t = c.s->nbl[k];
-                    t.v = (int8_t)v;
-                    t.dir = (int8_t)dir;
-                    t.mode = (int8_t)(mode == 1 && degok && g.typed_adj && !c.Q->homo ? 2 : mode);
-                    t.e = (int8_t)e;
-                    t.rel = rel;
-                    t.label = p.label;
-                    t.pin = p.pin;
-                    t.qdeg = p.qout | p.qin << 8;
-                }
-                ++k;
-            }
+            keep = keep && !((rm >> lane) & 1ull);
         }
-        if (threadIdx.x == 0) {
+        // The tests in the order of what they cost and drop: relation and
+        // type (or a pin) given, type, relation, neither, and last a parent
+        // test kept for its pushes alone.
+        const VPred &p = c.Q->pred[td.v];
+        const int32_t lab = p.label, pin = p.pin;
+        const int rank = known ? 4 : lab >= 0 || pin >= 0 ? (td.rel >= 0 || pin >= 0 ? 0 : 1)
+                                                          : (td.rel >= 0 ? 2 : 3);
+        int at = 0, n = 0;
+#pragma unroll
+        for (int r = 0; r < 5; ++r) {
+            const uint64_t m = __ballot(keep && rank == r);
+            if (rank == r) at = n + __popcll(m & lanemask_lt(lane));
+            n += __popcll(m);
+        }
+        if (keep) {
+            // the edge itself is one in-edge (dir 0) or out-edge of the
+            // neighbour: often all the degree its vertex asks for
+            const bool degok = td.dir ? p.qout <= 1 && p.qin == 0 : p.qin <= 1 && p.qout == 0;
+            NTest &t = c.s->nbl[at];
+            t.v = td.v;
+            t.dir = td.dir;
+            t.mode = (int8_t)(td.mode == 1 && degok && g.typed_adj && !c.Q->homo ? 2 : td.mode);
+            t.known = known;
+            t.rel = td.rel;
+            t.label = lab;
+            t.pin = pin;
+            t.qdeg = p.qout | p.qin << 8;
+        }
+        const uint64_t sp = __ballot(spar);
+        if (lane == 0) {
             c.s->revmask = rm;
-            c.s->nnbl = k;
-            c.s->skippar = skippar;
+            c.s->nnbl = n;
+            c.s->skippar = sp != 0;
         }
     }
     __syncthreads();
@@ -1247,9 +1459,16 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
     if (ncount == 0) {
         // every test was known to hold or done from the other side
     } else if (n_items <= NW) {
-        int32_t *def = defer_list(c, st);
-        for (int32_t it = 0; it < n_items; ++it) item_wg(c, st, nb, ncount, ul[it], ub, fb, def);
-        if (def) push_deferred(c, st, nb, ncount, def, fb);
+        // a wave per candidate; those with a long row get the whole workgroup
+        filter_items(c, LdsCtr{c.s}, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
+        __syncthreads();
+        const int32_t nl = c.s->nbig;
+        if (nl > 0) {
+            int32_t *def = defer_list(c, st);
+            const int32_t *ov = (const int32_t *)c.slab;
+            for (int32_t it = 0; it < nl; ++it) item_wg(c, st, nb, ncount, ov[it], ub, fb, def);
+            if (def) push_deferred(c, st, nb, ncount, def, fb);
+        }
     } else {
         // a step of many candidates is shared whether or not workgroups are
         // idle yet (in a batch they become idle while it runs)
@@ -1258,8 +1477,7 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         if (share)
             shared_items(c, st, nb, ncount, ul, ub, revd, n_items, helpers, fb);
         else
-            filter_items(c, LdsCtr{c.s}, st.push != 0, nb, ncount, ul, ub, revd,
-                         lanes_for(n_items, c.gmax), 0, n_items, fb);
+            filter_items(c, LdsCtr{c.s}, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
         const int lane = threadIdx.x & 63;
         int32_t *ov = (int32_t *)c.slab;
         __syncthreads();
@@ -1384,14 +1602,14 @@ __device__ __forceinline__ void filter_step(Ctx &c, const NStep &st) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if ((int)threadIdx.x < st.count) {
-            const NNbr &d = c.Q->nbr[st.first + threadIdx.x];
-            const int e = d.e, dir = d.dir;
-            c.s->okv[2 * e + dir] = c.s->ver[d.v];
-            if (st.push) c.s->okv[2 * e + 1 - dir] = c.s->ver[u];
+        if (in) {
+            c.s->okv[2 * td.e + td.dir] = c.s->ver[td.v];
+            if (st.push) c.s->okv[2 * td.e + 1 - td.dir] = c.s->ver[u];
         }
     }
+    const int32_t removed = c.s->removed;
     __syncthreads();
+    return removed;
 }
 
 // ---------------------------------------------------------------------------
@@ -2403,9 +2621,9 @@ __device__ __forceinline__ void clear_slot(Ctx &c, bool full) {
 }
 
 __device__ __forceinline__ void run_query(Ctx &c) {
-    const NQuery &Q = *c.Q;
     const DevGraph &g = c.g;
     Smem &s = *c.s;
+    const NQuery &Q = s.query;
     const int n = Q.n;
     if (threadIdx.x < SGM_MAX_QV) {
         s.cnt[threadIdx.x] = 0;
@@ -2474,10 +2692,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
     for (int r = 0; r < rounds && !aborted(c) && Q.n_ref > 0; ++r) {
         int removed = 0;
         for (int i = 0; i < Q.n_ref && !aborted(c); ++i) {
-            filter_step(c, Q.steps[Q.n_init + i]);
+            removed += filter_step(c, Q.steps[Q.n_init + i]);
             ev(c, SGM_EV_REFINE);
-            removed += s.removed;  // read after the step's final barrier
-            __syncthreads();
         }
         if (Q.refine_rounds < 0 && removed == 0) break;
     }
@@ -2500,7 +2716,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
     int64_t rows = 0;
     int32_t *table = nullptr;
     if (!s.empty) {
-        for (int u = 0; u < n && !aborted(c); ++u) sort_list(c, u);
+        for (int u = 0; u < n && !aborted(c); ++u)
+            if (s.cnt[u] > 1) sort_list(c, u);
         ev(c, SGM_EV_LISTS);
         if (Q.m == 0) {
             table = c.L(0);
@@ -2988,7 +3205,7 @@ __device__ __forceinline__ Ctx slot_ctx(const NArgs &a, Smem &s, unsigned char *
     uint64_t *bits = a.bits + (int64_t)slot * (SGM_MAX_QV + 1) * nwords;
     int32_t *lists = a.lists + (int64_t)slot * SGM_MAX_QV * a.lcap;
     char *slab = a.slab + (int64_t)slot * a.slab_bytes;
-    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.rootbits, &a.qs[q], &s,
+    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.rootbits, &s.query, &s,
                bits, bits + (int64_t)SGM_MAX_QV * nwords, lists, slab, dyn,
                a.trace ? a.trace + (int64_t)q * SGM_TRACE_CAP : nullptr, a.group_lanes,
                a.wg_rows, a.join_policy,
@@ -3027,8 +3244,8 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
     int32_t n = 0;
     while (ch >= 0) {
         if (kind == 0) {
-            filter_items(c, BoardCtr{j}, st.push != 0, s.nbl, ncount, hul, c.B(st.u), revd, G,
-                         ch * K, min(n_items, ch * K + K), fb, nodefer);
+            filter_items(c, BoardCtr{j}, st.push != 0, s.nbl, ncount, hul, c.B(st.u), revd, ch * K,
+                          min(n_items, ch * K + K), fb, nodefer);
         } else if (kind == 1) {
             push_segment(c, BoardCtr{j}, s.nbl, seg[ch], fb);
         } else if (kind == 3) {
@@ -3184,7 +3401,11 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
             continue;
         }
         Ctx c = slot_ctx(a, s, dyn, blockIdx.x, q, slab_cap);
+        static_assert(sizeof(NQuery) % 4 == 0, "staged as ints");
+        for (int i = threadIdx.x; i < (int)(sizeof(NQuery) / 4); i += NT)
+            ((int32_t *)&s.query)[i] = ((const int32_t *)&Q)[i];
         if (threadIdx.x == 0) s.nev = 0;
+        __syncthreads();
         run_query(c);
         __syncthreads();
         if (s.hostord) slab_cap = s.pin_off;  // keep that table until the launch ends

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import paper_1807_08804_amd as P
-from tests.micro import random_graph, random_query
+from tests.micro import MicroGraph, random_graph, random_query
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +61,32 @@ def test_types_in_adjacency_entries(n_types, n_rels, tbase, rbase):
             q2.elabel = np.where(q.elabel >= 0, q.elabel + rbase, q.elabel).astype(np.int32)
             assert np.array_equal(g.match_query(q2), og.match_query(q2))
         g.close()
+
+
+@pytest.mark.parametrize("V,deg,n_types,n_rels", [
+    (70, 1, 2, 1), (70, 6, 2, 2), (600, 3, 2, 2), (600, 40, 40, 8), (2000, 97, 60, 6),
+    (3000, 130, 80, 8), (1200, 600, 300, 16),
+])
+def test_flat_filter_rows(V, deg, n_types, n_rels):
+    """Filter steps whose candidates' rows are dealt to the lanes end to end:
+    rows shorter and longer than a wave's window, around the limits where a
+    row goes to the next tier, one candidate to several per lane; with the
+    steps shared over helpers and not."""
+    rng = np.random.default_rng(V + deg)
+    src = np.repeat(np.arange(V), rng.integers(max(0, deg - 2), deg + 3, V))
+    # a few rows up to five times as long
+    src = np.concatenate([src, np.repeat(rng.integers(0, V, 6), 4 * deg)])
+    mg = MicroGraph(V, src, rng.integers(0, V, len(src)), rng.integers(0, n_rels, len(src)),
+                    rng.integers(0, n_types, V))
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    qs = [random_query(rng, int(rng.integers(2, 6)), n_types, n_rels, V, p_any_label=p,
+                       p_any_rel=p, p_pin=0.2, extra=2) for p in (0.0, 0.1, 0.5) for _ in range(4)]
+    for tune in (dict(), dict(help_items=64, helpers=96), dict(help_items=0)):
+        g.set_tuning(**tune)
+        for i, q in enumerate(qs):
+            print("case: query", i, tune, flush=True)
+            if g.match_query(q, count_only=True) > 200000:
+                continue
+            assert np.array_equal(g.match_query(q), og.match_query(q))
