@@ -154,7 +154,7 @@ struct DevCounters {
 };
 
 // Resources of the persistent per-query kernel on one stream: slots,
-// descriptors, root sweep rows and the output arena.
+// descriptors and the output arena.
 struct NarrowCtx {
     hipStream_t stream = nullptr;
     // capacities of a context for queries that outgrew a regular slot (0:
@@ -170,9 +170,6 @@ struct NarrowCtx {
     int qcap = 0;
     NQuery *d_q = nullptr, *h_q = nullptr;
     NResult *d_res = nullptr, *h_res = nullptr;
-    VPred *d_preds = nullptr, *h_preds = nullptr;  // distinct root predicates
-    int root_cap = 0;
-    uint64_t *d_rootbits = nullptr;
     int32_t *d_out = nullptr;
     int64_t out_cap = 0;
     // [0] queue, [1] out used, [2] helper counters (posted steps, slot
@@ -189,22 +186,20 @@ struct NarrowCtx {
     // the context's own stream orders the next large table
     hipStream_t copy = nullptr;
     std::vector<hipEvent_t> copy_ev;
-    // one batch as a HIP graph: upload descriptors, upload root predicates,
-    // root sweep, persistent kernel, read back results, read back counters.
+    // one batch as a HIP graph: upload descriptors, reset counters,
+    // persistent kernel, read back results, counters and the arena's head.
     // Built on first use; every launch updates all node parameters.
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    hipGraphNode_t gn[7] = {};
-    SweepArgs sa{};
+    hipGraphNode_t gn[6] = {};
     NArgs na{};
     // parameters of the instantiated graph's last launch: nodes whose
     // parameters did not change are not updated again
-    SweepArgs last_sa{};
     NArgs last_na{};
-    int last_grid = -1, last_sweep_grid = -1;
-    size_t last_qb = 0, last_pb = 0, last_rb = 0;
+    int last_grid = -1;
+    size_t last_qb = 0, last_rb = 0;
     const void *last_hout = nullptr;
-    void *kargs[9] = {};
+    void *kargs[2] = {};
 };
 
 }  // namespace
@@ -233,7 +228,9 @@ struct sgm_graph {
     // device memory owned by the graph
     int32_t *d_out_off = nullptr, *d_in_off = nullptr;
     int2 *d_vinfo = nullptr;
-    int4 *d_vrow = nullptr;
+    int4 *d_vrow = nullptr, *d_trow = nullptr;
+    int32_t *d_tverts = nullptr;
+    std::vector<int32_t> type_off;  // first vertex of each type in d_tverts
     int2 *d_out_adj = nullptr, *d_in_adj = nullptr;
     int2 *d_out_ta = nullptr, *d_out_tb = nullptr, *d_in_ta = nullptr, *d_in_tb = nullptr;
     int32_t *d_hub_of = nullptr, *d_hub_toff = nullptr;
@@ -431,7 +428,7 @@ void free_graph_mem(sgm_graph *g) {
                   g->d_bits,    g->d_lists,  g->d_prefix, g->d_big,     g->d_desc,
                   g->d_cnt,     g->d_slots,  g->d_out_ta, g->d_out_tb,  g->d_in_ta,
                   g->d_in_tb,   g->d_hub_of, g->d_hub_toff, g->d_map_off, g->d_map_ids,
-                  g->d_vrow};
+                  g->d_vrow,    g->d_trow,   g->d_tverts};
     for (void *p : dp) {
         bool host = false;
         for (const auto &b : g->host_graph_bufs) host |= b.second == p;
@@ -1563,7 +1560,6 @@ struct Query {
 // ---------------------------------------------------------------------------
 
 constexpr int kNarrowMaxSlots = 512;                 // 2 workgroups per CU
-constexpr int32_t kTypeTable = 1024;                 // vertex types covered by the sweep's table
 constexpr int64_t kNarrowSlabMin = 8ll << 20;        // per slot, small graphs
 constexpr int64_t kNarrowSlabMax = 32ll << 20;       // per slot, large graphs (served form)
 // A graph's own batch context: 40 B per data vertex up to 160 MB per slot
@@ -1612,14 +1608,11 @@ void narrow_free(NarrowCtx &nw) {
     dev_free(nw.slab);
     dev_free(nw.d_q);
     dev_free(nw.d_res);
-    dev_free(nw.d_preds);
-    dev_free(nw.d_rootbits);
     dev_free(nw.d_out);
     dev_free(nw.d_ctr);
     dev_free(nw.d_board);
     host_free(nw.h_q);
     host_free(nw.h_res);
-    host_free(nw.h_preds);
     host_free(nw.h_ctr);
     host_free(nw.h_out);
     dev_free(nw.d_trace);
@@ -1643,7 +1636,7 @@ void narrow_free(NarrowCtx &nw) {
     nw.slab_want = keep.slab_want;
 }
 
-void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq, int nroot) {
+void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     if (nw.lcap == 0) {
         nw.lcap = std::min<int32_t>(g->V, nw.lcap_want ? nw.lcap_want : kNarrowListCap);
         nw.slab_bytes = nw.slab_want ? nw.slab_want : narrow_slab_bytes(g, nw.serve);
@@ -1687,26 +1680,11 @@ void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq, int nroot) {
         HIPX(hipHostMalloc(&nw.h_res, sizeof(NResult) * nq, hipHostMallocDefault));
         nw.qcap = nq;
     }
-    if (nroot > nw.root_cap) {
-        HIPX(hipStreamSynchronize(nw.stream));
-        dev_free(nw.d_preds);
-        dev_free(nw.d_rootbits);
-        host_free(nw.h_preds);
-        nw.root_cap = 0;
-        // root predicates, then the sweep's type-offset table (at most
-        // kTypeTable + 1 ints)
-        const size_t pb = sizeof(VPred) * nroot + sizeof(int32_t) * (kTypeTable + 1);
-        HIPX(hipMalloc(&nw.d_preds, pb));
-        HIPX(hipHostMalloc(&nw.h_preds, pb, hipHostMallocDefault));
-        HIPX(hipMalloc(&nw.d_rootbits, sizeof(uint64_t) * (size_t)g->nwords * nroot));
-        nw.root_cap = nroot;
-    }
 }
 
 // Pack one validated query and its plan; false if it exceeds the packed
 // descriptor's capacity (the query then runs on the multi-kernel path).
-bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, int *root_slot_next,
-                Plan *pl_out) {
+bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, Plan *pl_out) {
     Program pr;
     build_program(qi, pl, g->opts.low_conn_degree, g->opts.refine_reversed, &pr);
     if ((int)(pr.init.size() + pr.refine.size()) > kNMaxSteps || (int)pr.nbr.size() > kNMaxNbr)
@@ -1721,9 +1699,17 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, int *
         nq->elabel[e] = qi.elabel[e];
     }
     nq->root = pl.visit[0];
-    // unpinned roots get their bitmap row from the batch's root sweep; the
-    // row is assigned per distinct predicate after packing
-    nq->root_slot = qi.pin[nq->root] >= 0 ? -1 : (*root_slot_next)++;
+    // an unpinned root starts from its range of the vertices in type order
+    const int32_t lab = qi.label[nq->root];
+    if (qi.pin[nq->root] >= 0) {
+        nq->root_lo = nq->root_hi = -1;
+    } else if (lab < 0) {
+        nq->root_lo = 0;
+        nq->root_hi = g->V;
+    } else {
+        nq->root_lo = lab < g->n_types ? g->type_off[lab] : 0;
+        nq->root_hi = lab < g->n_types ? g->type_off[lab + 1] : 0;
+    }
     nq->n_init = (int)pr.init.size();
     nq->n_ref = (int)pr.refine.size();
     nq->refine_rounds = g->opts.refine_rounds < 0 ? -1 : std::min(g->opts.refine_rounds, 32);
@@ -1755,7 +1741,6 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, int *
 struct NarrowJob {
     std::vector<int> packed;   // query indices, in descriptor order
     std::vector<Plan> plans;
-    int nroot = 0;
     int64_t t0 = 0;
     bool traced = false;
 };
@@ -1770,7 +1755,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     job.packed.clear();
     job.plans.clear();
     const int max_slots = nw.slab_want ? kBigSlots : kNarrowMaxSlots;
-    narrow_reserve(g, nw, std::min(count, max_slots), count, 0);
+    narrow_reserve(g, nw, std::min(count, max_slots), count);
     // The work queue hands out descriptors in order: the expected-longest
     // query (an unpinned root with many candidates of its type, then more
     // query vertices), then the expected-shortest, then the next longest,
@@ -1812,16 +1797,14 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
         }
         order.swap(alt);
     }
-    // descriptors in queue order, packed in parallel (a root's sweep row is
-    // assigned below; here an unpinned root only gets a non-negative slot)
+    // descriptors in queue order, packed in parallel
     const int no = (int)order.size();
     std::vector<Plan> pls((size_t)no);
     std::vector<char> packed_ok((size_t)no, 0);
     parallel_for(no, 128, [&](int lo, int hi) {
         for (int k = lo; k < hi; ++k) {
             const int i = order[k];
-            int rs = 0;
-            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], &nw.h_q[k], &rs, &pls[k]);
+            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], &nw.h_q[k], &pls[k]);
         }
     });
     int np = 0;
@@ -1841,44 +1824,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
         job.plans.push_back(pls[k]);
         ++np;
     }
-    int nroot = 0;
     if (np == 0) return false;
-    // one sweep row per distinct root predicate (type, degree bounds), rows
-    // in (type, bounds) order with the untyped (-1) ones first, as the
-    // sweep expects
-    std::map<std::array<int32_t, 3>, int> row_of;
-    for (int i = 0; i < np; ++i) {
-        const NQuery &q = nw.h_q[i];
-        if (q.root_slot < 0) continue;
-        const VPred &p = q.pred[q.root];
-        row_of.emplace(std::array<int32_t, 3>{p.label, p.qout, p.qin}, 0);
-    }
-    std::vector<VPred> preds;
-    int n_any = 0;
-    for (auto &kv : row_of) {
-        kv.second = (int)preds.size();
-        preds.push_back(VPred{kv.first[0], -1, kv.first[1], kv.first[2]});
-        if (kv.first[0] < 0) ++n_any;
-    }
-    for (int i = 0; i < np; ++i) {
-        NQuery &q = nw.h_q[i];
-        if (q.root_slot < 0) continue;
-        const VPred &p = q.pred[q.root];
-        q.root_slot = row_of[std::array<int32_t, 3>{p.label, p.qout, p.qin}];
-    }
-    nroot = (int)preds.size();
-    job.nroot = nroot;
-    // at least one predicate row, so that a graph's copy node never has size 0
-    narrow_reserve(g, nw, std::min(np, max_slots), np, std::max(nroot, 1));
-    if (nroot) std::memcpy(nw.h_preds, preds.data(), sizeof(VPred) * nroot);
-    else nw.h_preds[0] = VPred{-1, -1, 0, 0};
-    // type_off[t] = first predicate of type >= t (predicates are sorted)
-    const int32_t n_types = nroot && g->n_types <= kTypeTable ? g->n_types : 0;
-    int32_t *type_off = (int32_t *)(nw.h_preds + std::max(nroot, 1));
-    for (int32_t t = 0, j = 0; t <= n_types && n_types > 0; ++t) {
-        while (j < nroot && preds[j].label < t) ++j;
-        type_off[t] = j;
-    }
     hipStream_t st = nw.stream;
     NArgs a{};
     a.g = g->dg;
@@ -1891,15 +1837,12 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     a.lcap = nw.lcap;
     a.slab = nw.slab;
     a.slab_bytes = nw.slab_bytes;
-    a.rootbits = nw.d_rootbits;
     a.out = nw.d_out;
     a.out_cap = nw.out_cap;
     a.out_used = nw.d_ctr + 1;
     a.group_lanes = g->tune.group_lanes;
     a.wg_rows = g->tune.wg_rows;
     a.join_policy = g->tune.join_policy;
-    nw.sa = SweepArgs{g->dg,       nw.d_preds, nroot, n_any, nw.d_rootbits, nw.d_ctr,
-                      (const int32_t *)(nw.d_preds + std::max(nroot, 1)), n_types};
     const int slot_grid =
         std::min(np, nw.slab_want ? nw.slots : std::min(nw.slots, g->tune.slots));
     // Shared filter steps need every workgroup of the launch resident at
@@ -1921,24 +1864,21 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     if (g->opts.graphs && !(profiled && g->opts.profile)) {
         nw.na = a;
         hipKernelNodeParams ps, pn;
-        narrow_node_params(&nw.sa, &nw.na, grid, nw.kargs, &ps, &pn);
-        const size_t qb = sizeof(NQuery) * np,
-                     pb = sizeof(VPred) * std::max(nroot, 1) + sizeof(int32_t) * (n_types + 1);
+        narrow_node_params(&nw.d_ctr, &nw.na, grid, nw.kargs, &ps, &pn);
+        const size_t qb = sizeof(NQuery) * np;
         const size_t rb = sizeof(NResult) * np, cb = sizeof(unsigned long long) * 2;
         const size_t ob = sizeof(int32_t) * kOutPrefix;
         const auto H2D = hipMemcpyHostToDevice, D2H = hipMemcpyDeviceToHost;
         if (!nw.gexec) {
             HIPX(hipGraphCreate(&nw.graph, 0));
             HIPX(hipGraphAddMemcpyNode1D(&nw.gn[0], nw.graph, nullptr, 0, nw.d_q, nw.h_q, qb, H2D));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[1], nw.graph, &nw.gn[0], 1, nw.d_preds, nw.h_preds,
-                                         pb, H2D));
-            HIPX(hipGraphAddKernelNode(&nw.gn[2], nw.graph, &nw.gn[1], 1, &ps));
-            HIPX(hipGraphAddKernelNode(&nw.gn[3], nw.graph, &nw.gn[2], 1, &pn));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[4], nw.graph, &nw.gn[3], 1, nw.h_res, nw.d_res, rb,
+            HIPX(hipGraphAddKernelNode(&nw.gn[1], nw.graph, &nw.gn[0], 1, &ps));
+            HIPX(hipGraphAddKernelNode(&nw.gn[2], nw.graph, &nw.gn[1], 1, &pn));
+            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[3], nw.graph, &nw.gn[2], 1, nw.h_res, nw.d_res, rb,
                                          D2H));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[5], nw.graph, &nw.gn[4], 1, nw.h_ctr, nw.d_ctr, cb,
+            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[4], nw.graph, &nw.gn[3], 1, nw.h_ctr, nw.d_ctr, cb,
                                          D2H));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[6], nw.graph, &nw.gn[5], 1, nw.h_out, nw.d_out, ob,
+            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[5], nw.graph, &nw.gn[4], 1, nw.h_out, nw.d_out, ob,
                                          D2H));
             HIPX(hipGraphInstantiate(&nw.gexec, nw.graph, nullptr, nullptr, 0));
         } else {
@@ -1946,30 +1886,21 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
             // every pointer a node uses is compared here
             if (qb != nw.last_qb || nw.na.qs != nw.last_na.qs)
                 HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[0], nw.d_q, nw.h_q, qb, H2D));
-            if (pb != nw.last_pb || nw.sa.preds != nw.last_sa.preds)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[1], nw.d_preds, nw.h_preds,
-                                                       pb, H2D));
-            if (std::memcmp(&nw.sa, &nw.last_sa, sizeof(SweepArgs)) != 0 ||
-                (int)ps.gridDim.x != nw.last_sweep_grid)
-                HIPX(hipGraphExecKernelNodeSetParams(nw.gexec, nw.gn[2], &ps));
             if (std::memcmp(&nw.na, &nw.last_na, sizeof(NArgs)) != 0 || grid != nw.last_grid)
-                HIPX(hipGraphExecKernelNodeSetParams(nw.gexec, nw.gn[3], &pn));
+                HIPX(hipGraphExecKernelNodeSetParams(nw.gexec, nw.gn[2], &pn));
             if (rb != nw.last_rb || nw.na.res != nw.last_na.res)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[4], nw.h_res, nw.d_res, rb,
+                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[3], nw.h_res, nw.d_res, rb,
                                                        D2H));
             if (nw.na.queue != nw.last_na.queue)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[5], nw.h_ctr, nw.d_ctr, cb,
+                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[4], nw.h_ctr, nw.d_ctr, cb,
                                                        D2H));
             if (nw.h_out != nw.last_hout || nw.na.out != nw.last_na.out)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[6], nw.h_out, nw.d_out, ob,
+                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[5], nw.h_out, nw.d_out, ob,
                                                        D2H));
         }
-        nw.last_sa = nw.sa;
         nw.last_na = nw.na;
         nw.last_grid = grid;
-        nw.last_sweep_grid = (int)ps.gridDim.x;
         nw.last_qb = qb;
-        nw.last_pb = pb;
         nw.last_rb = rb;
         nw.last_hout = nw.h_out;
         HIPX(hipGraphLaunch(nw.gexec, st));
@@ -1977,14 +1908,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
         return true;
     }
     HIPX(hipMemcpyAsync(nw.d_q, nw.h_q, sizeof(NQuery) * np, hipMemcpyHostToDevice, st));
-    if (nroot)
-        HIPX(hipMemcpyAsync(nw.d_preds, nw.h_preds,
-                            sizeof(VPred) * nroot + sizeof(int32_t) * (n_types + 1),
-                            hipMemcpyHostToDevice, st));
-    {
-        Prof p(g, SGM_K_CHECK, nroot ? (8.0 + 0.125 * nroot) * g->V : 0.0, profiled && nroot > 0);
-        launch_root_sweep(st, nw.sa);
-    }
+    launch_reset(st, nw.d_ctr);
     if (job.traced) {
         if (np > nw.trace_cap) {
             HIPX(hipStreamSynchronize(st));
@@ -2127,7 +2051,7 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
         for (int u = 0; u < qi.n; ++u)
             stt.peak_rows = std::max(stt.peak_rows, (int64_t)r.level_rows[u]);
         stt.n_chunks = 1;
-        stt.n_launches = job.nroot ? 2 : 1;
+        stt.n_launches = 1;
         stt.ns_total = t1 - job.t0;
         stt.ns_filter = (int64_t)(r.ticks[0] * g->ns_per_tick);
         stt.ns_collect = (int64_t)(r.ticks[1] * g->ns_per_tick);
@@ -2510,6 +2434,20 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             for (int32_t v = 0; v < n_vertices; ++v)
                 vr[v] = make_int4(off[v], off[v + 1], in_off[v], in_off[v + 1]);
             g->d_vrow = dev_upload(vr);
+            // the vertices in type order, ascending within a type
+            g->type_off.assign((size_t)g->n_types + 1, 0);
+            for (int32_t t = 0; t < g->n_types; ++t)
+                g->type_off[t + 1] = g->type_off[t] + (int32_t)g->type_freq[t];
+            std::vector<int32_t> at(g->type_off.begin(), g->type_off.end() - 1);
+            std::vector<int32_t> tv((size_t)n_vertices);
+            std::vector<int4> tr((size_t)n_vertices);
+            for (int32_t v = 0; v < n_vertices; ++v) {
+                const int32_t p = at[type[v]]++;
+                tv[p] = v;
+                tr[p] = vr[v];
+            }
+            g->d_tverts = dev_upload(tv);
+            g->d_trow = dev_upload(tr);
         }
         if (g->n_types <= kHubTypesMax) {
             HubIndex hx;
@@ -2541,6 +2479,8 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
         g->dg.in_adj = g->d_in_adj;
         g->dg.vinfo = g->d_vinfo;
         g->dg.vrow = g->d_vrow;
+        g->dg.tverts = g->d_tverts;
+        g->dg.trow = g->d_trow;
         g->dg.out_ta = g->d_out_ta;
         g->dg.out_tb = g->d_out_tb;
         g->dg.in_ta = g->d_in_ta;
@@ -3344,7 +3284,7 @@ int sgm_server_create(sgm_graph *g, const sgm_serve_options *opts, sgm_server **
         for (auto &c : S->ctx) {
             HIPX(hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking));
             c.serve = true;
-            narrow_reserve(g, c, std::min(o.max_batch, kNarrowMaxSlots), o.max_batch, 0);
+            narrow_reserve(g, c, std::min(o.max_batch, kNarrowMaxSlots), o.max_batch);
         }
     } catch (const DeviceError &e) {
         for (auto &c : S->ctx) {
@@ -3509,7 +3449,7 @@ int sgm_serve_replay(sgm_server *s, const sgm_query *qs, const int64_t *arrival_
 // ---------------------------------------------------------------------------
 // Single queries without allocation: every device buffer of the persistent
 // kernel's launch (one slot, descriptor, result, counters, helper board,
-// root sweep row, output arena) lives in one fixed array of device memory
+// output arena) lives in one fixed array of device memory
 // that each GPU holds until the process ends.
 // ---------------------------------------------------------------------------
 
@@ -3560,7 +3500,7 @@ __global__ void k_zero_words(uint64_t *p, int64_t n) {
 
 // Layout of the fixed area for a graph (byte offsets, 256-aligned).
 struct ScratchLayout {
-    int64_t bits, lists, slab, rootbits, preds, q, res, ctr, board, out, out_bytes;
+    int64_t bits, lists, slab, q, res, ctr, board, out, out_bytes;
     int32_t lcap;
     bool fits;
 };
@@ -3582,11 +3522,11 @@ ScratchLayout scratch_layout(const sgm_graph *g) {
     L.ctr = take(sizeof(unsigned long long) * 3);
     L.q = take(sizeof(NQuery));
     L.res = take(sizeof(NResult));
-    L.preds = take(sizeof(VPred));
     L.bits = take((int64_t)(SGM_MAX_QV + 1) * g->nwords * 8);
     L.lists = take((int64_t)SGM_MAX_QV * L.lcap * 4);
     L.slab = take(kScratchSlab);
-    L.rootbits = take((int64_t)g->nwords * 8);
+    // room kept free: the limits on graphs and rows stay what they were
+    (void)take((int64_t)g->nwords * 8);
     L.out = o;
     L.out_bytes = (kScratchBytes - o) & ~255ll;
     L.fits = L.out_bytes >= kScratchMinOut && kScratchSlab >= 8ll * L.lcap;
@@ -3619,15 +3559,10 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
     if (make_plan(qi, g->V, g->type_freq.data(), g->n_types, &pl) != SGM_OK) return SGM_EINVAL;
     NQuery nq;
     Plan pl_out;
-    int root_slots = 0;
-    if (!pack_query(g, qi, pl, &nq, &root_slots, &pl_out)) {
+    if (!pack_query(g, qi, pl, &nq, &pl_out)) {
         g_last_error = "query plan exceeds the packed descriptor";
         return SGM_EUNSUPPORTED;
     }
-    const bool sweep = nq.root_slot >= 0;
-    if (sweep) nq.root_slot = 0;
-    const VPred rootp = VPred{nq.pred[nq.root].label, -1, nq.pred[nq.root].qout,
-                              nq.pred[nq.root].qin};
     std::lock_guard<std::mutex> call(g_scratch_call_mu[g->device]);
     std::lock_guard<std::mutex> lk(g->mu);
     char *base = (char *)g_scratch_ptr[g->device];
@@ -3638,7 +3573,7 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
         unsigned long long *ctr = (unsigned long long *)(base + L.ctr);
         // what must start at zero: the helper board entry (every call), the
         // slot bitmaps where an earlier call on another graph left other
-        // data (the kernel clears the bitmaps it sets); the sweep zeroes the
+        // data (the kernel clears the bitmaps it sets); a reset zeroes the
         // work queue, the output counter and the helper counters. The zero
         // fill covers the front of the area, so it runs before the uploads.
         const int64_t bit_words = (int64_t)(SGM_MAX_QV + 1) * g->nwords;
@@ -3649,11 +3584,7 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
                            (uint64_t *)base, zero_words);
         HIPX(hipGetLastError());
         HIPX(hipMemcpyAsync(base + L.q, &nq, sizeof(NQuery), hipMemcpyHostToDevice, st));
-        if (sweep)
-            HIPX(hipMemcpyAsync(base + L.preds, &rootp, sizeof(VPred), hipMemcpyHostToDevice, st));
-        launch_root_sweep(st, SweepArgs{g->dg, (const VPred *)(base + L.preds), sweep ? 1 : 0,
-                                        sweep && rootp.label < 0 ? 1 : 0,
-                                        (uint64_t *)(base + L.rootbits), ctr, nullptr, 0});
+        launch_reset(st, ctr);
         HIPX(hipGetLastError());
         NArgs a{};
         a.g = g->dg;
@@ -3666,7 +3597,6 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
         a.lcap = L.lcap;
         a.slab = base + L.slab;
         a.slab_bytes = kScratchSlab;
-        a.rootbits = (const uint64_t *)(base + L.rootbits);
         a.out = (int32_t *)(base + L.out);
         a.out_cap = L.out_bytes / 4;
         a.out_used = ctr + 1;

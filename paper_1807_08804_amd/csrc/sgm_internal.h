@@ -31,6 +31,10 @@ struct DevGraph {
     // out_off[v + 1]; z, w: the same of in_off): a candidate's rows cost one
     // memory sector instead of two or three
     const int4 *vrow;
+    // the vertices in type order (ascending within a type) and their row
+    // extents in the same order
+    const int32_t *tverts;
+    const int4 *trow;
     // An adjacency entry's second word is its relation (y & rel_mask) and,
     // with typed_adj, the type of the entry's vertex above it (y >> 16), so
     // that a test against a typed query vertex reads no memory for the

@@ -48,7 +48,9 @@ struct NQuery {
     VPred pred[SGM_MAX_QV];
     int32_t esrc[SGM_MAX_QE], edst[SGM_MAX_QE], elabel[SGM_MAX_QE];
     int32_t root;           // first vertex of the visit order
-    int32_t root_slot;      // row of the root sweep output, -1 if the root is pinned
+    // the root's range in DevGraph::tverts (its type's vertices, or all of
+    // them for an untyped root); root_lo = -1 if the root is pinned
+    int32_t root_lo, root_hi;
     int32_t n_init, n_ref;  // explore steps, then refine steps (one round)
     int32_t refine_rounds;  // -1: until nothing is removed
     uint32_t proj;          // projected columns (bit u = query vertex u kept; 0: all)
@@ -166,6 +168,7 @@ struct HelpJob {
     // kind 0: 1 when the chunks' items are long rows, which one wave takes
     // up to wg_rows entries (longer ones go on to the workgroup tier)
     int32_t nodefer;
+    int32_t root;  // kind 0: the degree bounds of a root step, or -1
     int32_t cnt[SGM_MAX_QV];
     NTest nbl[SGM_MAX_QE];
     // kind 2: chunks of a join level's parent rows; jrows counts the output
@@ -186,7 +189,6 @@ struct NArgs {
     int32_t lcap;
     char *slab;               // [slots][slab_bytes]
     int64_t slab_bytes;
-    const uint64_t *rootbits; // [n_root_slots][nwords] root sweep output
     int32_t *out;             // output arena (int32 rows)
     int64_t out_cap;          // in int32 elements
     unsigned long long *out_used;
@@ -211,30 +213,13 @@ struct NArgs {
     int64_t host_order_rows;
 };
 
-// Root sweep: rootbits[j][w] = vertices satisfying predicate j, for the
-// distinct predicates of a batch's unpinned roots. It also zeroes ctr[0..2]
-// (the persistent kernel's work queue, output-arena use and helper
-// counters), so it runs
-// before every persistent launch, with n_pred = 0 when no root needs it.
-struct SweepArgs {
-    DevGraph g;
-    const VPred *preds;   // untyped first, then by type
-    int32_t n_pred;
-    int32_t n_any;        // predicates without a type
-    uint64_t *rootbits;
-    unsigned long long *ctr;
-    // type_off[t] = first predicate with type >= t, for t in [0, n_types];
-    // n_types = 0: no table (types found by binary search)
-    const int32_t *type_off;
-    int32_t n_types;
-};
-void launch_root_sweep(hipStream_t s, const SweepArgs &a);
+void launch_reset(hipStream_t s, unsigned long long *ctr);
 void launch_narrow(hipStream_t s, const NArgs &a, int grid);
-// Kernel-node parameters of the sweep and of the persistent kernel for a
-// HIP graph. The argument pointers refer to *sa, *na and args[0..8], which
-// must stay valid until the parameters have been handed to HIP.
-void narrow_node_params(SweepArgs *sa, NArgs *na, int narrow_grid, void **args,
-                        hipKernelNodeParams *sweep, hipKernelNodeParams *narrow);
+// Kernel-node parameters of the counters' reset and of the persistent kernel
+// for a HIP graph. The argument pointers refer to *ctr, *na and args[0..1],
+// which must stay valid until the parameters have been handed to HIP.
+void narrow_node_params(unsigned long long **ctr, NArgs *na, int narrow_grid, void **args,
+                        hipKernelNodeParams *reset, hipKernelNodeParams *narrow);
 size_t narrow_lds_bytes();
 
 }  // namespace sgm

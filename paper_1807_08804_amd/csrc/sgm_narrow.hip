@@ -7,8 +7,9 @@
 // whose queue ran dry) claim chunks of them.
 //
 // Phases (thesis Ch. 3):
-//   root candidates  -- kernel_check / kernel_collect of Alg. 3.2 (the sweep
-//                       itself runs once for a whole batch in k_root_sweep);
+//   root candidates  -- kernel_check / kernel_collect of Alg. 3.2, part of the
+//                       first explore step (a range of the graph's vertices
+//                       in type order);
 //   explore          -- kernel_explore of Alg. 3.2 along the spanning tree;
 //   refine           -- Sec. "Candidate Nodes Refinement" (prune only);
 //   candidate edges  -- Sec. "Joining Phase", two-step output per key;
@@ -134,7 +135,6 @@ struct Ctx {
     int32_t *out;
     int64_t out_cap;
     unsigned long long *out_used;
-    const uint64_t *rootbits;
     const NQuery *Q;
     Smem *s;
     uint64_t *bits;     // slot bitmaps [(SGM_MAX_QV + 1) * nwords]
@@ -378,9 +378,9 @@ __device__ __forceinline__ void compact_list(Ctx &c, int u) {
 }
 
 // Rebuild list u from its bitmap in ascending order (O(V/64) words).
-__device__ __forceinline__ void list_from_bits(Ctx &c, int u, const uint64_t *src, bool copy_bits) {
+__device__ __forceinline__ void list_from_bits(Ctx &c, int u) {
     const int32_t nwords = c.g.nwords;
-    uint64_t *b = c.B(u);
+    const uint64_t *src = c.B(u);
     int32_t *l = c.L(u);
     int64_t out = 0;
     // eight consecutive words per thread, all read before any is used (a
@@ -394,7 +394,6 @@ __device__ __forceinline__ void list_from_bits(Ctx &c, int u, const uint64_t *sr
         int32_t cnt = 0;
 #pragma unroll
         for (int k = 0; k < kW; ++k) {
-            if (copy_bits && w0 + k < nwords) b[w0 + k] = wd[k];
             cnt += __popcll(wd[k]);
         }
         int64_t tot;
@@ -417,7 +416,7 @@ __device__ __forceinline__ void list_from_bits(Ctx &c, int u, const uint64_t *sr
     __syncthreads();
     if (threadIdx.x == 0 && !c.s->abort_) {
         c.s->cnt[u] = (int32_t)out;
-        add_bytes(c, (copy_bits ? 16ull : 8ull) * nwords + 4ull * out);
+        add_bytes(c, 8ull * nwords + 4ull * out);
     }
     __syncthreads();
 }
@@ -437,7 +436,7 @@ __device__ __forceinline__ void sort_list(Ctx &c, int u) {
     const int64_t cost_bitonic = (int64_t)lg * (lg + 1) / 2 * ((N / 2 + NT - 1) / NT);
     const int64_t cost_bits = 2 * ((c.g.nwords + 8 * NT - 1) / (8 * NT));
     if (n > kListSortCap || cost_bits < cost_bitonic) {
-        list_from_bits(c, u, c.B(u), false);
+        list_from_bits(c, u);
         return;
     }
     int32_t *l = c.L(u);
@@ -846,27 +845,73 @@ __device__ __forceinline__ FlatLds *flat_lds(Ctx &c) {
     return (FlatLds *)c.dyn + (threadIdx.x >> 6);
 }
 
+// The first step of a query with an unpinned root takes its candidates from
+// the graph's vertices in type order (DevGraph::tverts), not from a list: the
+// root's type is a contiguous range of them, its row extents lie beside it
+// (trow), and only the survivors enter the root's list and bitmap. Building
+// the whole type's list and bitmap first, as every other vertex of the type
+// was then dropped from them, cost the large graph's queries 80 us for one
+// workgroup before the step began, and a sweep of all vertices per batch.
+// root: degree bounds of such a step (least out-degree | least in-degree
+// << 8 | 1 << 16 when they are read from vinfo: a compressed graph's bounds
+// are not its row lengths), -1 for a step over a list.
+__device__ __forceinline__ bool root_ok(const DevGraph &g, int32_t root, int32_t up, int4 vr) {
+    int32_t od = vr.y - vr.x, id = vr.w - vr.z;
+    if (root >> 16) {
+        const int32_t y = g.vinfo[up].y;
+        od = y & 255;
+        id = y >> 8;
+    }
+    return od >= (root & 255) && id >= ((root >> 8) & 255);
+}
+
+// Candidates that pass to the overflow list at the start of the slab, which
+// no phase uses while filtering (lcap entries).
+template <class K>
+__device__ __forceinline__ void to_overflow(Ctx &c, const K &k, int32_t up) {
+    const int32_t p = atomicAdd(k.nbig(), 1);
+    if (p < c.lcap) ((int32_t *)c.slab)[p] = up;
+    else *k.abort_() = kWhyList;
+}
+
+// Survivors of a root step (the lanes in m) into u's list and bitmap.
+template <class K>
+__device__ __forceinline__ void keep_root(Ctx &c, const K &k, int u, uint64_t *ub, uint64_t m,
+                                          int32_t up, int lane) {
+    if (!m) return;
+    int32_t p = 0;
+    if (lane == 0) p = atomicAdd(k.cnt(u), __popcll(m));
+    p = __builtin_amdgcn_readlane(p, 0) + __popcll(m & lanemask_lt(lane));
+    if ((m >> lane) & 1ull) {
+        if (p < c.lcap) c.L(u)[p] = up;
+        else *k.abort_() = kWhyList;
+        atomicOr((unsigned long long *)&ub[up >> 6], 1ull << (up & 63));
+    }
+}
+
 // One wave, candidates ul[i0, i1) (at most 64, one per lane), the tests one
 // after the other: a candidate that fails one reads no row for the next.
 template <class K>
-__device__ __forceinline__ void wave_items(Ctx &c, const K &k, bool push, const NTest *nb,
-                                           int ncount, const int32_t *ul, int32_t i0, int32_t i1,
-                                           uint64_t *ub, bool revd, int32_t bigdeg, uint64_t &fb) {
+__device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t root, bool push,
+                                           const NTest *nb, int ncount, const int32_t *ul,
+                                           int32_t i0, int32_t i1, uint64_t *ub, bool revd,
+                                           int32_t bigdeg, uint64_t &fb) {
     const DevGraph &g = c.g;
     const int lane = threadIdx.x & 63;
     FlatLds *w = flat_lds(c);
     bool have = i0 + lane < i1;
     const int32_t up = have ? ul[i0 + lane] : 0;
-    const int4 vr = g.vrow[up];
+    const int4 vr = root < 0 ? g.vrow[up] : have ? g.trow[(ul - g.tverts) + i0 + lane] : make_int4(0, 0, 0, 0);
+    if (root >= 0) have = have && root_ok(g, root, up, vr);
     if (revd) have = have && bit_test(ub, up);  // else already dropped
     int32_t maxd = 0;
     for (int j = 0; j < ncount; ++j) maxd = max(maxd, nb[j].dir ? vr.w - vr.z : vr.y - vr.x);
-    if (have && maxd > bigdeg) {
-        // The overflow list sits at the start of the slot's slab, which no
-        // phase uses while filtering (at most lcap entries).
-        ((int32_t *)c.slab)[atomicAdd(k.nbig(), 1)] = up;
+    const bool over = have && maxd > bigdeg;
+    if (over) {
+        to_overflow(c, k, up);
         have = false;
     }
+    const uint64_t overs = root >= 0 ? __ballot(over) : 0ull;  // candidates until a later tier drops them
     const uint64_t todo = __ballot(have);
     uint64_t alive = todo;
     int64_t seen = 0;
@@ -930,6 +975,11 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, bool push, const 
             }
             if (pass == 0) alive = __ballot(found);
         }
+    if (root >= 0) {
+        keep_root(c, k, u, ub, alive | overs, up, lane);
+        if (lane == 0) fb += 20ull * (i1 - i0) + 12ull * seen;
+        return;
+    }
     const uint64_t dead = todo & ~alive;
     if ((dead >> lane) & 1ull)
         atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
@@ -944,9 +994,10 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, bool push, const 
 // the row extents, one of the entries and one of what they are tested
 // against. Matches among the first 256 entries are pushed from registers.
 template <class K>
-__device__ __forceinline__ void wave_few(Ctx &c, const K &k, bool push, const NTest *nb, int ncount,
-                                         const int32_t *ul, int32_t i0, int32_t i1, uint64_t *ub,
-                                         bool revd, int32_t bigdeg, uint64_t &fb) {
+__device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root, bool push,
+                                         const NTest *nb, int ncount, const int32_t *ul,
+                                         int32_t i0, int32_t i1, uint64_t *ub, bool revd,
+                                         int32_t bigdeg, uint64_t &fb) {
     const DevGraph &g = c.g;
     const int lane = threadIdx.x & 63;
     FlatLds *w = flat_lds(c);
@@ -957,14 +1008,17 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, bool push, const NT
     bool have = it < n;
     const int32_t up = have ? ul[i0 + it] : 0;
     const int4 vr = g.vrow[up];
+    if (root >= 0) have = have && root_ok(g, root, up, vr);
     if (revd) have = have && bit_test(ub, up);
     const int dir = nb[tj].dir;
     const int32_t beg = dir ? vr.z : vr.x, end = dir ? vr.w : vr.y;
     // this candidate's segments among the wave's, and those that decide
     const uint64_t mine = (ncount == 64 ? ~0ull : (1ull << ncount) - 1ull) << (it * ncount & 63);
     const uint64_t need = mine & ~__ballot(nb[tj].known);
+    bool over = false;
     if (__ballot(have && end - beg > bigdeg) & mine) {
-        if (have && tj == 0) ((int32_t *)c.slab)[atomicAdd(k.nbig(), 1)] = up;
+        over = have && tj == 0;
+        if (over) to_overflow(c, k, up);
         have = false;
     }
     const bool todo = have;
@@ -1054,6 +1108,11 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, bool push, const NT
             alive &= (__ballot(found) & need) == need;
         }
     }
+    if (root >= 0) {
+        keep_root(c, k, u, ub, __ballot(tj == 0 && (alive || over)), up, lane);
+        if (lane == 0) fb += 20ull * n + 12ull * (uint64_t)T;
+        return;
+    }
     const bool drop = todo && !alive && tj == 0;
     if (drop) atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
     const uint64_t dead = __ballot(drop);
@@ -1072,10 +1131,10 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, bool push, const NT
 // would take next; longer ones stay with the owner, whose pushes become
 // shared row segments). Counters go to k.
 template <class K>
-__device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, const NTest *nb,
-                                             int ncount, const int32_t *ul, uint64_t *ub,
-                                             bool revd, int32_t it0, int32_t it1, uint64_t &fb,
-                                             bool nodefer = false) {
+__device__ __forceinline__ void filter_items(Ctx &c, const K &k, int u, int32_t root, bool push,
+                                             const NTest *nb, int ncount, const int32_t *ul,
+                                             uint64_t *ub, bool revd, int32_t it0, int32_t it1,
+                                             uint64_t &fb, bool nodefer = false) {
     const int wid = threadIdx.x >> 6;
     const int32_t per = nodefer ? 1 : min(64, (it1 - it0 + NW - 1) / NW);
     const int32_t bigdeg = nodefer ? max(4096, c.wg_rows) : per == 1 ? kFlatRowOne : kFlatRow;
@@ -1085,9 +1144,9 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, bool push, cons
         // rows of long-row passes are read test by test, which stops at the
         // first match
         if (!nodefer && ncount > 1 && (e - i) * ncount <= 64)
-            wave_few(c, k, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
+            wave_few(c, k, u, root, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
         else
-            wave_items(c, k, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
+            wave_items(c, k, u, root, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
     }
 }
 
@@ -1196,7 +1255,8 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
                                            int ncount, const int32_t *ul, uint64_t *ub, bool revd,
                                            int32_t n_items, int32_t K, int G, int32_t nch,
                                            const int4 *seg, uint64_t &fb,
-                                           const EcJob *ecj = nullptr, bool nodefer = false) {
+                                           const EcJob *ecj = nullptr, bool nodefer = false,
+                                           int32_t root = -1) {
     HelpJob *j = c.job;
     if (threadIdx.x == 0) {
         for (int v = 0; v < SGM_MAX_QV; ++v) j->cnt[v] = c.s->cnt[v];
@@ -1208,6 +1268,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         j->done = 0;
         j->kind = kind;
         j->nodefer = nodefer;
+        j->root = root;
         j->seg = seg;
         j->ul = ul;
         j->chunk = K;
@@ -1241,7 +1302,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         __syncthreads();
         if (ch < 0) break;
         if (kind == 0)
-            filter_items(c, BoardCtr{j}, st.push != 0, nb, ncount, ul, ub, revd, ch * K,
+            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, nb, ncount, ul, ub, revd, ch * K,
                          min(n_items, ch * K + K), fb, nodefer);
         else if (kind == 3)
             ec_chunk(c, *ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
@@ -1290,11 +1351,13 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
 // Chunks of u's candidate list shared as above.
 __device__ __forceinline__ void shared_items(Ctx &c, const NStep &st, const NTest *nb, int ncount,
                                              const int32_t *ul, uint64_t *ub, bool revd,
-                                             int32_t n_items, int32_t helpers, uint64_t &fb) {
+                                             int32_t n_items, int32_t helpers, int32_t root,
+                                             uint64_t &fb) {
     const int32_t K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
                                            (n_items + kMaxChunks - 1) / kMaxChunks)));
     const int32_t nch = (n_items + K - 1) / K;
-    shared_job(c, 0, st, nb, ncount, ul, ub, revd, n_items, K, 64, nch, nullptr, fb);
+    shared_job(c, 0, st, nb, ncount, ul, ub, revd, n_items, K, 64, nch, nullptr, fb, nullptr, false,
+               root);
 }
 
 // Workgroups that can help this slot now: the launch's extra ones and the
@@ -1348,12 +1411,13 @@ __device__ __forceinline__ int32_t *defer_list(Ctx &c, const NStep &st) {
 }
 
 // One step; returns the number of candidates it removed from C(u) (uniform).
-__device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
+// root: -1, or the first step of a query with an unpinned root (see root_ok).
+__device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t root = -1) {
     const DevGraph &g = c.g;
     const int u = st.u;
     uint64_t *ub = c.B(u);
-    int32_t *ul = c.L(u);
-    const int32_t n_items = c.s->cnt[u];
+    const int32_t *ul = root < 0 ? c.L(u) : g.tverts + c.Q->root_lo;
+    const int32_t n_items = root < 0 ? c.s->cnt[u] : c.Q->root_hi - c.Q->root_lo;
     uint64_t fb = 0;  // algorithmic bytes of this thread's work
     // A test known to hold is left out: every candidate of u was found (or
     // pushed) with a matching neighbour in C(v), C(v) has not changed since
@@ -1456,13 +1520,13 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
             const NNbr *d = c.Q->nbr + st.first + j;
             prune_reverse(c, u, d->v, d->dir, d->rel, fb);
         }
-    if (ncount == 0) {
+    if (ncount == 0 && root < 0) {
         // every test was known to hold or done from the other side
     } else if (n_items <= NW) {
         // a wave per candidate; those with a long row get the whole workgroup
-        filter_items(c, LdsCtr{c.s}, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
+        filter_items(c, LdsCtr{c.s}, u, root, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
         __syncthreads();
-        const int32_t nl = c.s->nbig;
+        const int32_t nl = min(c.s->nbig, c.lcap);
         if (nl > 0) {
             int32_t *def = defer_list(c, st);
             const int32_t *ov = (const int32_t *)c.slab;
@@ -1475,9 +1539,9 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
         const bool share = c.help_items > 0 && c.job && n_items >= c.help_items;
         const int32_t helpers = share ? helpers_now(c) : 0;
         if (share)
-            shared_items(c, st, nb, ncount, ul, ub, revd, n_items, helpers, fb);
+            shared_items(c, st, nb, ncount, ul, ub, revd, n_items, helpers, root, fb);
         else
-            filter_items(c, LdsCtr{c.s}, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
+            filter_items(c, LdsCtr{c.s}, u, root, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
         const int lane = threadIdx.x & 63;
         int32_t *ov = (int32_t *)c.slab;
         __syncthreads();
@@ -1487,7 +1551,7 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
             // shared like a step of many candidates (the rows move to a
             // list of their own; longer ones come back to the overflow list)
             ev(c, SGM_EV_LONGROWS);
-            const int32_t nl = c.s->nbig;
+            const int32_t nl = min(c.s->nbig, c.lcap);
             int32_t *rows = (int32_t *)(c.slab + 12 * (int64_t)c.lcap);
             for (int32_t i = threadIdx.x; i < nl; i += NT) rows[i] = ov[i];
             __syncthreads();
@@ -1498,7 +1562,7 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st) {
             __syncthreads();
         }
         // one wave per long row; rows above wg_rows get the whole workgroup
-        const int32_t nbig = c.s->nbig;
+        const int32_t nbig = min(c.s->nbig, c.lcap);
         if (nbig > 0) ev(c, SGM_EV_LONGROWS);
         int32_t *def = nbig > 0 ? defer_list(c, st) : nullptr;
         for (int32_t b = threadIdx.x >> 6; b < nbig; b += NW) {
@@ -2669,7 +2733,9 @@ __device__ __forceinline__ void run_query(Ctx &c) {
     ev(c, SGM_EV_START);
     // root candidates
     const int root = Q.root;
-    if (Q.root_slot < 0) {
+    const int32_t rootq = Q.root_lo < 0 ? -1
+                                        : Q.pred[root].qout | Q.pred[root].qin << 8 | (Q.homo ? 1 << 16 : 0);
+    if (rootq < 0) {
         if (threadIdx.x == 0) {
             const int32_t pin = Q.pred[root].pin;
             if (pin >= 0 && pin < g.V && vpred(g, Q.pred[root], pin)) {
@@ -2679,13 +2745,15 @@ __device__ __forceinline__ void run_query(Ctx &c) {
             }
         }
         __syncthreads();
-    } else {
-        list_from_bits(c, root, c.rootbits + (int64_t)Q.root_slot * g.nwords, true);
+    } else if (Q.n_init == 0) {
+        // a single query vertex: its whole range
+        filter_step(c, NStep{(int8_t)root, 1, -1, 0, 0, 0}, rootq);
     }
     ev(c, SGM_EV_ROOT);
     // explore along the spanning tree, then refinement rounds
     for (int i = 0; i < Q.n_init && !aborted(c); ++i) {
-        filter_step(c, Q.steps[i]);
+        // the first step is the root's
+        filter_step(c, Q.steps[i], i == 0 ? rootq : -1);
         ev(c, SGM_EV_EXPLORE);
     }
     const int rounds = Q.refine_rounds < 0 ? 32 : Q.refine_rounds;
@@ -3205,7 +3273,7 @@ __device__ __forceinline__ Ctx slot_ctx(const NArgs &a, Smem &s, unsigned char *
     uint64_t *bits = a.bits + (int64_t)slot * (SGM_MAX_QV + 1) * nwords;
     int32_t *lists = a.lists + (int64_t)slot * SGM_MAX_QV * a.lcap;
     char *slab = a.slab + (int64_t)slot * a.slab_bytes;
-    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.rootbits, &s.query, &s,
+    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, &s.query, &s,
                bits, bits + (int64_t)SGM_MAX_QV * nwords, lists, slab, dyn,
                a.trace ? a.trace + (int64_t)q * SGM_TRACE_CAP : nullptr, a.group_lanes,
                a.wg_rows, a.join_policy,
@@ -3229,6 +3297,7 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
     const int4 *seg = j->seg;
     const int32_t *hul = j->ul;
     const bool nodefer = j->nodefer != 0;
+    const int32_t root = j->root;
     if ((int)threadIdx.x < ncount) {
         s.nbl[threadIdx.x] = j->nbl[threadIdx.x];
     }
@@ -3244,7 +3313,7 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
     int32_t n = 0;
     while (ch >= 0) {
         if (kind == 0) {
-            filter_items(c, BoardCtr{j}, st.push != 0, s.nbl, ncount, hul, c.B(st.u), revd, ch * K,
+            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, s.nbl, ncount, hul, c.B(st.u), revd, ch * K,
                           min(n_items, ch * K + K), fb, nodefer);
         } else if (kind == 1) {
             push_segment(c, BoardCtr{j}, s.nbl, seg[ch], fb);
@@ -3448,140 +3517,10 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// root sweep for a batch: one wave per 64-vertex word, one ballot per
-// unpinned root
-// ---------------------------------------------------------------------------
-
-// Candidate initialisation for the unpinned roots of a batch (Alg. 3.2
-// kernel_check, one sweep for all of them): bitmap row j holds the vertices
-// that satisfy root predicate j. Predicates come sorted: the n_any of them
-// without a type first, the typed ones by type. A block owns a tile of 64
-// bitmap words (4096 vertices, 16 per thread, kept in registers after one
-// coalesced read). Per chunk of predicates the tile's rows are built in LDS:
-// untyped predicates by ballot, typed ones by each vertex OR-ing its bit
-// into the rows of the predicates of its own type only (found by binary
-// search), so a vertex is tested against about n_pred / (number of types)
-// predicates instead of all of them. Rows then leave as 512-byte runs.
-constexpr int kSweepTile = 64;    // bitmap words per block
-constexpr int kSweepThreads = 256;                     // 4 waves per block
-constexpr int kSweepSlots = kSweepTile / (kSweepThreads / 64);  // words per wave
-constexpr int kSweepChunk = 64;   // predicates per LDS pass (32 KB of rows)
-// LDS row stride in words. Lanes of one wave OR into the same word of the
-// rows of different predicates; an unpadded stride of 512 bytes would put all
-// of them in one bank, one more word spreads them over the banks.
-constexpr int kSweepStride = kSweepTile + 1;
-
-constexpr int kSweepTypes = 1024;  // type tables up to this size are staged in LDS
-constexpr int kSweepGroup = 4;     // slots whose typed predicates are walked together
-static_assert(kSweepSlots % kSweepGroup == 0, "slot groups must tile the slots");
-
-__global__ __launch_bounds__(kSweepThreads) void k_root_sweep(DevGraph g, const VPred *preds, int32_t n_pred,
-                                                    int32_t n_any, uint64_t *rootbits,
-                                                    unsigned long long *ctr,
-                                                    const int32_t *type_off, int32_t n_types) {
-    if (blockIdx.x == 0 && threadIdx.x < 3) ctr[threadIdx.x] = 0ull;
-    if (n_pred == 0) return;
-    __shared__ uint64_t rows[kSweepChunk * kSweepStride];
-    __shared__ VPred pl[kSweepChunk];
-    __shared__ int2 pq[kSweepChunk];  // (qout, qin) of the chunk's predicates
-    __shared__ int32_t toff[kSweepTypes + 1];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const bool table = n_types > 0 && n_types <= kSweepTypes;
-    if (table)
-        for (int t = threadIdx.x; t <= n_types; t += kSweepThreads) toff[t] = type_off[t];
-    const int32_t w0 = blockIdx.x * kSweepTile;
-    // vertex of slot i: word w0 + kSweepSlots * wid + i, bit lane
-    int2 vi[kSweepSlots];
-#pragma unroll
-    for (int i = 0; i < kSweepSlots; ++i) {
-        const int64_t v = (int64_t)(w0 + kSweepSlots * wid + i) * 64 + lane;
-        vi[i] = v < g.V ? g.vinfo[v] : make_int2(-1, -1);  // type -1: past the end
-    }
-    for (int32_t c0 = 0; c0 < n_pred; c0 += kSweepChunk) {
-        const int cn = min(kSweepChunk, n_pred - c0);
-        for (int i = threadIdx.x; i < cn * kSweepStride; i += kSweepThreads) rows[i] = 0ull;
-        if ((int)threadIdx.x < cn) {
-            const VPred p = preds[c0 + threadIdx.x];
-            pl[threadIdx.x] = p;
-            pq[threadIdx.x] = make_int2(p.qout, p.qin);
-        }
-        __syncthreads();
-        // untyped predicates: the same test for every lane; lane i keeps
-        // the ballot of slot i and the first kSweepSlots lanes store the
-        // wave's words
-        for (int j = 0; j < min(n_any - c0, cn); ++j) {
-            const int2 q = pq[j];
-            uint64_t mine = 0;
-#pragma unroll
-            for (int i = 0; i < kSweepSlots; ++i) {
-                const bool ok = vi[i].x >= 0 && (vi[i].y & 255) >= q.x && (vi[i].y >> 8) >= q.y;
-                const uint64_t b = __ballot(ok);
-                mine = lane == i ? b : mine;
-            }
-            if (lane < kSweepSlots) rows[j * kSweepStride + kSweepSlots * wid + lane] = mine;
-        }
-        // typed predicates of this chunk: [t0, cn), sorted by type
-        const int t0 = max(0, n_any - c0);
-        if (table) {
-            // each vertex's range of predicates of its type, all read
-            // before any is used (independent LDS reads), packed lo | hi << 16
-            int32_t r[kSweepSlots];
-#pragma unroll
-            for (int i = 0; i < kSweepSlots; ++i) {
-                const int32_t t = vi[i].x;
-                const bool ok = t >= 0 && t < n_types && t0 < cn;
-                const int32_t tc = ok ? t : 0;
-                const int32_t lo = max(t0, toff[tc] - c0), hi = min(cn, toff[tc + 1] - c0);
-                r[i] = ok && lo < hi ? (lo | (hi << 16)) : 0;
-            }
-            // kSweepGroup slots walk their ranges side by side, so that
-            // their predicate reads and ORs are independent LDS operations
-            // in flight together instead of one dependent chain per slot;
-            // a slot whose range has ended reads a clamped, unused entry
-#pragma unroll
-            for (int i0 = 0; i0 < kSweepSlots; i0 += kSweepGroup) {
-                int n = 0;
-#pragma unroll
-                for (int k = 0; k < kSweepGroup; ++k) n = max(n, (r[i0 + k] >> 16) - (r[i0 + k] & 0xffff));
-                for (int t = 0; t < n; ++t) {
-#pragma unroll
-                    for (int k = 0; k < kSweepGroup; ++k) {
-                        const int i = i0 + k;
-                        const int j = (r[i] & 0xffff) + t;
-                        const int2 q = pq[min(j, kSweepChunk - 1)];
-                        if (j < (r[i] >> 16) && (vi[i].y & 255) >= q.x && (vi[i].y >> 8) >= q.y)
-                            atomicOr((unsigned long long *)&rows[j * kSweepStride + kSweepSlots * wid + i],
-                                     1ull << lane);
-                    }
-                }
-            }
-        } else {
-            // more types than the table holds: binary search per vertex
-#pragma unroll
-            for (int i = 0; i < kSweepSlots; ++i) {
-                const int32_t t = vi[i].x;
-                if (t < 0 || t0 >= cn) continue;
-                int lo = t0, hi = cn;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (pl[mid].label < t) lo = mid + 1;
-                    else hi = mid;
-                }
-                const int od = vi[i].y & 255, id = vi[i].y >> 8;
-                for (int j = lo; j < cn && pl[j].label == t; ++j)
-                    if (od >= pq[j].x && id >= pq[j].y)
-                        atomicOr((unsigned long long *)&rows[j * kSweepStride + kSweepSlots * wid + i],
-                                 1ull << lane);
-            }
-        }
-        __syncthreads();
-        for (int k = threadIdx.x; k < cn * kSweepTile; k += kSweepThreads) {
-            const int j = k / kSweepTile, w = k % kSweepTile;
-            if (w0 + w < g.nwords) rootbits[(int64_t)(c0 + j) * g.nwords + w0 + w] = rows[j * kSweepStride + w];
-        }
-        __syncthreads();
-    }
+// Zeroes the launch's counters: the work queue, the output arena's use and
+// the helper counters.
+__global__ void k_reset(unsigned long long *ctr) {
+    if (threadIdx.x < 3) ctr[threadIdx.x] = 0ull;
 }
 
 }  // namespace
@@ -3592,42 +3531,27 @@ void launch_narrow(hipStream_t s, const NArgs &a, int grid) {
     hipLaunchKernelGGL(k_narrow, dim3(grid), dim3(NT), kDynLds, s, a);
 }
 
-namespace {
-int sweep_grid(const SweepArgs &a) {
-    if (a.n_pred == 0) return 1;
-    return std::max(1, (a.g.nwords + kSweepTile - 1) / kSweepTile);
-}
-}  // namespace
-
-void launch_root_sweep(hipStream_t s, const SweepArgs &a) {
-    hipLaunchKernelGGL(k_root_sweep, dim3(sweep_grid(a)), dim3(kSweepThreads), 0, s, a.g, a.preds, a.n_pred,
-                       a.n_any, a.rootbits, a.ctr, a.type_off, a.n_types);
+void launch_reset(hipStream_t s, unsigned long long *ctr) {
+    hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, ctr);
 }
 
-void narrow_node_params(SweepArgs *sa, NArgs *na, int narrow_grid, void **args,
-                        hipKernelNodeParams *sweep, hipKernelNodeParams *narrow) {
-    args[0] = &sa->g;
-    args[1] = &sa->preds;
-    args[2] = &sa->n_pred;
-    args[3] = &sa->n_any;
-    args[4] = &sa->rootbits;
-    args[5] = &sa->ctr;
-    args[6] = &sa->type_off;
-    args[7] = &sa->n_types;
-    args[8] = na;
-    *sweep = hipKernelNodeParams{};
-    sweep->func = reinterpret_cast<void *>(&k_root_sweep);
-    sweep->gridDim = dim3(sweep_grid(*sa));
-    sweep->blockDim = dim3(kSweepThreads);
-    sweep->sharedMemBytes = 0;
-    sweep->kernelParams = args;
-    sweep->extra = nullptr;
+void narrow_node_params(unsigned long long **ctr, NArgs *na, int narrow_grid, void **args,
+                        hipKernelNodeParams *reset, hipKernelNodeParams *narrow) {
+    args[0] = ctr;
+    args[1] = na;
+    *reset = hipKernelNodeParams{};
+    reset->func = reinterpret_cast<void *>(&k_reset);
+    reset->gridDim = dim3(1);
+    reset->blockDim = dim3(64);
+    reset->sharedMemBytes = 0;
+    reset->kernelParams = args;
+    reset->extra = nullptr;
     *narrow = hipKernelNodeParams{};
     narrow->func = reinterpret_cast<void *>(&k_narrow);
     narrow->gridDim = dim3(narrow_grid);
     narrow->blockDim = dim3(NT);
     narrow->sharedMemBytes = kDynLds;
-    narrow->kernelParams = args + 8;
+    narrow->kernelParams = args + 1;
     narrow->extra = nullptr;
 }
 
