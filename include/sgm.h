@@ -63,10 +63,8 @@ typedef struct {
                                   (sgm_trace_events) */
     int32_t path;              /* SGM_PATH_AUTO (default), SGM_PATH_WIDE or
                                   SGM_PATH_NARROW (see below) */
-    int32_t graphs;            /* 1 (default): a persistent-kernel batch (upload,
-                                  root sweep, kernel, readback) is one HIP graph
-                                  launch; 0: separate launches. Not used while
-                                  profile != 0 (kernels are timed one by one) */
+    int32_t graphs;            /* accepted, without effect: a persistent-kernel
+                                  batch is one kernel launch */
     int32_t out_only;          /* 1: keep only the outgoing graph (thesis Ch. 3,
                                   Sec. "GpSense Framework": the incoming graph is
                                   the second of the two representations). A query

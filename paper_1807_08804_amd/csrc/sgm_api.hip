@@ -168,13 +168,17 @@ struct NarrowCtx {
     int32_t *lists = nullptr;
     char *slab = nullptr;
     int qcap = 0;
-    NQuery *d_q = nullptr, *h_q = nullptr;
-    NResult *d_res = nullptr, *h_res = nullptr;
+    // descriptors and results live in pinned host memory: the kernel reads
+    // each descriptor once (into LDS) and writes each result once, in whole
+    // lines, over the host link
+    NQuery *h_q = nullptr;
+    NResult *h_res = nullptr;
     int32_t *d_out = nullptr;
     int64_t out_cap = 0;
     // [0] queue, [1] out used, [2] helper counters (posted steps, slot
-    // workgroups done)
-    unsigned long long *d_ctr = nullptr, *h_ctr = nullptr;
+    // workgroups done), [3] workgroups that have left; the last one to leave
+    // zeroes them all for the next launch
+    unsigned long long *d_ctr = nullptr;
     HelpJob *d_board = nullptr;  // [kNarrowMaxSlots] shared filter steps
     bool serve = false;          // a server's context: no shared steps
     int32_t *h_out = nullptr;
@@ -186,20 +190,9 @@ struct NarrowCtx {
     // the context's own stream orders the next large table
     hipStream_t copy = nullptr;
     std::vector<hipEvent_t> copy_ev;
-    // one batch as a HIP graph: upload descriptors, reset counters,
-    // persistent kernel, read back results, counters and the arena's head.
-    // Built on first use; every launch updates all node parameters.
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    hipGraphNode_t gn[6] = {};
-    NArgs na{};
-    // parameters of the instantiated graph's last launch: nodes whose
-    // parameters did not change are not updated again
-    NArgs last_na{};
-    int last_grid = -1;
-    size_t last_qb = 0, last_rb = 0;
-    const void *last_hout = nullptr;
-    void *kargs[2] = {};
+    // the output arena's first kOutPrefix ints: small tables go straight to
+    // host memory
+    int32_t *h_pre = nullptr;
 };
 
 }  // namespace
@@ -1572,8 +1565,8 @@ constexpr int64_t kBatchSlabMax = 160ll << 20;
 constexpr int32_t kNarrowListCap = 1 << 16;          // per query vertex
 constexpr int kNarrowQueryCap = 4096;                // queries per launch
 constexpr int64_t kNarrowOutCap = 256ll << 20;       // int32 elements (1 GB) per context
-// Every launch also reads back this many leading ints of the output arena,
-// so that small results need no second copy and wait.
+// The output arena's first ints are pinned host memory that the kernel writes
+// itself, so that small results need no copy and no second wait.
 constexpr int64_t kOutPrefix = 16384;
 constexpr int kBigSlots = 4;                         // large slots of the retry context
 constexpr int32_t kBigListCap = 1 << 22;             // per query vertex, large slot
@@ -1606,15 +1599,13 @@ void narrow_free(NarrowCtx &nw) {
     dev_free(nw.bits);
     dev_free(nw.lists);
     dev_free(nw.slab);
-    dev_free(nw.d_q);
-    dev_free(nw.d_res);
     dev_free(nw.d_out);
     dev_free(nw.d_ctr);
     dev_free(nw.d_board);
     host_free(nw.h_q);
     host_free(nw.h_res);
-    host_free(nw.h_ctr);
     host_free(nw.h_out);
+    host_free(nw.h_pre);
     dev_free(nw.d_trace);
     host_free(nw.h_trace);
     if (nw.done) (void)hipEventDestroy(nw.done);
@@ -1624,10 +1615,6 @@ void narrow_free(NarrowCtx &nw) {
         (void)hipStreamDestroy(nw.copy);
     }
     for (hipEvent_t e : nw.copy_ev) (void)hipEventDestroy(e);
-    if (nw.gexec) (void)hipGraphExecDestroy(nw.gexec);
-    if (nw.graph) (void)hipGraphDestroy(nw.graph);
-    nw.gexec = nullptr;
-    nw.graph = nullptr;
     const NarrowCtx keep = nw;
     nw = NarrowCtx{};
     nw.stream = keep.stream;
@@ -1636,14 +1623,23 @@ void narrow_free(NarrowCtx &nw) {
     nw.slab_want = keep.slab_want;
 }
 
+// Device address of pinned host memory.
+template <class T>
+T *host_ptr(T *h) {
+    void *d = nullptr;
+    HIPX(hipHostGetDevicePointer(&d, h, 0));
+    return (T *)d;
+}
+
 void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     if (nw.lcap == 0) {
         nw.lcap = std::min<int32_t>(g->V, nw.lcap_want ? nw.lcap_want : kNarrowListCap);
         nw.slab_bytes = nw.slab_want ? nw.slab_want : narrow_slab_bytes(g, nw.serve);
         // while filtering, a slot's slab holds two lists of up to lcap ints
         if (nw.slab_bytes < 8ll * nw.lcap) throw DeviceError{SGM_EUNSUPPORTED};
-        HIPX(hipMalloc(&nw.d_ctr, sizeof(unsigned long long) * 3));
-        HIPX(hipHostMalloc(&nw.h_ctr, sizeof(unsigned long long) * 2, hipHostMallocDefault));
+        HIPX(hipMalloc(&nw.d_ctr, sizeof(unsigned long long) * 4));
+        HIPX(hipMemsetAsync(nw.d_ctr, 0, sizeof(unsigned long long) * 4, nw.stream));
+        HIPX(hipHostMalloc(&nw.h_pre, sizeof(int32_t) * kOutPrefix, hipHostMallocDefault));
         // board entries start at sequence 0 with no chunks; the kernel
         // retires every step it posts, so they need no clearing later
         HIPX(hipMalloc(&nw.d_board, sizeof(HelpJob) * kNarrowMaxSlots));
@@ -1669,13 +1665,9 @@ void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     }
     if (nq > nw.qcap) {
         HIPX(hipStreamSynchronize(nw.stream));
-        dev_free(nw.d_q);
-        dev_free(nw.d_res);
         host_free(nw.h_q);
         host_free(nw.h_res);
         nw.qcap = 0;
-        HIPX(hipMalloc(&nw.d_q, sizeof(NQuery) * nq));
-        HIPX(hipMalloc(&nw.d_res, sizeof(NResult) * nq));
         HIPX(hipHostMalloc(&nw.h_q, sizeof(NQuery) * nq, hipHostMallocDefault));
         HIPX(hipHostMalloc(&nw.h_res, sizeof(NResult) * nq, hipHostMallocDefault));
         nw.qcap = nq;
@@ -1828,9 +1820,9 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     hipStream_t st = nw.stream;
     NArgs a{};
     a.g = g->dg;
-    a.qs = nw.d_q;
+    a.qs = host_ptr(nw.h_q);
     a.nq = np;
-    a.res = nw.d_res;
+    a.res = host_ptr(nw.h_res);
     a.queue = (int32_t *)nw.d_ctr;
     a.bits = nw.bits;
     a.lists = nw.lists;
@@ -1840,6 +1832,9 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     a.out = nw.d_out;
     a.out_cap = nw.out_cap;
     a.out_used = nw.d_ctr + 1;
+    a.host_out = host_ptr(nw.h_pre);
+    a.host_cap = kOutPrefix;
+    a.left = (int32_t *)(nw.d_ctr + 3);
     a.group_lanes = g->tune.group_lanes;
     a.wg_rows = g->tune.wg_rows;
     a.join_policy = g->tune.join_policy;
@@ -1861,54 +1856,6 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
         help ? std::min(kNarrowMaxSlots, std::max(slot_grid, g->tune.helpers)) : slot_grid;
     a.ngrid = grid;
     job.traced = profiled && g->opts.profile >= 2;
-    if (g->opts.graphs && !(profiled && g->opts.profile)) {
-        nw.na = a;
-        hipKernelNodeParams ps, pn;
-        narrow_node_params(&nw.d_ctr, &nw.na, grid, nw.kargs, &ps, &pn);
-        const size_t qb = sizeof(NQuery) * np;
-        const size_t rb = sizeof(NResult) * np, cb = sizeof(unsigned long long) * 2;
-        const size_t ob = sizeof(int32_t) * kOutPrefix;
-        const auto H2D = hipMemcpyHostToDevice, D2H = hipMemcpyDeviceToHost;
-        if (!nw.gexec) {
-            HIPX(hipGraphCreate(&nw.graph, 0));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[0], nw.graph, nullptr, 0, nw.d_q, nw.h_q, qb, H2D));
-            HIPX(hipGraphAddKernelNode(&nw.gn[1], nw.graph, &nw.gn[0], 1, &ps));
-            HIPX(hipGraphAddKernelNode(&nw.gn[2], nw.graph, &nw.gn[1], 1, &pn));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[3], nw.graph, &nw.gn[2], 1, nw.h_res, nw.d_res, rb,
-                                         D2H));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[4], nw.graph, &nw.gn[3], 1, nw.h_ctr, nw.d_ctr, cb,
-                                         D2H));
-            HIPX(hipGraphAddMemcpyNode1D(&nw.gn[5], nw.graph, &nw.gn[4], 1, nw.h_out, nw.d_out, ob,
-                                         D2H));
-            HIPX(hipGraphInstantiate(&nw.gexec, nw.graph, nullptr, nullptr, 0));
-        } else {
-            // buffers are reallocated only while no launch is in flight, and
-            // every pointer a node uses is compared here
-            if (qb != nw.last_qb || nw.na.qs != nw.last_na.qs)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[0], nw.d_q, nw.h_q, qb, H2D));
-            if (std::memcmp(&nw.na, &nw.last_na, sizeof(NArgs)) != 0 || grid != nw.last_grid)
-                HIPX(hipGraphExecKernelNodeSetParams(nw.gexec, nw.gn[2], &pn));
-            if (rb != nw.last_rb || nw.na.res != nw.last_na.res)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[3], nw.h_res, nw.d_res, rb,
-                                                       D2H));
-            if (nw.na.queue != nw.last_na.queue)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[4], nw.h_ctr, nw.d_ctr, cb,
-                                                       D2H));
-            if (nw.h_out != nw.last_hout || nw.na.out != nw.last_na.out)
-                HIPX(hipGraphExecMemcpyNodeSetParams1D(nw.gexec, nw.gn[5], nw.h_out, nw.d_out, ob,
-                                                       D2H));
-        }
-        nw.last_na = nw.na;
-        nw.last_grid = grid;
-        nw.last_qb = qb;
-        nw.last_rb = rb;
-        nw.last_hout = nw.h_out;
-        HIPX(hipGraphLaunch(nw.gexec, st));
-        HIPX(hipEventRecord(nw.done, st));
-        return true;
-    }
-    HIPX(hipMemcpyAsync(nw.d_q, nw.h_q, sizeof(NQuery) * np, hipMemcpyHostToDevice, st));
-    launch_reset(st, nw.d_ctr);
     if (job.traced) {
         if (np > nw.trace_cap) {
             HIPX(hipStreamSynchronize(st));
@@ -1930,10 +1877,6 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     if (job.traced)
         HIPX(hipMemcpyAsync(nw.h_trace, nw.d_trace, sizeof(int64_t) * SGM_TRACE_CAP * np,
                             hipMemcpyDeviceToHost, st));
-    HIPX(hipMemcpyAsync(nw.h_res, nw.d_res, sizeof(NResult) * np, hipMemcpyDeviceToHost, st));
-    HIPX(hipMemcpyAsync(nw.h_ctr, nw.d_ctr, sizeof(unsigned long long) * 2, hipMemcpyDeviceToHost,
-                        st));
-    HIPX(hipMemcpyAsync(nw.h_out, nw.d_out, sizeof(int32_t) * kOutPrefix, hipMemcpyDeviceToHost, st));
     HIPX(hipEventRecord(nw.done, st));
     return true;
 }
@@ -1952,7 +1895,18 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
         for (int i = 0; i < np; ++i) b += (double)nw.h_res[i].bytes;
         g->kstat[SGM_K_PERSIST].bytes_total += b;
     }
-    const int64_t used = std::min<int64_t>((int64_t)nw.h_ctr[1], nw.out_cap);
+    // the arena's used ints, and the first one that is not in host memory
+    // (places are handed out in ascending order, so every table that ends
+    // within the host part lies below the first that does not)
+    int64_t used = 0, dev_from = INT64_MAX;
+    for (int i = 0; i < np; ++i) {
+        const NResult &r = nw.h_res[i];
+        if (r.status != SGM_OK || r.host_order || r.n_rows == 0) continue;
+        const int64_t end = r.offset + r.n_rows * qis[job.packed[i]].n_out;
+        used = std::max(used, end);
+        if (end > kOutPrefix) dev_from = std::min(dev_from, r.offset);
+    }
+    const int64_t pre = std::min(used, dev_from);  // ints of the host part
     const bool want = !(flags & SGM_COUNT_ONLY);
     // bytes of rows this launch returns: the arena's used part, and room for
     // the large tables the host orders
@@ -1988,21 +1942,19 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
         if (!nw.copy) HIPX(hipStreamCreateWithFlags(&nw.copy, hipStreamNonBlocking));
         copy_wait.s = nw.copy;
         // the kernel has finished (nw.done): the arena is final
-        if (used > 0)
-            HIPX(hipMemcpyAsync(blk->ptr, nw.d_out, sizeof(int32_t) * used, hipMemcpyDeviceToHost,
-                                nw.copy));
-    } else if (want && used > kOutPrefix) {
-        // the launch read back the first kOutPrefix ints; the rest now
-        int64_t from = kOutPrefix;
+        if (used > pre)
+            HIPX(hipMemcpyAsync(blk->ptr + sizeof(int32_t) * pre, nw.d_out + pre,
+                                sizeof(int32_t) * (used - pre), hipMemcpyDeviceToHost, nw.copy));
+        if (pre > 0) std::memcpy(blk->ptr, nw.h_pre, sizeof(int32_t) * (size_t)pre);
+    } else if (want && used > pre) {
         if (nw.h_out_cap < used) {
             host_free(nw.h_out);
             nw.h_out_cap = 0;
             const int64_t cap = std::max<int64_t>(used, 1 << 20);
             HIPX(hipHostMalloc(&nw.h_out, sizeof(int32_t) * cap, hipHostMallocDefault));
             nw.h_out_cap = cap;
-            from = 0;
         }
-        HIPX(hipMemcpyAsync(nw.h_out + from, nw.d_out + from, sizeof(int32_t) * (used - from),
+        HIPX(hipMemcpyAsync(nw.h_out + pre, nw.d_out + pre, sizeof(int32_t) * (used - pre),
                             hipMemcpyDeviceToHost, st));
         HIPX(hipStreamSynchronize(st));
     }
@@ -2078,7 +2030,8 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
             } else {
                 out->rows = alloc_rows(bytes);
                 if (!out->rows) throw std::bad_alloc();
-                if (bytes) copies.push_back({out->rows, nw.h_out + r.offset, bytes});
+                if (bytes)
+                    copies.push_back({out->rows, (r.offset < pre ? nw.h_pre : nw.h_out) + r.offset, bytes});
             }
         }
     }

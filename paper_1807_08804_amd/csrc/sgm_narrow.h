@@ -192,6 +192,14 @@ struct NArgs {
     int32_t *out;             // output arena (int32 rows)
     int64_t out_cap;          // in int32 elements
     unsigned long long *out_used;
+    // tables that end within the arena's first host_cap ints are written to
+    // this host memory instead
+    int32_t *host_out;
+    int64_t host_cap;
+    // workgroups that have left the launch; the last one zeroes the launch's
+    // counters (queue, out_used, hctr, left) for the next (null: the host
+    // resets them)
+    int32_t *left;
     int64_t *trace;           // [nq][SGM_TRACE_CAP] step events, or null
     // work-division and schedule knobs (sgm_tuning); results do not depend
     // on them
@@ -215,11 +223,6 @@ struct NArgs {
 
 void launch_reset(hipStream_t s, unsigned long long *ctr);
 void launch_narrow(hipStream_t s, const NArgs &a, int grid);
-// Kernel-node parameters of the counters' reset and of the persistent kernel
-// for a HIP graph. The argument pointers refer to *ctr, *na and args[0..1],
-// which must stay valid until the parameters have been handed to HIP.
-void narrow_node_params(unsigned long long **ctr, NArgs *na, int narrow_grid, void **args,
-                        hipKernelNodeParams *reset, hipKernelNodeParams *narrow);
 size_t narrow_lds_bytes();
 
 }  // namespace sgm

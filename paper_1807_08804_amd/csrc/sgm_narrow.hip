@@ -135,6 +135,8 @@ struct Ctx {
     int32_t *out;
     int64_t out_cap;
     unsigned long long *out_used;
+    int32_t *host_out;
+    int64_t host_cap;
     const NQuery *Q;
     Smem *s;
     uint64_t *bits;     // slot bitmaps [(SGM_MAX_QV + 1) * nwords]
@@ -3235,10 +3237,11 @@ __device__ __forceinline__ void run_query(Ctx &c) {
             // no <= 16)
             const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
             const uint32_t inv = (65536u + (uint32_t)no - 1u) / (uint32_t)no;
+            int32_t *arena = off + rows * no <= c.host_cap ? c.host_out : c.out;
             for (int64_t r0 = (int64_t)wid * 64; r0 < rows; r0 += NT) {
                 const int32_t my = r0 + lane < rows ? idx[r0 + lane] : 0;
                 const int nr = (int)min((int64_t)64, rows - r0);
-                int32_t *dst = c.out + off + r0 * no;
+                int32_t *dst = arena + off + r0 * no;
                 const int ne = nr * no;
                 for (int e0 = 0; e0 < ne; e0 += 256) {
                     // four gathers in flight per lane; every lane takes part
@@ -3273,7 +3276,7 @@ __device__ __forceinline__ Ctx slot_ctx(const NArgs &a, Smem &s, unsigned char *
     uint64_t *bits = a.bits + (int64_t)slot * (SGM_MAX_QV + 1) * nwords;
     int32_t *lists = a.lists + (int64_t)slot * SGM_MAX_QV * a.lcap;
     char *slab = a.slab + (int64_t)slot * a.slab_bytes;
-    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, &s.query, &s,
+    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.host_out, a.host_cap, &s.query, &s,
                bits, bits + (int64_t)SGM_MAX_QV * nwords, lists, slab, dyn,
                a.trace ? a.trace + (int64_t)q * SGM_TRACE_CAP : nullptr, a.group_lanes,
                a.wg_rows, a.join_policy,
@@ -3412,12 +3415,25 @@ __device__ __forceinline__ void help_loop(const NArgs &a, Smem &s, unsigned char
     }
 }
 
+// A workgroup's last act: no workgroup reads a counter after counting itself
+// out, so the last one out can zero them all.
+__device__ __forceinline__ void leave(const NArgs &a) {
+    if (threadIdx.x != 0 || !a.left) return;
+    if (atomicAdd(a.left, 1) != (int)gridDim.x - 1) return;
+    atomicExch(a.queue, 0);
+    atomicExch(a.out_used, 0ull);
+    atomicExch(&a.hctr[0], 0);
+    atomicExch(&a.hctr[1], 0);
+    atomicExch(a.left, 0);
+}
+
 __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
     __shared__ Smem s;
     extern __shared__ unsigned char dyn[];
     const bool help = a.help_items > 0 && a.board != nullptr;
     if ((int)blockIdx.x >= a.nslot) {
         if (help) help_loop(a, s, dyn);
+        leave(a);
         return;
     }
     if (threadIdx.x == 0) {
@@ -3446,14 +3462,15 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
         __syncthreads();
         const int32_t q = s.q;
         if (q >= a.nq) break;
-        const NQuery &Q = a.qs[q];
+        const NQuery &Qd = a.qs[q];
+        const NQuery &Q = s.query;
         NResult &R = a.res[q];
         if (s.retired) {
             // the slot is out of use: the query is reported for a rerun
             if (threadIdx.x == 0) {
                 R.status = kNeedWide;
                 R.reason = kWhyHelp;
-                R.n_cols = Q.n;
+                R.n_cols = Qd.n;
                 R.n_rows = 0;
                 R.offset = 0;
                 for (int u = 0; u < SGM_MAX_QV; ++u) {
@@ -3472,30 +3489,34 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
         Ctx c = slot_ctx(a, s, dyn, blockIdx.x, q, slab_cap);
         static_assert(sizeof(NQuery) % 4 == 0, "staged as ints");
         for (int i = threadIdx.x; i < (int)(sizeof(NQuery) / 4); i += NT)
-            ((int32_t *)&s.query)[i] = ((const int32_t *)&Q)[i];
+            ((int32_t *)&s.query)[i] = ((const int32_t *)&Qd)[i];
         if (threadIdx.x == 0) s.nev = 0;
         __syncthreads();
         run_query(c);
         __syncthreads();
         if (s.hostord) slab_cap = s.pin_off;  // keep that table until the launch ends
-        if (threadIdx.x == 0) {
-            R.status = s.status;
-            R.reason = s.reason;
-            R.n_cols = Q.n;
-            R.n_rows = s.status == SGM_OK ? s.nrows : 0;
-            R.offset = s.offset;
-            for (int u = 0; u < SGM_MAX_QV; ++u) {
-                R.cand[u] = u < Q.n ? s.cand[u] : 0;
-                R.level_rows[u] = u < Q.n ? s.level_rows[u] : 0;
-                R.join_order[u] = u < Q.n ? s.jorder[u] : -1;
-            }
-            for (int e = 0; e < SGM_MAX_QE; ++e) R.ec[e] = e < Q.m ? s.ectot[e] : 0;
-            R.bytes = (int64_t)s.bytes;
-            R.need = s.need;
-            R.host_order = s.hostord;
-            R.key_bits = s.keybits;
-            R.table_ptr = (int64_t)(uintptr_t)s.tableptr;
-            R.list_ptr = (int64_t)(uintptr_t)s.listptr;
+        // the result is put together in LDS and leaves in whole lines
+        NResult &L = *(NResult *)dyn;
+        const int t = threadIdx.x;
+        if (t < SGM_MAX_QV) {
+            L.cand[t] = t < Q.n ? s.cand[t] : 0;
+            L.level_rows[t] = t < Q.n ? s.level_rows[t] : 0;
+            L.join_order[t] = t < Q.n ? s.jorder[t] : -1;
+        }
+        if (t < SGM_MAX_QE) L.ec[t] = t < Q.m ? s.ectot[t] : 0;
+        if (t == 0) {
+            L.status = s.status;
+            L.reason = s.reason;
+            L.n_cols = Q.n;
+            L.pad = 0;
+            L.n_rows = s.status == SGM_OK ? s.nrows : 0;
+            L.offset = s.offset;
+            L.bytes = (int64_t)s.bytes;
+            L.need = s.need;
+            L.host_order = s.hostord;
+            L.key_bits = s.keybits;
+            L.table_ptr = (int64_t)(uintptr_t)s.tableptr;
+            L.list_ptr = (int64_t)(uintptr_t)s.listptr;
             // phases a query skipped carry the time and bytes of the
             // previous mark
             int64_t prev = s.t[0];
@@ -3504,17 +3525,22 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
                 const bool hit = s.t[i] != 0;
                 const int64_t ti = hit ? s.t[i] : prev;
                 const unsigned long long bi = hit ? s.pb[i] : pbp;
-                R.ticks[i - 1] = ti - prev;
-                R.pbytes[i - 1] = (int64_t)(bi - pbp);
+                L.ticks[i - 1] = ti - prev;
+                L.pbytes[i - 1] = (int64_t)(bi - pbp);
                 prev = ti;
                 pbp = bi;
             }
         }
+        __syncthreads();
+        static_assert(sizeof(NResult) % 4 == 0, "copied as ints");
+        for (int i = t; i < (int)(sizeof(NResult) / 4); i += NT)
+            ((int32_t *)&R)[i] = ((const int32_t *)&L)[i];
     }
     if (help) {
         if (threadIdx.x == 0) atomicAdd(&a.hctr[1], 1);
         help_loop(a, s, dyn);
     }
+    leave(a);
 }
 
 // Zeroes the launch's counters: the work queue, the output arena's use and
@@ -3533,26 +3559,6 @@ void launch_narrow(hipStream_t s, const NArgs &a, int grid) {
 
 void launch_reset(hipStream_t s, unsigned long long *ctr) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, ctr);
-}
-
-void narrow_node_params(unsigned long long **ctr, NArgs *na, int narrow_grid, void **args,
-                        hipKernelNodeParams *reset, hipKernelNodeParams *narrow) {
-    args[0] = ctr;
-    args[1] = na;
-    *reset = hipKernelNodeParams{};
-    reset->func = reinterpret_cast<void *>(&k_reset);
-    reset->gridDim = dim3(1);
-    reset->blockDim = dim3(64);
-    reset->sharedMemBytes = 0;
-    reset->kernelParams = args;
-    reset->extra = nullptr;
-    *narrow = hipKernelNodeParams{};
-    narrow->func = reinterpret_cast<void *>(&k_narrow);
-    narrow->gridDim = dim3(narrow_grid);
-    narrow->blockDim = dim3(NT);
-    narrow->sharedMemBytes = kDynLds;
-    narrow->kernelParams = args + 1;
-    narrow->extra = nullptr;
 }
 
 }  // namespace sgm
