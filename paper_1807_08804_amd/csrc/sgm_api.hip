@@ -1676,7 +1676,8 @@ void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
 
 // Pack one validated query and its plan; false if it exceeds the packed
 // descriptor's capacity (the query then runs on the multi-kernel path).
-bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, Plan *pl_out) {
+bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, NQuery *nq,
+                Plan *pl_out) {
     Program pr;
     build_program(qi, pl, g->opts.low_conn_degree, g->opts.refine_reversed, &pr);
     if ((int)(pr.init.size() + pr.refine.size()) > kNMaxSteps || (int)pr.nbr.size() > kNMaxNbr)
@@ -1707,6 +1708,8 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, NQuery *nq, Plan 
     nq->refine_rounds = g->opts.refine_rounds < 0 ? -1 : std::min(g->opts.refine_rounds, 32);
     nq->proj = qi.proj;
     nq->homo = g->homomorphic ? 1 : 0;
+    // a projection's count needs its distinct rows
+    nq->count_only = (flags & SGM_COUNT_ONLY) && !qi.proj;
     int k = 0;
     auto put = [&](const PStep &s) {
         NStep &t = nq->steps[k++];
@@ -1741,7 +1744,7 @@ struct NarrowJob {
 // asynchronously on nw.stream; queries that do not fit a descriptor go to
 // `wide`. Returns false when nothing was launched.
 bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, const int *which,
-                   int count, NarrowJob &job, std::vector<int> &wide,
+                   int count, uint32_t flags, NarrowJob &job, std::vector<int> &wide,
                    std::vector<sgm_result *> &res, bool profiled) {
     job.t0 = now_ns();
     job.packed.clear();
@@ -1796,7 +1799,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     parallel_for(no, 128, [&](int lo, int hi) {
         for (int k = lo; k < hi; ++k) {
             const int i = order[k];
-            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], &nw.h_q[k], &pls[k]);
+            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], flags, &nw.h_q[k], &pls[k]);
         }
     });
     int np = 0;
@@ -1895,11 +1898,12 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
         for (int i = 0; i < np; ++i) b += (double)nw.h_res[i].bytes;
         g->kstat[SGM_K_PERSIST].bytes_total += b;
     }
+    const bool want = !(flags & SGM_COUNT_ONLY);
     // the arena's used ints, and the first one that is not in host memory
     // (places are handed out in ascending order, so every table that ends
     // within the host part lies below the first that does not)
     int64_t used = 0, dev_from = INT64_MAX;
-    for (int i = 0; i < np; ++i) {
+    for (int i = 0; want && i < np; ++i) {
         const NResult &r = nw.h_res[i];
         if (r.status != SGM_OK || r.host_order || r.n_rows == 0) continue;
         const int64_t end = r.offset + r.n_rows * qis[job.packed[i]].n_out;
@@ -1907,7 +1911,6 @@ void narrow_collect(sgm_graph *g, NarrowCtx &nw, NarrowJob &job, const std::vect
         if (end > kOutPrefix) dev_from = std::min(dev_from, r.offset);
     }
     const int64_t pre = std::min(used, dev_from);  // ints of the host part
-    const bool want = !(flags & SGM_COUNT_ONLY);
     // bytes of rows this launch returns: the arena's used part, and room for
     // the large tables the host orders
     size_t host_bytes = 0;
@@ -2146,7 +2149,8 @@ void narrow_batch(sgm_graph *g, const std::vector<QInfo> &qis, const std::vector
     for (size_t base = 0; base < which.size(); base += kNarrowQueryCap) {
         const int count = (int)std::min<size_t>(kNarrowQueryCap, which.size() - base);
         NarrowJob job;
-        if (narrow_launch(g, g->nw, qis, which.data() + base, count, job, wide, res, true))
+        if (narrow_launch(g, g->nw, qis, which.data() + base, count, flags, job, wide, res,
+                          true))
             narrow_collect(g, g->nw, job, qis, flags, res, wide, true);
     }
 }
@@ -2169,7 +2173,8 @@ void narrow_retry_large(sgm_graph *g, const std::vector<QInfo> &qis, uint32_t fl
     for (size_t base = 0; base < again.size(); base += kNarrowQueryCap) {
         const int count = (int)std::min<size_t>(kNarrowQueryCap, again.size() - base);
         NarrowJob job;
-        if (narrow_launch(g, g->nwb, qis, again.data() + base, count, job, wide, res, true))
+        if (narrow_launch(g, g->nwb, qis, again.data() + base, count, flags, job, wide, res,
+                          true))
             narrow_collect(g, g->nwb, job, qis, flags, res, wide, true);
     }
 }
@@ -3065,7 +3070,8 @@ void serve_dispatch(sgm_server *S) {
             if (b->res[i]->status == SGM_OK) b->which.push_back((int)i);
         try {
             b->launched = narrow_launch(g, S->ctx[ci], b->qis, b->which.data(),
-                                        (int)b->which.size(), b->job, b->wide, b->res, false);
+                                        (int)b->which.size(), b->flags, b->job, b->wide, b->res,
+                                        false);
         } catch (const DeviceError &e) {
             for (auto *r : b->res) r->status = e.code;
             b->which.clear();
@@ -3512,7 +3518,7 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
     if (make_plan(qi, g->V, g->type_freq.data(), g->n_types, &pl) != SGM_OK) return SGM_EINVAL;
     NQuery nq;
     Plan pl_out;
-    if (!pack_query(g, qi, pl, &nq, &pl_out)) {
+    if (!pack_query(g, qi, pl, flags, &nq, &pl_out)) {
         g_last_error = "query plan exceeds the packed descriptor";
         return SGM_EUNSUPPORTED;
     }

@@ -56,6 +56,7 @@ struct NQuery {
     uint32_t proj;          // projected columns (bit u = query vertex u kept; 0: all)
     int32_t fault;          // 1: fail as a device fault would (sgm_inject_fault)
     int32_t homo;           // 1: matches are homomorphisms (a compressed graph)
+    int32_t count_only;     // 1: the number of rows is wanted, not the rows
     NStep steps[kNMaxSteps];
     NNbr nbr[kNMaxNbr];
 };
@@ -126,7 +127,8 @@ struct JLevel {
     int32_t *out;
     int64_t cap;   // output rows that fit
     int32_t nsub;  // shared: chunks per block of NT parent rows
-    int32_t homo;  // 1: a value may repeat one of the row (a compressed graph)
+    uint32_t cmask;  // columns whose value the new one must differ from
+    int32_t count;   // 1: only the number of rows is wanted
     JChk chk[SGM_MAX_QE];
 };
 

@@ -62,6 +62,7 @@ struct Smem {
     JLevel jl;                 // the join level being built
     int32_t wnok[2][NW];       // shared join levels: rows per wave of a block of pairs
     int64_t wbase[2];          // and the block's first output row
+    unsigned long long cnt64;  // rows of a counting level
     int32_t abort_;
     int32_t q;
     int32_t nev;
@@ -2256,29 +2257,35 @@ __device__ __forceinline__ bool ec_contains(const Ctx &c, int e, int32_t keyval,
 constexpr int64_t kJoinChunkPairs = 16384;
 constexpr int64_t kJoinSharePairs = 2 * kJoinChunkPairs;
 constexpr int kJoinMaxSub = 64;
+// blocks of rows from which a level counted row by row is shared
+constexpr int64_t kCountShareBlocks = 4;
 // blocks of pairs whose accepted rows take one output reservation (shared
 // levels): up to 4 NT pairs, staged per wave in LDS
 constexpr int kJoinGroup = 4;
+
+// A level's block of parent rows, staged in LDS behind the waves' staged
+// output rows: every pair tests its new value against the whole row and every
+// accepted pair copies it, which from global memory was a chain of k dependent
+// reads per pair (a 14-column level of 22,000 pairs: 1.0 ms in one workgroup).
+constexpr int kJoinStageRows = NW * 512 * (int)sizeof(int32_t);
+static_assert(kJoinStageRows + NT * (SGM_MAX_QV - 1) * sizeof(int32_t) <= kDynLds, "parent rows");
 
 // Pair i of a block: its row rr within the block of parent rows (the last
 // whose pair offset is <= pi), its new value x, and whether the extended
 // row passes the injectivity test and every check edge of the level
 // (Sec. "Joining Phase").
-__device__ __forceinline__ bool join_pair(const Smem &s, const JLevel &L, int64_t r0, int64_t pi,
-                                          int32_t *rr_out, int32_t *x_out, uint64_t &jb) {
-    int32_t a0 = 0, a1 = NT;
-    while (a1 - a0 > 1) {
-        const int32_t mid = (a0 + a1) >> 1;
-        if (s.pairoff[mid] <= pi) a0 = mid;
-        else a1 = mid;
-    }
+__device__ __forceinline__ bool join_pair(const Smem &s, const JLevel &L, const int32_t *rows,
+                                          int64_t pi, int32_t *rr_out, int32_t *x_out,
+                                          uint64_t &jb) {
+    int32_t a0 = 0;
+#pragma unroll
+    for (int st = NT / 2; st > 0; st >>= 1)
+        if (s.pairoff[a0 + st] <= pi) a0 += st;
     const int32_t x = L.evals[s.rowlo[a0] + (pi - s.pairoff[a0])];
     const int k = L.k;
-    const int32_t *row = L.table + (r0 + a0) * k;
+    const int32_t *row = rows + a0 * k;
     bool ok = true;
-    if (!L.homo)
-        for (int cc = 0; cc < k; ++cc)
-            if (row[cc] == x) ok = false;
+    for (uint32_t m = L.cmask; m; m &= m - 1) ok &= row[__builtin_ctz(m)] != x;
     for (int ci = 0; ci < L.nchk && ok; ++ci) {
         // the check edge's values for the row's key vertex hold x
         const JChk &h = L.chk[ci];
@@ -2292,7 +2299,7 @@ __device__ __forceinline__ bool join_pair(const Smem &s, const JLevel &L, int64_
             ok = jx < vhi && h.vals[jx] == x;
         }
     }
-    jb += 4ull + 4ull * k + 24ull * L.nchk + (ok ? 4ull * (k + 1) : 0ull);
+    jb += 4ull + 4ull * k + 24ull * L.nchk + (ok && !L.count ? 4ull * (k + 1) : 0ull);
     *rr_out = a0;
     *x_out = x;
     return ok;
@@ -2300,16 +2307,17 @@ __device__ __forceinline__ bool join_pair(const Smem &s, const JLevel &L, int64_
 
 // Copy a wave's n staged output rows (parent row within the block, new
 // value) to out[base, base + n), consecutive lanes on consecutive ints.
-__device__ __forceinline__ void join_put(const JLevel &L, int64_t r0, const int32_t *wrr,
+__device__ __forceinline__ void join_put(const JLevel &L, const int32_t *rows, const int32_t *wrr,
                                          const int32_t *wx, int n, int64_t base, int lane) {
     const int k = L.k, w = k + 1;
     // e / w by a 16-bit reciprocal: exact for e < 4096, w <= 16
     const uint32_t inv = (65536u + (uint32_t)w - 1u) / (uint32_t)w;
     int32_t *dst = L.out + base * w;
+#pragma unroll 4
     for (int e = lane; e < n * w; e += 64) {
         const int rw = (int)(((uint32_t)e * inv) >> 16);
         const int cc = e - rw * w;
-        dst[e] = cc < k ? L.table[(r0 + wrr[rw]) * k + cc] : wx[rw];
+        dst[e] = cc < k ? rows[wrr[rw] * k + cc] : wx[rw];
     }
 }
 
@@ -2320,6 +2328,10 @@ __device__ __forceinline__ void join_put(const JLevel &L, int64_t r0, const int3
 // LDS atomic per wave. SHARED: the blocks sub, sub + nsub, ... only, and
 // the accepted rows of up to kJoinGroup of them take their places with one
 // device-scope atomic on *gctr.
+// A counting level (L.count, the last of a count-only query) writes no rows:
+// its accepted pairs are counted, and without check edges not even looked at,
+// since a row's pairs are its fan-out less the values of the row itself that
+// its candidate edges hold. Counts go to s.cnt64, or to *gctr when SHARED.
 template <bool SHARED>
 __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, int64_t r1,
                                           int32_t sub, int32_t nsub, unsigned long long *gctr,
@@ -2327,9 +2339,17 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
     Smem &s = *c.s;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t r = r0 + threadIdx.x;
+    int32_t *rows = (int32_t *)(c.dyn + kJoinStageRows);
+    {
+        const int32_t *src = L.table + r0 * L.k;
+        const int nint = (int)(r1 - r0) * L.k;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < nint; i += NT) rows[i] = src[i];
+    }
+    __syncthreads();
     int32_t fan = 0, lo = 0;
     if (r < r1) {
-        const int32_t pv = L.table[r * L.k + L.cp];
+        const int32_t pv = rows[threadIdx.x * L.k + L.cp];
         const int32_t i = lower_bound_i32(L.pk, 0, L.npk, pv);
         if (i < L.npk && L.pk[i] == pv) {
             lo = L.eoffs[i];
@@ -2337,9 +2357,34 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
         }
         jb += 16ull + 4ull * (32 - __clz(L.npk | 1));
     }
+    if (L.count && L.nchk == 0) {
+        int64_t mine = fan;
+        const int32_t *row = rows + threadIdx.x * L.k;
+        if (fan > 0)
+            for (uint32_t m = L.cmask; m; m &= m - 1) {
+                const int32_t x = row[__builtin_ctz(m)];
+                const int32_t j = lower_bound_i32(L.evals, lo, lo + fan, x);
+                mine -= j < lo + fan && L.evals[j] == x;
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+        if (lane == 0 && mine) atomicAdd(SHARED ? gctr : &s.cnt64, (unsigned long long)mine);
+        __syncthreads();
+        return;
+    }
     int64_t tot;
     const int64_t ex = block_excl_scan(fan, s.sh, &tot);
-    if (!SHARED && L.rows <= NT && tot > kPairSlack * L.cap) {
+    if (tot > INT32_MAX) {
+        // more pairs than a block's offsets hold: the multi-kernel path
+        if (threadIdx.x == 0) {
+            if (SHARED) atomicExch(gabort, kWhySlab);
+            else s.abort_ = kWhySlab;
+            s.need = INT64_MAX;
+        }
+        __syncthreads();
+        return;
+    }
+    if (!SHARED && !L.count && L.rows <= NT && tot > kPairSlack * L.cap) {
         // the level's only block of rows: its pairs bound the level, so a
         // level that could not fit even a much larger slot stops here
         if (threadIdx.x == 0) {
@@ -2354,11 +2399,22 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
     __syncthreads();
     int32_t *wrr = (int32_t *)c.dyn + wid * 512;  // this wave's staged rows
     int32_t *wx = wrr + 256;
-    if (!SHARED) {
+    if (L.count) {
+        const int64_t nblk = (tot + NT - 1) / NT;
+        int64_t mine = 0;
+        for (int64_t bi = SHARED ? sub : 0; bi < nblk; bi += SHARED ? nsub : 1) {
+            const int64_t pi = bi * NT + threadIdx.x;
+            int32_t rr, x;
+            mine += pi < tot && join_pair(s, L, rows, pi, &rr, &x, jb);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+        if (lane == 0 && mine) atomicAdd(SHARED ? gctr : &s.cnt64, (unsigned long long)mine);
+    } else if (!SHARED) {
         for (int64_t pb = 0; pb < tot; pb += NT) {
             const int64_t pi = pb + threadIdx.x;
             int32_t rr = 0, x = 0;
-            const bool ok = pi < tot && join_pair(s, L, r0, pi, &rr, &x, jb);
+            const bool ok = pi < tot && join_pair(s, L, rows, pi, &rr, &x, jb);
             const uint64_t bm = __ballot(ok);
             const int nok = __popcll(bm);
             int32_t base = 0;
@@ -2370,13 +2426,11 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
                 wrr[j] = rr;
                 wx[j] = x;
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_sync();
             if ((int64_t)base + nok > L.cap) {
                 if (lane == 0) s.abort_ = kWhySlab;
             } else {
-                join_put(L, r0, wrr, wx, nok, base, lane);
+                join_put(L, rows, wrr, wx, nok, base, lane);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -2390,7 +2444,7 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
                 if (bi >= nblk) break;
                 const int64_t pi = bi * NT + threadIdx.x;
                 int32_t rr = 0, x = 0;
-                const bool ok = pi < tot && join_pair(s, L, r0, pi, &rr, &x, jb);
+                const bool ok = pi < tot && join_pair(s, L, rows, pi, &rr, &x, jb);
                 const uint64_t bm = __ballot(ok);
                 if (ok) {
                     const int j = wn + __popcll(bm & lanemask_lt(lane));
@@ -2399,9 +2453,7 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
                 }
                 wn += __popcll(bm);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_sync();
             // one reservation for the group's accepted rows (two buffers: a
             // wave may run one group ahead)
             if (lane == 0) s.wnok[par][wid] = wn;
@@ -2417,7 +2469,7 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
             if (base + wn > L.cap) {
                 if (lane == 0 && wn) atomicExch(gabort, kWhySlab);
             } else {
-                join_put(L, r0, wrr, wx, wn, base, lane);
+                join_put(L, rows, wrr, wx, wn, base, lane);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -2505,10 +2557,11 @@ __device__ __forceinline__ void shared_join(Ctx &c, int32_t nch, uint64_t &jb) {
         atomicSub(&c.hctr[0], 1);
         const unsigned long long placed =
             __hip_atomic_load(&j->jrows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.cnt64 = placed;
         s.ctr = (int32_t)min((unsigned long long)s.jl.cap, placed);
         const int32_t ab = __hip_atomic_load(&j->abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (ab) s.abort_ = ab;
-        if (placed > (unsigned long long)s.jl.cap) s.abort_ = kWhySlab;
+        if (!s.jl.count && placed > (unsigned long long)s.jl.cap) s.abort_ = kWhySlab;
         if (got < nch) s.abort_ = kWhyHelp;
         add_bytes(c, __hip_atomic_load(&j->bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
@@ -2686,6 +2739,24 @@ __device__ __forceinline__ void clear_slot(Ctx &c, bool full) {
     __syncthreads();
 }
 
+// The one row over single-candidate query vertices vert(0 .. k): their
+// candidates to out[0 .. k), and level_rows[i] = 1 while the first i + 1 of
+// them are distinct (or may repeat), else 0. Ends without a barrier.
+template <class F>
+__device__ __forceinline__ void single_row(Ctx &c, int32_t *out, int k, F vert) {
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    const int32_t x = lane < k ? c.L(vert(lane))[0] : -1 - lane;
+    uint32_t dup = 0;  // lanes that repeat an earlier one
+    if (!c.Q->homo)
+        for (int i = 0; i + 1 < k; ++i)
+            dup |= (uint32_t)__ballot(lane > i && x == __builtin_amdgcn_readlane(x, i));
+    if (lane < k) {
+        out[lane] = x;
+        c.s->level_rows[lane] = (dup & ((2u << lane) - 1u)) == 0;
+    }
+}
+
 __device__ __forceinline__ void run_query(Ctx &c) {
     const DevGraph &g = c.g;
     Smem &s = *c.s;
@@ -2819,18 +2890,13 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                 // match exactly when they are distinct. The join binds the
                 // vertices in index order.
                 mark(c, 2);
+                single_row(c, one_row, n, [&](int u) { return u; });
+                if (threadIdx.x < n) {
+                    s.jorder[threadIdx.x] = threadIdx.x;
+                    s.jpos[threadIdx.x] = threadIdx.x;
+                }
                 if (threadIdx.x == 0) {
-                    int64_t r = 1;
-                    for (int u = 0; u < n; ++u) {
-                        const int32_t x = c.L(u)[0];
-                        if (!Q.homo)
-                            for (int w = 0; w < u; ++w) r &= (int64_t)(one_row[w] != x);
-                        one_row[u] = x;
-                        s.jorder[u] = u;
-                        s.jpos[u] = u;
-                        s.level_rows[u] = r;
-                    }
-                    s.nrows = r;
+                    s.nrows = s.level_rows[n - 1];
                     add_bytes(c, 8ull * n);
                 }
                 __syncthreads();
@@ -2844,9 +2910,15 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                 __syncthreads();
                 ev(c, SGM_EV_ORDER);
                 // edges the join looks up by their destination: rebuild keyed so
+                // The join's leading vertices of one candidate each make one
+                // row (every edge between them holds its pair, or the query
+                // had ended): no level and no re-keyed table is run for them.
+                int pre = 0;
+                while (pre < n && s.cnt[s.jorder[pre]] == 1) ++pre;
                 uint64_t redo = 0;
                 for (int e = 0; e < Q.m; ++e)
-                    if (s.eckey[e] != s.ecbuilt[e]) redo |= 1ull << e;
+                    if (s.eckey[e] != s.ecbuilt[e] && (s.jpos[Q.esrc[e]] >= pre || s.jpos[Q.edst[e]] >= pre))
+                        redo |= 1ull << e;
                 const uint64_t one2 = aborted(c) ? 0ull : ec_build_single(c, redo, 1);
                 if (one2) ev(c, SGM_EV_EDGES);
                 for (int e = 0; e < Q.m && !aborted(c); ++e)
@@ -2861,7 +2933,19 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                 rows = s.cnt[s.jorder[0]];
                 if (threadIdx.x == 0) s.level_rows[0] = rows;
                 int k = 1;
-                for (int lv = 0; lv < n - 1 && !aborted(c) && rows > 0; ++lv) {
+                if (pre > 1 && !aborted(c)) {
+                    int32_t *row = (int32_t *)slab_alloc(c, 4ll * pre);
+                    if (row) {
+                        single_row(c, row, pre, [&](int i) { return s.jorder[i]; });
+                        __syncthreads();
+                        table = row;
+                        rows = s.level_rows[pre - 1];
+                        k = pre;
+                        ev(c, SGM_EV_LEVEL);
+                    }
+                }
+                for (int lv = k - 1; lv < n - 1 && !aborted(c) && rows > 0; ++lv) {
+                    const bool counting = Q.count_only && lv == n - 2;
                     const int ext = s.lv_ext[lv];
                     const int p = s.eckey[ext];
                     const int cp = s.jpos[p];
@@ -2882,7 +2966,10 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                         __syncthreads();
                         break;
                     }
-                    if (threadIdx.x == 0) s.ctr = 0;
+                    if (threadIdx.x == 0) {
+                        s.ctr = 0;
+                        s.cnt64 = 0ull;
+                    }
                     __syncthreads();
                     // the level's pairs bound its rows: a level that could not
                     // fit even a much larger slot stops here rather than
@@ -2892,7 +2979,10 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                     // a block of rows whose pairs could reach a shared or a
                     // host-ordered level (rows times the extension edge's
                     // candidate edges bound them) counts them here too
-                    if (rows > NT || rows * s.ectot[ext] >= kJoinSharePairs) {
+                    if (counting && nchk == 0) {
+                        // counted row by row, shared by rows
+                        pairs = rows;
+                    } else if (rows > NT || rows * s.ectot[ext] >= kJoinSharePairs) {
                         int64_t mp = 0;
                         for (int64_t r = threadIdx.x; r < rows; r += NT) {
                             const int32_t pv = table[r * k + cp];
@@ -2900,7 +2990,7 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                             if (i < npk && pk[i] == pv) mp += ecnt[i];
                         }
                         block_excl_scan(mp, s.sh, &pairs);
-                        if (pairs > kPairSlack * cap) {
+                        if (!counting && pairs > kPairSlack * cap) {
                             if (threadIdx.x == 0) {
                                 s.abort_ = kWhySlab;
                                 s.need = used0 + pairs * 4 * (k + 1);
@@ -2914,7 +3004,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                     // with room above for the key columns' candidate lists:
                     // the slot's later queries keep the slab below it.
                     int32_t *out = nullptr;
-                    if (lv == n - 2 && c.host_order_rows > 0 && pairs >= c.host_order_rows) {
+                    if (counting) cap = INT32_MAX;  // no rows are written
+                    if (!counting && lv == n - 2 && c.host_order_rows > 0 && pairs >= c.host_order_rows) {
                         int64_t lint = 0;
                         for (int u = 0; u < n; ++u) lint += s.cnt[u];
                         const int64_t tneed = (pairs * 4 * (k + 1) + 255) & ~(int64_t)255;
@@ -2929,8 +3020,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                             __syncthreads();
                         }
                     }
-                    if (!out) out = (int32_t *)slab_alloc(c, cap * 4 * (k + 1));
-                    if (!out) {
+                    if (!out && !counting) out = (int32_t *)slab_alloc(c, cap * 4 * (k + 1));
+                    if (!out && !counting) {
                         if (threadIdx.x == 0) s.abort_ = kWhySlab;
                         __syncthreads();
                         break;
@@ -2959,7 +3050,16 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                         }
                         L.out = out;
                         L.cap = cap;
-                        L.homo = Q.homo;
+                        L.count = counting;
+                        // columns the new value may repeat: those of a vertex
+                        // that can hold a candidate of the new one
+                        const int w = s.jorder[lv + 1];
+                        uint32_t cm = 0;
+                        for (int i = 0; i < k && !Q.homo; ++i) {
+                            const int32_t a = Q.pred[s.jorder[i]].label, b = Q.pred[w].label;
+                            if (a < 0 || b < 0 || a == b) cm |= 1u << i;
+                        }
+                        L.cmask = cm;
                     }
                     // a level of many pairs is shared (whether or not
                     // workgroups are idle yet: those that become idle join)
@@ -2969,7 +3069,11 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                         nsub = min((int64_t)kJoinMaxSub,
                                    max((int64_t)1, (pairs + nrb * kJoinChunkPairs - 1) /
                                                        (nrb * kJoinChunkPairs)));
-                    const bool share = may_share && pairs >= kJoinSharePairs && nrb * nsub <= kMaxChunks;
+                    // (a counting level without check edges: blocks of rows)
+                    if (counting && nchk == 0) nsub = 1;
+                    const bool share =
+                        may_share && nrb * nsub <= kMaxChunks &&
+                        (counting && nchk == 0 ? nrb >= kCountShareBlocks : pairs >= kJoinSharePairs);
                     if (threadIdx.x == 0) s.jl.nsub = (int32_t)nsub;
                     __syncthreads();
                     uint64_t jb = 0;  // algorithmic bytes of this thread's rows and pairs
@@ -2982,11 +3086,11 @@ __device__ __forceinline__ void run_query(Ctx &c) {
                     }
                     add_bytes(c, jb);
                     __syncthreads();
-                    rows = s.ctr;
+                    rows = counting ? (int64_t)s.cnt64 : (int64_t)s.ctr;
                     if (threadIdx.x == 0) s.level_rows[lv + 1] = rows;
                     // give back the unused part of the table allocation
                     __syncthreads();
-                    if (threadIdx.x == 0 && !s.abort_)
+                    if (threadIdx.x == 0 && !s.abort_ && !counting)
                         s.slab_used = (int64_t)((char *)out - c.slab) + rows * 4 * (k + 1);
                     __syncthreads();
                     ev(c, SGM_EV_LEVEL);
@@ -3009,7 +3113,8 @@ __device__ __forceinline__ void run_query(Ctx &c) {
         return;
     }
     if (threadIdx.x == 0) s.nrows = rows;
-    if (rows > 0) {
+    // a count-only query is done (its last level wrote no table)
+    if (rows > 0 && !Q.count_only) {
         // ordering: key = concatenated candidate ranks in column order 0..n-1;
         // a projection (thesis Ch. 3, Sec. "GpSense") keys and keeps only
         // its columns

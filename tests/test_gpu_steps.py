@@ -90,3 +90,27 @@ def test_flat_filter_rows(V, deg, n_types, n_rels):
             if g.match_query(q, count_only=True) > 200000:
                 continue
             assert np.array_equal(g.match_query(q), og.match_query(q))
+
+
+@pytest.mark.parametrize("n_types,p_any", [(1, 1.0), (2, 0.4), (6, 0.2)])
+@pytest.mark.parametrize("V,E", [(8, 60), (40, 400), (150, 1500), (400, 2600)])
+def test_counts_without_rows(V, E, n_types, p_any):
+    """A count-only query's last join level counts without writing rows: the
+    counts are those of the tables, for levels with and without check edges,
+    one block of parent rows and several (shared or not), repeated values in
+    the fan-out, and leading single-candidate vertices."""
+    rng = np.random.default_rng(31 * V + n_types)
+    mg = random_graph(rng, V, E, n_types=n_types, n_rels=2)
+    rp, col, rel, typ = mg.csr()
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    qs = [random_query(rng, int(rng.integers(1, 5)), n_types, 2, V, p_any_label=p_any,
+                       p_any_rel=p_any, p_pin=p, extra=x) for p in (0.0, 0.4) for x in (0, 3)
+          for _ in range(4)]
+    g = P.Graph(rp, col, rel, typ)
+    wants = [len(og.match_query(q)) for q in qs]
+    for tune in (dict(), dict(help_items=0)):
+        g.set_tuning(**tune)
+        for i, (q, want) in enumerate(zip(qs, wants)):
+            print("case: query", i, "rows", want, flush=True)
+            assert g.match_query(q, count_only=True) == want
+        assert g.match_batch(qs, count_only=True) == wants
