@@ -54,9 +54,11 @@ __device__ __forceinline__ int32_t wave_incl_scan32(int32_t x, int lane) {
 // Block-wide exclusive scan of one int64 per thread. Returns the exclusive
 // prefix; *total receives the block sum. `sh` holds >= blockDim/64 entries.
 // Contains two barriers, the last one after every read of `sh`.
+// W: the block's waves where they are known (0: from blockDim).
+template <int W = 0>
 __device__ __forceinline__ int64_t block_excl_scan(int64_t x, int64_t *sh, int64_t *total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int nw = blockDim.x >> 6;
+    const int nw = W ? W : blockDim.x >> 6;
     const int64_t inc = wave_incl_scan(x, lane);
     if (lane == 63) sh[wid] = inc;
     __syncthreads();

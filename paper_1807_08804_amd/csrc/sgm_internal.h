@@ -20,6 +20,15 @@ constexpr int kMaxNbr = SGM_MAX_QE;
 // Read-only view of the device-resident data graph. Each adjacency entry is
 // {neighbour id, relation}; out-rows are sorted by (dst, rel), in-rows by
 // (src, rel), exact duplicate triples removed.
+// a or b by value: a conditional on the members themselves picks an address,
+// and a copy of the struct then has to live in scratch memory. (In a function
+// that is not inlined the generated choice between the two scratch addresses
+// was even wrong: an address computation overwrote the condition flag.)
+template <class T>
+__host__ __device__ inline T pick(int second, T a, T b) {
+    return second ? b : a;
+}
+
 struct DevGraph {
     int32_t V;
     int32_t nwords;  // ceil(V / 64): words of one candidate bitmap
@@ -58,6 +67,12 @@ struct DevGraph {
     const int32_t *hub_of;
     const int32_t *hub_toff;
     int32_t hub_types;
+    // the arrays of one direction (1: incoming)
+    __host__ __device__ const int32_t *off(int dir) const { return pick(dir, out_off, in_off); }
+    __host__ __device__ const int2 *adj(int dir) const { return pick(dir, out_adj, in_adj); }
+    __host__ __device__ const int2 *tab(int dir, int order) const {
+        return pick(dir, pick(order, out_ta, out_tb), pick(order, in_ta, in_tb));
+    }
 };
 
 // rows this long get the per-type index above

@@ -159,7 +159,9 @@ struct HelpJob {
                                    // 2: parent rows of a join level; 3: keys of an
                                    // edge-candidate table; 4: rows above wg_rows of a
                                    // prune-only step, one per chunk
-    int32_t n_items, G, ncount, revd;
+    int32_t n_items, G, ncount;
+    int32_t nodrop;       // 1: the items stay candidates whatever the tests say
+    int32_t defer, ndef;  // kind 4: survivors' pushes go to the deferred list
     NStep st;
     int32_t nbig, removed, nmarks, abort_;
     // 1 after the owner gave up on a step whose claimed chunks had not all
@@ -225,6 +227,5 @@ struct NArgs {
 
 void launch_reset(hipStream_t s, unsigned long long *ctr);
 void launch_narrow(hipStream_t s, const NArgs &a, int grid);
-size_t narrow_lds_bytes();
 
 }  // namespace sgm

@@ -33,8 +33,8 @@ namespace {
 constexpr int NT = kNarrowThreads;
 constexpr int NW = NT / 64;
 constexpr int kBigCap = 256;         // LDS list of items for the whole workgroup
-// A shared step with at least kLongShare long rows (over 64 strides of its
-// lanes) shares them too, kLongChunk rows per chunk, one wave per row.
+// A step with at least kLongShare rows beyond its flat window shares them
+// too, kLongChunk rows per chunk, one wave per row.
 constexpr int32_t kLongShare = 32;
 constexpr int32_t kLongChunk = 16;
 constexpr int32_t kRevMin = 256;      // candidates of u before a reverse check can pay
@@ -65,6 +65,9 @@ struct Smem {
     unsigned long long cnt64;  // rows of a counting level
     int32_t abort_;
     int32_t q;
+    int64_t slab_cap;  // this query's slab (see k_narrow)
+    int64_t below_top; // a last join level placed at the slab's top: the slab used below it (-1: none)
+    int32_t *table;    // the join's last table
     int32_t nev;
     int32_t nbig;
     int32_t ngiant;
@@ -84,7 +87,7 @@ struct Smem {
     int8_t qsrc[SGM_MAX_QE], qdst[SGM_MAX_QE];  // the query's edges, staged for join_order
     uint64_t revmask;
     NQuery query;           // the descriptor, staged for its many small reads
-    NTest nbl[SGM_MAX_QE];  // neighbours a step still tests per candidate
+    NTest nbl[SGM_MAX_QE + 1];  // neighbours a step still tests (and a reverse test)
     // What filtering has established so far. ver[v] counts the changes of
     // C(v); okv[2 e + s] is the version of one endpoint's candidates for
     // which every candidate of the other (s = 0: the source of query edge e,
@@ -93,6 +96,7 @@ struct Smem {
     int32_t okv[2 * SGM_MAX_QE];
     int32_t skippar;  // the step's test against its parent is known to hold
     int32_t removed;
+    int32_t rdrop;  // candidates a step's reverse tests removed
     int32_t ctr;
     int32_t empty;
     // per-query outcome, written to global memory by thread 0 at the end
@@ -113,7 +117,7 @@ struct Smem {
     unsigned long long pb[5];  // bytes at the phase boundaries
 };
 
-// Dynamic LDS, 46 KB: with the static part a workgroup stays within 64 KB,
+// Scratch LDS (g_dyn), 46 KB: with the rest a workgroup stays within 64 KB,
 // and two workgroups per CU remain resident (registers allow no more). List
 // sorting uses [0, 32 KB); the final ordering keeps keys and indices
 // (bitonic) or digit counts (radix) in [0, 24 KB) and stages the candidate
@@ -123,8 +127,18 @@ constexpr size_t kStageOff = 24 << 10;
 constexpr int32_t kStageInts = (int32_t)((kDynLds - kStageOff) / sizeof(int32_t));
 static_assert(sizeof(int32_t) * kListSortCap <= kDynLds, "list sort space");
 static_assert((sizeof(uint64_t) + sizeof(int32_t)) * kRowSortCap <= kStageOff, "row sort space");
-static_assert(kDynLds + sizeof(Smem) <= (64 << 10), "LDS per workgroup");
+static_assert(kDynLds + sizeof(Smem) + sizeof(NArgs) <= (64 << 10), "LDS per workgroup");
 static_assert(8 * 256 * sizeof(int32_t) <= kStageOff, "radix counts");
+
+// The workgroup's LDS, at file scope: a query's phases and the shared tiers
+// are functions that are not inlined, each with registers of its own, and
+// reach it as LDS too; they rebuild their context from the launch's arguments
+// kept here. In one body the small steps paid for the large tiers' spills: an
+// explore step of one candidate took 9 us, now 6 (a pinned 12-vertex chain
+// 162 -> 126 us), and the kernel's code is a seventh of the former 750 KB.
+__shared__ Smem g_s;
+__shared__ NArgs g_args;
+__shared__ __align__(16) unsigned char g_dyn[kDynLds];
 
 struct Ctx {
     // the launch's graph, read in place from the kernel arguments (a copy in
@@ -139,12 +153,10 @@ struct Ctx {
     int32_t *host_out;
     int64_t host_cap;
     const NQuery *Q;
-    Smem *s;
     uint64_t *bits;     // slot bitmaps [(SGM_MAX_QV + 1) * nwords]
     uint64_t *scratch;  // the extra bitmap of the slot
     int32_t *lists;     // slot lists [SGM_MAX_QV * lcap]
     char *slab;
-    unsigned char *dyn;
     int64_t *trace;     // this query's step events, or null
     int32_t gmax;       // most lanes per candidate group
     int32_t wg_rows;    // rows longer than this get the whole workgroup
@@ -157,19 +169,96 @@ struct Ctx {
     int32_t nslot, ngrid;  // slot workgroups, all workgroups of the launch
     int64_t help_wait;  // polls of a shared step's completion before giving up
     int64_t host_order_rows;  // final tables of this many rows go to the host (0: none)
-    int64_t below_top;  // a last join level placed at the slab's top: the slab used below it
     __device__ uint64_t *B(int u) const { return bits + (int64_t)u * g.nwords; }
     __device__ int32_t *L(int u) const { return lists + (int64_t)u * lcap; }
 };
 
-__device__ __forceinline__ bool aborted(const Ctx &c) { return c.s->abort_ != 0; }
+// slab_cap: the slot's slab below tables its earlier queries of the launch
+// left for the host to order (the whole slab otherwise)
+__device__ __forceinline__ Ctx slot_ctx(const NArgs &a, int slot,
+                                        int32_t q, int64_t slab_cap) {
+    const int32_t nwords = a.g.nwords;
+    uint64_t *bits = a.bits + (int64_t)slot * (SGM_MAX_QV + 1) * nwords;
+    int32_t *lists = a.lists + (int64_t)slot * SGM_MAX_QV * a.lcap;
+    char *slab = a.slab + (int64_t)slot * a.slab_bytes;
+    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.host_out, a.host_cap, &g_s.query,
+               bits, bits + (int64_t)SGM_MAX_QV * nwords, lists, slab,
+               a.trace ? a.trace + (int64_t)q * SGM_TRACE_CAP : nullptr, a.group_lanes,
+               a.wg_rows, a.join_policy,
+               // while filtering the slab holds the long-row overflow list in
+               // [0, 4 lcap) bytes and the marks in [4 lcap, 8 lcap)
+               (int32_t *)(slab + 4 * (int64_t)a.lcap), a.board ? a.board + slot : nullptr, a.hctr,
+               a.help_items, q, a.nslot, a.ngrid, a.help_wait, a.host_order_rows};
+}
+
+// A copy from LDS of what is the same in every lane, in scalar registers.
+template <class T>
+__device__ __forceinline__ T uniform_copy(const T &in) {
+    static_assert(sizeof(T) % 4 == 0, "copied as ints");
+    int32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &in, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    T out;
+    __builtin_memcpy(&out, w, sizeof(T));
+    return out;
+}
+
+template <class T>
+__device__ __forceinline__ T uniform(T x) {
+    return uniform_copy(x);
+}
+
+// Pointers to device memory, known as such (read back from LDS they could
+// point anywhere, and every access through them would be a flat one).
+template <class T>
+__device__ __forceinline__ void in_memory(T *&p) {
+    p = (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+
+// The launch's arguments, inside a function that is not inlined.
+__device__ __forceinline__ NArgs own_args() {
+    NArgs a = uniform_copy(g_args);
+    DevGraph &g = a.g;
+    in_memory(g.out_off);
+    in_memory(g.in_off);
+    in_memory(g.out_adj);
+    in_memory(g.in_adj);
+    in_memory(g.vrow);
+    in_memory(g.tverts);
+    in_memory(g.trow);
+    in_memory(g.vinfo);
+    in_memory(g.out_ta);
+    in_memory(g.out_tb);
+    in_memory(g.in_ta);
+    in_memory(g.in_tb);
+    in_memory(g.hub_of);
+    in_memory(g.hub_toff);
+    in_memory(a.bits);
+    in_memory(a.lists);
+    in_memory(a.slab);
+    in_memory(a.out);
+    in_memory(a.trace);
+    in_memory(a.board);
+    in_memory(a.hctr);
+    return a;
+}
+
+// The slot workgroup's context for its current query, inside a function that
+// is not inlined.
+#define SGM_OWN_CTX(c)                                                                    \
+    const NArgs c##_args = own_args();                                                    \
+    Ctx c = slot_ctx(c##_args, blockIdx.x, __builtin_amdgcn_readfirstlane(g_s.q),         \
+                     uniform_copy(g_s.slab_cap))
+
+__device__ __forceinline__ bool aborted(const Ctx &c) { return g_s.abort_ != 0; }
 
 // Algorithmic byte accounting: every phase adds the global-memory words its
 // algorithm must read or write (adjacency entries 8 B, neighbour tests 4 B,
 // list / table / edge-table ints 4 B, bitmap words 8 B), not what caches
 // happen to serve.
 __device__ __forceinline__ void add_bytes(Ctx &c, uint64_t b) {
-    if (b) atomicAdd(&c.s->bytes, (unsigned long long)b);
+    if (b) atomicAdd(&g_s.bytes, (unsigned long long)b);
 }
 
 // wave-reduced variant: every lane of the wave must call it
@@ -182,7 +271,7 @@ __device__ __forceinline__ void add_bytes_wave(Ctx &c, uint64_t b) {
 // step event (uniform call; thread 0 records)
 __device__ __forceinline__ void ev(Ctx &c, int code) {
     if (c.trace && threadIdx.x == 0) {
-        const int k = c.s->nev++;
+        const int k = g_s.nev++;
         if (k < SGM_TRACE_CAP) c.trace[k] = (int64_t)(wall_clock64() << 8) | code;
     }
 }
@@ -192,8 +281,8 @@ __device__ __forceinline__ void ev(Ctx &c, int code) {
 // have passed a barrier since the phase's last byte count.
 __device__ __forceinline__ void mark(Ctx &c, int i) {
     if (threadIdx.x == 0) {
-        c.s->t[i] = wall_clock64();
-        c.s->pb[i] = c.s->bytes;
+        g_s.t[i] = wall_clock64();
+        g_s.pb[i] = g_s.bytes;
     }
 }
 
@@ -208,12 +297,12 @@ __device__ __forceinline__ int64_t kPinFloor(const Ctx &c) {
 // overflow).
 __device__ __forceinline__ char *slab_alloc(Ctx &c, int64_t bytes) {
     __syncthreads();
-    const int64_t off = (c.s->slab_used + 255) & ~(int64_t)255;
+    const int64_t off = (g_s.slab_used + 255) & ~(int64_t)255;
     char *p = (off + bytes <= c.slab_bytes) ? c.slab + off : nullptr;
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (p) c.s->slab_used = off + bytes;
-        else c.s->abort_ = kWhySlab;
+        if (p) g_s.slab_used = off + bytes;
+        else g_s.abort_ = kWhySlab;
     }
     __syncthreads();
     return p;
@@ -222,12 +311,12 @@ __device__ __forceinline__ char *slab_alloc(Ctx &c, int64_t bytes) {
 // Counters a filter step updates: in the workgroup's LDS, or on the helper
 // board while several workgroups share the step.
 struct LdsCtr {
-    Smem *s;
-    __device__ int32_t *cnt(int v) const { return &s->cnt[v]; }
-    __device__ int32_t *nbig() const { return &s->nbig; }
-    __device__ int32_t *removed() const { return &s->removed; }
-    __device__ int32_t *nmarks() const { return &s->nmarks; }
-    __device__ int32_t *abort_() const { return &s->abort_; }
+    __device__ int32_t *cnt(int v) const { return &g_s.cnt[v]; }
+    __device__ int32_t *nbig() const { return &g_s.nbig; }
+    __device__ int32_t *removed() const { return &g_s.removed; }
+    __device__ int32_t *nmarks() const { return &g_s.nmarks; }
+    __device__ int32_t *ndef() const { return &g_s.ndef; }
+    __device__ int32_t *abort_() const { return &g_s.abort_; }
 };
 struct BoardCtr {
     HelpJob *j;
@@ -235,6 +324,7 @@ struct BoardCtr {
     __device__ int32_t *nbig() const { return &j->nbig; }
     __device__ int32_t *removed() const { return &j->removed; }
     __device__ int32_t *nmarks() const { return &j->nmarks; }
+    __device__ int32_t *ndef() const { return &j->ndef; }
     __device__ int32_t *abort_() const { return &j->abort_; }
 };
 
@@ -259,7 +349,7 @@ __device__ __forceinline__ void push_bit(Ctx &c, const K &k, uint64_t *tb, int32
 }
 
 __device__ __forceinline__ void push_bit(Ctx &c, uint64_t *tb, int32_t *tl, int v, int32_t x) {
-    push_bit(c, LdsCtr{c.s}, tb, tl, v, x);
+    push_bit(c, LdsCtr{}, tb, tl, v, x);
 }
 
 // Set bit x in tb; true if it was clear. With `look`, a plain read first
@@ -342,11 +432,32 @@ __device__ __forceinline__ bool nbr_hit(const Ctx &c, const NTest &d, int2 e) {
 }
 
 // Keep only the list entries whose bit is still set, preserving order.
+__device__ __forceinline__ void list_from_bits(Ctx &c, int u);
+
+// Zero the bitmap words of u's n listed candidates: one by one, or all words
+// in order when the list is longer (a list of millions took one workgroup
+// milliseconds of scattered stores).
+__device__ __forceinline__ void clear_words(Ctx &c, int u, int32_t n) {
+    uint64_t *b = c.B(u);
+    const int32_t *l = c.L(u);
+    if (n > c.g.nwords / 4) {
+        for (int32_t w = threadIdx.x; w < c.g.nwords; w += NT) b[w] = 0ull;
+    } else {
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < n; i += NT) b[l[i] >> 6] = 0ull;
+    }
+}
+
 __device__ __forceinline__ void compact_list(Ctx &c, int u) {
+    if (g_s.cnt[u] > c.g.nwords) {
+        // longer than the bitmap: read that instead
+        list_from_bits(c, u);
+        return;
+    }
     int32_t *l = c.L(u);
     const uint64_t *b = c.B(u);
     __syncthreads();
-    const int32_t n = c.s->cnt[u];
+    const int32_t n = g_s.cnt[u];
     int64_t out = 0;
     // eight consecutive entries per thread, their reads and bit tests all in
     // flight before the block scan; entries keep their order
@@ -364,7 +475,7 @@ __device__ __forceinline__ void compact_list(Ctx &c, int u) {
             cnt += keep[k] ? 1 : 0;
         }
         int64_t tot;
-        int64_t p = out + block_excl_scan(cnt, c.s->sh, &tot);
+        int64_t p = out + block_excl_scan<NW>(cnt, g_s.sh, &tot);
         // the block scan's barriers ordered every read of this round before
         // these writes, which stay at or below the entries just read
 #pragma unroll
@@ -374,7 +485,7 @@ __device__ __forceinline__ void compact_list(Ctx &c, int u) {
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        c.s->cnt[u] = (int32_t)out;
+        g_s.cnt[u] = (int32_t)out;
         add_bytes(c, 12ull * n + 4ull * out);
     }
     __syncthreads();
@@ -382,6 +493,7 @@ __device__ __forceinline__ void compact_list(Ctx &c, int u) {
 
 // Rebuild list u from its bitmap in ascending order (O(V/64) words).
 __device__ __forceinline__ void list_from_bits(Ctx &c, int u) {
+    __syncthreads();
     const int32_t nwords = c.g.nwords;
     const uint64_t *src = c.B(u);
     int32_t *l = c.L(u);
@@ -400,9 +512,9 @@ __device__ __forceinline__ void list_from_bits(Ctx &c, int u) {
             cnt += __popcll(wd[k]);
         }
         int64_t tot;
-        const int64_t ex = block_excl_scan(cnt, c.s->sh, &tot);
+        const int64_t ex = block_excl_scan<NW>(cnt, g_s.sh, &tot);
         if (out + tot > c.lcap) {
-            if (threadIdx.x == 0) c.s->abort_ = kWhyList;
+            if (threadIdx.x == 0) g_s.abort_ = kWhyList;
             break;  // uniform: tot and out are block-uniform
         }
         int64_t p = out + ex;
@@ -417,8 +529,8 @@ __device__ __forceinline__ void list_from_bits(Ctx &c, int u) {
         out += tot;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && !c.s->abort_) {
-        c.s->cnt[u] = (int32_t)out;
+    if (threadIdx.x == 0 && !g_s.abort_) {
+        g_s.cnt[u] = (int32_t)out;
         add_bytes(c, 8ull * nwords + 4ull * out);
     }
     __syncthreads();
@@ -427,7 +539,7 @@ __device__ __forceinline__ void list_from_bits(Ctx &c, int u) {
 // Sort list u ascending (LDS bitonic, or a rebuild from the bitmap).
 __device__ __forceinline__ void sort_list(Ctx &c, int u) {
     __syncthreads();
-    const int32_t n = c.s->cnt[u];
+    const int32_t n = g_s.cnt[u];
     if (n <= 1) return;
     int32_t N = 1, lg = 0;
     while (N < n) {
@@ -443,7 +555,7 @@ __device__ __forceinline__ void sort_list(Ctx &c, int u) {
         return;
     }
     int32_t *l = c.L(u);
-    int32_t *t = (int32_t *)c.dyn;
+    int32_t *t = (int32_t *)g_dyn;
     for (int32_t i = threadIdx.x; i < N; i += NT) t[i] = i < n ? l[i] : INT32_MAX;
     __syncthreads();
     for (int32_t size = 2; size <= N; size <<= 1) {
@@ -477,17 +589,35 @@ __device__ __forceinline__ void row_of(const DevGraph &g, int32_t up, int dir, i
     *end = dir ? r.w : r.y;
 }
 
+// First index in [b, e) where less() no longer holds (e if none); the same
+// arguments in all 64 lanes, all active. Each round reads 64 places at once:
+// three dependent reads where a binary search of a hub's row takes 15 to 20.
+template <class F>
+__device__ __forceinline__ int32_t wave_bound(int32_t b, int32_t e, F less) {
+    const int lane = threadIdx.x & 63;
+    while (e - b > 64) {
+        const int64_t len = e - b;
+        auto at = [&](int l) { return b + (int32_t)((int64_t)(l + 1) * len / 65); };
+        const int n = __popcll(__ballot(less(at(lane))));
+        const int32_t nb = n == 0 ? b : at(n - 1) + 1;
+        if (n < 64) e = at(n);
+        b = nb;
+    }
+    return b + __popcll(__ballot(b + lane < e && less(b + lane)));
+}
+
 // Entries of candidate up's row that can pass test d: a hub row (at least
 // kHubRow entries) tested against a typed query vertex is read from its
 // copy sorted by the other end's type (then by relation for a labelled
 // test), restricted to that type (and relation); any other row in full.
 // Every entry left out fails the test (wrong type or relation), so the
 // outcome is the full row's; the slice keeps the other ends ascending.
+template <bool UNI = true>
 __device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const NTest &d,
                                                 int32_t *beg, int32_t *end) {
     const DevGraph &g = c.g;
     row_of(g, up, d.dir, beg, end);
-    const int2 *adj = d.dir ? g.in_adj : g.out_adj;
+    const int2 *adj = g.adj(d.dir);
     if (g.hub_types == 0 || *end - *beg < kHubRow) return adj;
     const int32_t t = d.label;
     if (t < 0 || t + 1 >= g.hub_types) return adj;
@@ -495,9 +625,17 @@ __device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const 
     const int order = d.rel >= 0 ? 0 : 1;
     const int32_t *toff = g.hub_toff + ((int64_t)(h * 2 + d.dir) * 2 + order) * g.hub_types;
     int32_t b = *beg + toff[t], e = *beg + toff[t + 1];
-    const int2 *arr = d.dir ? (order ? g.in_tb : g.in_ta) : (order ? g.out_tb : g.out_ta);
+    const int2 *arr = g.tab(d.dir, order);
     if (d.rel >= 0) {
         // the type's entries are sorted by relation: its relation's range
+        if (UNI) {
+            const int32_t b0 = b;
+            b = wave_bound(b0, e, [&](int32_t i) { return (arr[i].y & g.rel_mask) < d.rel; });
+            e = wave_bound(b0, e, [&](int32_t i) { return (arr[i].y & g.rel_mask) <= d.rel; });
+            *beg = b;
+            *end = e;
+            return arr;
+        }
         int32_t lo = b, hi = e;
         while (lo < hi) {
             const int32_t mid = (lo + hi) >> 1;
@@ -518,6 +656,15 @@ __device__ __forceinline__ const int2 *test_row(const Ctx &c, int32_t up, const 
     return arr;
 }
 
+// Candidate up leaves its set (ub; null: a step that only looks, see
+// filter_step's reverse tests).
+template <class K>
+__device__ __forceinline__ void drop_item(const K &k, uint64_t *ub, int32_t up) {
+    if (!ub) return;
+    atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
+    atomicAdd(k.removed(), 1);
+}
+
 // Whole workgroup on one candidate (uniform call). Prune: the candidate
 // survives if every listed query edge has a matching neighbour; explore
 // then pushes every matching neighbour.
@@ -533,12 +680,12 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
         // once (bit 4j + k of `hits`: entry threadIdx.x + k NT of row j
         // matches), one barrier decides whether the candidate lives, and
         // pushes replay the recorded hits.
-        if (threadIdx.x == 0) c.s->rowhit = 0ull;
+        if (threadIdx.x == 0) g_s.rowhit = 0ull;
         __syncthreads();
         uint64_t hits = 0, seen = 0;
         for (int j = 0; j < ncount; ++j) {
             const NTest d = nb[j];
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
+            const int2 *adj = g.adj(d.dir);
             int32_t beg, end;
             row_of(g, up, d.dir, &beg, &end);
             const int32_t i = beg + threadIdx.x;
@@ -548,17 +695,16 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
                                (uint64_t)((i + NT < end) & nbr_hit(c, d, e1)) << 1 |
                                (uint64_t)((i + 2 * NT < end) & nbr_hit(c, d, e2)) << 2 |
                                (uint64_t)((i + 3 * NT < end) & nbr_hit(c, d, e3)) << 3;
-            if (h) atomicOr(&c.s->rowhit, 1ull << j);
+            if (h) atomicOr(&g_s.rowhit, 1ull << j);
             hits |= h << (4 * j);
             seen += end - beg;
         }
         __syncthreads();
-        const bool alive = __popcll(c.s->rowhit) == ncount;
+        const bool alive = __popcll(g_s.rowhit) == ncount;
         __syncthreads();  // rowhit is read by all before the next candidate clears it
         if (!alive) {
             if (threadIdx.x == 0) {
-                atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
-                atomicAdd(k.removed(), 1);
+                drop_item(k, ub, up);
                 fb += 20ull + 12ull * seen;
             }
             return;
@@ -568,7 +714,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
                 const uint32_t hj = (uint32_t)(hits >> (4 * j)) & 15u;
                 if (!hj) continue;
                 const NTest d = nb[j];
-                const int2 *adj = d.dir ? g.in_adj : g.out_adj;
+                const int2 *adj = g.adj(d.dir);
                 int32_t beg, end;
                 row_of(g, up, d.dir, &beg, &end);
                 uint64_t *tb = d.mode == 0 ? c.scratch : c.B(d.v);
@@ -605,15 +751,14 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
     }
     if (!alive) {
         if (threadIdx.x == 0) {
-            atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
-            atomicAdd(k.removed(), 1);
+            drop_item(k, ub, up);
             fb += 20ull + 12ull * seen;
         }
         return;
     }
     if (st.push && defer) {
         if (threadIdx.x == 0) {
-            defer[c.s->ndef++] = up;
+            defer[atomicAdd(k.ndef(), 1)] = up;
             fb += 20ull + 12ull * seen;
         }
         return;
@@ -649,7 +794,7 @@ __device__ __forceinline__ void item_wg_k(Ctx &c, const K &k, const NStep &st, c
 
 __device__ __forceinline__ void item_wg(Ctx &c, const NStep &st, const NTest *nb, int ncount, int32_t up,
                                         uint64_t *ub, uint64_t &fb, int32_t *defer = nullptr) {
-    item_wg_k(c, LdsCtr{c.s}, st, nb, ncount, up, ub, fb, defer);
+    item_wg_k(c, LdsCtr{}, st, nb, ncount, up, ub, fb, defer);
 }
 
 // One wave on one candidate (wave-uniform call, no workgroup barrier), four
@@ -685,8 +830,7 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NTest *
     }
     if (!alive) {
         if (lane == 0) {
-            atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
-            atomicAdd(&c.s->removed, 1);
+            drop_item(LdsCtr{}, ub, up);
             fb += 20ull + 12ull * seen;
         }
         return;
@@ -694,7 +838,7 @@ __device__ __forceinline__ void item_wave(Ctx &c, const NStep &st, const NTest *
     if (st.push && defer) {
         // the pushes go to row segments that several workgroups share
         if (lane == 0) {
-            defer[atomicAdd(&c.s->ndef, 1)] = up;
+            defer[atomicAdd(&g_s.ndef, 1)] = up;
             fb += 20ull + 12ull * seen;
         }
         return;
@@ -736,55 +880,6 @@ __device__ __forceinline__ int lanes_for(int32_t n, int gmax) {
     int G = gmax;
     while (G > 1 && (int64_t)G * n > NT) G >>= 1;
     return G;
-}
-
-// Reverse form of the prune test against one initialised neighbour v with
-// few candidates (prune-only steps): mark the candidates of u that have a
-// matching edge to some candidate of v, found in the rows of v's candidates
-// in the other direction, then drop the unmarked ones. The survivors are the
-// same as when each candidate of u scans its own row for a member of v's
-// bitmap. Marks go to the slot's scratch bitmap, which a prune-only step
-// does not otherwise use; they fall inside u's candidates, so clearing the
-// words of u's list leaves it zero again.
-__device__ __forceinline__ void prune_reverse(Ctx &c, int u, int v, int dir, int32_t rel,
-                                              uint64_t &fb) {
-    const DevGraph &g = c.g;
-    uint64_t *ub = c.B(u);
-    const int32_t *ul = c.L(u);
-    const int32_t n = c.s->cnt[u];
-    const int32_t *vl = c.L(v);
-    const int32_t nv = c.s->cnt[v];
-    const int32_t ulabel = c.Q->pred[u].label;
-    // a candidate's out-edge (dir 0) is an in-edge of the neighbour, and so on
-    const int32_t *off = dir ? g.out_off : g.in_off;
-    const int2 *adj = dir ? g.out_adj : g.in_adj;
-    const int lane = threadIdx.x & 63;
-    uint64_t seen = 0;
-    for (int32_t i = threadIdx.x >> 6; i < nv; i += NW) {
-        const int32_t y = vl[i];
-        const int32_t beg = off[y], end = off[y + 1];
-        for (int32_t k = beg + lane; k < end; k += 64) {
-            const int2 e = adj[k];
-            if (adj_rel_ok(g, e, rel) && adj_type_ok(g, e, ulabel) && bit_test(ub, e.x))
-                atomicOr((unsigned long long *)&c.scratch[e.x >> 6], 1ull << (e.x & 63));
-        }
-        if (lane == 0) seen += 12ull + 16ull * (end - beg);
-    }
-    fb += seen;
-    __syncthreads();
-    int32_t removed = 0;
-    for (int32_t i = threadIdx.x; i < n; i += NT) {
-        const int32_t x = ul[i];
-        if (bit_test(ub, x) && !bit_test(c.scratch, x)) {
-            atomicAnd((unsigned long long *)&ub[x >> 6], ~(1ull << (x & 63)));
-            ++removed;
-        }
-    }
-    if (removed) atomicAdd(&c.s->removed, removed);
-    __syncthreads();
-    for (int32_t i = threadIdx.x; i < n; i += NT) c.scratch[ul[i] >> 6] = 0ull;
-    if (threadIdx.x == 0) fb += 28ull * n;
-    __syncthreads();
 }
 
 // Flat scan of several adjacency rows by one wave: the entries of up to 64
@@ -845,7 +940,7 @@ __device__ __forceinline__ void flat_owner(const FlatLds *w, const int32_t (&e)[
 }
 
 __device__ __forceinline__ FlatLds *flat_lds(Ctx &c) {
-    return (FlatLds *)c.dyn + (threadIdx.x >> 6);
+    return (FlatLds *)g_dyn + (threadIdx.x >> 6);
 }
 
 // The first step of a query with an unpinned root takes its candidates from
@@ -897,8 +992,8 @@ __device__ __forceinline__ void keep_root(Ctx &c, const K &k, int u, uint64_t *u
 template <class K>
 __device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t root, bool push,
                                            const NTest *nb, int ncount, const int32_t *ul,
-                                           int32_t i0, int32_t i1, uint64_t *ub, bool revd,
-                                           int32_t bigdeg, uint64_t &fb) {
+                                           int32_t i0, int32_t i1, uint64_t *ub, int32_t bigdeg,
+                                           uint64_t &fb) {
     const DevGraph &g = c.g;
     const int lane = threadIdx.x & 63;
     FlatLds *w = flat_lds(c);
@@ -906,7 +1001,6 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t ro
     const int32_t up = have ? ul[i0 + lane] : 0;
     const int4 vr = root < 0 ? g.vrow[up] : have ? g.trow[(ul - g.tverts) + i0 + lane] : make_int4(0, 0, 0, 0);
     if (root >= 0) have = have && root_ok(g, root, up, vr);
-    if (revd) have = have && bit_test(ub, up);  // else already dropped
     int32_t maxd = 0;
     for (int j = 0; j < ncount; ++j) maxd = max(maxd, nb[j].dir ? vr.w - vr.z : vr.y - vr.x);
     const bool over = have && maxd > bigdeg;
@@ -923,7 +1017,7 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t ro
         for (int j = 0; j < ncount && alive; ++j) {
             const NTest d = nb[j];
             if (pass == 0 && d.known && !direct) continue;  // pushes only
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
+            const int2 *adj = g.adj(d.dir);
             const bool on = (alive >> lane) & 1ull;
             int32_t beg = d.dir ? vr.z : vr.x;
             int32_t len = on ? (d.dir ? vr.w : vr.y) - beg : 0;
@@ -983,7 +1077,7 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t ro
         if (lane == 0) fb += 20ull * (i1 - i0) + 12ull * seen;
         return;
     }
-    const uint64_t dead = todo & ~alive;
+    const uint64_t dead = ub ? todo & ~alive : 0ull;
     if ((dead >> lane) & 1ull)
         atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
     if (lane == 0) {
@@ -999,8 +1093,8 @@ __device__ __forceinline__ void wave_items(Ctx &c, const K &k, int u, int32_t ro
 template <class K>
 __device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root, bool push,
                                          const NTest *nb, int ncount, const int32_t *ul,
-                                         int32_t i0, int32_t i1, uint64_t *ub, bool revd,
-                                         int32_t bigdeg, uint64_t &fb) {
+                                         int32_t i0, int32_t i1, uint64_t *ub, int32_t bigdeg,
+                                         uint64_t &fb) {
     const DevGraph &g = c.g;
     const int lane = threadIdx.x & 63;
     FlatLds *w = flat_lds(c);
@@ -1012,7 +1106,6 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root
     const int32_t up = have ? ul[i0 + it] : 0;
     const int4 vr = g.vrow[up];
     if (root >= 0) have = have && root_ok(g, root, up, vr);
-    if (revd) have = have && bit_test(ub, up);
     const int dir = nb[tj].dir;
     const int32_t beg = dir ? vr.z : vr.x, end = dir ? vr.w : vr.y;
     // this candidate's segments among the wave's, and those that decide
@@ -1046,7 +1139,7 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root
                 const int oi = (int)(((uint32_t)o[q] * inv) >> 16);
                 d[q] = nb[o[q] - oi * ncount];
                 h[q] = e[q] < T && (pass == 0 || ((live >> o[q]) & 1ull));
-                const int2 *adj = d[q].dir ? g.in_adj : g.out_adj;
+                const int2 *adj = g.adj(d[q].dir);
                 en[q] = h[q] ? adj[w->adr[o[q]] + e[q]] : make_int2(0, -1);
             }
 #pragma unroll
@@ -1116,7 +1209,7 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root
         if (lane == 0) fb += 20ull * n + 12ull * (uint64_t)T;
         return;
     }
-    const bool drop = todo && !alive && tj == 0;
+    const bool drop = ub && todo && !alive && tj == 0;
     if (drop) atomicAnd((unsigned long long *)&ub[up >> 6], ~(1ull << (up & 63)));
     const uint64_t dead = __ballot(drop);
     if (lane == 0) {
@@ -1136,7 +1229,7 @@ __device__ __forceinline__ void wave_few(Ctx &c, const K &k, int u, int32_t root
 template <class K>
 __device__ __forceinline__ void filter_items(Ctx &c, const K &k, int u, int32_t root, bool push,
                                              const NTest *nb, int ncount, const int32_t *ul,
-                                             uint64_t *ub, bool revd, int32_t it0, int32_t it1,
+                                             uint64_t *ub, int32_t it0, int32_t it1,
                                              uint64_t &fb, bool nodefer = false) {
     const int wid = threadIdx.x >> 6;
     const int32_t per = nodefer ? 1 : min(64, (it1 - it0 + NW - 1) / NW);
@@ -1147,9 +1240,9 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, int u, int32_t 
         // rows of long-row passes are read test by test, which stops at the
         // first match
         if (!nodefer && ncount > 1 && (e - i) * ncount <= 64)
-            wave_few(c, k, u, root, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
+            wave_few(c, k, u, root, push, nb, ncount, ul, i, e, ub, bigdeg, fb);
         else
-            wave_items(c, k, u, root, push, nb, ncount, ul, i, e, ub, revd, bigdeg, fb);
+            wave_items(c, k, u, root, push, nb, ncount, ul, i, e, ub, bigdeg, fb);
     }
 }
 
@@ -1226,16 +1319,16 @@ __device__ __forceinline__ int32_t build_segments(Ctx &c, const NTest *nb, int n
         if (i < nd)
             for (int j = 0; j < ncount; ++j) {
                 int32_t b, e;
-                test_row(c, def[i], nb[j], &b, &e);
+                test_row<false>(c, def[i], nb[j], &b, &e);
                 cnt += (e - b + kSegEntries - 1) / kSegEntries;
             }
         int64_t tot;
-        const int64_t ex = block_excl_scan(cnt, c.s->sh, &tot);
+        const int64_t ex = block_excl_scan<NW>(cnt, g_s.sh, &tot);
         if (i < nd && carry + tot <= cap) {
             int64_t p = carry + ex;
             for (int j = 0; j < ncount; ++j) {
                 int32_t b, e;
-                test_row(c, def[i], nb[j], &b, &e);
+                test_row<false>(c, def[i], nb[j], &b, &e);
                 for (int32_t x = b; x < e; x += kSegEntries)
                     seg[p++] = make_int4(def[i], j, x, min(e, x + kSegEntries));
             }
@@ -1255,17 +1348,17 @@ __device__ __forceinline__ void ec_chunk(Ctx &c, const EcJob &E, HelpJob *j, int
 // u's list, G lanes each; kind 1: one row segment each), and the owner waits
 // for the chunks its helpers claimed before taking the counters back.
 __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, const NTest *nb,
-                                           int ncount, const int32_t *ul, uint64_t *ub, bool revd,
+                                           int ncount, const int32_t *ul, uint64_t *ub,
                                            int32_t n_items, int32_t K, int G, int32_t nch,
                                            const int4 *seg, uint64_t &fb,
                                            const EcJob *ecj = nullptr, bool nodefer = false,
-                                           int32_t root = -1) {
+                                           int32_t root = -1, int32_t *def = nullptr) {
     HelpJob *j = c.job;
     if (threadIdx.x == 0) {
-        for (int v = 0; v < SGM_MAX_QV; ++v) j->cnt[v] = c.s->cnt[v];
+        for (int v = 0; v < SGM_MAX_QV; ++v) j->cnt[v] = g_s.cnt[v];
         j->nbig = 0;
         j->removed = 0;
-        j->nmarks = c.s->nmarks;
+        j->nmarks = g_s.nmarks;
         j->abort_ = 0;
         j->bytes = 0ull;
         j->done = 0;
@@ -1279,7 +1372,9 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         j->n_items = n_items;
         j->G = G;
         j->ncount = ncount;
-        j->revd = revd;
+        j->nodrop = ub == nullptr;
+        j->ndef = g_s.ndef;
+        j->defer = def != nullptr;
         j->st = st;
         for (int i = 0; i < ncount; ++i) j->nbl[i] = nb[i];
         if (ecj) {
@@ -1298,19 +1393,19 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
     for (;;) {
         if (threadIdx.x == 0) {
             const unsigned long long w = take_chunk(j);
-            c.s->hch = claim_next(w) < claim_nch(w) ? claim_next(w) : -1;
+            g_s.hch = claim_next(w) < claim_nch(w) ? claim_next(w) : -1;
         }
         __syncthreads();
-        const int32_t ch = c.s->hch;
+        const int32_t ch = g_s.hch;
         __syncthreads();
         if (ch < 0) break;
         if (kind == 0)
-            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, nb, ncount, ul, ub, revd, ch * K,
+            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, nb, ncount, ul, ub, ch * K,
                          min(n_items, ch * K + K), fb, nodefer);
         else if (kind == 3)
             ec_chunk(c, *ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
         else if (kind == 4)
-            item_wg_k(c, BoardCtr{j}, st, nb, ncount, ul[ch], ub, fb);
+            item_wg_k(c, BoardCtr{j}, st, nb, ncount, ul[ch], ub, fb, def);
         else
             push_segment(c, BoardCtr{j}, nb, seg[ch], fb);
         ++own;
@@ -1334,33 +1429,22 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
                 __hip_atomic_load(&j->claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             atomicExch(&j->claim, claim_word(seq, 0));
             atomicExch(&j->dirty, 1);
-            c.s->retired = 1;
+            g_s.retired = 1;
         }
         __threadfence();
         atomicSub(&c.hctr[0], 1);
         for (int v = 0; v < SGM_MAX_QV; ++v)
-            c.s->cnt[v] = __hip_atomic_load(&j->cnt[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        c.s->nbig += __hip_atomic_load(&j->nbig, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        c.s->removed += __hip_atomic_load(&j->removed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        c.s->nmarks = __hip_atomic_load(&j->nmarks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            g_s.cnt[v] = __hip_atomic_load(&j->cnt[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g_s.nbig += __hip_atomic_load(&j->nbig, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g_s.removed += __hip_atomic_load(&j->removed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g_s.ndef = __hip_atomic_load(&j->ndef, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        g_s.nmarks = __hip_atomic_load(&j->nmarks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int32_t ab = __hip_atomic_load(&j->abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (ab) c.s->abort_ = ab;
-        if (got < nch) c.s->abort_ = kWhyHelp;
+        if (ab) g_s.abort_ = ab;
+        if (got < nch) g_s.abort_ = kWhyHelp;
         add_bytes(c, __hip_atomic_load(&j->bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
     __syncthreads();
-}
-
-// Chunks of u's candidate list shared as above.
-__device__ __forceinline__ void shared_items(Ctx &c, const NStep &st, const NTest *nb, int ncount,
-                                             const int32_t *ul, uint64_t *ub, bool revd,
-                                             int32_t n_items, int32_t helpers, int32_t root,
-                                             uint64_t &fb) {
-    const int32_t K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
-                                           (n_items + kMaxChunks - 1) / kMaxChunks)));
-    const int32_t nch = (n_items + K - 1) / K;
-    shared_job(c, 0, st, nb, ncount, ul, ub, revd, n_items, K, 64, nch, nullptr, fb, nullptr, false,
-               root);
 }
 
 // Workgroups that can help this slot now: the launch's extra ones and the
@@ -1370,37 +1454,12 @@ __device__ __forceinline__ int32_t helpers_now(Ctx &c) {
     if (c.ngrid > c.nslot) return c.ngrid - c.nslot;
     __syncthreads();
     if (threadIdx.x == 0)
-        c.s->hch = c.ngrid - c.nslot +
+        g_s.hch = c.ngrid - c.nslot +
                    __hip_atomic_load(&c.hctr[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const int32_t h = c.s->hch;
+    const int32_t h = g_s.hch;
     __syncthreads();
     return h;
-}
-
-// The pushes deferred by the wave and workgroup tiers, as shared row
-// segments (or by this workgroup alone when they do not fit the slab).
-__device__ __forceinline__ void push_deferred(Ctx &c, const NStep &st, const NTest *nb, int ncount,
-                                              const int32_t *def, uint64_t &fb) {
-    __syncthreads();
-    const int32_t nd = c.s->ndef;
-    if (nd == 0) return;
-    int4 *seg = (int4 *)(c.slab + 12 * (int64_t)c.lcap);
-    // room in the slab, and no more chunks than a claim word can count
-    const int64_t cap = min((c.slab_bytes - 12 * (int64_t)c.lcap) / (int64_t)sizeof(int4),
-                            (int64_t)kMaxChunks);
-    const int32_t nseg = build_segments(c, nb, ncount, def, nd, seg, cap);
-    if (nseg > 0) {
-        shared_job(c, 1, st, nb, ncount, nullptr, nullptr, false, 0, 1, NT, nseg, seg, fb);
-    } else {
-        for (int32_t i = 0; i < nd; ++i)
-            for (int j = 0; j < ncount; ++j) {
-                int32_t b, e;
-                test_row(c, def[i], nb[j], &b, &e);
-                push_segment(c, LdsCtr{c.s}, nb, make_int4(def[i], j, b, e), fb);
-            }
-        __syncthreads();
-    }
 }
 
 // Where the wave and workgroup tiers of a pushing step list the candidates
@@ -1413,6 +1472,222 @@ __device__ __forceinline__ int32_t *defer_list(Ctx &c, const NStep &st) {
     return (int32_t *)(c.slab + 8 * (int64_t)c.lcap);
 }
 
+// The candidates ul[0, n_items) through a step's tests, in tiers: waves over
+// rows laid end to end; one wave per long row; the workgroup per row above
+// wg_rows; the pushes of the last two as row segments. Each tier is shared
+// with idle workgroups when it has enough to do (from one place: a copy of
+// the shared tiers' code per tier made the kernel twice as large). ub: the
+// bitmap the dropped candidates leave (null: none is dropped). The step's
+// counters are zero on entry (from: the tier to start with).
+__device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t root, const NTest *nb,
+                                            int ncount, const int32_t *ul, uint64_t *ub,
+                                            int32_t n_items, int32_t from, uint64_t &fb) {
+    const DevGraph &g = c.g;
+    const int u = st.u;
+    const int lane = threadIdx.x & 63;
+    // slab while filtering, in units of 4 lcap bytes: overflow list, marks,
+    // deferred list, then the lists of rows and the row segments
+    int32_t *ov = (int32_t *)c.slab;
+    const bool room = c.slab_bytes >= 16 * (int64_t)c.lcap;
+    int32_t *rows = (int32_t *)(c.slab + 12 * (int64_t)c.lcap);
+    const bool can = c.help_items > 0 && c.job;
+    // a step resumed at its pushes has listed them already
+    int32_t *def = from == 3 ? (int32_t *)(c.slab + 8 * (int64_t)c.lcap) : nullptr;
+    for (int tier = from; tier < 4; ++tier) {
+        // what the tier shares: kind (-1: nothing), items, chunk size, chunks
+        int kind = -1;
+        int32_t nsh = 0, K = 1, nch = 0;
+        const int32_t *items = rows;
+        const int4 *seg = nullptr;
+        if (tier == 0) {
+            // a step of many candidates is shared whether or not workgroups
+            // are idle yet (in a batch they become idle while it runs)
+            if (can && n_items >= c.help_items) {
+                const int32_t helpers = helpers_now(c);
+                kind = 0;
+                items = ul;
+                nsh = n_items;
+                K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
+                                         (n_items + kMaxChunks - 1) / kMaxChunks)));
+                nch = (n_items + K - 1) / K;
+            } else {
+                filter_items(c, LdsCtr{}, u, root, st.push != 0, nb, ncount, ul, ub, 0, n_items, fb);
+            }
+        } else if (tier == 1) {
+            __syncthreads();
+            const int32_t nl = min(g_s.nbig, c.lcap);
+            if (nl == 0) return;
+            def = defer_list(c, st);
+            ev(c, SGM_EV_LONGROWS);
+            if (can && room && nl >= kLongShare) {
+                // many long rows: one wave per row up to wg_rows entries,
+                // shared like a step of many candidates (the rows move to a
+                // list of their own; longer ones come back to the overflow
+                // list)
+                for (int32_t i = threadIdx.x; i < nl; i += NT) rows[i] = ov[i];
+                __syncthreads();
+                if (threadIdx.x == 0) g_s.nbig = 0;
+                kind = 0;
+                nsh = nl;
+                K = kLongChunk;
+                nch = (nl + kLongChunk - 1) / kLongChunk;
+            }
+        } else if (tier == 2) {
+            // one wave per long row; rows above wg_rows get the whole
+            // workgroup (listed in the slab where it has room), and so does
+            // every row when there are fewer than waves
+            __syncthreads();
+            const int32_t nbig = min(g_s.nbig, c.lcap);
+            int32_t *giant = room ? rows : g_s.big;
+            const int32_t gcap = room ? c.lcap : kBigCap;
+            for (int32_t b = threadIdx.x >> 6; b < nbig; b += NW) {
+                const int32_t up = ov[b];
+                if (n_items <= NW || max_row(g, nb, ncount, up) > c.wg_rows) {
+                    int32_t p = 0;
+                    if (lane == 0) p = atomicAdd(&g_s.ngiant, 1);
+                    p = __shfl(p, 0, 64);
+                    if (p < gcap) {
+                        if (lane == 0) giant[p] = up;
+                        continue;
+                    }
+                    // list full: this wave handles the row itself
+                }
+                item_wave(c, st, nb, ncount, up, ub, fb, def);
+            }
+            __syncthreads();
+            const int32_t ngiant = min(g_s.ngiant, gcap);
+            if (ngiant >= 2 && room && can && n_items > NW && (!st.push || def)) {
+                // one workgroup each, shared; the rows of a pushing step's
+                // survivors then go out as shared row segments. (A step over
+                // 81 hub rows: 2.6 ms by the owner alone, most of it the
+                // tests.)
+                kind = 4;
+                nsh = nch = ngiant;
+            } else {
+                for (int32_t b = 0; b < ngiant; ++b) item_wg(c, st, nb, ncount, giant[b], ub, fb, def);
+            }
+        } else {
+            // the deferred pushes (by this workgroup alone when they do not
+            // fit the slab)
+            __syncthreads();
+            const int32_t nd = g_s.ndef;
+            if (!def || nd == 0) return;
+            // room in the slab, and no more chunks than a claim word counts
+            const int64_t cap = min((c.slab_bytes - 12 * (int64_t)c.lcap) / (int64_t)sizeof(int4),
+                                    (int64_t)kMaxChunks);
+            const int32_t nseg = build_segments(c, nb, ncount, def, nd, (int4 *)rows, cap);
+            if (nseg > 0) {
+                kind = 1;
+                items = nullptr;
+                seg = (const int4 *)rows;
+                nch = nseg;
+            } else {
+                for (int32_t i = 0; i < nd; ++i)
+                    for (int j = 0; j < ncount; ++j) {
+                        int32_t b, e;
+                        test_row(c, def[i], nb[j], &b, &e);
+                        push_segment(c, LdsCtr{}, nb, make_int4(def[i], j, b, e), fb);
+                    }
+                __syncthreads();
+            }
+        }
+        if (kind >= 0)
+            shared_job(c, kind, st, nb, ncount, items, ub, nsh, K, 64, nch, seg, fb, nullptr,
+                       tier == 1, tier == 0 ? root : -1, kind == 4 ? def : nullptr);
+    }
+}
+
+// Intersect p's candidates with the pushed marks (all of them candidates of
+// p): the marks are the intersection, so unless nothing left, its bitmap and
+// list are rebuilt from them. Clears the scratch bitmap; true if p lost
+// candidates (uniform).
+__device__ __forceinline__ bool keep_marked(Ctx &c, int p) {
+    uint64_t *pb = c.B(p);
+    int32_t *pl = c.L(p);
+    const int32_t n = g_s.cnt[p], nm = g_s.nmarks;
+    if (nm < n) {
+        clear_words(c, p, n);
+        __syncthreads();
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < nm; i += NT) {
+            const int32_t x = c.marks[i];
+            atomicOr((unsigned long long *)&pb[x >> 6], 1ull << (x & 63));
+            pl[i] = x;
+        }
+    }
+#pragma unroll 4
+    for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[c.marks[i] >> 6] = 0ull;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        g_s.cnt[p] = nm;
+        add_bytes(c, nm < n ? 12ull * n + 24ull * nm : 12ull * nm);
+    }
+    __syncthreads();
+    return nm < n;
+}
+
+// The tiers of a step beyond its first few candidates' short rows, in a
+// function of its own (see g_s). from: the tier to start with. Returns the
+// bytes of this thread's work.
+__device__ __attribute__((noinline)) uint64_t filter_far(int step_u, int push, int parent, int first,
+                                                         int32_t root, int32_t from) {
+    SGM_OWN_CTX(c);
+    const NStep st{(int8_t)__builtin_amdgcn_readfirstlane(step_u), (int8_t)__builtin_amdgcn_readfirstlane(push),
+                   (int8_t)__builtin_amdgcn_readfirstlane(parent), 0,
+                   (int16_t)__builtin_amdgcn_readfirstlane(first), 0};
+    root = __builtin_amdgcn_readfirstlane(root);
+    from = __builtin_amdgcn_readfirstlane(from);
+    const int u = st.u;
+    uint64_t *ub = c.B(u);
+    const int32_t *ul = root < 0 ? c.L(u) : c.g.tverts + c.Q->root_lo;
+    const int32_t n_items = root < 0 ? g_s.cnt[u] : c.Q->root_hi - c.Q->root_lo;
+    uint64_t fb = 0;
+    const int ncount = g_s.nnbl;
+    // Reverse tests first: the neighbour's candidates push the members of
+    // C(u) they reach over the edge, and those stay. What an explore step
+    // does for its parent, with nothing dropped from C(v).
+    for (uint64_t rm = g_s.revmask;;) {
+        const bool rev = rm != 0;
+        if ((!rev && ncount == 0 && root < 0) || aborted(c)) break;
+        const NNbr d = c.Q->nbr[st.first + (rev ? __builtin_ctzll(rm) : 0)];
+        if (rev && threadIdx.x == 0) {
+            NTest *rt = g_s.nbl + SGM_MAX_QE;
+            rt->v = (int8_t)u;
+            rt->dir = 1 - d.dir;
+            rt->mode = 0;
+            rt->known = 0;
+            rt->rel = d.rel;
+            rt->label = c.Q->pred[u].label;
+            rt->pin = c.Q->pred[u].pin;
+            rt->qdeg = 0;
+        }
+        if (rev) __syncthreads();
+        const int32_t n = g_s.cnt[u];
+        filter_pass(c, rev ? NStep{d.v, 1, (int8_t)u, 0, 0, 0} : st, rev ? -1 : root,
+                    g_s.nbl + (rev ? SGM_MAX_QE : 0), rev ? 1 : ncount, rev ? c.L(d.v) : ul,
+                    rev ? nullptr : ub, rev ? g_s.cnt[d.v] : root < 0 ? n : n_items, from, fb);
+        if (!rev) break;
+        __syncthreads();
+        keep_marked(c, u);
+        if (threadIdx.x == 0) g_s.rdrop += n - g_s.cnt[u];
+        if (threadIdx.x == 0) {
+            g_s.nbig = 0;
+            g_s.ngiant = 0;
+            g_s.nmarks = 0;
+            g_s.ndef = 0;
+        }
+        __syncthreads();
+        rm &= rm - 1;
+    }
+    return fb;
+}
+
+// compact_list of more than a few entries, likewise.
+__device__ __attribute__((noinline)) void compact_far(int u) {
+    SGM_OWN_CTX(c);
+    compact_list(c, __builtin_amdgcn_readfirstlane(u));
+}
+
 // One step; returns the number of candidates it removed from C(u) (uniform).
 // root: -1, or the first step of a query with an unpinned root (see root_ok).
 __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t root = -1) {
@@ -1420,7 +1695,7 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
     const int u = st.u;
     uint64_t *ub = c.B(u);
     const int32_t *ul = root < 0 ? c.L(u) : g.tverts + c.Q->root_lo;
-    const int32_t n_items = root < 0 ? c.s->cnt[u] : c.Q->root_hi - c.Q->root_lo;
+    const int32_t n_items = root < 0 ? g_s.cnt[u] : c.Q->root_hi - c.Q->root_lo;
     uint64_t fb = 0;  // algorithmic bytes of this thread's work
     // A test known to hold is left out: every candidate of u was found (or
     // pushed) with a matching neighbour in C(v), C(v) has not changed since
@@ -1432,25 +1707,26 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
     // any candidate of u survives.
     const bool in = (int)(threadIdx.x & 63) < st.count;
     const NNbr td = c.Q->nbr[st.first + (in ? threadIdx.x & 63 : 0)];
-    const bool known = in && td.mode == 0 && c.s->okv[2 * td.e + td.dir] == c.s->ver[td.v];
+    const bool known = in && td.mode == 0 && g_s.okv[2 * td.e + td.dir] == g_s.ver[td.v];
     if (!st.push && __popcll(__ballot(known)) == st.count) return 0;  // every wave alike
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         if (lane == 0) {
-            c.s->nbig = 0;
-            c.s->ngiant = 0;
-            c.s->removed = 0;
-            c.s->nmarks = 0;
-            c.s->ndef = 0;
+            g_s.nbig = 0;
+            g_s.ngiant = 0;
+            g_s.removed = 0;
+            g_s.rdrop = 0;
+            g_s.nmarks = 0;
+            g_s.ndef = 0;
         }
-        const bool spar = known && st.push && c.s->cnt[td.v] == 1;
+        const bool spar = known && st.push && g_s.cnt[td.v] == 1;
         bool keep = in && !spar && (st.push || !known);
         // In prune-only steps over many candidates, a neighbour with few
         // candidates whose rows together are shorter than u's list is
-        // checked from its side instead (prune_reverse).
+        // checked from its side instead.
         uint64_t rm = 0;
         if (!st.push && n_items >= kRevMin) {
-            const int32_t nvl = c.s->cnt[td.v];
+            const int32_t nvl = g_s.cnt[td.v];
             uint64_t cand = __ballot(keep && nvl <= kRevMaxCand && nvl < n_items);
             while (cand) {
                 const int j = __builtin_ctzll(cand);
@@ -1459,8 +1735,8 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
                 const int dir = __builtin_amdgcn_readlane((int)td.dir, j);
                 // reverse cost: v's list plus its rows, against at least one
                 // read per candidate of u forward
-                const int32_t nv = c.s->cnt[v];
-                const int32_t *off = dir ? g.out_off : g.in_off;
+                const int32_t nv = g_s.cnt[v];
+                const int32_t *off = g.off(!dir);
                 const int32_t *vl = c.L(v);
                 int64_t sum = nv;
                 for (int32_t b = 0; b < nv && sum <= n_items; b += 64) {
@@ -1495,7 +1771,7 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
             // the edge itself is one in-edge (dir 0) or out-edge of the
             // neighbour: often all the degree its vertex asks for
             const bool degok = td.dir ? p.qout <= 1 && p.qin == 0 : p.qin <= 1 && p.qout == 0;
-            NTest &t = c.s->nbl[at];
+            NTest &t = g_s.nbl[at];
             t.v = td.v;
             t.dir = td.dir;
             t.mode = (int8_t)(td.mode == 1 && degok && g.typed_adj && !c.Q->homo ? 2 : td.mode);
@@ -1507,153 +1783,63 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
         }
         const uint64_t sp = __ballot(spar);
         if (lane == 0) {
-            c.s->revmask = rm;
-            c.s->nnbl = n;
-            c.s->skippar = sp != 0;
+            g_s.revmask = rm;
+            g_s.nnbl = n;
+            g_s.skippar = sp != 0;
         }
     }
     __syncthreads();
-    const NTest *nb = c.s->nbl;
-    const int ncount = c.s->nnbl;
-    const int par = c.s->skippar ? -1 : st.parent;  // parent this step's marks intersect
-    const uint64_t rm = c.s->revmask;
-    const bool revd = rm != 0;
-    for (int j = 0; j < st.count && revd; ++j)
-        if ((rm >> j) & 1ull) {
-            const NNbr *d = c.Q->nbr + st.first + j;
-            prune_reverse(c, u, d->v, d->dir, d->rel, fb);
-        }
-    if (ncount == 0 && root < 0) {
-        // every test was known to hold or done from the other side
-    } else if (n_items <= NW) {
-        // a wave per candidate; those with a long row get the whole workgroup
-        filter_items(c, LdsCtr{c.s}, u, root, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
+    const int par = g_s.skippar ? -1 : st.parent;  // parent this step's marks intersect
+    const int ncount = g_s.nnbl;
+    if (n_items <= NW && g_s.revmask == 0) {
+        // a handful of candidates: a wave each; those with a long row the
+        // whole workgroup
+        if (ncount > 0 || root >= 0)
+            filter_items(c, LdsCtr{}, u, root, st.push != 0, g_s.nbl, ncount, ul, ub, 0, n_items, fb);
         __syncthreads();
-        const int32_t nl = min(c.s->nbig, c.lcap);
-        if (nl > 0) {
+        const int32_t nl = g_s.nbig;
+        if (nl) {
             int32_t *def = defer_list(c, st);
-            const int32_t *ov = (const int32_t *)c.slab;
-            for (int32_t it = 0; it < nl; ++it) item_wg(c, st, nb, ncount, ov[it], ub, fb, def);
-            if (def) push_deferred(c, st, nb, ncount, def, fb);
+            for (int32_t b = 0; b < nl; ++b)
+                item_wg(c, st, g_s.nbl, ncount, ((const int32_t *)c.slab)[b], ub, fb, def);
+            __syncthreads();
+            if (def && g_s.ndef) fb += filter_far(u, st.push, st.parent, st.first, root, 3);
         }
     } else {
-        // a step of many candidates is shared whether or not workgroups are
-        // idle yet (in a batch they become idle while it runs)
-        const bool share = c.help_items > 0 && c.job && n_items >= c.help_items;
-        const int32_t helpers = share ? helpers_now(c) : 0;
-        if (share)
-            shared_items(c, st, nb, ncount, ul, ub, revd, n_items, helpers, root, fb);
-        else
-            filter_items(c, LdsCtr{c.s}, u, root, st.push != 0, nb, ncount, ul, ub, revd, 0, n_items, fb);
-        const int lane = threadIdx.x & 63;
-        int32_t *ov = (int32_t *)c.slab;
-        __syncthreads();
-        if (c.help_items > 0 && c.job && c.s->nbig >= kLongShare &&
-            c.slab_bytes >= 16 * (int64_t)c.lcap) {
-            // many long rows: one wave per row up to wg_rows entries,
-            // shared like a step of many candidates (the rows move to a
-            // list of their own; longer ones come back to the overflow list)
-            ev(c, SGM_EV_LONGROWS);
-            const int32_t nl = min(c.s->nbig, c.lcap);
-            int32_t *rows = (int32_t *)(c.slab + 12 * (int64_t)c.lcap);
-            for (int32_t i = threadIdx.x; i < nl; i += NT) rows[i] = ov[i];
-            __syncthreads();
-            if (threadIdx.x == 0) c.s->nbig = 0;
-            const int32_t nch = (nl + kLongChunk - 1) / kLongChunk;
-            shared_job(c, 0, st, nb, ncount, rows, ub, revd, nl, kLongChunk, 64, nch, nullptr,
-                       fb, nullptr, true);
-            __syncthreads();
-        }
-        // one wave per long row; rows above wg_rows get the whole workgroup
-        const int32_t nbig = min(c.s->nbig, c.lcap);
-        if (nbig > 0) ev(c, SGM_EV_LONGROWS);
-        int32_t *def = nbig > 0 ? defer_list(c, st) : nullptr;
-        for (int32_t b = threadIdx.x >> 6; b < nbig; b += NW) {
-            const int32_t up = ov[b];
-            if (max_row(g, nb, ncount, up) > c.wg_rows) {
-                int32_t p = 0;
-                if (lane == 0) p = atomicAdd(&c.s->ngiant, 1);
-                p = __shfl(p, 0, 64);
-                if (p < kBigCap) {
-                    if (lane == 0) c.s->big[p] = up;
-                    continue;
-                }
-                // LDS list full: this wave handles the row itself
-            }
-            item_wave(c, st, nb, ncount, up, ub, fb, def);
-        }
-        __syncthreads();
-        const int32_t ngiant = min(c.s->ngiant, kBigCap);
-        if (!st.push && ngiant >= 2 && c.help_items > 0 && c.job &&
-            c.slab_bytes >= 16 * (int64_t)c.lcap) {
-            // rows above wg_rows in a prune-only step: one workgroup each,
-            // shared (a pushing step's rows go out as shared row segments)
-            int32_t *rows = (int32_t *)(c.slab + 12 * (int64_t)c.lcap);
-            for (int32_t i = threadIdx.x; i < ngiant; i += NT) rows[i] = c.s->big[i];
-            __syncthreads();
-            shared_job(c, 4, st, nb, ncount, rows, ub, revd, ngiant, 1, NT, ngiant, nullptr, fb);
-        } else {
-            for (int32_t b = 0; b < ngiant; ++b) item_wg(c, st, nb, ncount, c.s->big[b], ub, fb, def);
-        }
-        if (def) push_deferred(c, st, nb, ncount, def, fb);
+        fb += filter_far(u, st.push, st.parent, st.first, root, 0);
     }
     add_bytes_wave(c, fb);
     __syncthreads();
-    const bool shrunk = c.s->removed != 0;
-    if (shrunk) compact_list(c, u);
+    const bool shrunk = g_s.removed != 0 || g_s.rdrop != 0;
+    if (g_s.removed) {
+        const int32_t n = g_s.cnt[u];
+        if (n <= 64) {
+            // one wave's worth
+            if (threadIdx.x < 64) {
+                int32_t *l = c.L(u);
+                const int32_t x = (int32_t)threadIdx.x < n ? l[threadIdx.x] : 0;
+                const bool keep = (int32_t)threadIdx.x < n && bit_test(ub, x);
+                const uint64_t m = __ballot(keep);
+                if (keep) l[__popcll(m & lanemask_lt(threadIdx.x))] = x;
+                if (threadIdx.x == 0) {
+                    g_s.cnt[u] = __popcll(m);
+                    add_bytes(c, 12ull * n + 4ull * __popcll(m));
+                }
+            }
+            __syncthreads();
+        } else {
+            compact_far(u);
+        }
+    }
     bool pshrunk = false;  // the parent lost candidates
-    if (par >= 0 && c.s->nmarks == c.s->cnt[par]) {
-        // every candidate of the parent was pushed: only the marks go
-        const int32_t nm = c.s->nmarks;
-        for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[c.marks[i] >> 6] = 0ull;
-        if (threadIdx.x == 0) add_bytes(c, 12ull * nm);
-        __syncthreads();
-    } else if (par >= 0 && 4 * c.s->nmarks < c.s->cnt[par]) {
-        // Intersect the parent's candidates with the pushed marks. The marks
-        // are parent candidates, so the intersection is the marks
-        // themselves: with few of them, clear the parent's old words and
-        // rebuild its bitmap and list from the marks.
-        uint64_t *pb = c.B(par);
-        int32_t *pl = c.L(par);
-        const int32_t n = c.s->cnt[par], nm = c.s->nmarks;
-        for (int32_t i = threadIdx.x; i < n; i += NT) pb[pl[i] >> 6] = 0ull;
-        __syncthreads();
-        for (int32_t i = threadIdx.x; i < nm; i += NT) {
-            const int32_t x = c.marks[i];
-            atomicOr((unsigned long long *)&pb[x >> 6], 1ull << (x & 63));
-            pl[i] = x;
-        }
-        __syncthreads();
-        for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[pl[i] >> 6] = 0ull;
-        if (threadIdx.x == 0) {
-            c.s->cnt[par] = nm;
-            add_bytes(c, 12ull * n + 24ull * nm);
-        }
-        pshrunk = true;
-        __syncthreads();
-    } else if (par >= 0) {
-        // intersect the parent's candidates with the pushed scratch bitmap
-        uint64_t *pb = c.B(par);
-        const int32_t *pl = c.L(par);
-        const int32_t n = c.s->cnt[par];
-        for (int32_t i = threadIdx.x; i < n; i += NT) {
-            const int32_t x = pl[i];
-            if (!bit_test(c.scratch, x))
-                atomicAnd((unsigned long long *)&pb[x >> 6], ~(1ull << (x & 63)));
-        }
-        __syncthreads();
-        // scratch only holds parent candidates: zero their words
-        for (int32_t i = threadIdx.x; i < n; i += NT) c.scratch[pl[i] >> 6] = 0ull;
-        if (threadIdx.x == 0) add_bytes(c, 28ull * n);
-        pshrunk = true;
-        __syncthreads();
-        compact_list(c, par);
-    } else if (c.s->skippar && c.s->cnt[u] == 0) {
+    if (par >= 0) {
+        pshrunk = keep_marked(c, par);
+    } else if (g_s.skippar && g_s.cnt[u] == 0) {
         // no candidate left to push the parent's single one
         const int p = st.parent;
         if (threadIdx.x == 0) {
             c.B(p)[c.L(p)[0] >> 6] = 0ull;
-            c.s->cnt[p] = 0;
+            g_s.cnt[p] = 0;
         }
         pshrunk = true;
         __syncthreads();
@@ -1663,18 +1849,18 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
         // explore step the other way round too (the children's and the
         // parent's candidates are the neighbours its survivors pushed)
         if (threadIdx.x == 0) {
-            if (shrunk) ++c.s->ver[u];
-            if (pshrunk) ++c.s->ver[st.parent];
+            if (shrunk) ++g_s.ver[u];
+            if (pshrunk) ++g_s.ver[st.parent];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (in) {
-            c.s->okv[2 * td.e + td.dir] = c.s->ver[td.v];
-            if (st.push) c.s->okv[2 * td.e + 1 - td.dir] = c.s->ver[u];
+            g_s.okv[2 * td.e + td.dir] = g_s.ver[td.v];
+            if (st.push) g_s.okv[2 * td.e + 1 - td.dir] = g_s.ver[u];
         }
     }
-    const int32_t removed = c.s->removed;
+    const int32_t removed = g_s.removed + g_s.rdrop;
     __syncthreads();
     return removed;
 }
@@ -1719,6 +1905,21 @@ __device__ __forceinline__ bool row_has(const DevGraph &g, const int2 *adj, int3
     return false;
 }
 
+// The same, one value for the whole wave (uniform call).
+__device__ __forceinline__ bool wave_row_has(const DevGraph &g, const int2 *adj, int32_t beg,
+                                             int32_t end, int32_t x, int32_t rel) {
+    const int32_t b = wave_bound(beg, end, [&](int32_t i) { return adj[i].x < x; });
+    // (a neighbour has one entry per relation: a few at most)
+    for (int32_t i = b; i < end; i += 64) {
+        const int32_t j = i + (int32_t)(threadIdx.x & 63);
+        const int2 e = j < end ? adj[j] : make_int2(-1, -1);
+        if (__ballot(e.x == x && adj_rel_ok(g, e, rel))) return true;
+        if (__ballot(e.x != x)) return false;
+    }
+    return false;
+}
+constexpr int32_t kProbeOne = 4;  // values up to which a wave looks them up one by one
+
 // Looking each of `no` candidates up in a row of `len` entries costs about
 // no * log2(len) reads against len for a scan of the row.
 __device__ __forceinline__ bool probe_cheaper(int32_t no, int32_t len) {
@@ -1735,12 +1936,22 @@ __device__ __forceinline__ int64_t ec_probe_wg(Ctx &c, int32_t rel, const int32_
                                                const int2 *adj, int32_t beg, int32_t end, int32_t k,
                                                int32_t *dst) {
     int64_t n = 0;
+    if (no <= kProbeOne) {
+        // every wave does the same searches; the first one writes
+        for (int32_t i = 0; i < no; ++i) {
+            const int32_t x = ol[i];
+            if (x == k || !wave_row_has(c.g, adj, beg, end, x, rel)) continue;
+            if (threadIdx.x == 0) dst[n] = x;
+            ++n;
+        }
+        return n;
+    }
     for (int32_t base = 0; base < no; base += NT) {
         const int32_t i = base + threadIdx.x;
         const int32_t x = i < no ? ol[i] : -1;
         const bool hit = x >= 0 && x != k && row_has(c.g, adj, beg, end, x, rel);
         int64_t tot;
-        const int64_t p = n + block_excl_scan(hit ? 1 : 0, c.s->sh, &tot);
+        const int64_t p = n + block_excl_scan<NW>(hit ? 1 : 0, g_s.sh, &tot);
         if (hit) dst[p] = x;
         n += tot;
     }
@@ -1753,6 +1964,16 @@ __device__ __forceinline__ int64_t ec_probe_wave(const Ctx &c, int32_t rel, cons
                                                  int32_t k, int32_t *dst) {
     const int lane = threadIdx.x & 63;
     int64_t n = 0;
+    if (no <= kProbeOne) {
+        // a handful of values: the wave searches for one at a time
+        for (int32_t i = 0; i < no; ++i) {
+            const int32_t x = ol[i];
+            if (x == k || !wave_row_has(c.g, adj, beg, end, x, rel)) continue;
+            if (lane == 0) dst[n] = x;
+            ++n;
+        }
+        return n;
+    }
     for (int32_t base = 0; base < no; base += 64) {
         const int32_t i = base + lane;
         const int32_t x = i < no ? ol[i] : -1;
@@ -1775,7 +1996,7 @@ __device__ __forceinline__ int64_t ec_key_wg(Ctx &c, int32_t rel, int32_t olabel
         for (int t = 0; t < 4; ++t)
             if (i0 + t < end && ec_hit(c.g, rel, olabel, ob, adj, beg, i0 + t, k)) h |= 1u << t;
         int64_t tot;
-        int64_t p = n + block_excl_scan(__popc(h), c.s->sh, &tot);
+        int64_t p = n + block_excl_scan<NW>(__popc(h), g_s.sh, &tot);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
             if ((h >> t) & 1u) dst[p++] = adj[i0 + t].x;
@@ -1811,8 +2032,8 @@ __device__ __forceinline__ int64_t ec_key_wave(const Ctx &c, int32_t rel, int32_
 __device__ __forceinline__ int64_t ec_keys(const Ctx &c, const EcJob &Ej, int32_t i0, int32_t i1,
                                            int G, int32_t *nbig, uint64_t &fb) {
     const EcJob E = Ej;  // once, before the stores below
-    const int32_t *off = E.dir ? c.g.in_off : c.g.out_off;
-    const int2 *adj = E.dir ? c.g.in_adj : c.g.out_adj;
+    const int32_t *off = c.g.off(E.dir);
+    const int2 *adj = c.g.adj(E.dir);
     const int NGr = NT / G;
     const int lane = threadIdx.x & 63, gl = lane & (G - 1), gb = lane & ~(G - 1);
     const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << gb;
@@ -1849,8 +2070,8 @@ __device__ __forceinline__ int64_t ec_keys(const Ctx &c, const EcJob &Ej, int32_
 __device__ __forceinline__ int64_t ec_long_keys(const Ctx &c, const EcJob &Ej, int32_t i0,
                                                 int32_t i1, int32_t *ngiant, uint64_t &fb) {
     const EcJob E = Ej;
-    const int32_t *off = E.dir ? c.g.in_off : c.g.out_off;
-    const int2 *adj = E.dir ? c.g.in_adj : c.g.out_adj;
+    const int32_t *off = c.g.off(E.dir);
+    const int2 *adj = c.g.adj(E.dir);
     const int lane = threadIdx.x & 63;
     int64_t mytot = 0;
     for (int32_t b = i0 + (int32_t)(threadIdx.x >> 6); b < i1; b += NW) {
@@ -1880,8 +2101,8 @@ __device__ __forceinline__ int64_t ec_long_keys(const Ctx &c, const EcJob &Ej, i
 __device__ __forceinline__ int64_t ec_giant_keys(Ctx &c, const EcJob &Ej, int32_t i0, int32_t i1,
                                                  uint64_t &fb) {
     const EcJob E = Ej;
-    const int32_t *off = E.dir ? c.g.in_off : c.g.out_off;
-    const int2 *adj = E.dir ? c.g.in_adj : c.g.out_adj;
+    const int32_t *off = c.g.off(E.dir);
+    const int2 *adj = c.g.adj(E.dir);
     int64_t mytot = 0;
     for (int32_t b = i0; b < i1; ++b) {
         const int32_t it = E.items[b];
@@ -1920,12 +2141,12 @@ __device__ __forceinline__ void ec_chunk(Ctx &c, const EcJob &E, HelpJob *j, int
 __device__ __forceinline__ bool ec_shared(Ctx &c, int e, const EcJob &E, int32_t n_items,
                                           int32_t K, int G, const int32_t *ovl, uint64_t &fb,
                                           int64_t &mytot) {
-    shared_job(c, 3, NStep{}, nullptr, 0, nullptr, nullptr, false, n_items, K, G,
+    shared_job(c, 3, NStep{}, nullptr, 0, nullptr, nullptr, n_items, K, G,
                (n_items + K - 1) / K, nullptr, fb, &E);
     if (aborted(c)) {
         if (threadIdx.x == 0) {
-            c.s->ectot[e] = 0;
-            c.s->slab_used = (int64_t)((const char *)ovl - c.slab);
+            g_s.ectot[e] = 0;
+            g_s.slab_used = (int64_t)((const char *)ovl - c.slab);
         }
         __syncthreads();
         return false;
@@ -1945,13 +2166,13 @@ __device__ __forceinline__ bool ec_shared(Ctx &c, int e, const EcJob &E, int32_t
 __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int dir) {
     const DevGraph &g = c.g;
     const int32_t *keys = c.L(key);
-    const int32_t nk = c.s->cnt[key];
+    const int32_t nk = g_s.cnt[key];
     const uint64_t *ob = c.B(other);
     const int32_t *ol = c.L(other);  // sorted
-    const int32_t no = c.s->cnt[other];
+    const int32_t no = g_s.cnt[other];
     const int32_t rel = c.Q->elabel[e];
-    const int32_t *off = dir ? g.in_off : g.out_off;
-    const int2 *adj = dir ? g.in_adj : g.out_adj;
+    const int32_t *off = g.off(dir);
+    const int2 *adj = g.adj(dir);
     int32_t *degoff = (int32_t *)slab_alloc(c, 4ll * nk + 4);
     int32_t *num = (int32_t *)slab_alloc(c, 4ll * nk + 4);
     if (!degoff || !num) return;
@@ -1961,7 +2182,7 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
         const int32_t i = base + threadIdx.x;
         const int32_t d = i < nk ? off[keys[i] + 1] - off[keys[i]] : 0;
         int64_t tot;
-        const int64_t ex = block_excl_scan(d, c.s->sh, &tot);
+        const int64_t ex = block_excl_scan<NW>(d, g_s.sh, &tot);
         if (i < nk) degoff[i] = (int32_t)(carry + ex);
         carry += tot;
     }
@@ -1973,12 +2194,12 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
     if (!ovl) return;
     if (threadIdx.x == 0) {
         degoff[nk] = (int32_t)carry;
-        c.s->ec_offs[e] = degoff;
-        c.s->ec_cnt[e] = num;
-        c.s->ec_vals[e] = vals;
-        c.s->eckey[e] = key;
-        c.s->nbig = 0;
-        c.s->ngiant = 0;
+        g_s.ec_offs[e] = degoff;
+        g_s.ec_cnt[e] = num;
+        g_s.ec_vals[e] = vals;
+        g_s.eckey[e] = key;
+        g_s.nbig = 0;
+        g_s.ngiant = 0;
     }
     __syncthreads();
     int64_t mytot = 0;
@@ -1995,7 +2216,7 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
             const int32_t k = keys[wave];
             const int32_t beg = off[k], end = off[k + 1];
             if (end - beg > c.wg_rows) {
-                if (lane == 0) c.s->big[atomicAdd(&c.s->ngiant, 1)] = wave;  // at most NW
+                if (lane == 0) g_s.big[atomicAdd(&g_s.ngiant, 1)] = wave;  // at most NW
             } else {
                 const bool probe = probe_cheaper(no, end - beg);
                 const int32_t ks = homo ? -1 : k;
@@ -2008,165 +2229,201 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
                 }
             }
         }
-    } else {
+    }
+    // tiers: G lanes per key, one wave per long key, one workgroup per key
+    // with a row above wg_rows; each shared from the same place when it has
+    // enough keys
+    for (int tier = nk <= NW ? 2 : 0; tier < 3; ++tier) {
         const int lane = threadIdx.x & 63;
-        if (can_share && nk >= c.help_items) {
-            const int32_t helpers = helpers_now(c);
-            const int32_t K = min(512, max(64, max((nk + helpers) / (helpers + 1),
-                                                   (nk + kMaxChunks - 1) / kMaxChunks)));
-            if (!ec_shared(c, e, E, nk, K, lanes_for(K, c.gmax), ovl, fb, mytot)) return;
-        } else {
-            mytot += ec_keys(c, E, 0, nk, lanes_for(nk, c.gmax), &c.s->nbig, fb);
-        }
-        __syncthreads();
-        const int32_t nl = c.s->nbig;
-        if (can_share && nl >= kLongShare) {
-            // many long keys: one wave per key, shared the same way (the
-            // keys move to a list of their own; rows longer than wg_rows
-            // come back to ovl)
-            int32_t *items = (int32_t *)slab_alloc(c, 4ll * nl + 4);
-            if (!items) return;
-            for (int32_t i = threadIdx.x; i < nl; i += NT) items[i] = ovl[i];
+        EcJob E1 = E;
+        E1.tier = tier;
+        int32_t nsh = 0, K = 1;  // items to share (0: none), per chunk
+        int G = 64;
+        if (tier == 0) {
+            if (can_share && nk >= c.help_items) {
+                const int32_t helpers = helpers_now(c);
+                nsh = nk;
+                K = min(512, max(64, max((nk + helpers) / (helpers + 1),
+                                         (nk + kMaxChunks - 1) / kMaxChunks)));
+                G = lanes_for(K, c.gmax);
+            } else {
+                mytot += ec_keys(c, E, 0, nk, lanes_for(nk, c.gmax), &g_s.nbig, fb);
+            }
+        } else if (tier == 1) {
             __syncthreads();
-            if (threadIdx.x == 0) c.s->nbig = 0;
-            EcJob E1 = E;
-            E1.items = items;
-            E1.tier = 1;
-            if (!ec_shared(c, e, E1, nl, kLongChunk, 64, ovl, fb, mytot)) return;
-        }
-        __syncthreads();
-        const int32_t nbig = c.s->nbig;
-        for (int32_t b = threadIdx.x >> 6; b < nbig; b += NW) {
-            const int32_t it = ovl[b];
-            const int32_t k = keys[it];
-            const int32_t beg = off[k], end = off[k + 1];
-            if (end - beg > c.wg_rows) {
-                int32_t p = 0;
-                if (lane == 0) p = atomicAdd(&c.s->ngiant, 1);
-                p = __shfl(p, 0, 64);
-                if (p < kBigCap) {
-                    if (lane == 0) c.s->big[p] = it;
-                    continue;
+            const int32_t nl = g_s.nbig;
+            if (can_share && nl >= kLongShare) {
+                // the keys move to a list of their own; rows longer than
+                // wg_rows come back to ovl
+                int32_t *items = (int32_t *)slab_alloc(c, 4ll * nl + 4);
+                if (!items) return;
+                for (int32_t i = threadIdx.x; i < nl; i += NT) items[i] = ovl[i];
+                __syncthreads();
+                if (threadIdx.x == 0) g_s.nbig = 0;
+                E1.items = items;
+                nsh = nl;
+                K = kLongChunk;
+            }
+        } else {
+            __syncthreads();
+            const int32_t nbig = nk <= NW ? 0 : g_s.nbig;
+            for (int32_t b = threadIdx.x >> 6; b < nbig; b += NW) {
+                const int32_t it = ovl[b];
+                const int32_t k = keys[it];
+                const int32_t beg = off[k], end = off[k + 1];
+                if (end - beg > c.wg_rows) {
+                    int32_t p = 0;
+                    if (lane == 0) p = atomicAdd(&g_s.ngiant, 1);
+                    p = __shfl(p, 0, 64);
+                    if (p < kBigCap) {
+                        if (lane == 0) g_s.big[p] = it;
+                        continue;
+                    }
+                }
+                const bool probe = probe_cheaper(no, end - beg);
+                const int32_t ks = homo ? -1 : k;
+                const int64_t n = probe ? ec_probe_wave(c, rel, ol, no, adj, beg, end, ks, vals + degoff[it])
+                                        : ec_key_wave(c, rel, olabel, ob, adj, beg, end, ks, vals + degoff[it]);
+                if (lane == 0) {
+                    num[it] = (int32_t)n;
+                    mytot += n;
+                    fb += 16ull + 4ull * n + (probe ? probe_bytes(no, end - beg) : 12ull * (end - beg));
                 }
             }
-            const bool probe = probe_cheaper(no, end - beg);
-            const int32_t ks = homo ? -1 : k;
-            const int64_t n = probe ? ec_probe_wave(c, rel, ol, no, adj, beg, end, ks, vals + degoff[it])
-                                    : ec_key_wave(c, rel, olabel, ob, adj, beg, end, ks, vals + degoff[it]);
-            if (lane == 0) {
-                num[it] = (int32_t)n;
-                mytot += n;
-                fb += 16ull + 4ull * n + (probe ? probe_bytes(no, end - beg) : 12ull * (end - beg));
+            __syncthreads();
+            const int32_t ngiant = min(g_s.ngiant, kBigCap);
+            if (can_share && ngiant >= 2) {
+                int32_t *items = (int32_t *)slab_alloc(c, 4ll * ngiant + 4);
+                if (!items) return;
+                for (int32_t i = threadIdx.x; i < ngiant; i += NT) items[i] = g_s.big[i];
+                __syncthreads();
+                E1.items = items;
+                nsh = ngiant;
+                G = NT;
+            } else if (ngiant > 0) {
+                E1.items = g_s.big;
+                mytot += ec_giant_keys(c, E1, 0, ngiant, fb);
             }
         }
-    }
-    __syncthreads();
-    // keys with rows above wg_rows: one workgroup each, shared when several
-    const int32_t ngiant = min(c.s->ngiant, kBigCap);
-    if (can_share && ngiant >= 2) {
-        int32_t *items = (int32_t *)slab_alloc(c, 4ll * ngiant + 4);
-        if (!items) return;
-        for (int32_t i = threadIdx.x; i < ngiant; i += NT) items[i] = c.s->big[i];
-        __syncthreads();
-        EcJob E2 = E;
-        E2.items = items;
-        E2.tier = 2;
-        if (!ec_shared(c, e, E2, ngiant, 1, NT, ovl, fb, mytot)) return;
-    } else if (ngiant > 0) {
-        int32_t *items = c.s->big;
-        EcJob E2 = E;
-        E2.items = items;
-        mytot += ec_giant_keys(c, E2, 0, ngiant, fb);
+        if (nsh > 0 && !ec_shared(c, e, E1, nsh, K, G, ovl, fb, mytot)) return;
     }
     add_bytes_wave(c, fb);
     int64_t tot;
-    block_excl_scan(mytot, c.s->sh, &tot);
+    block_excl_scan<NW>(mytot, g_s.sh, &tot);
     if (threadIdx.x == 0) {
-        c.s->ectot[e] = tot;
-        c.s->slab_used = (int64_t)((char *)ovl - c.slab);  // the last allocation
+        g_s.ectot[e] = tot;
+        g_s.slab_used = (int64_t)((char *)ovl - c.slab);  // the last allocation
     }
     __syncthreads();
 }
 
-// Tables of the edges in `mask` whose key vertex has a single candidate with
-// a row of at most wg_rows entries (dir as in ec_build), built together: one
-// wave per edge and one slab allocation for all of them, instead of the
-// barriers and allocations of a full build per edge. Returns the edges built
-// (uniform). Uses the dynamic LDS, which no other phase holds meanwhile.
-__device__ __forceinline__ uint64_t ec_build_single(Ctx &c, uint64_t mask, int dir) {
+__device__ __attribute__((noinline)) void ec_build_far(int e, int key, int other, int dir) {
+    SGM_OWN_CTX(c);
+    ec_build(c, __builtin_amdgcn_readfirstlane(e), __builtin_amdgcn_readfirstlane(key),
+             __builtin_amdgcn_readfirstlane(other), __builtin_amdgcn_readfirstlane(dir));
+}
+
+// Tables of the edges in `mask` whose key vertex has up to kFewKeys
+// candidates, with rows of at most wg_rows entries (dir as in ec_build),
+// built together: one wave per (edge, key) and one slab allocation for all of
+// them, instead of the barriers and allocations of a full build per edge (8 us
+// each). Returns the edges built (uniform). Uses the dynamic LDS, which no
+// other phase holds meanwhile.
+constexpr int kFewKeys = 8;
+static_assert(SGM_MAX_QE * kFewKeys <= NT, "a thread per (edge, key)");
+
+__device__ __forceinline__ uint64_t ec_build_few(Ctx &c, uint64_t mask, int dir) {
     const DevGraph &g = c.g;
     const NQuery &Q = *c.Q;
-    const int32_t *off = dir ? g.in_off : g.out_off;
-    const int2 *adj = dir ? g.in_adj : g.out_adj;
-    int32_t *dsz = (int32_t *)c.dyn;  // [SGM_MAX_QE] bytes of each table, 0: not here
-    int32_t *dk = dsz + SGM_MAX_QE;   // [SGM_MAX_QE] the key's candidate
-    int32_t *dpos = dk + SGM_MAX_QE;  // [SGM_MAX_QE] byte offset in the allocation
-    int32_t *ql = dpos + SGM_MAX_QE;  // [SGM_MAX_QE] edges built here
-    int32_t *meta = ql + SGM_MAX_QE;  // [0] edges, [1] bytes
-    const int e = threadIdx.x;
-    if (e < Q.m) {
-        int32_t sz = 0, k = -1;
-        if ((mask >> e) & 1ull) {
-            const int key = dir ? Q.edst[e] : Q.esrc[e];
-            if (c.s->cnt[key] == 1) {
-                k = c.L(key)[0];
-                const int32_t deg = off[k + 1] - off[k];
-                // offsets [2], count [1], values [deg], rounded to 16 bytes
-                if (deg <= c.wg_rows) sz = (4 * (3 + deg) + 15) & ~15;
-            }
-        }
-        dsz[e] = sz;
-        dk[e] = k;
+    Smem &s = g_s;
+    const int2 *adj = g.adj(dir);
+    // per thread t = (edge t / kFewKeys, key t % kFewKeys), for the waves
+    struct Task {
+        int32_t key, beg, end, at;  // at: first value in the edge's array
+    };
+    Task *task = (Task *)g_dyn;                      // [NT]
+    int32_t *esz = (int32_t *)(task + NT);           // [SGM_MAX_QE] bytes of each table, 0: not here
+    int32_t *epos = esz + SGM_MAX_QE;                // [SGM_MAX_QE] byte offset in the allocation
+    int32_t *list = epos + SGM_MAX_QE;               // [NT] tasks
+    int32_t *meta = list + NT;                       // [0] tasks, [1] bytes
+    const int t = threadIdx.x, e = t / kFewKeys, i = t % kFewKeys;
+    const int lane = t & 63, wid = t >> 6;
+    const bool in = e < Q.m && ((mask >> e) & 1ull);
+    const int kv = in ? (dir ? Q.edst[e] : Q.esrc[e]) : 0;
+    const int32_t nk = in ? s.cnt[kv] : 0;
+    const bool on = in && nk <= kFewKeys && i < nk;
+    int32_t len = 0;
+    Task tk{-1, 0, 0, 0};
+    if (on) {
+        tk.key = c.L(kv)[i];
+        const int4 r = g.vrow[tk.key];
+        tk.beg = dir ? r.z : r.x;
+        tk.end = dir ? r.w : r.y;
+        len = tk.end - tk.beg;
+    }
+    // the edge's rows side by side; a row above wg_rows leaves the edge out
+    const uint64_t grp = 0xffull << (lane & ~(kFewKeys - 1));
+    const bool big = (__ballot(on && len > min(c.wg_rows, 32768)) & grp) != 0;
+    int32_t inc = len;
+#pragma unroll
+    for (int o = 1; o < kFewKeys; o <<= 1) {
+        const int32_t y = __shfl_up(inc, o, kFewKeys);
+        if (i >= o) inc += y;
+    }
+    const int32_t sum = __shfl(inc, kFewKeys - 1, kFewKeys);
+    tk.at = inc - len;
+    const bool here = on && !big;
+    if (t == 0) meta[0] = 0;
+    // offsets [nk + 1], counts [nk], values [sum], rounded to 16 bytes
+    if (i == 0 && e < SGM_MAX_QE) esz[e] = here ? (4 * (2 * nk + 1 + sum) + 15) & ~15 : 0;
+    task[t] = tk;
+    __syncthreads();
+    if (here) list[atomicAdd(&meta[0], 1)] = t;
+    if (wid == 0) {
+        // exclusive scan of the tables' sizes
+        const int32_t sz = esz[lane];
+        const int32_t ic = wave_incl_scan32(sz, lane);
+        epos[lane] = ic - sz;
+        if (lane == 63) meta[1] = ic;
+        if (sz) s.ectot[lane] = 0;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t nq = 0, tot = 0;
-        for (int i = 0; i < Q.m; ++i)
-            if (dsz[i]) {
-                dpos[i] = tot;
-                tot += dsz[i];
-                ql[nq++] = i;
-            }
-        meta[0] = nq;
-        meta[1] = tot;
-    }
-    __syncthreads();
-    const int32_t nq = meta[0];
-    if (nq == 0) return 0ull;
+    const int32_t nt = meta[0];
+    if (nt == 0) return 0ull;
     char *base = slab_alloc(c, meta[1]);
     if (!base) return 0ull;
-    const int lane = threadIdx.x & 63;
+    if (here) {
+        int32_t *degoff = (int32_t *)(base + epos[e]);
+        degoff[i] = tk.at;
+        if (i == nk - 1) degoff[nk] = sum;
+        if (i == 0) {
+            s.ec_offs[e] = degoff;
+            s.ec_cnt[e] = degoff + nk + 1;
+            s.ec_vals[e] = degoff + 2 * nk + 1;
+            s.eckey[e] = kv;
+        }
+    }
+    __syncthreads();
     uint64_t fb = 0;
-    for (int i = threadIdx.x >> 6; i < nq; i += NW) {
-        const int ed = ql[i];
-        const int key = dir ? Q.edst[ed] : Q.esrc[ed];
+    for (int q = wid; q < nt; q += NW) {
+        const int ti = list[q], ed = ti / kFewKeys, ki = ti % kFewKeys;
+        const Task w = task[ti];
         const int other = dir ? Q.esrc[ed] : Q.edst[ed];
-        const int32_t k = dk[ed];
-        const int32_t beg = off[k], end = off[k + 1];
-        int32_t *degoff = (int32_t *)(base + dpos[ed]);
-        int32_t *num = degoff + 2;
-        int32_t *vals = degoff + 3;
-        const int32_t no = c.s->cnt[other];
-        const int32_t rel = Q.elabel[ed];
-        const bool probe = probe_cheaper(no, end - beg);
-        const int32_t ks = Q.homo ? -1 : k;
-        const int64_t n = probe ? ec_probe_wave(c, rel, c.L(other), no, adj, beg, end, ks, vals)
-                                : ec_key_wave(c, rel, Q.pred[other].label, c.B(other), adj, beg, end, ks, vals);
+        const int32_t no = s.cnt[other], rel = Q.elabel[ed], wl = w.end - w.beg;
+        int32_t *vals = s.ec_vals[ed] + w.at;
+        const bool probe = probe_cheaper(no, wl);
+        const int32_t ks = Q.homo ? -1 : w.key;
+        const int64_t n = probe ? ec_probe_wave(c, rel, c.L(other), no, adj, w.beg, w.end, ks, vals)
+                                : ec_key_wave(c, rel, Q.pred[other].label, c.B(other), adj, w.beg, w.end, ks, vals);
         if (lane == 0) {
-            degoff[0] = 0;
-            degoff[1] = end - beg;
-            num[0] = (int32_t)n;
-            c.s->ec_offs[ed] = degoff;
-            c.s->ec_cnt[ed] = num;
-            c.s->ec_vals[ed] = vals;
-            c.s->eckey[ed] = key;
-            c.s->ectot[ed] = n;
-            fb += 28ull + 4ull * n + (probe ? probe_bytes(no, end - beg) : 12ull * (end - beg));
+            s.ec_cnt[ed][ki] = (int32_t)n;
+            if (n) atomicAdd((unsigned long long *)&s.ectot[ed], (unsigned long long)n);
+            fb += 28ull + 4ull * n + (probe ? probe_bytes(no, wl) : 12ull * wl);
         }
     }
     add_bytes_wave(c, fb);
     uint64_t built = 0;
-    for (int i = 0; i < nq; ++i) built |= 1ull << ql[i];
+    for (int q = 0; q < Q.m; ++q) built |= (uint64_t)(esz[q] != 0) << q;
     __syncthreads();
     return built;
 }
@@ -2186,7 +2443,7 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
 __device__ __forceinline__ void join_order(Ctx &c) {
     if (threadIdx.x >= 64) return;
     const NQuery &Q = *c.Q;
-    Smem &s = *c.s;
+    Smem &s = g_s;
     const int lane = threadIdx.x;
     const bool has = lane < Q.m;
     const int xs = has ? s.qsrc[lane] : 0, xd = has ? s.qdst[lane] : 0;
@@ -2240,13 +2497,13 @@ __device__ __forceinline__ void join_order(Ctx &c) {
 }
 
 __device__ __forceinline__ bool ec_contains(const Ctx &c, int e, int32_t keyval, int32_t x) {
-    const int kv = c.s->eckey[e];
+    const int kv = g_s.eckey[e];
     const int32_t *kl = c.L(kv);
-    const int32_t i = lower_bound_i32(kl, 0, c.s->cnt[kv], keyval);
-    if (i >= c.s->cnt[kv] || kl[i] != keyval) return false;
-    const int32_t lo = c.s->ec_offs[e][i], hi = lo + c.s->ec_cnt[e][i];
-    const int32_t j = lower_bound_i32(c.s->ec_vals[e], lo, hi, x);
-    return j < hi && c.s->ec_vals[e][j] == x;
+    const int32_t i = lower_bound_i32(kl, 0, g_s.cnt[kv], keyval);
+    if (i >= g_s.cnt[kv] || kl[i] != keyval) return false;
+    const int32_t lo = g_s.ec_offs[e][i], hi = lo + g_s.ec_cnt[e][i];
+    const int32_t j = lower_bound_i32(g_s.ec_vals[e], lo, hi, x);
+    return j < hi && g_s.ec_vals[e][j] == x;
 }
 
 // Shared join levels: a chunk is one block of NT parent rows, or 1/nsub of
@@ -2336,10 +2593,10 @@ template <bool SHARED>
 __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, int64_t r1,
                                           int32_t sub, int32_t nsub, unsigned long long *gctr,
                                           int32_t *gabort, uint64_t &jb) {
-    Smem &s = *c.s;
+    Smem &s = g_s;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t r = r0 + threadIdx.x;
-    int32_t *rows = (int32_t *)(c.dyn + kJoinStageRows);
+    int32_t *rows = (int32_t *)(g_dyn + kJoinStageRows);
     {
         const int32_t *src = L.table + r0 * L.k;
         const int nint = (int)(r1 - r0) * L.k;
@@ -2373,7 +2630,7 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
         return;
     }
     int64_t tot;
-    const int64_t ex = block_excl_scan(fan, s.sh, &tot);
+    const int64_t ex = block_excl_scan<NW>(fan, s.sh, &tot);
     if (tot > INT32_MAX) {
         // more pairs than a block's offsets hold: the multi-kernel path
         if (threadIdx.x == 0) {
@@ -2397,7 +2654,7 @@ __device__ __forceinline__ void join_rows(Ctx &c, const JLevel &L, int64_t r0, i
     s.pairoff[threadIdx.x] = (int32_t)ex;
     s.rowlo[threadIdx.x] = lo;
     __syncthreads();
-    int32_t *wrr = (int32_t *)c.dyn + wid * 512;  // this wave's staged rows
+    int32_t *wrr = (int32_t *)g_dyn + wid * 512;  // this wave's staged rows
     int32_t *wx = wrr + 256;
     if (L.count) {
         const int64_t nblk = (tot + NT - 1) / NT;
@@ -2495,7 +2752,7 @@ __device__ __forceinline__ void join_chunk(Ctx &c, const JLevel &L, int32_t ch,
 // s.ctr.
 __device__ __forceinline__ void shared_join(Ctx &c, int32_t nch, uint64_t &jb) {
     HelpJob *j = c.job;
-    Smem &s = *c.s;
+    Smem &s = g_s;
     {
         const uint64_t *src = (const uint64_t *)&s.jl;
         uint64_t *dst = (uint64_t *)&j->jl;
@@ -2568,6 +2825,13 @@ __device__ __forceinline__ void shared_join(Ctx &c, int32_t nch, uint64_t &jb) {
     __syncthreads();
 }
 
+__device__ __attribute__((noinline)) uint64_t shared_join_far(int32_t nch) {
+    SGM_OWN_CTX(c);
+    uint64_t jb = 0;
+    shared_join(c, __builtin_amdgcn_readfirstlane(nch), jb);
+    return jb;
+}
+
 // ---------------------------------------------------------------------------
 // final ordering helpers
 // ---------------------------------------------------------------------------
@@ -2578,7 +2842,7 @@ __device__ __forceinline__ void shared_join(Ctx &c, int32_t nch, uint64_t &jb) {
 // eight columns advance together, so their probes are independent loads;
 // s.kdepth steps bring every search to its end.
 __device__ __forceinline__ uint64_t row_key(const Ctx &c, const int32_t *row) {
-    const Smem &s = *c.s;
+    const Smem &s = g_s;
     const int n = c.Q->n;
     const int depth = s.kdepth;
     uint64_t key = 0;
@@ -2621,26 +2885,26 @@ __device__ __forceinline__ uint64_t row_key(const Ctx &c, const int32_t *row) {
 // Point rkl[u] at the sorted candidate list of every key column, copying
 // the lists into LDS while they fit (binary searches then stay on chip).
 __device__ __forceinline__ void stage_key_lists(Ctx &c) {
-    int32_t *stage = (int32_t *)(c.dyn + kStageOff);
+    int32_t *stage = (int32_t *)(g_dyn + kStageOff);
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t used = 0;
         for (int u = 0; u < c.Q->n; ++u) {
-            const int32_t m = c.s->cnt[u];
-            if (c.s->bitsn[u] > 0 && used + m <= kStageInts) {
-                c.s->rkl[u] = stage + used;
+            const int32_t m = g_s.cnt[u];
+            if (g_s.bitsn[u] > 0 && used + m <= kStageInts) {
+                g_s.rkl[u] = stage + used;
                 used += m;
             } else {
-                c.s->rkl[u] = c.L(u);
+                g_s.rkl[u] = c.L(u);
             }
         }
     }
     __syncthreads();
     for (int u = 0; u < c.Q->n; ++u) {
-        int32_t *dst = const_cast<int32_t *>(c.s->rkl[u]);
+        int32_t *dst = const_cast<int32_t *>(g_s.rkl[u]);
         if (dst == c.L(u)) continue;
         const int32_t *src = c.L(u);
-        for (int32_t i = threadIdx.x; i < c.s->cnt[u]; i += NT) dst[i] = src[i];
+        for (int32_t i = threadIdx.x; i < g_s.cnt[u]; i += NT) dst[i] = src[i];
     }
     __syncthreads();
 }
@@ -2653,7 +2917,7 @@ __device__ __forceinline__ void stage_key_lists(Ctx &c) {
 __device__ __forceinline__ void wg_radix_pass(Ctx &c, const uint64_t *kin, const int32_t *iin,
                                               uint64_t *kout, int32_t *iout, int64_t n,
                                               int shift) {
-    int32_t *cnt = (int32_t *)c.dyn;  // [NW][256] counts, then running offsets
+    int32_t *cnt = (int32_t *)g_dyn;  // [NW][256] counts, then running offsets
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t seg = ((n + NW - 1) / NW + 63) & ~(int64_t)63;
     const int64_t lo = min(n, wid * seg), hi = min(n, lo + seg);
@@ -2673,7 +2937,7 @@ __device__ __forceinline__ void wg_radix_pass(Ctx &c, const uint64_t *kin, const
                 sum += col[w];
             }
         int64_t tot;
-        int64_t run = block_excl_scan(sum, c.s->sh, &tot);
+        int64_t run = block_excl_scan<NW>(sum, g_s.sh, &tot);
         if (threadIdx.x < 256)
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
@@ -2729,12 +2993,7 @@ __device__ __forceinline__ void clear_slot(Ctx &c, bool full) {
             for (int32_t w = threadIdx.x; w < nwords; w += NT) c.B(u)[w] = 0ull;
         for (int32_t w = threadIdx.x; w < nwords; w += NT) c.scratch[w] = 0ull;
     } else {
-        for (int u = 0; u < n; ++u) {
-            const int32_t *l = c.L(u);
-            uint64_t *b = c.B(u);
-            const int32_t cn = c.s->cnt[u];
-            for (int32_t i = threadIdx.x; i < cn; i += NT) b[l[i] >> 6] = 0ull;
-        }
+        for (int u = 0; u < n; ++u) clear_words(c, u, g_s.cnt[u]);
     }
     __syncthreads();
 }
@@ -2753,13 +3012,605 @@ __device__ __forceinline__ void single_row(Ctx &c, int32_t *out, int k, F vert) 
             dup |= (uint32_t)__ballot(lane > i && x == __builtin_amdgcn_readlane(x, i));
     if (lane < k) {
         out[lane] = x;
-        c.s->level_rows[lane] = (dup & ((2u << lane) - 1u)) == 0;
+        g_s.level_rows[lane] = (dup & ((2u << lane) - 1u)) == 0;
     }
 }
 
-__device__ __forceinline__ void run_query(Ctx &c) {
+// A query's phases, each in a function of its own (see g_s).
+
+// Filtering: root candidates, exploration, refinement.
+__device__ __attribute__((noinline)) void filter_phase() {
+    SGM_OWN_CTX(c);
     const DevGraph &g = c.g;
-    Smem &s = *c.s;
+    Smem &s = g_s;
+    const NQuery &Q = s.query;
+    const int n = uniform(Q.n);
+    // root candidates
+    const int root = Q.root;
+    const int32_t rootq = Q.root_lo < 0 ? -1
+                                        : Q.pred[root].qout | Q.pred[root].qin << 8 | (Q.homo ? 1 << 16 : 0);
+    if (rootq < 0) {
+        if (threadIdx.x == 0) {
+            const int32_t pin = Q.pred[root].pin;
+            if (pin >= 0 && pin < g.V && vpred(g, Q.pred[root], pin)) {
+                c.B(root)[pin >> 6] |= 1ull << (pin & 63);
+                c.L(root)[0] = pin;
+                s.cnt[root] = 1;
+            }
+        }
+        __syncthreads();
+    }
+    ev(c, SGM_EV_ROOT);
+    // Explore along the spanning tree, then refinement rounds: one loop, so
+    // that the kernel holds the steps' code once. (A single query vertex has
+    // no step; an unpinned one takes its whole range in one without tests.)
+    const bool alone = Q.n_init == 0 && rootq >= 0;
+    const int n_exp = alone ? 1 : Q.n_init;
+    const int rounds = Q.n_ref > 0 ? (Q.refine_rounds < 0 ? 32 : Q.refine_rounds) : 0;
+    int removed = 0;
+    for (int i = 0, r = 0; i < n_exp + (r < rounds ? Q.n_ref : 0) && !aborted(c);) {
+        const NStep st = alone ? NStep{(int8_t)root, 1, -1, 0, 0, 0} : Q.steps[i];
+        // the first step is the root's
+        removed += filter_step(c, st, i == 0 ? rootq : -1);
+        const bool exploring = i < n_exp;
+        ev(c, exploring ? SGM_EV_EXPLORE : SGM_EV_REFINE);
+        if (exploring) removed = 0;
+        if (++i == n_exp + Q.n_ref && r < rounds) {
+            // a round is over
+            ++r;
+            if (r < rounds && !(Q.refine_rounds < 0 && removed == 0)) i = n_exp;
+            removed = 0;
+        }
+    }
+}
+
+// Candidate edges and join levels: the rows found and their table.
+__device__ __attribute__((noinline)) void match_phase() {
+    SGM_OWN_CTX(c);
+    Smem &s = g_s;
+    const NQuery &Q = s.query;
+    const int n = uniform(Q.n);
+    int64_t rows = 0;
+    int32_t *table = nullptr;
+    for (int u = 0; u < n && !aborted(c); ++u)
+        if (s.cnt[u] > 1) sort_list(c, u);
+    ev(c, SGM_EV_LISTS);
+    if (Q.m == 0) {
+        table = c.L(0);
+        rows = s.cnt[0];
+        if (threadIdx.x == 0) {
+            s.jorder[0] = 0;
+            s.jpos[0] = 0;
+        }
+        __syncthreads();
+    } else if (!aborted(c)) {
+        // candidate edges keyed by each edge's source: totals for the order
+        // (dir 0), then the edges the join looks up by their destination
+        // again, keyed so (dir 1)
+        bool join = false;
+        int pre = 0;
+        uint64_t todo = Q.m == 64 ? ~0ull : (1ull << Q.m) - 1ull;
+        for (int dir = 0; dir < 2 && todo && !aborted(c); ++dir) {
+            const uint64_t few = ec_build_few(c, todo, dir);
+            if (few) ev(c, SGM_EV_EDGES);
+            for (int e = 0; e < Q.m && !aborted(c); ++e) {
+                if (!(((todo & ~few) >> e) & 1ull)) continue;
+                ec_build_far(e, dir ? Q.edst[e] : Q.esrc[e], dir ? Q.esrc[e] : Q.edst[e], dir);
+                ev(c, SGM_EV_EDGES);
+            }
+            __syncthreads();
+            if (dir == 1) break;
+            bool none = false, single = true;
+            for (int e = 0; e < Q.m; ++e) none |= s.ectot[e] == 0;
+            for (int u = 0; u < n; ++u) single &= s.cnt[u] == 1;
+            if (aborted(c) || none) break;
+            if (single) {
+                // One candidate per query vertex and its pair in every
+                // edge table: those candidates are the only possible
+                // row, and a match exactly when they are distinct. The
+                // join binds the vertices in index order.
+                int32_t *one_row = (int32_t *)slab_alloc(c, 4ll * n);
+                if (!one_row) break;
+                mark(c, 2);
+                single_row(c, one_row, n, [&](int u) { return u; });
+                if (threadIdx.x < n) {
+                    s.jorder[threadIdx.x] = threadIdx.x;
+                    s.jpos[threadIdx.x] = threadIdx.x;
+                }
+                if (threadIdx.x == 0) {
+                    s.nrows = s.level_rows[n - 1];
+                    add_bytes(c, 8ull * n);
+                }
+                __syncthreads();
+                table = one_row;
+                rows = s.nrows;
+                ev(c, SGM_EV_LEVEL);
+                break;
+            }
+            join = true;
+            if (threadIdx.x < Q.m) s.ecbuilt[threadIdx.x] = s.eckey[threadIdx.x];
+            __syncthreads();
+            join_order(c);
+            __syncthreads();
+            ev(c, SGM_EV_ORDER);
+            // The join's leading vertices of one candidate each make one
+            // row (every edge between them holds its pair, or the query
+            // had ended): no level and no re-keyed table is run for them.
+            while (pre < n && s.cnt[s.jorder[pre]] == 1) ++pre;
+            todo = 0;
+            for (int e = 0; e < Q.m; ++e)
+                if (s.eckey[e] != s.ecbuilt[e] && (s.jpos[Q.esrc[e]] >= pre || s.jpos[Q.edst[e]] >= pre))
+                    todo |= 1ull << e;
+        }
+        if (join && !aborted(c)) {
+            // join levels
+            mark(c, 2);
+            table = c.L(s.jorder[0]);
+            rows = s.cnt[s.jorder[0]];
+            if (threadIdx.x == 0) s.level_rows[0] = rows;
+            int k = 1;
+            if (pre > 1 && !aborted(c)) {
+                int32_t *row = (int32_t *)slab_alloc(c, 4ll * pre);
+                if (row) {
+                    single_row(c, row, pre, [&](int i) { return s.jorder[i]; });
+                    __syncthreads();
+                    table = row;
+                    rows = s.level_rows[pre - 1];
+                    k = pre;
+                    ev(c, SGM_EV_LEVEL);
+                }
+            }
+            for (int lv = k - 1; lv < n - 1 && !aborted(c) && rows > 0; ++lv) {
+                const bool counting = Q.count_only && lv == n - 2;
+                const int ext = s.lv_ext[lv];
+                const int p = s.eckey[ext];
+                const int cp = s.jpos[p];
+                const int32_t *pk = c.L(p);
+                const int32_t npk = s.cnt[p];
+                const int32_t *eoffs = s.ec_offs[ext];
+                const int32_t *ecnt = s.ec_cnt[ext];
+                const int32_t *evals = s.ec_vals[ext];
+                in_memory(eoffs);
+                in_memory(ecnt);
+                in_memory(evals);
+                const int nchk = s.lv_nchk[lv];
+                const int cfirst = s.lv_first[lv];
+                // output capacity: what is left of the slab
+                __syncthreads();
+                const int64_t used0 = (s.slab_used + 255) & ~(int64_t)255;
+                const int64_t left = c.slab_bytes - used0;
+                int64_t cap = left / (4 * (k + 1));
+                if (cap <= 0) {
+                    if (threadIdx.x == 0) s.abort_ = kWhySlab;
+                    __syncthreads();
+                    break;
+                }
+                if (threadIdx.x == 0) {
+                    s.ctr = 0;
+                    s.cnt64 = 0ull;
+                }
+                __syncthreads();
+                // the level's pairs bound its rows: a level that could not
+                // fit even a much larger slot stops here rather than
+                // after filling this one
+                int64_t pairs = -1;
+                const bool may_share = c.job && c.help_items > 0;
+                // a block of rows whose pairs could reach a shared or a
+                // host-ordered level (rows times the extension edge's
+                // candidate edges bound them) counts them here too
+                if (counting && nchk == 0) {
+                    // counted row by row, shared by rows
+                    pairs = rows;
+                } else if (rows > NT || rows * s.ectot[ext] >= kJoinSharePairs) {
+                    int64_t mp = 0;
+                    for (int64_t r = threadIdx.x; r < rows; r += NT) {
+                        const int32_t pv = table[r * k + cp];
+                        const int32_t i = lower_bound_i32(pk, 0, npk, pv);
+                        if (i < npk && pk[i] == pv) mp += ecnt[i];
+                    }
+                    block_excl_scan<NW>(mp, s.sh, &pairs);
+                    if (!counting && pairs > kPairSlack * cap) {
+                        if (threadIdx.x == 0) {
+                            s.abort_ = kWhySlab;
+                            s.need = used0 + pairs * 4 * (k + 1);
+                        }
+                        __syncthreads();
+                        break;
+                    }
+                }
+                // A last level that may reach the size the host orders
+                // goes to the top of the slab (its pairs bound its rows),
+                // with room above for the key columns' candidate lists:
+                // the slot's later queries keep the slab below it.
+                int32_t *out = nullptr;
+                if (counting) cap = INT32_MAX;  // no rows are written
+                if (!counting && lv == n - 2 && c.host_order_rows > 0 && pairs >= c.host_order_rows) {
+                    int64_t lint = 0;
+                    for (int u = 0; u < n; ++u) lint += s.cnt[u];
+                    const int64_t tneed = (pairs * 4 * (k + 1) + 255) & ~(int64_t)255;
+                    const int64_t lneed = (4 * lint + 256 * (n + 1)) & ~(int64_t)255;
+                    const int64_t at = (c.slab_bytes - tneed - lneed) & ~(int64_t)255;
+                    if (at >= kPinFloor(c) && at >= used0) {
+                        out = (int32_t *)(c.slab + at);
+                        cap = pairs;
+                        if (threadIdx.x == 0) s.below_top = used0;
+                        __syncthreads();
+                        if (threadIdx.x == 0) s.slab_used = at + pairs * 4 * (k + 1);
+                        __syncthreads();
+                    }
+                }
+                if (!out && !counting) out = (int32_t *)slab_alloc(c, cap * 4 * (k + 1));
+                if (!out && !counting) {
+                    if (threadIdx.x == 0) s.abort_ = kWhySlab;
+                    __syncthreads();
+                    break;
+                }
+                // the level's view (parent column, edge tables of its
+                // extension and check edges, output), the same for the
+                // owner and for helpers
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    JLevel &L = s.jl;
+                    L.table = table;
+                    L.rows = rows;
+                    L.k = k;
+                    L.cp = cp;
+                    L.pk = pk;
+                    L.npk = npk;
+                    L.eoffs = eoffs;
+                    L.ecnt = ecnt;
+                    L.evals = evals;
+                    L.nchk = nchk;
+                    for (int ci = 0; ci < nchk; ++ci) {
+                        const int e = s.chk[cfirst + ci];
+                        const int kv = s.eckey[e];
+                        L.chk[ci] = JChk{c.L(kv), s.ec_offs[e], s.ec_cnt[e], s.ec_vals[e],
+                                         s.cnt[kv], s.jpos[kv]};
+                    }
+                    L.out = out;
+                    L.cap = cap;
+                    L.count = counting;
+                    // columns the new value may repeat: those of a vertex
+                    // that can hold a candidate of the new one
+                    const int w = s.jorder[lv + 1];
+                    uint32_t cm = 0;
+                    for (int i = 0; i < k && !Q.homo; ++i) {
+                        const int32_t a = Q.pred[s.jorder[i]].label, b = Q.pred[w].label;
+                        if (a < 0 || b < 0 || a == b) cm |= 1u << i;
+                    }
+                    L.cmask = cm;
+                }
+                // a level of many pairs is shared (whether or not
+                // workgroups are idle yet: those that become idle join)
+                const int64_t nrb = (rows + NT - 1) / NT;
+                int64_t nsub = 1;
+                if (may_share && pairs >= kJoinSharePairs)
+                    nsub = min((int64_t)kJoinMaxSub,
+                               max((int64_t)1, (pairs + nrb * kJoinChunkPairs - 1) /
+                                                   (nrb * kJoinChunkPairs)));
+                // (a counting level without check edges: blocks of rows)
+                if (counting && nchk == 0) nsub = 1;
+                const bool share =
+                    may_share && nrb * nsub <= kMaxChunks &&
+                    (counting && nchk == 0 ? nrb >= kCountShareBlocks : pairs >= kJoinSharePairs);
+                if (threadIdx.x == 0) s.jl.nsub = (int32_t)nsub;
+                __syncthreads();
+                uint64_t jb = 0;  // algorithmic bytes of this thread's rows and pairs
+                if (share) {
+                    jb += shared_join_far((int32_t)(nrb * nsub));
+                } else {
+                    for (int64_t rbase = 0; rbase < rows && !aborted(c); rbase += NT)
+                        join_rows<false>(c, s.jl, rbase, min(rows, rbase + NT), 0, 1,
+                                         nullptr, nullptr, jb);
+                }
+                add_bytes(c, jb);
+                __syncthreads();
+                rows = counting ? (int64_t)s.cnt64 : (int64_t)s.ctr;
+                if (threadIdx.x == 0) s.level_rows[lv + 1] = rows;
+                // give back the unused part of the table allocation
+                __syncthreads();
+                if (threadIdx.x == 0 && !s.abort_ && !counting)
+                    s.slab_used = (int64_t)((char *)out - c.slab) + rows * 4 * (k + 1);
+                __syncthreads();
+                ev(c, SGM_EV_LEVEL);
+                table = out;
+                ++k;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s.nrows = rows;
+        s.table = table;
+    }
+}
+
+// Ordering and output of the rows found.
+__device__ __attribute__((noinline)) void order_phase() {
+    SGM_OWN_CTX(c);
+    Smem &s = g_s;
+    const NQuery &Q = s.query;
+    const int n = uniform(Q.n);
+    int64_t rows = uniform(s.nrows);
+    int32_t *table = uniform(s.table);
+    in_memory(table);
+    // ordering: key = concatenated candidate ranks in column order 0..n-1;
+    // a projection (thesis Ch. 3, Sec. "GpSense") keys and keeps only
+    // its columns
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int tb = 0, no = 0, depth = 0;
+        for (int u = 0; u < n; ++u) {
+            const bool kept = Q.proj == 0u || ((Q.proj >> u) & 1u);
+            int b = 0;
+            while (kept && (1ll << b) < s.cnt[u]) ++b;
+            s.bitsn[u] = b;
+            tb += b;
+            if (kept) s.ocol[no++] = s.jpos[u];
+            // a lower bound over m entries ends after bit_length(m) halvings
+            if (b > 0) depth = max(depth, 32 - __clz(s.cnt[u]));
+        }
+        s.ctr = tb;
+        s.nout = no;
+        s.kdepth = depth;
+    }
+    __syncthreads();
+    if (s.ctr > 64 && rows > 1) {
+        if (threadIdx.x == 0) {
+            s.status = kNeedWide;
+            s.reason = kWhyKey;
+        }
+        return;
+    }
+    const int tb = s.ctr;
+    const int k = n;
+    const int no = s.nout;
+    int32_t *idx;
+    const uint64_t *skeys = nullptr;  // the sorted keys (rows > 1)
+    // A large final table in the slab, with room below it for the slot's
+    // later queries: the key columns' sorted candidate lists go beside
+    // it and the host orders it (and collapses a projection) with
+    // whole-GPU kernels after the launch; one workgroup would spend
+    // milliseconds on the keys, the passes and the gather.
+    int64_t toff = (int64_t)((const char *)table - c.slab);
+    if (c.host_order_rows > 0 && rows >= c.host_order_rows && toff >= 0 &&
+        toff < c.slab_bytes) {
+        int64_t lint = 0;
+        for (int u = 0; u < n; ++u)
+            if (s.bitsn[u] > 0) lint += s.cnt[u];
+        int32_t *lst = nullptr;
+        const int64_t tbytes = (rows * k * 4 + 255) & ~(int64_t)255;
+        const int64_t top = ((c.slab_bytes - 4 * lint) & ~(int64_t)255) - tbytes;
+        if (toff >= kPinFloor(c)) {
+            lst = (int32_t *)slab_alloc(c, 4 * lint);
+        } else if (top >= kPinFloor(c) && top > toff) {
+            // too low in the slab to keep for the host: move it up to
+            // the top, lists above it; overlapping, so the chunks go
+            // from the end (every read of a chunk before its writes)
+            int32_t *dst = (int32_t *)(c.slab + top);
+            const int64_t nint = rows * k;
+            for (int64_t end = nint; end > 0; end -= 4 * NT) {
+                const int64_t beg = end - 4 * NT > 0 ? end - 4 * NT : 0;
+                int32_t v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t i = beg + q * NT + threadIdx.x;
+                    v[q] = i < end ? table[i] : 0;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t i = beg + q * NT + threadIdx.x;
+                    if (i < end) dst[i] = v[q];
+                }
+                __syncthreads();
+            }
+            if (threadIdx.x == 0) add_bytes(c, 8ull * nint);
+            table = dst;
+            toff = top;
+            lst = (int32_t *)(c.slab + top + tbytes);
+        }
+        if (lst) {
+            int64_t o = 0;
+            for (int u = 0; u < n; ++u) {
+                if (s.bitsn[u] == 0) continue;
+                const int32_t *src = c.L(u);
+                for (int32_t i = threadIdx.x; i < s.cnt[u]; i += NT) lst[o + i] = src[i];
+                o += s.cnt[u];
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                s.hostord = 1;
+                s.keybits = tb;
+                s.pin_off = toff;
+                s.tableptr = table;
+                s.listptr = lst;
+                add_bytes(c, 8ull * lint);
+            }
+            __syncthreads();
+            ev(c, SGM_EV_SORT);
+            return;
+        }
+    }
+    if (rows > 1) stage_key_lists(c);
+    if (s.below_top >= 0 && rows > kRowSortCap) {
+        // the last level sits at the slab's top but stayed on this
+        // workgroup: its sort buffers go into the slab below it
+        __syncthreads();
+        if (threadIdx.x == 0) s.slab_used = s.below_top;
+        __syncthreads();
+        c.slab_bytes = toff;
+    }
+    if (rows == 1) {
+        int32_t *ix = (int32_t *)g_dyn;
+        if (threadIdx.x == 0) ix[0] = 0;
+        __syncthreads();
+        idx = ix;
+    } else if (rows <= kRowSortCap) {
+        // bitonic network in LDS
+        uint64_t *keys = (uint64_t *)g_dyn;
+        int32_t *ix = (int32_t *)(g_dyn + sizeof(uint64_t) * kRowSortCap);
+        int32_t N = 1;
+        while (N < rows) N <<= 1;
+        for (int32_t r = threadIdx.x; r < N; r += NT) {
+            keys[r] = r < rows ? row_key(c, table + (int64_t)r * k) : ~0ull;
+            ix[r] = r;
+        }
+        __syncthreads();
+        for (int32_t size = 2; size <= N; size <<= 1) {
+            for (int32_t stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int32_t i = threadIdx.x; i < N / 2; i += NT) {
+                    const int32_t lo = 2 * i - (i & (stride - 1));
+                    const int32_t hi = lo + stride;
+                    const bool up = (lo & size) == 0;
+                    // ties (a key of all ones against the padding)
+                    // by row index, so padding stays last
+                    const uint64_t x = keys[lo], y = keys[hi];
+                    const bool gt = x > y || (x == y && ix[lo] > ix[hi]);
+                    if (gt == up) {
+                        keys[lo] = y;
+                        keys[hi] = x;
+                        const int32_t t = ix[lo];
+                        ix[lo] = ix[hi];
+                        ix[hi] = t;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        idx = ix;
+        skeys = keys;
+    } else {
+        // LSD radix on (key, row) pairs in the slab, 8 bits per pass
+        uint64_t *ka = (uint64_t *)slab_alloc(c, 8 * rows);
+        uint64_t *kb = (uint64_t *)slab_alloc(c, 8 * rows);
+        int32_t *ia = (int32_t *)slab_alloc(c, 4 * rows);
+        int32_t *ib = (int32_t *)slab_alloc(c, 4 * rows);
+        if (!ka || !kb || !ia || !ib) {
+            if (threadIdx.x == 0) {
+                s.status = kNeedWide;
+                s.reason = kWhySlab;
+            }
+            return;
+        }
+        if (threadIdx.x == 0) s.unsorted = 0;
+        for (int64_t r = threadIdx.x; r < rows; r += NT) {
+            ka[r] = row_key(c, table + r * k);
+            ia[r] = (int32_t)r;
+        }
+        __syncthreads();
+        // a join that bound the key columns in key order has left the
+        // rows in order already: then no pass is needed
+        bool down = false;
+        for (int64_t r = threadIdx.x; r + 1 < rows; r += NT) down |= ka[r] > ka[r + 1];
+        if (down) s.unsorted = 1;
+        __syncthreads();
+        if (threadIdx.x == 0) add_bytes(c, 8ull * rows);
+        const bool passes = s.unsorted != 0;
+        for (int sh = 0; passes && sh < tb; sh += 8) {
+            wg_radix_pass(c, ka, ia, kb, ib, rows, sh);
+            uint64_t *tk = ka;
+            ka = kb;
+            kb = tk;
+            int32_t *ti = ia;
+            ia = ib;
+            ib = ti;
+        }
+        if (threadIdx.x == 0 && passes) add_bytes(c, 24ull * rows * ((tb + 7) / 8));
+        idx = ia;
+        skeys = ka;
+    }
+    if (Q.proj && rows > 1) {
+        // equal projected rows now have equal, adjacent keys: keep the
+        // first row of each run (in-place compaction of the order)
+        int64_t kept = 0;
+        for (int64_t base = 0; base < rows; base += NT) {
+            const int64_t i = base + threadIdx.x;
+            const bool head = i < rows && (i == 0 || skeys[i] != skeys[i - 1]);
+            const int32_t v = i < rows ? idx[i] : 0;
+            int64_t tot;
+            const int64_t ex = block_excl_scan<NW>((int64_t)(head ? 1 : 0), s.sh, &tot);
+            if (head) idx[kept + ex] = v;
+            kept += tot;
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) add_bytes(c, 16ull * rows);
+        rows = kept;
+        if (threadIdx.x == 0) s.nrows = rows;
+        __syncthreads();
+    }
+    ev(c, SGM_EV_SORT);
+    if (threadIdx.x == 0) {
+        const unsigned long long need = (unsigned long long)rows * no;
+        const unsigned long long off = atomicAdd(c.out_used, need);
+        s.offset = (off + need <= (unsigned long long)c.out_cap) ? (int64_t)off : -1;
+    }
+    __syncthreads();
+    const int64_t off = s.offset;
+    if (off < 0) {
+        if (threadIdx.x == 0) s.status = kOutFull;
+    } else {
+        // one wave per 64 output rows: consecutive lanes write
+        // consecutive ints of the rows, columns back in query-vertex
+        // order; e / no by a 16-bit reciprocal (exact for e < 64 no,
+        // no <= 16)
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        const uint32_t inv = (65536u + (uint32_t)no - 1u) / (uint32_t)no;
+        int32_t *arena = off + rows * no <= c.host_cap ? c.host_out : c.out;
+        for (int64_t r0 = (int64_t)wid * 64; r0 < rows; r0 += NT) {
+            const int32_t my = r0 + lane < rows ? idx[r0 + lane] : 0;
+            const int nr = (int)min((int64_t)64, rows - r0);
+            int32_t *dst = arena + off + r0 * no;
+            const int ne = nr * no;
+            for (int e0 = 0; e0 < ne; e0 += 256) {
+                // four gathers in flight per lane; every lane takes part
+                // in the shuffles
+                int32_t v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int e = e0 + q * 64 + lane;
+                    const int r = min(63, (int)(((uint32_t)e * inv) >> 16));
+                    const int32_t src = __shfl(my, r, 64);
+                    v[q] = e < ne ? table[(int64_t)src * k + s.ocol[e - r * no]] : 0;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (e0 + q * 64 + lane < ne) dst[e0 + q * 64 + lane] = v[q];
+            }
+        }
+        if (threadIdx.x == 0) add_bytes(c, 20ull * rows * no);
+    }
+}
+
+// The output of a query with one row: nothing to order (2 us less than the
+// ordering phase takes to find that out).
+__device__ __forceinline__ void one_row_out(Ctx &c) {
+    Smem &s = g_s;
+    ev(c, SGM_EV_SORT);
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        const uint32_t all = (1u << c.Q->n) - 1u;
+        const uint32_t kept = c.Q->proj ? c.Q->proj & all : all;
+        const int no = __popc(kept);
+        unsigned long long off = 0;
+        if (lane == 0) {
+            off = atomicAdd(c.out_used, (unsigned long long)no);
+            const bool fits = off + no <= (unsigned long long)c.out_cap;
+            s.offset = fits ? (int64_t)off : -1;
+            if (!fits) s.status = kOutFull;
+            add_bytes(c, fits ? 20ull * no : 0ull);
+        }
+        off = __shfl(off, 0, 64);
+        if (off + no <= (unsigned long long)c.out_cap && lane < c.Q->n && ((kept >> lane) & 1u)) {
+            int32_t *arena = (int64_t)off + no <= c.host_cap ? c.host_out : c.out;
+            arena[off + __popc(kept & ((1u << lane) - 1u))] = s.table[s.jpos[lane]];
+        }
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void run_query(Ctx &c) {
+    Smem &s = g_s;
     const NQuery &Q = s.query;
     const int n = Q.n;
     if (threadIdx.x < SGM_MAX_QV) {
@@ -2786,6 +3637,7 @@ __device__ __forceinline__ void run_query(Ctx &c) {
         s.listptr = nullptr;
         s.abort_ = 0;
         s.slab_used = 0;
+        s.below_top = -1;
         s.empty = 0;
         s.status = SGM_OK;
         s.reason = 0;
@@ -2804,40 +3656,7 @@ __device__ __forceinline__ void run_query(Ctx &c) {
     __syncthreads();
     mark(c, 0);
     ev(c, SGM_EV_START);
-    // root candidates
-    const int root = Q.root;
-    const int32_t rootq = Q.root_lo < 0 ? -1
-                                        : Q.pred[root].qout | Q.pred[root].qin << 8 | (Q.homo ? 1 << 16 : 0);
-    if (rootq < 0) {
-        if (threadIdx.x == 0) {
-            const int32_t pin = Q.pred[root].pin;
-            if (pin >= 0 && pin < g.V && vpred(g, Q.pred[root], pin)) {
-                c.B(root)[pin >> 6] |= 1ull << (pin & 63);
-                c.L(root)[0] = pin;
-                s.cnt[root] = 1;
-            }
-        }
-        __syncthreads();
-    } else if (Q.n_init == 0) {
-        // a single query vertex: its whole range
-        filter_step(c, NStep{(int8_t)root, 1, -1, 0, 0, 0}, rootq);
-    }
-    ev(c, SGM_EV_ROOT);
-    // explore along the spanning tree, then refinement rounds
-    for (int i = 0; i < Q.n_init && !aborted(c); ++i) {
-        // the first step is the root's
-        filter_step(c, Q.steps[i], i == 0 ? rootq : -1);
-        ev(c, SGM_EV_EXPLORE);
-    }
-    const int rounds = Q.refine_rounds < 0 ? 32 : Q.refine_rounds;
-    for (int r = 0; r < rounds && !aborted(c) && Q.n_ref > 0; ++r) {
-        int removed = 0;
-        for (int i = 0; i < Q.n_ref && !aborted(c); ++i) {
-            removed += filter_step(c, Q.steps[Q.n_init + i]);
-            ev(c, SGM_EV_REFINE);
-        }
-        if (Q.refine_rounds < 0 && removed == 0) break;
-    }
+    filter_phase();
     __syncthreads();
     mark(c, 1);
     if (aborted(c)) {
@@ -2854,254 +3673,7 @@ __device__ __forceinline__ void run_query(Ctx &c) {
             if (s.cnt[u] == 0) s.empty = 1;
         }
     __syncthreads();
-    int64_t rows = 0;
-    int32_t *table = nullptr;
-    if (!s.empty) {
-        for (int u = 0; u < n && !aborted(c); ++u)
-            if (s.cnt[u] > 1) sort_list(c, u);
-        ev(c, SGM_EV_LISTS);
-        if (Q.m == 0) {
-            table = c.L(0);
-            rows = s.cnt[0];
-            if (threadIdx.x == 0) {
-                s.jorder[0] = 0;
-                s.jpos[0] = 0;
-            }
-            __syncthreads();
-        } else if (!aborted(c)) {
-            // candidate edges keyed by each edge's source: totals for the order
-            const uint64_t all = Q.m == 64 ? ~0ull : (1ull << Q.m) - 1ull;
-            const uint64_t one = ec_build_single(c, all, 0);
-            if (one) ev(c, SGM_EV_EDGES);
-            for (int e = 0; e < Q.m && !aborted(c); ++e) {
-                if ((one >> e) & 1ull) continue;
-                ec_build(c, e, Q.esrc[e], Q.edst[e], 0);
-                ev(c, SGM_EV_EDGES);
-            }
-            __syncthreads();
-            bool none = false, single = true;
-            for (int e = 0; e < Q.m; ++e) none |= s.ectot[e] == 0;
-            for (int u = 0; u < n; ++u) single &= s.cnt[u] == 1;
-            int32_t *one_row = nullptr;
-            if (!aborted(c) && !none && single) one_row = (int32_t *)slab_alloc(c, 4ll * n);
-            if (one_row) {
-                // One candidate per query vertex and its pair in every edge
-                // table: those candidates are the only possible row, and a
-                // match exactly when they are distinct. The join binds the
-                // vertices in index order.
-                mark(c, 2);
-                single_row(c, one_row, n, [&](int u) { return u; });
-                if (threadIdx.x < n) {
-                    s.jorder[threadIdx.x] = threadIdx.x;
-                    s.jpos[threadIdx.x] = threadIdx.x;
-                }
-                if (threadIdx.x == 0) {
-                    s.nrows = s.level_rows[n - 1];
-                    add_bytes(c, 8ull * n);
-                }
-                __syncthreads();
-                table = one_row;
-                rows = s.nrows;
-                ev(c, SGM_EV_LEVEL);
-            } else if (!aborted(c) && !none) {
-                if (threadIdx.x == 0)
-                    for (int e = 0; e < Q.m; ++e) s.ecbuilt[e] = s.eckey[e];
-                join_order(c);
-                __syncthreads();
-                ev(c, SGM_EV_ORDER);
-                // edges the join looks up by their destination: rebuild keyed so
-                // The join's leading vertices of one candidate each make one
-                // row (every edge between them holds its pair, or the query
-                // had ended): no level and no re-keyed table is run for them.
-                int pre = 0;
-                while (pre < n && s.cnt[s.jorder[pre]] == 1) ++pre;
-                uint64_t redo = 0;
-                for (int e = 0; e < Q.m; ++e)
-                    if (s.eckey[e] != s.ecbuilt[e] && (s.jpos[Q.esrc[e]] >= pre || s.jpos[Q.edst[e]] >= pre))
-                        redo |= 1ull << e;
-                const uint64_t one2 = aborted(c) ? 0ull : ec_build_single(c, redo, 1);
-                if (one2) ev(c, SGM_EV_EDGES);
-                for (int e = 0; e < Q.m && !aborted(c); ++e)
-                    if (((redo & ~one2) >> e) & 1ull) {
-                        ec_build(c, e, Q.edst[e], Q.esrc[e], 1);
-                        ev(c, SGM_EV_EDGES);
-                    }
-                __syncthreads();
-                // join levels
-                mark(c, 2);
-                table = c.L(s.jorder[0]);
-                rows = s.cnt[s.jorder[0]];
-                if (threadIdx.x == 0) s.level_rows[0] = rows;
-                int k = 1;
-                if (pre > 1 && !aborted(c)) {
-                    int32_t *row = (int32_t *)slab_alloc(c, 4ll * pre);
-                    if (row) {
-                        single_row(c, row, pre, [&](int i) { return s.jorder[i]; });
-                        __syncthreads();
-                        table = row;
-                        rows = s.level_rows[pre - 1];
-                        k = pre;
-                        ev(c, SGM_EV_LEVEL);
-                    }
-                }
-                for (int lv = k - 1; lv < n - 1 && !aborted(c) && rows > 0; ++lv) {
-                    const bool counting = Q.count_only && lv == n - 2;
-                    const int ext = s.lv_ext[lv];
-                    const int p = s.eckey[ext];
-                    const int cp = s.jpos[p];
-                    const int32_t *pk = c.L(p);
-                    const int32_t npk = s.cnt[p];
-                    const int32_t *eoffs = s.ec_offs[ext];
-                    const int32_t *ecnt = s.ec_cnt[ext];
-                    const int32_t *evals = s.ec_vals[ext];
-                    const int nchk = s.lv_nchk[lv];
-                    const int cfirst = s.lv_first[lv];
-                    // output capacity: what is left of the slab
-                    __syncthreads();
-                    const int64_t used0 = (s.slab_used + 255) & ~(int64_t)255;
-                    const int64_t left = c.slab_bytes - used0;
-                    int64_t cap = left / (4 * (k + 1));
-                    if (cap <= 0) {
-                        if (threadIdx.x == 0) s.abort_ = kWhySlab;
-                        __syncthreads();
-                        break;
-                    }
-                    if (threadIdx.x == 0) {
-                        s.ctr = 0;
-                        s.cnt64 = 0ull;
-                    }
-                    __syncthreads();
-                    // the level's pairs bound its rows: a level that could not
-                    // fit even a much larger slot stops here rather than
-                    // after filling this one
-                    int64_t pairs = -1;
-                    const bool may_share = c.job && c.help_items > 0;
-                    // a block of rows whose pairs could reach a shared or a
-                    // host-ordered level (rows times the extension edge's
-                    // candidate edges bound them) counts them here too
-                    if (counting && nchk == 0) {
-                        // counted row by row, shared by rows
-                        pairs = rows;
-                    } else if (rows > NT || rows * s.ectot[ext] >= kJoinSharePairs) {
-                        int64_t mp = 0;
-                        for (int64_t r = threadIdx.x; r < rows; r += NT) {
-                            const int32_t pv = table[r * k + cp];
-                            const int32_t i = lower_bound_i32(pk, 0, npk, pv);
-                            if (i < npk && pk[i] == pv) mp += ecnt[i];
-                        }
-                        block_excl_scan(mp, s.sh, &pairs);
-                        if (!counting && pairs > kPairSlack * cap) {
-                            if (threadIdx.x == 0) {
-                                s.abort_ = kWhySlab;
-                                s.need = used0 + pairs * 4 * (k + 1);
-                            }
-                            __syncthreads();
-                            break;
-                        }
-                    }
-                    // A last level that may reach the size the host orders
-                    // goes to the top of the slab (its pairs bound its rows),
-                    // with room above for the key columns' candidate lists:
-                    // the slot's later queries keep the slab below it.
-                    int32_t *out = nullptr;
-                    if (counting) cap = INT32_MAX;  // no rows are written
-                    if (!counting && lv == n - 2 && c.host_order_rows > 0 && pairs >= c.host_order_rows) {
-                        int64_t lint = 0;
-                        for (int u = 0; u < n; ++u) lint += s.cnt[u];
-                        const int64_t tneed = (pairs * 4 * (k + 1) + 255) & ~(int64_t)255;
-                        const int64_t lneed = (4 * lint + 256 * (n + 1)) & ~(int64_t)255;
-                        const int64_t at = (c.slab_bytes - tneed - lneed) & ~(int64_t)255;
-                        if (at >= kPinFloor(c) && at >= used0) {
-                            out = (int32_t *)(c.slab + at);
-                            cap = pairs;
-                            c.below_top = used0;
-                            __syncthreads();
-                            if (threadIdx.x == 0) s.slab_used = at + pairs * 4 * (k + 1);
-                            __syncthreads();
-                        }
-                    }
-                    if (!out && !counting) out = (int32_t *)slab_alloc(c, cap * 4 * (k + 1));
-                    if (!out && !counting) {
-                        if (threadIdx.x == 0) s.abort_ = kWhySlab;
-                        __syncthreads();
-                        break;
-                    }
-                    // the level's view (parent column, edge tables of its
-                    // extension and check edges, output), the same for the
-                    // owner and for helpers
-                    __syncthreads();
-                    if (threadIdx.x == 0) {
-                        JLevel &L = s.jl;
-                        L.table = table;
-                        L.rows = rows;
-                        L.k = k;
-                        L.cp = cp;
-                        L.pk = pk;
-                        L.npk = npk;
-                        L.eoffs = eoffs;
-                        L.ecnt = ecnt;
-                        L.evals = evals;
-                        L.nchk = nchk;
-                        for (int ci = 0; ci < nchk; ++ci) {
-                            const int e = s.chk[cfirst + ci];
-                            const int kv = s.eckey[e];
-                            L.chk[ci] = JChk{c.L(kv), s.ec_offs[e], s.ec_cnt[e], s.ec_vals[e],
-                                             s.cnt[kv], s.jpos[kv]};
-                        }
-                        L.out = out;
-                        L.cap = cap;
-                        L.count = counting;
-                        // columns the new value may repeat: those of a vertex
-                        // that can hold a candidate of the new one
-                        const int w = s.jorder[lv + 1];
-                        uint32_t cm = 0;
-                        for (int i = 0; i < k && !Q.homo; ++i) {
-                            const int32_t a = Q.pred[s.jorder[i]].label, b = Q.pred[w].label;
-                            if (a < 0 || b < 0 || a == b) cm |= 1u << i;
-                        }
-                        L.cmask = cm;
-                    }
-                    // a level of many pairs is shared (whether or not
-                    // workgroups are idle yet: those that become idle join)
-                    const int64_t nrb = (rows + NT - 1) / NT;
-                    int64_t nsub = 1;
-                    if (may_share && pairs >= kJoinSharePairs)
-                        nsub = min((int64_t)kJoinMaxSub,
-                                   max((int64_t)1, (pairs + nrb * kJoinChunkPairs - 1) /
-                                                       (nrb * kJoinChunkPairs)));
-                    // (a counting level without check edges: blocks of rows)
-                    if (counting && nchk == 0) nsub = 1;
-                    const bool share =
-                        may_share && nrb * nsub <= kMaxChunks &&
-                        (counting && nchk == 0 ? nrb >= kCountShareBlocks : pairs >= kJoinSharePairs);
-                    if (threadIdx.x == 0) s.jl.nsub = (int32_t)nsub;
-                    __syncthreads();
-                    uint64_t jb = 0;  // algorithmic bytes of this thread's rows and pairs
-                    if (share) {
-                        shared_join(c, (int32_t)(nrb * nsub), jb);
-                    } else {
-                        for (int64_t rbase = 0; rbase < rows && !aborted(c); rbase += NT)
-                            join_rows<false>(c, s.jl, rbase, min(rows, rbase + NT), 0, 1,
-                                             nullptr, nullptr, jb);
-                    }
-                    add_bytes(c, jb);
-                    __syncthreads();
-                    rows = counting ? (int64_t)s.cnt64 : (int64_t)s.ctr;
-                    if (threadIdx.x == 0) s.level_rows[lv + 1] = rows;
-                    // give back the unused part of the table allocation
-                    __syncthreads();
-                    if (threadIdx.x == 0 && !s.abort_ && !counting)
-                        s.slab_used = (int64_t)((char *)out - c.slab) + rows * 4 * (k + 1);
-                    __syncthreads();
-                    ev(c, SGM_EV_LEVEL);
-                    table = out;
-                    ++k;
-                }
-            } else if (none) {
-                rows = 0;
-            }
-        }
-    }
+    if (!s.empty) match_phase();
     __syncthreads();
     mark(c, 3);
     if (aborted(c)) {
@@ -3112,295 +3684,29 @@ __device__ __forceinline__ void run_query(Ctx &c) {
         }
         return;
     }
-    if (threadIdx.x == 0) s.nrows = rows;
     // a count-only query is done (its last level wrote no table)
-    if (rows > 0 && !Q.count_only) {
-        // ordering: key = concatenated candidate ranks in column order 0..n-1;
-        // a projection (thesis Ch. 3, Sec. "GpSense") keys and keeps only
-        // its columns
+    if (s.nrows > 0 && !Q.count_only) {
+        if (s.nrows == 1 && (c.host_order_rows <= 0 || c.host_order_rows > 1)) one_row_out(c);
+        else order_phase();
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int tb = 0, no = 0, depth = 0;
-            for (int u = 0; u < n; ++u) {
-                const bool kept = Q.proj == 0u || ((Q.proj >> u) & 1u);
-                int b = 0;
-                while (kept && (1ll << b) < s.cnt[u]) ++b;
-                s.bitsn[u] = b;
-                tb += b;
-                if (kept) s.ocol[no++] = s.jpos[u];
-                // a lower bound over m entries ends after bit_length(m) halvings
-                if (b > 0) depth = max(depth, 32 - __clz(s.cnt[u]));
-            }
-            s.ctr = tb;
-            s.nout = no;
-            s.kdepth = depth;
-        }
-        __syncthreads();
-        if (s.ctr > 64 && rows > 1) {
-            clear_slot(c, false);
-            if (threadIdx.x == 0) {
-                s.status = kNeedWide;
-                s.reason = kWhyKey;
-            }
-            return;
-        }
-        const int tb = s.ctr;
-        const int k = n;
-        const int no = s.nout;
-        int32_t *idx;
-        const uint64_t *skeys = nullptr;  // the sorted keys (rows > 1)
-        // A large final table in the slab, with room below it for the slot's
-        // later queries: the key columns' sorted candidate lists go beside
-        // it and the host orders it (and collapses a projection) with
-        // whole-GPU kernels after the launch; one workgroup would spend
-        // milliseconds on the keys, the passes and the gather.
-        int64_t toff = (int64_t)((const char *)table - c.slab);
-        if (c.host_order_rows > 0 && rows >= c.host_order_rows && toff >= 0 &&
-            toff < c.slab_bytes) {
-            int64_t lint = 0;
-            for (int u = 0; u < n; ++u)
-                if (s.bitsn[u] > 0) lint += s.cnt[u];
-            int32_t *lst = nullptr;
-            const int64_t tbytes = (rows * k * 4 + 255) & ~(int64_t)255;
-            const int64_t top = ((c.slab_bytes - 4 * lint) & ~(int64_t)255) - tbytes;
-            if (toff >= kPinFloor(c)) {
-                lst = (int32_t *)slab_alloc(c, 4 * lint);
-            } else if (top >= kPinFloor(c) && top > toff) {
-                // too low in the slab to keep for the host: move it up to
-                // the top, lists above it; overlapping, so the chunks go
-                // from the end (every read of a chunk before its writes)
-                int32_t *dst = (int32_t *)(c.slab + top);
-                const int64_t nint = rows * k;
-                for (int64_t end = nint; end > 0; end -= 4 * NT) {
-                    const int64_t beg = end - 4 * NT > 0 ? end - 4 * NT : 0;
-                    int32_t v[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int64_t i = beg + q * NT + threadIdx.x;
-                        v[q] = i < end ? table[i] : 0;
-                    }
-                    __syncthreads();
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int64_t i = beg + q * NT + threadIdx.x;
-                        if (i < end) dst[i] = v[q];
-                    }
-                    __syncthreads();
-                }
-                if (threadIdx.x == 0) add_bytes(c, 8ull * nint);
-                table = dst;
-                toff = top;
-                lst = (int32_t *)(c.slab + top + tbytes);
-            }
-            if (lst) {
-                int64_t o = 0;
-                for (int u = 0; u < n; ++u) {
-                    if (s.bitsn[u] == 0) continue;
-                    const int32_t *src = c.L(u);
-                    for (int32_t i = threadIdx.x; i < s.cnt[u]; i += NT) lst[o + i] = src[i];
-                    o += s.cnt[u];
-                }
-                __syncthreads();
-                if (threadIdx.x == 0) {
-                    s.hostord = 1;
-                    s.keybits = tb;
-                    s.pin_off = toff;
-                    s.tableptr = table;
-                    s.listptr = lst;
-                    add_bytes(c, 8ull * lint);
-                }
-                __syncthreads();
-                ev(c, SGM_EV_SORT);
-                ev(c, SGM_EV_OUTPUT);
-                clear_slot(c, false);
-                mark(c, 4);
-                return;
-            }
-        }
-        if (rows > 1) stage_key_lists(c);
-        if (c.below_top >= 0 && rows > kRowSortCap) {
-            // the last level sits at the slab's top but stayed on this
-            // workgroup: its sort buffers go into the slab below it
-            __syncthreads();
-            if (threadIdx.x == 0) s.slab_used = c.below_top;
-            __syncthreads();
-            c.slab_bytes = toff;
-        }
-        if (rows == 1) {
-            int32_t *ix = (int32_t *)c.dyn;
-            if (threadIdx.x == 0) ix[0] = 0;
-            __syncthreads();
-            idx = ix;
-        } else if (rows <= kRowSortCap) {
-            // bitonic network in LDS
-            uint64_t *keys = (uint64_t *)c.dyn;
-            int32_t *ix = (int32_t *)(c.dyn + sizeof(uint64_t) * kRowSortCap);
-            int32_t N = 1;
-            while (N < rows) N <<= 1;
-            for (int32_t r = threadIdx.x; r < N; r += NT) {
-                keys[r] = r < rows ? row_key(c, table + (int64_t)r * k) : ~0ull;
-                ix[r] = r;
-            }
-            __syncthreads();
-            for (int32_t size = 2; size <= N; size <<= 1) {
-                for (int32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                    for (int32_t i = threadIdx.x; i < N / 2; i += NT) {
-                        const int32_t lo = 2 * i - (i & (stride - 1));
-                        const int32_t hi = lo + stride;
-                        const bool up = (lo & size) == 0;
-                        // ties (a key of all ones against the padding)
-                        // by row index, so padding stays last
-                        const uint64_t x = keys[lo], y = keys[hi];
-                        const bool gt = x > y || (x == y && ix[lo] > ix[hi]);
-                        if (gt == up) {
-                            keys[lo] = y;
-                            keys[hi] = x;
-                            const int32_t t = ix[lo];
-                            ix[lo] = ix[hi];
-                            ix[hi] = t;
-                        }
-                    }
-                    __syncthreads();
-                }
-            }
-            idx = ix;
-            skeys = keys;
-        } else {
-            // LSD radix on (key, row) pairs in the slab, 8 bits per pass
-            uint64_t *ka = (uint64_t *)slab_alloc(c, 8 * rows);
-            uint64_t *kb = (uint64_t *)slab_alloc(c, 8 * rows);
-            int32_t *ia = (int32_t *)slab_alloc(c, 4 * rows);
-            int32_t *ib = (int32_t *)slab_alloc(c, 4 * rows);
-            if (!ka || !kb || !ia || !ib) {
-                clear_slot(c, false);
-                if (threadIdx.x == 0) {
-                    s.status = kNeedWide;
-                    s.reason = kWhySlab;
-                }
-                return;
-            }
-            if (threadIdx.x == 0) s.unsorted = 0;
-            for (int64_t r = threadIdx.x; r < rows; r += NT) {
-                ka[r] = row_key(c, table + r * k);
-                ia[r] = (int32_t)r;
-            }
-            __syncthreads();
-            // a join that bound the key columns in key order has left the
-            // rows in order already: then no pass is needed
-            bool down = false;
-            for (int64_t r = threadIdx.x; r + 1 < rows; r += NT) down |= ka[r] > ka[r + 1];
-            if (down) s.unsorted = 1;
-            __syncthreads();
-            if (threadIdx.x == 0) add_bytes(c, 8ull * rows);
-            const bool passes = s.unsorted != 0;
-            for (int sh = 0; passes && sh < tb; sh += 8) {
-                wg_radix_pass(c, ka, ia, kb, ib, rows, sh);
-                uint64_t *tk = ka;
-                ka = kb;
-                kb = tk;
-                int32_t *ti = ia;
-                ia = ib;
-                ib = ti;
-            }
-            if (threadIdx.x == 0 && passes) add_bytes(c, 24ull * rows * ((tb + 7) / 8));
-            idx = ia;
-            skeys = ka;
-        }
-        if (Q.proj && rows > 1) {
-            // equal projected rows now have equal, adjacent keys: keep the
-            // first row of each run (in-place compaction of the order)
-            int64_t kept = 0;
-            for (int64_t base = 0; base < rows; base += NT) {
-                const int64_t i = base + threadIdx.x;
-                const bool head = i < rows && (i == 0 || skeys[i] != skeys[i - 1]);
-                const int32_t v = i < rows ? idx[i] : 0;
-                int64_t tot;
-                const int64_t ex = block_excl_scan((int64_t)(head ? 1 : 0), s.sh, &tot);
-                if (head) idx[kept + ex] = v;
-                kept += tot;
-                __syncthreads();
-            }
-            if (threadIdx.x == 0) add_bytes(c, 16ull * rows);
-            rows = kept;
-            if (threadIdx.x == 0) s.nrows = rows;
-            __syncthreads();
-        }
-        ev(c, SGM_EV_SORT);
-        if (threadIdx.x == 0) {
-            const unsigned long long need = (unsigned long long)rows * no;
-            const unsigned long long off = atomicAdd(c.out_used, need);
-            s.offset = (off + need <= (unsigned long long)c.out_cap) ? (int64_t)off : -1;
-        }
-        __syncthreads();
-        const int64_t off = s.offset;
-        if (off < 0) {
-            if (threadIdx.x == 0) s.status = kOutFull;
-        } else {
-            // one wave per 64 output rows: consecutive lanes write
-            // consecutive ints of the rows, columns back in query-vertex
-            // order; e / no by a 16-bit reciprocal (exact for e < 64 no,
-            // no <= 16)
-            const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-            const uint32_t inv = (65536u + (uint32_t)no - 1u) / (uint32_t)no;
-            int32_t *arena = off + rows * no <= c.host_cap ? c.host_out : c.out;
-            for (int64_t r0 = (int64_t)wid * 64; r0 < rows; r0 += NT) {
-                const int32_t my = r0 + lane < rows ? idx[r0 + lane] : 0;
-                const int nr = (int)min((int64_t)64, rows - r0);
-                int32_t *dst = arena + off + r0 * no;
-                const int ne = nr * no;
-                for (int e0 = 0; e0 < ne; e0 += 256) {
-                    // four gathers in flight per lane; every lane takes part
-                    // in the shuffles
-                    int32_t v[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int e = e0 + q * 64 + lane;
-                        const int r = min(63, (int)(((uint32_t)e * inv) >> 16));
-                        const int32_t src = __shfl(my, r, 64);
-                        v[q] = e < ne ? table[(int64_t)src * k + s.ocol[e - r * no]] : 0;
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        if (e0 + q * 64 + lane < ne) dst[e0 + q * 64 + lane] = v[q];
-                }
-            }
-            if (threadIdx.x == 0) add_bytes(c, 20ull * rows * no);
-        }
     }
-    ev(c, SGM_EV_OUTPUT);
+    const bool ended = s.status != kNeedWide;
+    if (ended) ev(c, SGM_EV_OUTPUT);
     clear_slot(c, false);
-    mark(c, 4);
-}
-
-// at least 4 waves per SIMD (registers <= 128): two workgroups per CU
-// slab_cap: the slot's slab below tables its earlier queries of the launch
-// left for the host to order (the whole slab otherwise)
-__device__ __forceinline__ Ctx slot_ctx(const NArgs &a, Smem &s, unsigned char *dyn, int slot,
-                                        int32_t q, int64_t slab_cap) {
-    const int32_t nwords = a.g.nwords;
-    uint64_t *bits = a.bits + (int64_t)slot * (SGM_MAX_QV + 1) * nwords;
-    int32_t *lists = a.lists + (int64_t)slot * SGM_MAX_QV * a.lcap;
-    char *slab = a.slab + (int64_t)slot * a.slab_bytes;
-    return Ctx{a.g,  a.lcap, slab_cap, a.out, a.out_cap, a.out_used, a.host_out, a.host_cap, &s.query, &s,
-               bits, bits + (int64_t)SGM_MAX_QV * nwords, lists, slab, dyn,
-               a.trace ? a.trace + (int64_t)q * SGM_TRACE_CAP : nullptr, a.group_lanes,
-               a.wg_rows, a.join_policy,
-               // while filtering the slab holds the long-row overflow list in
-               // [0, 4 lcap) bytes and the marks in [4 lcap, 8 lcap)
-               (int32_t *)(slab + 4 * (int64_t)a.lcap), a.board ? a.board + slot : nullptr, a.hctr,
-               a.help_items, q, a.nslot, a.ngrid, a.help_wait, a.host_order_rows, -1};
+    if (ended) mark(c, 4);
 }
 
 // Chunks of the step posted on board entry e, starting with chunk ch, until
 // the step has none left; then the chunks are reported done (one release
 // fence for all of them).
-__device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char *dyn, int e,
-                                          int32_t ch) {
+__device__ __forceinline__ void help_step(const NArgs &a, int e, int32_t ch) {
+    Smem &s = g_s;
     HelpJob *j = a.board + e;
     // the parameters stay fixed while this workgroup holds unreported chunks
     const NStep st = j->st;
     const int32_t K = j->chunk, G = j->G, n_items = j->n_items, ncount = j->ncount;
-    const bool revd = j->revd != 0;
+    int32_t *def = j->defer ? (int32_t *)(a.slab + (int64_t)e * a.slab_bytes + 8 * (int64_t)a.lcap) : nullptr;
+    const bool nodrop = j->nodrop != 0;
     const int kind = j->kind;
     const int4 *seg = j->seg;
     const int32_t *hul = j->ul;
@@ -3415,20 +3721,20 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
         for (int i = threadIdx.x; i < (int)(sizeof(JLevel) / 8); i += NT) dst[i] = src[i];
     }
     __syncthreads();
-    Ctx c = slot_ctx(a, s, dyn, e, j->q, a.slab_bytes);
+    Ctx c = slot_ctx(a, e, j->q, a.slab_bytes);
     c.trace = nullptr;
     uint64_t fb = 0;
     int32_t n = 0;
     while (ch >= 0) {
         if (kind == 0) {
-            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, s.nbl, ncount, hul, c.B(st.u), revd, ch * K,
+            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, s.nbl, ncount, hul, nodrop ? nullptr : c.B(st.u), ch * K,
                           min(n_items, ch * K + K), fb, nodefer);
         } else if (kind == 1) {
             push_segment(c, BoardCtr{j}, s.nbl, seg[ch], fb);
         } else if (kind == 3) {
             ec_chunk(c, j->ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
         } else if (kind == 4) {
-            item_wg_k(c, BoardCtr{j}, st, s.nbl, ncount, hul[ch], c.B(st.u), fb);
+            item_wg_k(c, BoardCtr{j}, st, s.nbl, ncount, hul[ch], nodrop ? nullptr : c.B(st.u), fb, def);
         } else {
             join_chunk(c, s.jl, ch, &j->jrows, &j->abort_, fb);
         }
@@ -3452,9 +3758,15 @@ __device__ __forceinline__ void help_step(const NArgs &a, Smem &s, unsigned char
     }
 }
 
+__device__ __attribute__((noinline)) void help_step_far(int e, int32_t ch) {
+    const NArgs a = own_args();
+    help_step(a, __builtin_amdgcn_readfirstlane(e), __builtin_amdgcn_readfirstlane(ch));
+}
+
 // Helpers: claim chunks of posted steps until every slot workgroup has run
 // out of queries (or after kHelpIdle empty polls in a row).
-__device__ __forceinline__ void help_loop(const NArgs &a, Smem &s, unsigned char *dyn) {
+__device__ __forceinline__ void help_loop(const NArgs &a) {
+    Smem &s = g_s;
     const int lane = threadIdx.x & 63;
     int64_t idle = 0;
     for (;;) {
@@ -3516,7 +3828,7 @@ __device__ __forceinline__ void help_loop(const NArgs &a, Smem &s, unsigned char
             continue;
         }
         idle = 0;
-        help_step(a, s, dyn, e, ch);
+        help_step_far(e, ch);
     }
 }
 
@@ -3533,11 +3845,12 @@ __device__ __forceinline__ void leave(const NArgs &a) {
 }
 
 __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
-    __shared__ Smem s;
-    extern __shared__ unsigned char dyn[];
+    Smem &s = g_s;
+    if (threadIdx.x == 0) g_args = a;
+    __syncthreads();
     const bool help = a.help_items > 0 && a.board != nullptr;
     if ((int)blockIdx.x >= a.nslot) {
-        if (help) help_loop(a, s, dyn);
+        if (help) help_loop(a);
         leave(a);
         return;
     }
@@ -3591,7 +3904,8 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
             }
             continue;
         }
-        Ctx c = slot_ctx(a, s, dyn, blockIdx.x, q, slab_cap);
+        if (threadIdx.x == 0) s.slab_cap = slab_cap;
+        Ctx c = slot_ctx(a, blockIdx.x, q, slab_cap);
         static_assert(sizeof(NQuery) % 4 == 0, "staged as ints");
         for (int i = threadIdx.x; i < (int)(sizeof(NQuery) / 4); i += NT)
             ((int32_t *)&s.query)[i] = ((const int32_t *)&Qd)[i];
@@ -3601,7 +3915,7 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
         __syncthreads();
         if (s.hostord) slab_cap = s.pin_off;  // keep that table until the launch ends
         // the result is put together in LDS and leaves in whole lines
-        NResult &L = *(NResult *)dyn;
+        NResult &L = *(NResult *)g_dyn;
         const int t = threadIdx.x;
         if (t < SGM_MAX_QV) {
             L.cand[t] = t < Q.n ? s.cand[t] : 0;
@@ -3643,7 +3957,7 @@ __global__ __launch_bounds__(NT, 4) void k_narrow(NArgs a) {
     }
     if (help) {
         if (threadIdx.x == 0) atomicAdd(&a.hctr[1], 1);
-        help_loop(a, s, dyn);
+        help_loop(a);
     }
     leave(a);
 }
@@ -3656,10 +3970,8 @@ __global__ void k_reset(unsigned long long *ctr) {
 
 }  // namespace
 
-size_t narrow_lds_bytes() { return kDynLds; }
-
 void launch_narrow(hipStream_t s, const NArgs &a, int grid) {
-    hipLaunchKernelGGL(k_narrow, dim3(grid), dim3(NT), kDynLds, s, a);
+    hipLaunchKernelGGL(k_narrow, dim3(grid), dim3(NT), 0, s, a);
 }
 
 void launch_reset(hipStream_t s, unsigned long long *ctr) {

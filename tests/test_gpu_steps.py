@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import paper_1807_08804_amd as P
-from tests.micro import MicroGraph, random_graph, random_query
+from tests.micro import MicroGraph, MicroQuery, random_graph, random_query
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,47 @@ def test_counts_without_rows(V, E, n_types, p_any):
             print("case: query", i, "rows", want, flush=True)
             assert g.match_query(q, count_only=True) == want
         assert g.match_batch(qs, count_only=True) == wants
+
+
+def hub_graph(hubs, row, V=20000):
+    """`hubs` vertices of type 1, each with edges to `row` of the V vertices
+    of types 0 and 2 (relation 0, every 40th 1) and back from a twentieth;
+    the vertices among themselves carry sparse relation-1 edges."""
+    rng = np.random.default_rng(hubs + row)
+    vt = np.concatenate([np.where(rng.random(V) < 0.02, 2, 0), np.full(hubs, 1)])
+    e = []
+    for h in range(V, V + hubs):
+        to = rng.permutation(V)[:row]
+        e.append((np.full(row, h), to, np.arange(row) % 40 == 0))
+        e.append((to[::20], np.full(len(to[::20]), h), np.ones(len(to[::20]))))
+    a = rng.integers(0, V, 3000)
+    e.append((a, rng.integers(0, V, 3000), np.ones(3000)))
+    src, dst, rel = (np.concatenate(x).astype(np.int32) for x in zip(*e))
+    return MicroGraph(V + hubs, src, dst, rel, vt)
+
+
+@pytest.mark.parametrize("hubs,row", [(1, 16384), (4, 16383), (5, 16384), (8, 300), (9, 300),
+                                      (8, 16385), (9, 2048), (40, 1200)])
+def test_hub_candidates_against_many(hubs, row):
+    """Few candidates with long rows beside neighbours with thousands: tests
+    checked from the few's side, rows at the limits of the typed hub index
+    and of the wave and workgroup tiers, edge tables of up to eight keys built
+    together and of nine alone, values looked up one by one or scanned."""
+    mg = hub_graph(hubs, row)
+    og = oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    hub = mg.V - 1
+    qs = [MicroQuery(3, [1, 0, 2], [-1, -1, -1], [0, 1], [1, 2], [0, 1]),
+          MicroQuery(3, [1, 0, 2], [-1, -1, -1], [1, 1, 0], [0, 2, 2], [1, 1, -1]),
+          MicroQuery(3, [1, 0, 1], [hub, -1, -1], [0, 1, 2], [1, 2, 1], [0, 1, 0]),
+          MicroQuery(4, [0, 1, -1, 2], [-1, hub, -1, -1], [1, 0, 2, 1], [0, 2, 3, 3], [1, 1, 1, -1])]
+    gs = [P.Graph(rp, col, rel, typ, path=p) for p in (P.SGM_PATH_NARROW, P.SGM_PATH_WIDE)]
+    for tune in (dict(), dict(help_items=64), dict(help_items=0)):
+        gs[0].set_tuning(**tune)
+        for i, q in enumerate(qs):
+            print("case: query", i, tune, flush=True)
+            (rn, sn), (rw, sw) = [g.match_query(q, with_stats=True) for g in gs]
+            assert np.array_equal(rn, rw) and np.array_equal(rn, og.match_query(q))
+            assert sn["cand"] == sw["cand"]
+            if min(sn["cand"]) > 0:
+                assert sn["ec"] == sw["ec"]
