@@ -863,7 +863,7 @@ struct Query {
         int64_t gsz = (items + (kBlock / 16) - 1) / (kBlock / 16);
         return (int)std::max<int64_t>(1, std::min<int64_t>(gsz, 2048));
     }
-    int grid_big() const { return std::max(1, std::min(g->n_big, 1024)); }
+    int grid_big() const { return std::max(1, std::min(g->n_big, 512)); }
 
     int filter_launch(int u, const NbrDesc *dev_desc, int n_nbr, bool push, int64_t items_bound,
                       unsigned long long *removed, int kid) {

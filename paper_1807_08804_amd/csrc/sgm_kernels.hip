@@ -67,8 +67,10 @@ __global__ void k_check_pin(DevGraph g, VPred p, uint64_t *bits) {
 // ---------------------------------------------------------------------------
 
 // One workgroup (1024 threads) per bitmap; blockIdx.x selects the bitmap.
-// Words are taken 1024 at a time (coalesced); a block scan of the word
-// popcounts gives each word's output offset.
+// A round takes four consecutive words per thread; a block scan of their
+// popcounts gives each thread's output offset.
+constexpr int kCollectWords = 4;
+
 __global__ __launch_bounds__(1024) void k_collect(const uint64_t *bits_base, int64_t bits_stride,
                                                   int32_t nwords, int32_t *list_base,
                                                   int64_t list_stride, int32_t *count_base,
@@ -81,10 +83,15 @@ __global__ __launch_bounds__(1024) void k_collect(const uint64_t *bits_base, int
     __shared__ int32_t wsum[16];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     int32_t carry = 0;
-    for (int32_t base = 0; base < nwords; base += 1024) {
-        const int32_t w = base + tid;
-        uint64_t word = (w < nwords) ? bits[w] : 0ull;
-        const int32_t c = __popcll(word);
+    for (int32_t base = 0; base < nwords; base += 1024 * kCollectWords) {
+        const int32_t w0 = base + tid * kCollectWords;
+        uint64_t word[kCollectWords];
+        int32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < kCollectWords; ++q) {
+            word[q] = w0 + q < nwords ? bits[w0 + q] : 0ull;
+            c += __popcll(word[q]);
+        }
         const int32_t inc = wave_incl_scan32(c, lane);
         if (lane == 63) wsum[wid] = inc;
         __syncthreads();
@@ -95,14 +102,14 @@ __global__ __launch_bounds__(1024) void k_collect(const uint64_t *bits_base, int
             if (i < wid) wo += s;
             tot += s;
         }
-        const int32_t excl = carry + wo + inc - c;
-        if (w < nwords) {
-            prefix[w] = excl;
-            int32_t pos = excl;
-            while (word) {
-                const int b = __builtin_ctzll(word);
-                list[pos++] = w * 64 + b;
-                word &= word - 1ull;
+        int32_t pos = carry + wo + inc - c;
+#pragma unroll
+        for (int q = 0; q < kCollectWords; ++q) {
+            if (w0 + q < nwords) prefix[w0 + q] = pos;
+            while (word[q]) {
+                const int b = __builtin_ctzll(word[q]);
+                list[pos++] = (w0 + q) * 64 + b;
+                word[q] &= word[q] - 1ull;
             }
         }
         carry += tot;
@@ -185,8 +192,15 @@ __global__ __launch_bounds__(kBlock) void k_filter_small(FilterArgs a) {
     }
 }
 
-// One workgroup per high-degree candidate.
-__global__ __launch_bounds__(kBlock) void k_filter_big(FilterArgs a) {
+// Rounds of the workgroups that take a long row whole: 1024 threads, eight
+// entries each in flight (a row of 340,000 entries: 42 rounds and their
+// barriers instead of 1,300 of one entry for each of 256 threads).
+constexpr int kBigBlock = 1024;
+constexpr int kBigItems = 8;
+
+// One workgroup per high-degree candidate. A test starts with a round of one
+// entry per thread: most rows have a match that early.
+__global__ __launch_bounds__(kBigBlock) void k_filter_big(FilterArgs a) {
     const DevGraph &g = a.g;
     const int32_t n = *a.big_count;
     for (int32_t it = blockIdx.x; it < n; it += gridDim.x) {
@@ -198,15 +212,16 @@ __global__ __launch_bounds__(kBlock) void k_filter_big(FilterArgs a) {
             const NbrDesc d = a.nbr[j];
             const int2 *adj = d.dir ? g.in_adj : g.out_adj;
             const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            bool found = false;
-            for (int32_t base = beg; base < end; base += blockDim.x) {
-                const int32_t i = base + threadIdx.x;
+            const int32_t i0 = beg + threadIdx.x;
+            bool found = __syncthreads_or(i0 < end && nbr_ok(g, d, adj[i0]));
+            for (int32_t base = beg + kBigBlock; base < end && !found; base += kBigBlock * kBigItems) {
                 bool hit = false;
-                if (i < end) hit = nbr_ok(g, d, adj[i]);
-                if (__syncthreads_or(hit)) {
-                    found = true;
-                    break;
+#pragma unroll
+                for (int q = 0; q < kBigItems; ++q) {
+                    const int32_t i = base + q * kBigBlock + (int32_t)threadIdx.x;
+                    if (i < end) hit |= nbr_ok(g, d, adj[i]);
                 }
+                found = __syncthreads_or(hit);
             }
             alive = found;
         }
@@ -223,9 +238,17 @@ __global__ __launch_bounds__(kBlock) void k_filter_big(FilterArgs a) {
             if (!d.push) continue;
             const int2 *adj = d.dir ? g.in_adj : g.out_adj;
             const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            for (int32_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
-                const int2 e = adj[i];
-                if (nbr_ok(g, d, e)) bit_set_atomic(d.push_bits, e.x);
+            for (int32_t base = beg; base < end; base += kBigBlock * kBigItems) {
+                int2 e[kBigItems];
+#pragma unroll
+                for (int q = 0; q < kBigItems; ++q) {
+                    const int32_t i = base + q * kBigBlock + (int32_t)threadIdx.x;
+                    e[q] = adj[i < end ? i : beg];
+                }
+#pragma unroll
+                for (int q = 0; q < kBigItems; ++q)
+                    if (base + q * kBigBlock + (int32_t)threadIdx.x < end && nbr_ok(g, d, e[q]))
+                        bit_set_atomic(d.push_bits, e[q].x);
             }
         }
     }
@@ -295,9 +318,11 @@ __global__ __launch_bounds__(kBlock) void k_ec_small(DevGraph g, ECDesc d) {
     }
 }
 
+// One workgroup per key with a long row, in rounds as above; each wave takes
+// a contiguous stretch of a round, so that its values stay in row order.
 template <bool WRITE>
-__global__ __launch_bounds__(kBlock) void k_ec_big(DevGraph g, ECDesc d) {
-    __shared__ int32_t wcnt[kBlock / 64];
+__global__ __launch_bounds__(kBigBlock) void k_ec_big(DevGraph g, ECDesc d) {
+    __shared__ int32_t wcnt[2][kBigBlock / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int32_t n = *d.big_count;
     const int32_t *off = d.dir ? g.in_off : g.out_off;
@@ -307,21 +332,40 @@ __global__ __launch_bounds__(kBlock) void k_ec_big(DevGraph g, ECDesc d) {
         const int32_t key = d.keys[it];
         const int32_t beg = off[key], end = off[key + 1];
         int32_t c = WRITE ? d.offs[it] : 0;
-        for (int32_t base = beg; base < end; base += blockDim.x) {
-            const int32_t i = base + threadIdx.x;
-            const bool hit = i < end && ec_hit(g, d, adj, beg, i, key);
-            const uint64_t b = __ballot(hit);
-            if (lane == 0) wcnt[wid] = __popcll(b);
+        int par = 0;  // the counts alternate: one barrier per round
+        for (int32_t base = beg; base < end; base += kBigBlock * kBigItems, par ^= 1) {
+            uint64_t b[kBigItems];
+            int32_t x[kBigItems];
+            int32_t mine = 0;
+            const int32_t at = base + wid * (64 * kBigItems) + lane;
+#pragma unroll
+            for (int q = 0; q < kBigItems; ++q) {
+                const int32_t i = at + q * 64;
+                const bool hit = i < end && ec_hit(g, d, adj, beg, i, key);
+                x[q] = WRITE && hit ? adj[i].x : 0;
+                b[q] = __ballot(hit);
+                mine += __popcll(b[q]);
+            }
+            if (lane == 0) wcnt[par][wid] = mine;
             __syncthreads();
             int32_t wo = 0, tot = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-                if (w < wid) wo += wcnt[w];
-                tot += wcnt[w];
+#pragma unroll
+            for (int w = 0; w < kBigBlock / 64; ++w) {
+                const int32_t v = wcnt[par][w];
+                if (w < wid) wo += v;
+                tot += v;
             }
-            if (WRITE && hit) d.vals[c + wo + __popcll(b & lanemask_lt(lane))] = adj[i].x;
+            if (WRITE) {
+                int32_t o = c + wo;
+#pragma unroll
+                for (int q = 0; q < kBigItems; ++q) {
+                    if ((b[q] >> lane) & 1ull) d.vals[o + __popcll(b[q] & lanemask_lt(lane))] = x[q];
+                    o += __popcll(b[q]);
+                }
+            }
             c += tot;
-            __syncthreads();
         }
+        __syncthreads();
         if (!WRITE && threadIdx.x == 0) {
             d.cnt[it] = c;
             if (c) atomicAdd(d.total, (unsigned long long)c);
@@ -415,20 +459,47 @@ __global__ __launch_bounds__(kBlock) void k_scan_partials(int64_t *part, int64_t
     if (threadIdx.x == 0) part[nb] = carry;
 }
 
+// The scan of kItems consecutive values per thread: one block scan for all of
+// them (a scan per value and its two barriers cost 6.4 us in a grid of any
+// size, of which 4 were these).
+template <int kItems>
+__device__ __forceinline__ int64_t scan_run(const int64_t *in, int64_t n, int64_t base,
+                                            int64_t carry, int64_t *sh, int64_t *out) {
+    const int64_t i0 = base + (int64_t)threadIdx.x * kItems;
+    int64_t x[kItems], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        x[k] = i0 + k < n ? in[i0 + k] : 0;
+        sum += x[k];
+    }
+    int64_t tot;
+    int64_t run = carry + block_excl_scan(sum, sh, &tot);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        if (i0 + k < n) out[i0 + k] = run;
+        run += x[k];
+    }
+    return carry + tot;
+}
+
 __global__ __launch_bounds__(kBlock) void k_scan_down(const int64_t *in, int64_t n,
                                                       const int64_t *part, int64_t *out) {
     __shared__ int64_t sh[kBlock / 64 + 1];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int64_t carry = part[blockIdx.x];
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = base + (int64_t)k * kBlock + threadIdx.x;
-        const int64_t x = i < n ? in[i] : 0;
-        int64_t tot;
-        const int64_t ex = block_excl_scan(x, sh, &tot);
-        if (i < n) out[i] = carry + ex;
-        carry += tot;
-    }
+    scan_run<kScanItems>(in, n, (int64_t)blockIdx.x * kScanTile, part[blockIdx.x], sh, out);
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = part[gridDim.x];
+}
+
+// A whole scan in one workgroup, for inputs of a few of its rounds: a launch
+// instead of three, of which each costs more than a round's 3 us. (The digit
+// counts of a sort of 20,000 rows, 2,560 of them: 12.2 -> 3.6 us.)
+constexpr int64_t kScanOne = 4 * 1024 * kScanItems;
+
+__global__ __launch_bounds__(1024) void k_scan_one(const int64_t *in, int64_t n, int64_t *out) {
+    __shared__ int64_t sh[1024 / 64 + 1];
+    int64_t carry = 0;
+    for (int64_t base = 0; base < n; base += 1024 * kScanItems)
+        carry = scan_run<kScanItems>(in, n, base, carry, sh, out);
+    if (threadIdx.x == 0) out[n] = carry;
 }
 
 // ---------------------------------------------------------------------------
@@ -771,7 +842,7 @@ void launch_collect_multi(hipStream_t s, const DevGraph &g, const uint64_t *bits
 
 void launch_filter(hipStream_t s, const FilterArgs &a, int grid_small, int grid_big) {
     hipLaunchKernelGGL(k_filter_small<16>, dim3(grid_small), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_filter_big, dim3(grid_big), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_filter_big, dim3(grid_big), dim3(kBigBlock), 0, s, a);
 }
 
 void launch_and(hipStream_t s, uint64_t *dst, const uint64_t *src, int32_t nwords,
@@ -783,13 +854,13 @@ void launch_and(hipStream_t s, uint64_t *dst, const uint64_t *src, int32_t nword
 void launch_ec_count(hipStream_t s, const DevGraph &g, const ECDesc &d, int grid_small,
                      int grid_big) {
     hipLaunchKernelGGL((k_ec_small<16, false>), dim3(grid_small), dim3(kBlock), 0, s, g, d);
-    hipLaunchKernelGGL((k_ec_big<false>), dim3(grid_big), dim3(kBlock), 0, s, g, d);
+    hipLaunchKernelGGL((k_ec_big<false>), dim3(grid_big), dim3(kBigBlock), 0, s, g, d);
 }
 
 void launch_ec_write(hipStream_t s, const DevGraph &g, const ECDesc &d, int grid_small,
                      int grid_big) {
     hipLaunchKernelGGL((k_ec_small<16, true>), dim3(grid_small), dim3(kBlock), 0, s, g, d);
-    hipLaunchKernelGGL((k_ec_big<true>), dim3(grid_big), dim3(kBlock), 0, s, g, d);
+    hipLaunchKernelGGL((k_ec_big<true>), dim3(grid_big), dim3(kBigBlock), 0, s, g, d);
 }
 
 void launch_scan_i32(hipStream_t s, const int32_t *in, const int32_t *n, int32_t *out) {
@@ -800,8 +871,8 @@ int64_t scan_tmp_words(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; 
 
 void launch_scan_i64(hipStream_t s, const int64_t *in, int64_t n, int64_t *out, int64_t *tmp) {
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb == 0) {  // empty input: out[0] = 0
-        hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, out, (int64_t)0);
+    if (n <= kScanOne) {  // (an empty input leaves out[0] = 0)
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, s, in, n, out);
         return;
     }
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, tmp);

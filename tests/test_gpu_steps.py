@@ -158,3 +158,36 @@ def test_hub_candidates_against_many(hubs, row):
             assert sn["cand"] == sw["cand"]
             if min(sn["cand"]) > 0:
                 assert sn["ec"] == sw["ec"]
+
+
+@pytest.mark.parametrize("row", [256, 257, 1024, 1025, 8192, 8193, 9216, 9217, 16384])
+def test_long_rows_multi_kernel_path(row):
+    """Rows a workgroup takes whole in the multi-kernel path: at the limit of
+    the tier and at the ends of its rounds; both adjacency directions and the
+    outgoing graph only."""
+    mg = hub_graph(3, row)
+    og = oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    qs = [MicroQuery(3, [1, 0, 2], [-1, -1, -1], [0, 1], [1, 2], [0, 1]),
+          MicroQuery(3, [1, 0, 1], [mg.V - 1, -1, -1], [0, 1, 2], [1, 2, 1], [0, 1, -1]),
+          MicroQuery(2, [2, 1], [-1, -1], [1, 0], [0, 1], [-1, 1])]
+    for opt in (dict(path=P.SGM_PATH_WIDE), dict(out_only=1)):
+        g = P.Graph(rp, col, rel, typ, **opt)
+        for i, q in enumerate(qs):
+            print("case: query", i, opt, flush=True)
+            assert np.array_equal(g.match_query(q), og.match_query(q))
+        g.close()
+
+
+@pytest.mark.parametrize("n", [1, 8191, 8193, 32767, 32768, 32769, 40000])
+def test_scans_of_one_and_several_workgroups(n):
+    """A join level's pair offsets over n parent rows: one round, several,
+    and the sizes from which the scan runs in several workgroups."""
+    i = np.arange(n)
+    dst = n + np.concatenate([i, (i[::7] * 3 + 1) % n])
+    mg = MicroGraph(2 * n, np.concatenate([i, i[::7]]), dst, np.zeros(len(dst)), i.repeat(2) * 0)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ, path=P.SGM_PATH_WIDE)
+    q = MicroQuery(2, [-1, -1], [-1, -1], [0], [1], [0])
+    want = np.unique(np.stack([mg.src, mg.dst], 1), axis=0)
+    assert np.array_equal(g.match_query(q), want)
