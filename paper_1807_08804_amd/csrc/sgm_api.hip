@@ -1244,7 +1244,9 @@ struct Query {
             int64_t *bcnt = sc.get<int64_t>(tiles);
             int64_t *boff = sc.get<int64_t>(tiles + 1);
             int64_t *tmp2 = sc.get<int64_t>(scan_tmp_words(tiles) + 1);
+            uint64_t *found = sc.get<uint64_t>(join_found_words(p1 - p0));
             a.block_cnt = bcnt;
+            a.found = found;
             {
                 Prof p(g, SGM_K_JOIN, (p1 - p0) * (4.0 * k + 16.0 + 24.0 * L.n_chk));
                 launch_join_count(st(), a);
@@ -1263,6 +1265,7 @@ struct Query {
             if (R2 == 0 || (last && (flags & SGM_COUNT_ONLY))) {
                 if (last) fin_rows_ += R2;
                 sc.release(boff);
+                sc.release(found);
                 continue;
             }
             int32_t *out = sc.get<int32_t>(R2 * (k + 1));
@@ -1275,6 +1278,7 @@ struct Query {
                 launch_join_write(st(), a);
             }
             sc.release(boff);
+            sc.release(found);
             res->stats.peak_rows = std::max(res->stats.peak_rows, R2);
             res->stats.peak_bytes = std::max<int64_t>(res->stats.peak_bytes, R2 * 4 * (k + 1));
             if (last && !fin_ && p0 == 0 && p1 == P) {

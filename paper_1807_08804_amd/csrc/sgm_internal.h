@@ -159,6 +159,7 @@ struct JoinArgs {
     int64_t P;                // one past the last pair of this launch
     int32_t *out;             // [..][k+1] (write pass)
     int64_t *block_cnt;       // per-tile valid counts (count pass) / offsets (write pass)
+    uint64_t *found;          // [join_found_words] a bit per pair: it is a row (count pass)
     int64_t out_base;         // first output row (chunking)
     int32_t homomorphic;      // 1: the new value may repeat one of the row (compressed graphs)
 };
@@ -192,6 +193,7 @@ int64_t scan_tmp_words(int64_t n);
 void launch_scan_i64(hipStream_t s, const int64_t *in, int64_t n, int64_t *out, int64_t *tmp);
 void launch_join_fan(hipStream_t s, const JoinArgs &a, int64_t *fan);
 int64_t join_tiles(int64_t P);
+int64_t join_found_words(int64_t P);
 void launch_join_count(hipStream_t s, const JoinArgs &a);
 void launch_join_write(hipStream_t s, const JoinArgs &a);
 void launch_keys_to_table(hipStream_t s, const int32_t *keys, const int32_t *key_cnt_dev,

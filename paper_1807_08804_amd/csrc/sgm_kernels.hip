@@ -459,7 +459,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_partials(int64_t *part, int64_t
     if (threadIdx.x == 0) part[nb] = carry;
 }
 
-// The scan of kItems consecutive values per thread: one block scan for all of
+// The scan of kItems consecutive values per thread (in and out start on 16
+// bytes, as every scratch block does): one block scan for all of
 // them (a scan per value and its two barriers cost 6.4 us in a grid of any
 // size, of which 4 were these).
 template <int kItems>
@@ -467,17 +468,32 @@ __device__ __forceinline__ int64_t scan_run(const int64_t *in, int64_t n, int64_
                                             int64_t carry, int64_t *sh, int64_t *out) {
     const int64_t i0 = base + (int64_t)threadIdx.x * kItems;
     int64_t x[kItems], sum = 0;
+    const bool whole = i0 + kItems <= n;
+    if (whole) {
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        x[k] = i0 + k < n ? in[i0 + k] : 0;
-        sum += x[k];
+        for (int k = 0; k < kItems; k += 2) {
+            const longlong2 v = *(const longlong2 *)(in + i0 + k);
+            x[k] = v.x;
+            x[k + 1] = v.y;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) x[k] = i0 + k < n ? in[i0 + k] : 0;
     }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) sum += x[k];
     int64_t tot;
     int64_t run = carry + block_excl_scan(sum, sh, &tot);
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        if (i0 + k < n) out[i0 + k] = run;
-        run += x[k];
+    for (int k = 0; k < kItems; k += 2) {
+        const int64_t next = run + x[k];
+        if (whole) {
+            *(longlong2 *)(out + i0 + k) = make_longlong2(run, next);
+        } else {
+            if (i0 + k < n) out[i0 + k] = run;
+            if (i0 + k + 1 < n) out[i0 + k + 1] = next;
+        }
+        run = next + x[k + 1];
     }
     return carry + tot;
 }
@@ -519,27 +535,79 @@ __global__ __launch_bounds__(kBlock) void k_join_fan(JoinArgs a, int64_t *fan) {
 constexpr int kJoinItems = 8;
 constexpr int64_t kJoinTile = (int64_t)kBlock * kJoinItems;
 
-// Pair t -> (row, j): the last row whose pair offset is <= t.
-__device__ __forceinline__ int64_t pair_row(const int64_t *pair_off, int64_t R, int64_t t) {
-    int64_t lo = 0, hi = R;  // answer in [0, R)
+// First index i in (lo, hi] with v[i] > t, minus one: the last of v[lo, hi)
+// that is <= t (v ascending, v[lo] <= t). 64 places at a time by one wave.
+__device__ __forceinline__ int64_t wave_last_le(const int64_t *v, int64_t lo, int64_t hi, int64_t t) {
+    const int lane = threadIdx.x & 63;
     while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (pair_off[mid] <= t) lo = mid;
-        else hi = mid;
+        const int64_t step = (hi - lo + 63) >> 6;
+        const int64_t i = lo + lane * step;
+        const uint64_t m = __ballot(i < hi && v[i] <= t);
+        const int64_t at = lo + (63 - __builtin_clzll(m)) * step;  // lane 0 always counts
+        lo = at;
+        hi = min(hi, at + step);
     }
     return lo;
 }
 
-// Validity of pair t; on success *w = the new vertex's data vertex and *row
-// the parent row index.
-__device__ __forceinline__ bool join_pair(const JoinArgs &a, int64_t t, int32_t *w,
-                                          int64_t *row) {
-    const int64_t r = pair_row(a.pair_off, a.R, t);
-    const int64_t j = t - a.pair_off[r];
-    const int32_t *rp = a.table + r * a.k;
-    const int32_t pv = rp[a.ext.col];
-    const int32_t pi = rank_of(a.ext.rank, pv);
-    const int32_t x = a.ext.vals[a.ext.offs[pi] + j];
+// A tile's pairs and their parent rows: the rows' pair offsets (from the
+// tile's first pair) and where their values start, staged in LDS once per
+// tile. A search of all rows per pair was a chain of 27 reads of memory
+// (rows of 79 million), and the place of the row's values two more.
+struct JoinTile {
+    int32_t off[kJoinTile];  // off[i]: pair offset of row r0 + i, or 0 for the first
+    int32_t val[kJoinTile];  // its first value in ext.vals, less off[i]
+    int64_t r0, r1;          // rows of the first and the last pair
+};
+
+__device__ __forceinline__ void join_stage(const JoinArgs &a, JoinTile &s, int64_t base) {
+    const int wid = threadIdx.x >> 6;
+    const int64_t last = min(base + kJoinTile, a.P) - 1;
+    if (wid < 2) {
+        const int64_t r = wave_last_le(a.pair_off, 0, a.R, wid ? last : base);
+        if ((threadIdx.x & 63) == 0) (wid ? s.r1 : s.r0) = r;
+    }
+    __syncthreads();
+    const int64_t r0 = s.r0, n = s.r1 - r0 + 1;
+    if (n <= kJoinTile)
+        for (int32_t i = threadIdx.x; i < (int32_t)n; i += kBlock) {
+            // the first row may begin before the tile
+            const int64_t o = a.pair_off[r0 + i] - base;
+            const int32_t p = rank_of(a.ext.rank, a.table[(r0 + i) * a.k + a.ext.col]);
+            s.off[i] = (int32_t)max(o, (int64_t)0);
+            s.val[i] = (int32_t)(a.ext.offs[p] - o);
+        }
+    __syncthreads();
+}
+
+// The row of pair base + i and its new vertex. (More rows than a tile has
+// pairs: rows without pairs lie between; searched in memory.)
+__device__ __forceinline__ int64_t join_row(const JoinArgs &a, const JoinTile &s, int64_t base,
+                                            int32_t i, int32_t *x) {
+    const int64_t n = s.r1 - s.r0 + 1;
+    if (n <= kJoinTile) {
+        int32_t lo = 0, hi = (int32_t)n;
+        while (hi - lo > 1) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (s.off[mid] <= i) lo = mid;
+            else hi = mid;
+        }
+        *x = a.ext.vals[s.val[lo] + i];
+        return s.r0 + lo;
+    }
+    int64_t lo = s.r0, hi = s.r1 + 1;
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (a.pair_off[mid] <= base + i) lo = mid;
+        else hi = mid;
+    }
+    const int32_t p = rank_of(a.ext.rank, a.table[lo * a.k + a.ext.col]);
+    *x = a.ext.vals[a.ext.offs[p] + (base + i - a.pair_off[lo])];
+    return lo;
+}
+
+// Whether the pair of parent row rp and new vertex x is a row of the level.
+__device__ __forceinline__ bool join_ok(const JoinArgs &a, const int32_t *rp, int32_t x) {
     if (!a.homomorphic)
         for (int c = 0; c < a.k; ++c)
             if (rp[c] == x) return false;  // injectivity
@@ -556,24 +624,32 @@ __device__ __forceinline__ bool join_pair(const JoinArgs &a, int64_t t, int32_t 
         }
         if (l >= hi || ce.vals[l] != x) return false;
     }
-    *w = x;
-    *row = r;
     return true;
 }
 
+// Count pass: the rows of each tile, and which of its pairs they are (one bit
+// a pair: the write pass then tests nothing again).
 __global__ __launch_bounds__(kBlock) void k_join_count(JoinArgs a) {
+    __shared__ JoinTile tile;
     __shared__ int32_t sh[kBlock / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t base = a.p0 + (int64_t)blockIdx.x * kJoinTile;
+    join_stage(a, tile, base);
+    const int32_t np = (int32_t)min(a.P - base, kJoinTile);
     int32_t cnt = 0;
     for (int k = 0; k < kJoinItems; ++k) {
-        const int64_t t = base + (int64_t)k * kBlock + threadIdx.x;
-        int32_t w;
-        int64_t r;
-        if (t < a.P && join_pair(a, t, &w, &r)) ++cnt;
+        const int32_t i = k * kBlock + threadIdx.x;
+        bool ok = false;
+        if (i < np) {
+            int32_t x;
+            const int64_t r = join_row(a, tile, base, i, &x);
+            ok = join_ok(a, a.table + r * a.k, x);
+        }
+        const uint64_t b = __ballot(ok);
+        cnt += __popcll(b);
+        if (lane == 0) a.found[(int64_t)blockIdx.x * (kJoinTile / 64) + (i >> 6)] = b;
     }
-    const int32_t inc = wave_incl_scan32(cnt, lane);
-    if (lane == 63) sh[wid] = inc;
+    if (lane == 0) sh[wid] = cnt;
     __syncthreads();
     if (threadIdx.x == 0) {
         int64_t s = 0;
@@ -582,35 +658,50 @@ __global__ __launch_bounds__(kBlock) void k_join_count(JoinArgs a) {
     }
 }
 
-// Write pass: tile rounds in pair order, block-local ordered compaction.
+// A wave's LDS writes before, its reads after (no other wave's are involved).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Write pass: the pairs found, in pair order. A wave's rows are put together
+// in LDS and leave as one run of consecutive ints; bound by the table's
+// traffic. (Both passes searching and testing every pair and each lane
+// writing its own row: 4.6 ms per pass over the levels of a query with
+// 79 and 97 million rows in two of them; now 1.1 ms.)
 __global__ __launch_bounds__(kBlock) void k_join_write(JoinArgs a) {
-    __shared__ int32_t sh[kBlock / 64];
+    static_assert(kJoinTile / 64 <= 64, "a lane per word");
+    __shared__ JoinTile tile;
+    __shared__ int32_t stage[kBlock / 64][64 * SGM_MAX_QV];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t base = a.p0 + (int64_t)blockIdx.x * kJoinTile;
-    int64_t pos = a.out_base + a.block_cnt[blockIdx.x];
+    const int64_t pos = a.out_base + a.block_cnt[blockIdx.x];
+    // every wave holds the tile's words and the rows before each
+    const uint64_t word =
+        lane < kJoinTile / 64 ? a.found[(int64_t)blockIdx.x * (kJoinTile / 64) + lane] : 0ull;
+    if (__ballot(word != 0) == 0ull) return;
+    const int32_t before = wave_incl_scan32(__popcll(word), lane) - __popcll(word);
+    join_stage(a, tile, base);
     const int k1 = a.k + 1;
     for (int k = 0; k < kJoinItems; ++k) {
-        const int64_t t = base + (int64_t)k * kBlock + threadIdx.x;
-        int32_t w = 0;
-        int64_t r = 0;
-        const bool ok = t < a.P && join_pair(a, t, &w, &r);
-        const uint64_t b = __ballot(ok);
-        if (lane == 0) sh[wid] = __popcll(b);
-        __syncthreads();
-        int32_t wo = 0, tot = 0;
-        for (int i = 0; i < kBlock / 64; ++i) {
-            if (i < wid) wo += sh[i];
-            tot += sh[i];
-        }
-        if (ok) {
-            const int64_t o = pos + wo + __popcll(b & lanemask_lt(lane));
-            int32_t *dst = a.out + o * k1;
+        const int at = k * (kBlock / 64) + wid;
+        const uint64_t b = __shfl(word, at, 64);
+        if (b == 0) continue;
+        const int64_t o = pos + __shfl(before, at, 64);
+        if ((b >> lane) & 1ull) {
+            int32_t x;
+            const int64_t r = join_row(a, tile, base, at * 64 + lane, &x);
+            int32_t *dst = stage[wid] + __popcll(b & lanemask_lt(lane)) * k1;
             const int32_t *src = a.table + r * a.k;
             for (int c = 0; c < a.k; ++c) dst[c] = src[c];
-            dst[a.k] = w;
+            dst[a.k] = x;
         }
-        pos += tot;
-        __syncthreads();
+        wave_lds_fence();
+        const int32_t n = __popcll(b) * k1;
+        int32_t *out = a.out + o * k1;
+        for (int32_t i = lane; i < n; i += 64) out[i] = stage[wid][i];
+        wave_lds_fence();
     }
 }
 
@@ -962,6 +1053,8 @@ void launch_join_fan(hipStream_t s, const JoinArgs &a, int64_t *fan) {
 }
 
 int64_t join_tiles(int64_t P) { return (P + kJoinTile - 1) / kJoinTile; }
+
+int64_t join_found_words(int64_t P) { return join_tiles(P) * (kJoinTile / 64); }
 
 void launch_join_count(hipStream_t s, const JoinArgs &a) {
     const int64_t nb = join_tiles(a.P - a.p0);
