@@ -144,6 +144,8 @@ struct Scope {
 constexpr int kMaxSlots = 1024;
 constexpr int kMaxRounds = 32;
 constexpr int kMaxDesc = 2048;
+// rows of the table an expansion fills while it counts
+constexpr int64_t kExpandRows = 1 << 16;
 
 // Small per-query counters, cleared with one memset per query.
 struct DevCounters {
@@ -2591,29 +2593,57 @@ int sgm_match_compressed(sgm_graph *g, sgm_graph *gw, const sgm_query *q, uint32
                 HIPX(hipMemcpyAsync(wrows, rw->rows, sizeof(int32_t) * (size_t)(nw * n),
                                     hipMemcpyHostToDevice, st));
                 a.wrows = wrows;
-                a.cnt = sc.get<int64_t>(nw);
-                int64_t *offs = sc.get<int64_t>(nw + 1);
-                int64_t *tmp = sc.get<int64_t>(scan_tmp_words(nw) + 1);
-                launch_expand_count(st, a);
-                launch_scan_i64(st, a.cnt, nw, offs, tmp);
-                HIPX(hipMemcpyAsync(g->h_small, offs + nw, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-                HIPX(hipStreamSynchronize(st));
-                total = g->h_small[0];
-                a.offs = offs;
-                if (total > 0 && !(flags & SGM_COUNT_ONLY)) {
-                    table = sc.get<int32_t>(total * n);
-                    a.out = table;
-                    launch_expand_write(st, a);
+                auto readback = [&](const void *d) {
+                    HIPX(hipMemcpyAsync(g->h_small, d, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+                    HIPX(hipStreamSynchronize(st));
+                    return g->h_small[0];
+                };
+                const bool want = !(flags & SGM_COUNT_ONLY);
+                if (expand_by_waves(nw)) {
+                    // the matches are distinct and sorted below: a table for
+                    // kExpandRows of them is filled while they are counted,
+                    // and the expansion runs again only when there are more
+                    a.total = sc.get<unsigned long long>(1);
+                    a.cap = want ? kExpandRows : 0;
+                    for (;;) {
+                        if (want) a.out = table = sc.get<int32_t>(a.cap * n);
+                        HIPX(hipMemsetAsync(a.total, 0, sizeof(unsigned long long), st));
+                        launch_expand_wave(st, a);
+                        total = readback(a.total);
+                        if (!want || total <= a.cap) break;
+                        sc.release(table);
+                        a.cap = total;
+                    }
+                } else {
+                    a.cnt = sc.get<int64_t>(nw);
+                    int64_t *offs = sc.get<int64_t>(nw + 1);
+                    int64_t *tmp = sc.get<int64_t>(scan_tmp_words(nw) + 1);
+                    launch_expand_count(st, a);
+                    launch_scan_i64(st, a.cnt, nw, offs, tmp);
+                    total = readback(offs + nw);
+                    a.offs = offs;
+                    if (total > 0 && want) {
+                        table = sc.get<int32_t>(total * n);
+                        a.out = table;
+                        launch_expand_write(st, a);
+                    }
                 }
             }
             res->n_rows = total;
             if (g->opts.result_cap_rows > 0 && total > g->opts.result_cap_rows) {
                 rc = SGM_ETOOBIG;
             } else if (!(flags & SGM_COUNT_ONLY)) {
-                // ascending lexicographic order: stable LSD passes over the
-                // columns, last column first
+                // ascending lexicographic order: in one workgroup, or by
+                // stable LSD passes over the columns, last column first
                 int32_t *rows = table;
-                if (total > 1) {
+                int32_t colpos[SGM_MAX_QV];
+                for (int c = 0; c < n; ++c) colpos[c] = c;
+                if (total > 1 && total <= small_sort_limit()) {
+                    int32_t *idx = sc.get<int32_t>(total);
+                    launch_sort_small(st, table, n, colpos, n, (int32_t)total, idx);
+                    rows = sc.get<int32_t>(total * n);
+                    launch_gather_rows(st, table, n, idx, total, colpos, n, rows);
+                } else if (total > 1) {
                     int nbits = 1;
                     while ((1ll << nbits) < g->V) ++nbits;
                     int32_t *ia = sc.get<int32_t>(total), *ib = sc.get<int32_t>(total);
@@ -2633,8 +2663,6 @@ int sgm_match_compressed(sgm_graph *g, sgm_graph *gw, const sgm_query *q, uint32
                             std::swap(ia, ib);
                         }
                     }
-                    int32_t colpos[SGM_MAX_QV];
-                    for (int c = 0; c < n; ++c) colpos[c] = c;
                     rows = sc.get<int32_t>(total * n);
                     launch_gather_rows(st, table, n, ia, total, colpos, n, rows);
                 }

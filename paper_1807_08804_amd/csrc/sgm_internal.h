@@ -268,7 +268,13 @@ struct ExpandArgs {
     int64_t *cnt;          // [nw] matches per weighted match (count pass)
     const int64_t *offs;   // [nw + 1] their exclusive scan (write pass)
     int32_t *out;          // [total][n] (write pass)
+    // by waves: the matches found (zero before) and room for cap of them in
+    // out, taken in any order
+    unsigned long long *total;
+    int64_t cap;
 };
+bool expand_by_waves(int64_t nw);
+void launch_expand_wave(hipStream_t s, const ExpandArgs &a);
 void launch_expand_count(hipStream_t s, const ExpandArgs &a);
 void launch_expand_write(hipStream_t s, const ExpandArgs &a);
 

@@ -975,76 +975,194 @@ void launch_scan_i64(hipStream_t s, const int64_t *in, int64_t n, int64_t *out, 
 // expansion of weighted matches into the original graph's matches
 // ---------------------------------------------------------------------------
 
-// does g hold the edge s -> t with relation rel (-1: any)? (out-rows are
-// sorted by (neighbour, relation))
+// does g hold the edge s -> t with relation rel (-1: any)? (rows are sorted
+// by (neighbour, relation); looked up in the shorter of s's outgoing and t's
+// incoming row)
 __device__ __forceinline__ bool has_edge(const DevGraph &g, int32_t s, int32_t t, int32_t rel) {
-    int32_t lo = g.out_off[s], hi = g.out_off[s + 1];
+    int32_t lo = g.out_off[s], end = g.out_off[s + 1], want = t;
+    const int2 *adj = g.out_adj;
+    if (g.in_adj) {
+        const int32_t ib = g.in_off[t], ie = g.in_off[t + 1];
+        if (ie - ib < end - lo) {
+            lo = ib;
+            end = ie;
+            want = s;
+            adj = g.in_adj;
+        }
+    }
+    int32_t hi = end;
     while (lo < hi) {
         const int32_t mid = lo + ((hi - lo) >> 1);
-        if (g.out_adj[mid].x < t) lo = mid + 1;
+        if (adj[mid].x < want) lo = mid + 1;
         else hi = mid;
     }
-    for (int32_t i = lo; i < g.out_off[s + 1]; ++i) {
-        const int2 e = g.out_adj[i];
-        if (e.x != t) return false;
+    for (int32_t i = lo; i < end; ++i) {
+        const int2 e = adj[i];
+        if (e.x != want) return false;
         if (adj_rel_ok(g, e, rel)) return true;
     }
     return false;
 }
 
-// One thread per weighted match: a depth-first walk over the members of the
-// mapping lists in the query's order; the count pass counts the matches,
-// the write pass writes them at the match's offset, in walk order.
-template <bool WRITE>
-__global__ __launch_bounds__(kBlock) void k_expand(ExpandArgs a) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < a.nw;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t *wr = a.wrows + r * a.n;
-        int32_t x[SGM_MAX_QV];    // chosen member per query vertex
-        int32_t pos[SGM_MAX_QV];  // next list position per depth
-        int64_t c = 0;
-        const int64_t o = WRITE ? a.offs[r] : 0;
-        int d = 0;
-        pos[0] = a.map_off[wr[a.order[0]]];
-        while (d >= 0) {
-            const int u = a.order[d];
-            const int32_t end = a.map_off[wr[u] + 1];
-            bool placed = false;
-            while (pos[d] < end && !placed) {
-                const int32_t m = a.map_ids[pos[d]++];
-                bool ok = a.pin[u] < 0 || m == a.pin[u];
-                for (int i = 0; i < d && ok; ++i) ok = x[a.order[i]] != m;
-                for (int e = a.eb[d]; e < a.eb[d + 1] && ok; ++e) {
-                    const int32_t s = a.es[e] == u ? m : x[a.es[e]];
-                    const int32_t t = a.ed[e] == u ? m : x[a.ed[e]];
-                    ok = has_edge(a.g, s, t, a.el[e]);
-                }
-                if (ok) {
-                    x[u] = m;
-                    placed = true;
-                }
-            }
-            if (!placed) {
-                --d;
-            } else if (d == a.n - 1) {
-                if (WRITE)
-                    for (int v = 0; v < a.n; ++v) a.out[(o + c) * a.n + v] = x[v];
-                ++c;
-            } else {
-                ++d;
-                pos[d] = a.map_off[wr[a.order[d]]];
-            }
+// Threads of an expansion block, and what each lane holds in LDS (indexed by
+// run-time query vertices and depths; in scratch memory every step of a walk
+// paid for it).
+constexpr int kExpand = 64;
+struct ExpandLds {
+    int32_t (*x)[kExpand];    // [n] chosen member per query vertex
+    int32_t (*pos)[kExpand];  // [n] next list position per depth
+};
+
+// may the d-th vertex take member m, given the lane's choices before it?
+__device__ __forceinline__ bool expand_ok(const ExpandArgs &a, ExpandLds s, int lane, int d,
+                                          int32_t m) {
+    const int u = a.order[d];
+    bool ok = a.pin[u] < 0 || m == a.pin[u];
+    for (int i = 0; i < d && ok; ++i) ok = s.x[a.order[i]][lane] != m;
+    for (int e = a.eb[d]; e < a.eb[d + 1] && ok; ++e) {
+        const int32_t f = a.es[e] == u ? m : s.x[a.es[e]][lane];
+        const int32_t t = a.ed[e] == u ? m : s.x[a.ed[e]][lane];
+        ok = has_edge(a.g, f, t, a.el[e]);
+    }
+    return ok;
+}
+
+// Depth-first walk of a lane over the members of weighted match wr's mapping
+// lists in the query's order, from depth d0 (the choices before it made).
+// found() takes each match from the lane's choices.
+template <class F>
+__device__ __forceinline__ void expand_walk(const ExpandArgs &a, ExpandLds s, int lane,
+                                            const int32_t *wr, int d0, F found) {
+    int d = d0;
+    s.pos[d][lane] = a.map_off[wr[a.order[d]]];
+    while (d >= d0) {
+        const int u = a.order[d];
+        const int32_t end = a.map_off[wr[u] + 1];
+        int32_t p = s.pos[d][lane];
+        bool placed = false;
+        while (p < end && !placed) {
+            const int32_t m = a.map_ids[p++];
+            placed = expand_ok(a, s, lane, d, m);
+            if (placed) s.x[u][lane] = m;
         }
+        s.pos[d][lane] = p;
+        if (!placed) {
+            --d;
+        } else if (d == a.n - 1) {
+            found();
+        } else {
+            ++d;
+            s.pos[d][lane] = a.map_off[wr[a.order[d]]];
+        }
+    }
+}
+
+// Many weighted matches: a thread each; a pass counts and one writes at the
+// counts' scan.
+template <bool WRITE>
+__global__ __launch_bounds__(kExpand) void k_expand(ExpandArgs a) {
+    extern __shared__ int32_t lds[][kExpand];  // sized by n: more waves in flight
+    ExpandLds s{lds, lds + a.n};
+    const int lane = threadIdx.x;
+    for (int64_t r = (int64_t)blockIdx.x * kExpand + lane; r < a.nw; r += (int64_t)gridDim.x * kExpand) {
+        int64_t c = 0;
+        int32_t *row = WRITE ? a.out + a.offs[r] * a.n : nullptr;
+        expand_walk(a, s, lane, a.wrows + r * a.n, 0, [&] {
+            if (WRITE)
+                for (int v = 0; v < a.n; ++v) row[c * a.n + v] = s.x[v][lane];
+            ++c;
+        });
         if (!WRITE) a.cnt[r] = c;
     }
 }
 
+// Few weighted matches: a wave each. Level by level, a lane per pair of a
+// partial assignment and a member of the next vertex's list, while at most 64
+// partial assignments result; from there each lane walks on from its own.
+// Matches take the next free place of the table while it has one.
+__global__ __launch_bounds__(kExpand) void k_expand_wave(ExpandArgs a) {
+    __shared__ int32_t lds[3 * SGM_MAX_QV][kExpand];
+    ExpandLds s{lds, lds + SGM_MAX_QV};
+    int32_t (*const next)[kExpand] = lds + 2 * SGM_MAX_QV;  // the next level's assignments
+    const int lane = threadIdx.x;
+    for (int64_t r = blockIdx.x; r < a.nw; r += gridDim.x) {
+        const int32_t *wr = a.wrows + r * a.n;
+        int d = 0;
+        int32_t F = 1;  // partial assignments, in the lanes' columns of s.x
+        bool wide = true;
+        while (wide && F > 0 && d < a.n) {
+            const int u = a.order[d];
+            const int32_t beg = a.map_off[wr[u]], M = a.map_off[wr[u] + 1] - beg;
+            const bool last = d == a.n - 1;
+            int32_t kept = 0;
+            for (int64_t b = 0; b < (int64_t)F * M; b += 64) {
+                const int64_t i = b + lane;
+                const bool in = i < (int64_t)F * M;
+                const int32_t f = in ? (int32_t)(i / M) : 0;
+                const int32_t m = a.map_ids[beg + (in ? (int32_t)(i - (int64_t)f * M) : 0)];
+                const bool ok = in && expand_ok(a, s, f, d, m);
+                const uint64_t w = __ballot(ok);
+                const int nw = __popcll(w), at = __popcll(w & lanemask_lt(lane));
+                if (w == 0) continue;
+                if (last) {
+                    unsigned long long o = 0;
+                    if (lane == 0) o = atomicAdd(a.total, (unsigned long long)nw);
+                    o = __shfl(o, 0, 64) + at;
+                    if (ok && (int64_t)o < a.cap)
+                        for (int v = 0; v < a.n; ++v)
+                            a.out[(int64_t)o * a.n + v] = v == u ? m : s.x[v][f];
+                    continue;
+                }
+                if (kept + nw > 64) {
+                    wide = false;
+                    break;
+                }
+                if (ok) {
+                    for (int j = 0; j < d; ++j) next[a.order[j]][kept + at] = s.x[a.order[j]][f];
+                    next[u][kept + at] = m;
+                }
+                kept += nw;
+            }
+            if (!wide) break;
+            wave_lds_fence();
+            if (!last)
+                for (int j = 0; j <= d; ++j)
+                    if (lane < kept) s.x[a.order[j]][lane] = next[a.order[j]][lane];
+            wave_lds_fence();
+            F = last ? 0 : kept;
+            ++d;
+        }
+        if (!wide && lane < F)
+            expand_walk(a, s, lane, wr, d, [&] {
+                const int64_t o = (int64_t)atomicAdd(a.total, 1ull);
+                if (o < a.cap)
+                    for (int v = 0; v < a.n; ++v) a.out[o * a.n + v] = s.x[v][lane];
+            });
+        wave_lds_fence();
+    }
+}
+
+// A wave per weighted match below this many, and their matches counted and
+// written in one pass (400 of them: 28 us against 73 with a thread each; a
+// single one with 16 matches: 30 against 145 in two passes). A thread each
+// from there on: equal at 5,270, 0.31 ms against 1.07 at 67,215; in two
+// passes, since a place taken per match cost 3 ms for 5.8 million.
+constexpr int64_t kExpandThreads = 4096;
+
+bool expand_by_waves(int64_t nw) { return nw < kExpandThreads; }
+
+void launch_expand_wave(hipStream_t s, const ExpandArgs &a) {
+    hipLaunchKernelGGL(k_expand_wave, dim3((unsigned)a.nw), dim3(kExpand), 0, s, a);
+}
+
 void launch_expand_count(hipStream_t s, const ExpandArgs &a) {
-    hipLaunchKernelGGL(k_expand<false>, dim3(grid_for(a.nw, kBlock, kGridCap)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_expand<false>, dim3(grid_for(a.nw, kExpand, 4 * kGridCap)), dim3(kExpand),
+                       2 * a.n * kExpand * sizeof(int32_t), s, a);
 }
 
 void launch_expand_write(hipStream_t s, const ExpandArgs &a) {
-    hipLaunchKernelGGL(k_expand<true>, dim3(grid_for(a.nw, kBlock, kGridCap)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_expand<true>, dim3(grid_for(a.nw, kExpand, 4 * kGridCap)), dim3(kExpand),
+                       2 * a.n * kExpand * sizeof(int32_t), s, a);
 }
 
 void launch_join_fan(hipStream_t s, const JoinArgs &a, int64_t *fan) {

@@ -191,3 +191,34 @@ def test_scans_of_one_and_several_workgroups(n):
     q = MicroQuery(2, [-1, -1], [-1, -1], [0], [1], [0])
     want = np.unique(np.stack([mg.src, mg.dst], 1), axis=0)
     assert np.array_equal(g.match_query(q), want)
+
+
+@pytest.mark.parametrize("members,links", [(1, 1), (5, 64), (5, 65), (24, 4095), (24, 4096), (260, 300)])
+def test_expansion_by_waves_and_threads(members, links):
+    """Expansions of weighted matches: one to 260 members per mapping list
+    (partial assignments below and above a wave's 64, more matches than the
+    first table holds) and weighted matches on both sides of the number from
+    which a thread takes each."""
+    # `links` pairs of single vertices and one pair of groups of `members`
+    # alike vertices, complete between the groups; types keep pairs apart
+    n = 2 * links
+    a, b = n + np.arange(members), n + members + np.arange(members)
+    src = np.concatenate([np.arange(links), np.repeat(a, members)])
+    dst = np.concatenate([links + np.arange(links), np.tile(b, members)])
+    vt = np.concatenate([np.zeros(links), np.ones(links), np.full(members, 2), np.full(members, 3)])
+    mg = MicroGraph(n + 2 * members, src, dst, np.zeros(len(src)), vt)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    cg = P.CompressedGraph(g, P.Compressed(rp, col, rel, typ, max_levels=8))
+    og = oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+    qs = [MicroQuery(2, [0, 1], [-1, -1], [0], [1], [0]), MicroQuery(2, [2, 3], [-1, -1], [0], [1], [0]),
+          MicroQuery(2, [-1, -1], [-1, -1], [0], [1], [-1])]
+    if members <= 24:
+        qs.append(MicroQuery(3, [2, 3, 2], [-1, -1, -1], [0, 2], [1, 1], [0, 0]))
+    for i, q in enumerate(qs):
+        print("case: query", i, flush=True)
+        want = og.match_query(q)
+        assert np.array_equal(cg.match_query(q), want)
+        assert cg.match_query(q, count_only=True) == len(want)
+    cg.close()
+    g.close()
