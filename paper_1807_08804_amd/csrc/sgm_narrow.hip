@@ -82,7 +82,6 @@ struct Smem {
     const int32_t *tableptr;
     const int32_t *listptr;  // the key columns' sorted candidate lists beside it
     unsigned long long rowhit;  // item_wg: listed rows with a matching entry
-    unsigned long long hseq;    // sequence number of the step this workgroup posted
     int32_t hq, hch;            // helper: board entry and chunk claimed (-1: none)
     int8_t qsrc[SGM_MAX_QE], qdst[SGM_MAX_QE];  // the query's edges, staged for join_order
     uint64_t revmask;
@@ -350,17 +349,6 @@ __device__ __forceinline__ void push_bit(Ctx &c, const K &k, uint64_t *tb, int32
 
 __device__ __forceinline__ void push_bit(Ctx &c, uint64_t *tb, int32_t *tl, int v, int32_t x) {
     push_bit(c, LdsCtr{}, tb, tl, v, x);
-}
-
-// Set bit x in tb; true if it was clear. With `look`, a plain read first
-// skips the atomic for a bit already set (pushes from many candidates that
-// share neighbours); without, the atomic alone saves a round trip.
-template <bool look>
-__device__ __forceinline__ bool set_new(uint64_t *tb, int32_t x) {
-    const uint64_t m = 1ull << (x & 63);
-    uint64_t *w = tb + (x >> 6);
-    if (look && (__atomic_load_n(w, __ATOMIC_RELAXED) & m)) return false;
-    return (atomicOr((unsigned long long *)w, m) & m) == 0;
 }
 
 // push_bit for up to four entries per lane (hk: push xk), appending the
@@ -2494,16 +2482,6 @@ __device__ __forceinline__ void join_order(Ctx &c) {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (has) s.eckey[lane] = s.jpos[xs] < s.jpos[xd] ? xs : xd;
-}
-
-__device__ __forceinline__ bool ec_contains(const Ctx &c, int e, int32_t keyval, int32_t x) {
-    const int kv = g_s.eckey[e];
-    const int32_t *kl = c.L(kv);
-    const int32_t i = lower_bound_i32(kl, 0, g_s.cnt[kv], keyval);
-    if (i >= g_s.cnt[kv] || kl[i] != keyval) return false;
-    const int32_t lo = g_s.ec_offs[e][i], hi = lo + g_s.ec_cnt[e][i];
-    const int32_t j = lower_bound_i32(g_s.ec_vals[e], lo, hi, x);
-    return j < hi && g_s.ec_vals[e][j] == x;
 }
 
 // Shared join levels: a chunk is one block of NT parent rows, or 1/nsub of
