@@ -5,13 +5,13 @@ Default workload ("large"): the large synthetic knowledge graph (4M
 vertices, 20M directed edges, 64 vertex types, 32 Zipf relations, int32 CSR)
 resident in HBM and the stored 1,024-query mixed batch (3-16 vertices;
 paths, stars, trees, cyclic; 0-50% pinned). One step = the 1,024 queries as
-one sgm_match_batch call (one persistent-kernel launch in a HIP graph, full
+one sgm_match_batch call (one persistent-kernel launch, full
 sorted embedding tables copied back to the host); ``value`` = batched
 queries/s. Beside it: embeddings/s, the same 1,024 queries one at a time on
 the same GPU (queries/s, p50/p99 latency), the served form on the same
 graph at 200 / 1,000 / 5,000 Poisson arrivals per second (sustained qps,
 p50/p99 of completion minus arrival, admission stalls), the roofline of the
-persistent kernel and of the batch's root sweep, and the CPU oracle on a
+persistent kernel, and the CPU oracle on a
 bounded sample of the same batch.
 
 ``--workload medium``: the medium graph (300,000 vertices, 1.6M edges) and
@@ -279,7 +279,7 @@ def bench_medium(args, P, kggen):
         g.match_batch(queries)
     el_b = time.perf_counter() - t
     log(f"batch path {el_b:.3f}s")
-    # the same batches with separate launches instead of one HIP graph
+    # the same batches with graphs=0 (accepted, without effect)
     gd = P.Graph.from_kg(kg, graphs=0)
     gd.match_batch(queries)
     t = time.perf_counter()
@@ -449,7 +449,6 @@ def bench_large(args, P, kggen):
                            "queries_per_s": round(args.steps * len(queries) / el_default, 3)},
         "served": served,
         "roofline": roofline(ks, "persist", "large:persist"),
-        "roofline_root_sweep": roofline(ks, "check", "large:check"),
         "persistent_kernel_phases": phases,
         "refinement_ablation": ablation,
         "cpu_baseline": cpu,
