@@ -1593,18 +1593,34 @@ __device__ __forceinline__ bool keep_marked(Ctx &c, int p) {
     uint64_t *pb = c.B(p);
     int32_t *pl = c.L(p);
     const int32_t n = g_s.cnt[p], nm = g_s.nmarks;
-    if (nm < n) {
-        clear_words(c, p, n);
-        __syncthreads();
+    const int32_t nwords = c.g.nwords;
+    if (nm > nwords / 4) {
+        // many marks: the scratch bitmap holds them, word by word (one by one,
+        // a scattered atomic and a scattered store each: six cyclic queries
+        // on 4M vertices 41.5 ms instead of 39.8)
 #pragma unroll 4
-        for (int32_t i = threadIdx.x; i < nm; i += NT) {
-            const int32_t x = c.marks[i];
-            atomicOr((unsigned long long *)&pb[x >> 6], 1ull << (x & 63));
-            pl[i] = x;
+        for (int32_t w = threadIdx.x; w < nwords; w += NT) {
+            const uint64_t m = c.scratch[w];
+            if (nm < n) pb[w] = m;
+            c.scratch[w] = 0ull;
         }
-    }
+        if (nm < n)
 #pragma unroll 4
-    for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[c.marks[i] >> 6] = 0ull;
+            for (int32_t i = threadIdx.x; i < nm; i += NT) pl[i] = c.marks[i];
+    } else {
+        if (nm < n) {
+            clear_words(c, p, n);
+            __syncthreads();
+#pragma unroll 4
+            for (int32_t i = threadIdx.x; i < nm; i += NT) {
+                const int32_t x = c.marks[i];
+                atomicOr((unsigned long long *)&pb[x >> 6], 1ull << (x & 63));
+                pl[i] = x;
+            }
+        }
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < nm; i += NT) c.scratch[c.marks[i] >> 6] = 0ull;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         g_s.cnt[p] = nm;

@@ -222,3 +222,34 @@ def test_expansion_by_waves_and_threads(members, links):
         assert cg.match_query(q, count_only=True) == len(want)
     cg.close()
     g.close()
+
+
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 18, 300, 4000])
+@pytest.mark.parametrize("back", [0, 1])
+def test_marks_kept_word_by_word_and_one_by_one(k, back):
+    """A parent's candidates cut to the k that a step marked, below and above
+    a quarter of the bitmap's 64 words, where the marks are taken from the
+    scratch bitmap instead of one by one; all of them kept, and some."""
+    V = 4096
+    rng = np.random.default_rng(k)
+    par = rng.permutation(V - 40)[:k]  # parents with a child of type 1
+    src = np.concatenate([np.arange(V - 40), par])
+    dst = np.concatenate([np.full(V - 40, V - 40), V - 39 + rng.integers(0, 39, k)])
+    if back:
+        src, dst = dst, src
+    vt = np.concatenate([np.zeros(V - 40), [2], np.full(39, 1)])
+    mg = MicroGraph(V, src, dst, np.zeros(len(src)), vt)
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    qs = [MicroQuery(3, [1, 0, 2], [-1, -1, V - 40], [1, 1], [0, 2], [0, 0]),
+          MicroQuery(3, [2, 0, 1], [V - 40, -1, -1], [1, 1], [0, 2], [0, 0])]
+    if back:
+        qs = [MicroQuery(3, q.vlabel, q.vpin, q.edst, q.esrc, q.elabel) for q in qs]
+    gs = [P.Graph(rp, col, rel, typ, path=p) for p in (P.SGM_PATH_NARROW, P.SGM_PATH_WIDE)]
+    for tune in (dict(help_items=64), dict(help_items=0)):
+        gs[0].set_tuning(**tune)
+        for i, q in enumerate(qs):
+            print("case: query", i, tune, flush=True)
+            (rn, sn), (rw, sw) = [g.match_query(q, with_stats=True) for g in gs]
+            assert len(rn) == k and np.array_equal(rn, rw) and np.array_equal(rn, og.match_query(q))
+            assert sn["cand"] == sw["cand"] and sn["ec"] == sw["ec"]
