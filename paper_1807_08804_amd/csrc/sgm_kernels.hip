@@ -608,9 +608,14 @@ __device__ __forceinline__ int64_t join_row(const JoinArgs &a, const JoinTile &s
 
 // Whether the pair of parent row rp and new vertex x is a row of the level.
 __device__ __forceinline__ bool join_ok(const JoinArgs &a, const int32_t *rp, int32_t x) {
-    if (!a.homomorphic)
-        for (int c = 0; c < a.k; ++c)
-            if (rp[c] == x) return false;  // injectivity
+    if (!a.homomorphic) {
+        // injectivity (no way out at the first equal column: the reads of
+        // the row go out together)
+        bool dup = false;
+#pragma unroll 4
+        for (int c = 0; c < a.k; ++c) dup |= rp[c] == x;
+        if (dup) return false;
+    }
     for (int e = 0; e < a.n_chk; ++e) {
         const JoinEdge &ce = a.chk[e];
         const int32_t bi = rank_of(ce.rank, rp[ce.col]);
@@ -694,6 +699,7 @@ __global__ __launch_bounds__(kBlock) void k_join_write(JoinArgs a) {
             const int64_t r = join_row(a, tile, base, at * 64 + lane, &x);
             int32_t *dst = stage[wid] + __popcll(b & lanemask_lt(lane)) * k1;
             const int32_t *src = a.table + r * a.k;
+#pragma unroll 4
             for (int c = 0; c < a.k; ++c) dst[c] = src[c];
             dst[a.k] = x;
         }
