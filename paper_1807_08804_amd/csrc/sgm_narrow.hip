@@ -1814,6 +1814,10 @@ __device__ __forceinline__ int32_t filter_step(Ctx &c, const NStep &st, int32_t 
     }
     add_bytes_wave(c, fb);
     __syncthreads();
+    // A step that failed leaves counts past the lists they belong to (a root
+    // step appends its survivors as it goes, and counts them on past lcap):
+    // nothing below may read a list by them. The query leaves the slot.
+    if (aborted(c)) return 0;
     const bool shrunk = g_s.removed != 0 || g_s.rdrop != 0;
     if (g_s.removed) {
         const int32_t n = g_s.cnt[u];

@@ -1,0 +1,63 @@
+"""Filter steps that outgrow their slot's candidate lists: the query leaves
+the slot and is answered in a larger one, and nothing else is touched."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1807_08804_amd as P
+from tests.micro import MicroGraph, MicroQuery
+
+pytestmark = pytest.mark.gpu
+
+LCAP = 65536  # entries of a regular slot's candidate list
+
+
+def wide_root_graph(V, keep, longs=40):
+    """Type 0: `keep` vertices with one relation-0 edge to a type-1 vertex and
+    `longs` with rows of 97 to 9,000 entries of relation 1 only; all other
+    vertices are of type 1."""
+    rng = np.random.default_rng(keep)
+    n0 = keep + longs
+    lens = np.concatenate([[97, 513, 2049, 8193, 9000], rng.integers(97, 700, longs)])[:longs]
+    src = np.concatenate([np.arange(keep), np.repeat(keep + np.arange(longs), lens)])
+    dst = np.concatenate([n0 + np.arange(keep), n0 + rng.integers(0, V - n0, int(lens.sum()))])
+    rel = np.concatenate([np.zeros(keep), np.ones(int(lens.sum()))])
+    return MicroGraph(V, src, dst, rel, (np.arange(V) >= n0).astype(np.int32))
+
+
+@pytest.fixture(scope="module", params=[LCAP - 40, LCAP - 39, 70000, 78085])
+def overflow(request):
+    """Roots at a regular list's capacity, one past it, and between it and the
+    words of the bitmap (which a graph of more than 64 * 65,536 vertices has
+    more of than a list has entries)."""
+    mg = wide_root_graph(5_000_000, request.param)
+    return request.param, mg, oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+
+
+@pytest.mark.parametrize("help_items", [1024, 0])
+def test_root_survivors_past_the_list(overflow, help_items):
+    """A root step whose survivors outgrow the list while longer rows still
+    fail their test: the counts run past the list, which then is not
+    compacted by them. The root as the first and the last query vertex; the
+    slots beside it and the next queries in its slot keep their answers."""
+    keep, mg, og = overflow
+    print("case: survivors", keep, "help_items", help_items, flush=True)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    g.set_tuning(help_items=help_items)
+    big = [MicroQuery(2, [0, 1], [-1, -1], [0], [1], [0]),
+           MicroQuery(3, [1, 1, 0], [-1, -1, -1], [2, 2], [0, 1], [0, -1])]
+    small = [MicroQuery(2, [0, 1], [keep + k, -1], [0], [1], [1]) for k in range(8)]
+    want = [og.match_query(q) for q in big + small]
+    assert len(want[0]) == keep and len(want[1]) == 0
+    for q, w in zip(big + small, want):
+        assert np.array_equal(g.match_query(q), w)
+    for r, w in zip(g.match_batch(big + small), want):
+        assert np.array_equal(r, w)
+    # the fixed area's one slot: refused past its list, whole again after
+    if keep + 40 > LCAP:
+        with pytest.raises(P.SGMError):
+            g.match_query_noalloc(big[0], 1 << 17)
+    for q, w in zip(small, want[2:]):
+        assert np.array_equal(g.match_query_noalloc(q, 1 << 14), w)
+    g.close()
