@@ -1482,6 +1482,16 @@ __device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t roo
     // a step resumed at its pushes has listed them already
     int32_t *def = from == 3 ? (int32_t *)(c.slab + 8 * (int64_t)c.lcap) : nullptr;
     for (int tier = from; tier < 4; ++tier) {
+        if (tier > 0) {
+            // A step that has failed goes no further: the query leaves the
+            // slot, and after a give-up a helper may still hold a chunk of
+            // the tier before, so nothing more may be posted on the board
+            // entry. (Every wave reads the word before the tier can set it.)
+            __syncthreads();
+            const bool failed = aborted(c);
+            __syncthreads();
+            if (failed) return;
+        }
         // what the tier shares: kind (-1: nothing), items, chunk size, chunks
         int kind = -1;
         int32_t nsh = 0, K = 1, nch = 0;
@@ -1502,7 +1512,6 @@ __device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t roo
                 filter_items(c, LdsCtr{}, u, root, st.push != 0, nb, ncount, ul, ub, 0, n_items, fb);
             }
         } else if (tier == 1) {
-            __syncthreads();
             const int32_t nl = min(g_s.nbig, c.lcap);
             if (nl == 0) return;
             def = defer_list(c, st);
@@ -1524,7 +1533,6 @@ __device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t roo
             // one wave per long row; rows above wg_rows get the whole
             // workgroup (listed in the slab where it has room), and so does
             // every row when there are fewer than waves
-            __syncthreads();
             const int32_t nbig = min(g_s.nbig, c.lcap);
             int32_t *giant = room ? rows : g_s.big;
             const int32_t gcap = room ? c.lcap : kBigCap;
@@ -1557,7 +1565,6 @@ __device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t roo
         } else {
             // the deferred pushes (by this workgroup alone when they do not
             // fit the slab)
-            __syncthreads();
             const int32_t nd = g_s.ndef;
             if (!def || nd == 0) return;
             // room in the slab, and no more chunks than a claim word counts
@@ -1672,6 +1679,7 @@ __device__ __attribute__((noinline)) uint64_t filter_far(int step_u, int push, i
                     rev ? nullptr : ub, rev ? g_s.cnt[d.v] : root < 0 ? n : n_items, from, fb);
         if (!rev) break;
         __syncthreads();
+        if (aborted(c)) break;  // (its marks may be incomplete)
         keep_marked(c, u);
         if (threadIdx.x == 0) g_s.rdrop += n - g_s.cnt[u];
         if (threadIdx.x == 0) {

@@ -61,3 +61,45 @@ def test_root_survivors_past_the_list(overflow, help_items):
     for q, w in zip(small, want[2:]):
         assert np.array_equal(g.match_query_noalloc(q, 1 << 14), w)
     g.close()
+
+
+def tier_graph(cands, hubs, row):
+    """`cands` vertices of type 0 with short rows, `hubs` with `row` entries
+    and six with 6,000, to the 20,000 vertices of types 1 and 2; each of those
+    points back to a few of type 0."""
+    rng = np.random.default_rng(cands + hubs)
+    n0, T = cands + hubs, 20000
+    deg = np.concatenate([rng.integers(1, 6, cands), np.full(hubs - 6, row), np.full(6, 6000)])
+    src = np.repeat(np.arange(n0), deg)
+    dst = n0 + rng.integers(0, T, len(src))
+    back = rng.integers(0, n0, 2 * T)
+    src, dst = (np.concatenate([src, n0 + np.arange(2 * T) % T]), np.concatenate([dst, back]))
+    vt = np.concatenate([np.zeros(n0), 1 + (np.arange(T) % 8 == 0)])
+    return MicroGraph(n0 + T, src, dst, rng.integers(0, 2, len(src)), vt)
+
+
+@pytest.mark.parametrize("wg_rows", [64, 1024])
+def test_no_tier_is_posted_after_a_give_up(wg_rows):
+    """Steps whose candidates, long rows, longest rows and row segments are
+    all shared, given up after one poll (forced from the host): the step ends
+    there, and every table is the oracle's."""
+    mg = tier_graph(3000, 80, 1200)
+    og = oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    qs = [MicroQuery(3, [2, 0, 2], [-1, -1, -1], [0, 1], [1, 2], [0, r]) for r in (0, 1, -1)]
+    qs += [MicroQuery(3, [0, 2, 0], [k, -1, -1], [0, 1, 2], [1, 2, 1], [-1, 0, -1]) for k in (0, 3010)]
+    want = [og.match_query(q) for q in qs]
+    g.set_tuning(slots=2, wg_rows=wg_rows, help_items=64, helpers=512, help_wait=1)
+    gave_up = 0
+    for rep in range(4):
+        got, stats = g.match_batch(qs, with_stats=True)
+        for i, (r, w) in enumerate(zip(got, want)):
+            print("case: launch", rep, "query", i, flush=True)
+            assert np.array_equal(r, w)
+        gave_up += sum(st["fallback"] == 32 for st in stats)
+    g.set_tuning(help_wait=0)
+    for r, w in zip(g.match_batch(qs), want):
+        assert np.array_equal(r, w)
+    print("given up:", gave_up, flush=True)
+    g.close()
