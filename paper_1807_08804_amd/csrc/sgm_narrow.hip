@@ -1659,7 +1659,7 @@ __device__ __attribute__((noinline)) uint64_t filter_far(int step_u, int push, i
     // does for its parent, with nothing dropped from C(v).
     for (uint64_t rm = g_s.revmask;;) {
         const bool rev = rm != 0;
-        if ((!rev && ncount == 0 && root < 0) || aborted(c)) break;
+        if (!rev && ncount == 0 && root < 0) break;
         const NNbr d = c.Q->nbr[st.first + (rev ? __builtin_ctzll(rm) : 0)];
         if (rev && threadIdx.x == 0) {
             NTest *rt = g_s.nbl + SGM_MAX_QE;
@@ -1679,7 +1679,11 @@ __device__ __attribute__((noinline)) uint64_t filter_far(int step_u, int push, i
                     rev ? nullptr : ub, rev ? g_s.cnt[d.v] : root < 0 ? n : n_items, from, fb);
         if (!rev) break;
         __syncthreads();
-        if (aborted(c)) break;  // (its marks may be incomplete)
+        // The marks of a failed pass may be incomplete. (The abort word is read
+        // between barriers only: at the head of the loop a fast wave's pushes
+        // could already have set it when a slow one looked, and the waves
+        // would have parted before a barrier.)
+        if (aborted(c)) break;
         keep_marked(c, u);
         if (threadIdx.x == 0) g_s.rdrop += n - g_s.cnt[u];
         if (threadIdx.x == 0) {

@@ -103,3 +103,23 @@ def test_no_tier_is_posted_after_a_give_up(wg_rows):
         assert np.array_equal(r, w)
     print("given up:", gave_up, flush=True)
     g.close()
+
+
+@pytest.mark.parametrize("help_items", [1024, 0])
+@pytest.mark.parametrize("kids", [LCAP - 1, LCAP, LCAP + 1, 90000])
+def test_child_list_past_its_capacity(kids, help_items):
+    """A step over a few candidates, one with a long row and nine or more
+    beside it, that pushes up to and past a list's capacity of children."""
+    n0, V = 60, 60 + 100000
+    src = np.concatenate([np.repeat(np.arange(n0 - 1), 90), np.full(kids, n0 - 1)])[:kids]
+    dst = n0 + np.arange(kids)
+    mg = MicroGraph(V, src, dst, np.zeros(kids), (np.arange(V) >= n0).astype(np.int32))
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    g.set_tuning(help_items=help_items)
+    for q in (MicroQuery(2, [0, 1], [-1, -1], [0], [1], [0]),
+              MicroQuery(2, [0, 1], [n0 - 1, -1], [0], [1], [0])):
+        print("case: children", kids, "pin", q.vpin[0], flush=True)
+        assert np.array_equal(g.match_query(q), og.match_query(q))
+    g.close()
