@@ -316,6 +316,7 @@ struct LdsCtr {
     __device__ int32_t *nmarks() const { return &g_s.nmarks; }
     __device__ int32_t *ndef() const { return &g_s.ndef; }
     __device__ int32_t *abort_() const { return &g_s.abort_; }
+    __device__ bool failed() const { return __atomic_load_n(&g_s.abort_, __ATOMIC_RELAXED) != 0; }
 };
 struct BoardCtr {
     HelpJob *j;
@@ -325,6 +326,7 @@ struct BoardCtr {
     __device__ int32_t *nmarks() const { return &j->nmarks; }
     __device__ int32_t *ndef() const { return &j->ndef; }
     __device__ int32_t *abort_() const { return &j->abort_; }
+    __device__ bool failed() const { return false; }  // a chunk is short: the owner looks
 };
 
 // Set bit x; on a newly set bit append x to list tl, or, for a push into
@@ -1222,7 +1224,7 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, int u, int32_t 
     const int wid = threadIdx.x >> 6;
     const int32_t per = nodefer ? 1 : min(64, (it1 - it0 + NW - 1) / NW);
     const int32_t bigdeg = nodefer ? max(4096, c.wg_rows) : per == 1 ? kFlatRowOne : kFlatRow;
-    for (int32_t i = it0 + wid * per; i < it1; i += NW * per) {
+    for (int32_t i = it0 + wid * per; i < it1 && !k.failed(); i += NW * per) {
         const int32_t e = min(it1, i + per);
         // few candidates and several tests: all their rows at once; the
         // rows of long-row passes are read test by test, which stops at the
@@ -1377,10 +1379,20 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         atomicAdd(&c.hctr[0], 1);
     }
     __syncthreads();
-    int32_t own = 0;
+    int32_t own = 0, claimed = nch;  // (thread 0's: chunks that will be reported)
     for (;;) {
         if (threadIdx.x == 0) {
-            const unsigned long long w = take_chunk(j);
+            const int32_t failed =
+                __hip_atomic_load(&j->abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long w = take_chunk(j);
+            if (failed && claim_next(w) < claim_nch(w)) {
+                // the query leaves the slot: no chunk beyond those taken (this
+                // one, which is reported without work, among them)
+                const unsigned long long v = atomicExch(&j->claim, claim_word(claim_seq(w), 0));
+                claimed = min(claim_next(v), nch);
+                ++own;
+                w = 0ull;
+            }
             g_s.hch = claim_next(w) < claim_nch(w) ? claim_next(w) : -1;
         }
         __syncthreads();
@@ -1403,12 +1415,12 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         // the owner's own chunks need no fence: it reads them itself
         int32_t got = atomicAdd(&j->done, own) + own;
         int64_t n = 0;
-        while (got < nch && n < c.help_wait) {
+        while (got < claimed && n < c.help_wait) {
             __builtin_amdgcn_s_sleep(1);
             got = __hip_atomic_load(&j->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             ++n;
         }
-        if (got < nch) {
+        if (got < claimed) {
             // give up: no further claims on the step (a claim against zero
             // chunks fails), and the slot stays out of use until the next
             // launch clears it, since chunks claimed earlier may still write
@@ -1429,7 +1441,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         g_s.nmarks = __hip_atomic_load(&j->nmarks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int32_t ab = __hip_atomic_load(&j->abort_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (ab) g_s.abort_ = ab;
-        if (got < nch) g_s.abort_ = kWhyHelp;
+        if (got < claimed) g_s.abort_ = kWhyHelp;
         add_bytes(c, __hip_atomic_load(&j->bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
     __syncthreads();

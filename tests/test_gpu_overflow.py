@@ -123,3 +123,22 @@ def test_child_list_past_its_capacity(kids, help_items):
         print("case: children", kids, "pin", q.vpin[0], flush=True)
         assert np.array_equal(g.match_query(q), og.match_query(q))
     g.close()
+
+
+@pytest.mark.parametrize("help_items", [1024, 0])
+def test_an_overflowing_root_step_stops(help_items):
+    """A root whose survivors outgrow the regular list early: the attempt ends
+    there, with a small part of the bytes that the whole step moves in the
+    larger slot which answers the query."""
+    V = 1_500_000
+    a = np.arange(V, dtype=np.int32)
+    g = P.Graph(np.arange(V + 1, dtype=np.int32), (a + 1) % V, a * 0, a * 0, profile=1)
+    g.set_tuning(help_items=help_items)
+    print("case: root of", V, "vertices, help_items", help_items, flush=True)
+    q = MicroQuery(2, [-1, -1], [-1, -1], [0], [1], [0])
+    g.reset_kernel_stats()
+    n, st = g.match_query(q, count_only=True, with_stats=True)
+    assert n == V and st["fallback"] == 1 and st["path"] == P.SGM_PATH_NARROW
+    total = g.kernel_stats()["persist"]["bytes"]
+    assert total - st["device_bytes"] < 0.5 * st["phase_bytes"][0]
+    g.close()
