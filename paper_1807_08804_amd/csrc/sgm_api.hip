@@ -226,6 +226,10 @@ struct sgm_graph {
     int4 *d_vrow = nullptr, *d_trow = nullptr;
     int32_t *d_tverts = nullptr;
     std::vector<int32_t> type_off;  // first vertex of each type in d_tverts
+    // For each type of at least kRootTab vertices, and last for all vertices:
+    // how many have out-degree >= a and in-degree >= b, at [16 a + b] of its
+    // 256 counts (root_tab_of[t]: the type's entry, -1: none).
+    std::vector<int32_t> root_tab, root_tab_of;
     int2 *d_out_adj = nullptr, *d_in_adj = nullptr;
     int2 *d_out_ta = nullptr, *d_out_tb = nullptr, *d_in_ta = nullptr, *d_in_tb = nullptr;
     int32_t *d_hub_of = nullptr, *d_hub_toff = nullptr;
@@ -1564,6 +1568,7 @@ constexpr int64_t kNarrowSlabMax = 32ll << 20;       // per slot, large graphs (
 // A graph's own batch context: 40 B per data vertex up to 160 MB per slot
 // (512 slots of a 4M-vertex graph hold about 87 GB of HBM), so that queries
 // with tables of ~1e6 rows finish in their slot and a batch is one launch.
+constexpr int32_t kRootTab = 1024;        // vertices of a type from which its degrees are counted
 constexpr int32_t kHubTypesMax = 4096;    // more vertex types: no hub-row index
 constexpr int64_t kHostOrderRows = 65536;  // final tables from this size are ordered by the host
 constexpr int64_t kBatchSlabPerVertex = 40;
@@ -1680,6 +1685,39 @@ void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     }
 }
 
+// Fills g->root_tab from the vertices' types and clamped degrees (vinfo).
+void count_root_degrees(sgm_graph *g, const std::vector<int2> &vi) {
+    g->root_tab_of.assign((size_t)g->n_types, -1);
+    int32_t n = 0;
+    for (int32_t t = 0; t < g->n_types; ++t)
+        if (g->type_freq[t] >= kRootTab) g->root_tab_of[t] = n++;
+    g->root_tab.assign((size_t)(n + 1) * 256, 0);
+    for (const int2 &v : vi) {
+        const int32_t at = std::min(v.y & 255, 15) * 16 + std::min(v.y >> 8, 15);
+        if (g->root_tab_of[v.x] >= 0) ++g->root_tab[(size_t)g->root_tab_of[v.x] * 256 + at];
+        ++g->root_tab[(size_t)n * 256 + at];
+    }
+    for (int32_t i = 0; i <= n; ++i) {
+        int32_t *c = &g->root_tab[(size_t)i * 256];
+        for (int a = 15; a >= 0; --a)
+            for (int b = 15; b >= 0; --b)
+                c[a * 16 + b] += (a < 15 ? c[a * 16 + 16 + b] : 0) + (b < 15 ? c[a * 16 + b + 1] : 0) -
+                                 (a < 15 && b < 15 ? c[a * 16 + 17 + b] : 0);
+    }
+}
+
+// Vertices that the predicate of an unpinned root admits (for a type of few
+// vertices, at most that many).
+int32_t root_passing(const sgm_graph *g, int32_t label, int32_t qout, int32_t qin) {
+    const int32_t *c = g->root_tab.data() + g->root_tab.size() - 256;
+    if (label >= 0) {
+        if (label >= g->n_types) return 0;
+        if (g->root_tab_of[label] < 0) return (int32_t)g->type_freq[label];
+        c = &g->root_tab[(size_t)g->root_tab_of[label] * 256];
+    }
+    return c[std::min(qout, 15) * 16 + std::min(qin, 15)];
+}
+
 // Pack one validated query and its plan; false if it exceeds the packed
 // descriptor's capacity (the query then runs on the multi-kernel path).
 bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, NQuery *nq,
@@ -1763,8 +1801,14 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     // and so on. Longest first alone makes the first slots' heavy root
     // steps all run at once and contend; alternating them with short
     // queries ends the large batch's launch about 5 % sooner.
+    // Without helpers (see below) a root step over more candidates than the
+    // slot's list holds stays with one workgroup: such a query goes on to a
+    // larger slot, with helpers, at once, as one whose list overflows does
+    // (served, 500,000 root candidates of 2M vertices: 10,970 -> 900 us).
+    const bool help = !nw.serve && g->tune.help_items > 0;
     std::vector<Plan> plans((size_t)count);
     std::vector<int64_t> cost((size_t)count, -1);
+    std::vector<char> large((size_t)count, 0);
     std::vector<int> order;
     order.reserve((size_t)count);
     parallel_for(count, 128, [&](int lo, int hi) {
@@ -1777,14 +1821,16 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
             const int64_t rootc = qi.pin[r] >= 0 ? 1
                                   : (lab >= 0 && lab < g->n_types ? g->type_freq[lab] : g->V);
             cost[i] = rootc * (SGM_MAX_QV + 1) + qi.n;
+            large[i] = !help && qi.pin[r] < 0 &&
+                       root_passing(g, lab, qi.qout[r], qi.qin[r]) > nw.lcap;
         }
     });
     for (int i = 0; i < count; ++i) {
-        if (cost[i] >= 0) {
+        if (cost[i] >= 0 && !large[i]) {
             order.push_back(i);
         } else {
             wide.push_back(which[i]);
-            res[which[i]]->stats.fallback = 16;
+            res[which[i]]->stats.fallback = cost[i] < 0 ? 16 : kWhyList;
         }
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
@@ -1851,8 +1897,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
         std::min(np, nw.slab_want ? nw.slots : std::min(nw.slots, g->tune.slots));
     // Shared filter steps need every workgroup of the launch resident at
     // once (two per CU): helpers then wait only for work that exists. A
-    // server's contexts launch side by side, so they share no steps.
-    const bool help = !nw.serve && g->tune.help_items > 0;
+    // server's contexts launch side by side, so they share no steps (help).
     a.nslot = slot_grid;
     a.help_items = help ? g->tune.help_items : 0;
     a.board = nw.d_board;
@@ -2393,6 +2438,7 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             vi[v] = make_int2(type[v], std::min(od, 255) | std::min(id, 255) << 8);
         }
         g->d_vinfo = dev_upload(vi);
+        count_root_degrees(g, vi);
         {
             std::vector<int4> vr((size_t)n_vertices);
             for (int32_t v = 0; v < n_vertices; ++v)

@@ -142,3 +142,34 @@ def test_an_overflowing_root_step_stops(help_items):
     total = g.kernel_stats()["persist"]["bytes"]
     assert total - st["device_bytes"] < 0.5 * st["phase_bytes"][0]
     g.close()
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+def test_roots_past_the_list_without_helpers(extra):
+    """Served queries and launches without helpers give a root with more
+    candidates than a regular list on to the larger slot at once (few of them
+    would survive here); one with just as many, by its degree bounds, stays."""
+    n0, V = LCAP + extra, 200000
+    a = np.arange(n0)
+    # n0 vertices of type 0 with an out-edge, 1,000 more without
+    src, dst = a, V - 1 - a % 5000
+    vt = np.where(np.arange(V) < n0 + 1000, 0, 1)
+    mg = MicroGraph(V, src, dst, (a % 1000 != 0), vt)
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    q = MicroQuery(2, [0, 1], [-1, -1], [0], [1], [0])
+    want = og.match_query(q)
+    assert len(want) == 66
+    g = P.Graph(rp, col, rel, typ)
+    print("case: root candidates", n0, flush=True)
+    srv = P.Server(g)
+    status, rows, st = srv.wait(srv.submit(q), q.n)
+    srv.close()
+    assert status == P.SGM_OK and np.array_equal(rows, want) and st["fallback"] == extra
+    g.set_tuning(help_items=0)
+    rows, st = g.match_query(q, with_stats=True)
+    assert np.array_equal(rows, want) and st["fallback"] == extra
+    g.set_tuning(help_items=1024)
+    rows, st = g.match_query(q, with_stats=True)
+    assert np.array_equal(rows, want) and st["fallback"] == 0
+    g.close()
