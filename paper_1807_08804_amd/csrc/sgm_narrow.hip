@@ -26,6 +26,7 @@
 
 #include "sgm_device.h"
 #include "sgm_narrow.h"
+#include "sgm_share.h"
 
 namespace sgm {
 namespace {
@@ -1254,11 +1255,6 @@ __device__ __forceinline__ int32_t claim_nch(unsigned long long w) {
 __device__ __forceinline__ int32_t claim_next(unsigned long long w) {
     return (int32_t)(w & 0xfffffull);
 }
-// A step has at most this many chunks; unsuccessful claims raise the next
-// field past the chunk count by at most one per workgroup of the launch, so
-// it never reaches the chunk field.
-constexpr int32_t kMaxChunks = 1 << 19;
-
 // Take one chunk of board entry j (thread 0): the returned claim word's next
 // field is the chunk, which exists if it is below the chunk field. The step
 // named by the word stays posted, with fixed parameters, until every chunk
@@ -1517,9 +1513,8 @@ __device__ __forceinline__ void filter_pass(Ctx &c, const NStep &st, int32_t roo
                 kind = 0;
                 items = ul;
                 nsh = n_items;
-                K = min(512, max(64, max((n_items + helpers) / (helpers + 1),
-                                         (n_items + kMaxChunks - 1) / kMaxChunks)));
-                nch = (n_items + K - 1) / K;
+                K = chunk_items(n_items, helpers, 64, 512);
+                nch = chunk_count(n_items, K);
             } else {
                 filter_items(c, LdsCtr{}, u, root, st.push != 0, nb, ncount, ul, ub, 0, n_items, fb);
             }
@@ -2275,8 +2270,7 @@ __device__ __forceinline__ void ec_build(Ctx &c, int e, int key, int other, int 
             if (can_share && nk >= c.help_items) {
                 const int32_t helpers = helpers_now(c);
                 nsh = nk;
-                K = min(512, max(64, max((nk + helpers) / (helpers + 1),
-                                         (nk + kMaxChunks - 1) / kMaxChunks)));
+                K = chunk_items(nk, helpers, 64, 512);
                 G = lanes_for(K, c.gmax);
             } else {
                 mytot += ec_keys(c, E, 0, nk, lanes_for(nk, c.gmax), &g_s.nbig, fb);
