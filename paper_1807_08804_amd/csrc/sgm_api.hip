@@ -225,6 +225,7 @@ struct sgm_graph {
     int2 *d_vinfo = nullptr;
     int4 *d_vrow = nullptr, *d_trow = nullptr;
     int32_t *d_tverts = nullptr;
+    uint16_t *d_tdeg = nullptr;
     std::vector<int32_t> type_off;  // first vertex of each type in d_tverts
     // For each type of at least kRootTab vertices, and last for all vertices:
     // how many have out-degree >= a and in-degree >= b, at [16 a + b] of its
@@ -427,7 +428,7 @@ void free_graph_mem(sgm_graph *g) {
                   g->d_bits,    g->d_lists,  g->d_prefix, g->d_big,     g->d_desc,
                   g->d_cnt,     g->d_slots,  g->d_out_ta, g->d_out_tb,  g->d_in_ta,
                   g->d_in_tb,   g->d_hub_of, g->d_hub_toff, g->d_map_off, g->d_map_ids,
-                  g->d_vrow,    g->d_trow,   g->d_tverts};
+                  g->d_vrow,    g->d_trow,   g->d_tverts, g->d_tdeg};
     for (void *p : dp) {
         bool host = false;
         for (const auto &b : g->host_graph_bufs) host |= b.second == p;
@@ -1569,6 +1570,9 @@ constexpr int64_t kNarrowSlabMax = 32ll << 20;       // per slot, large graphs (
 // (512 slots of a 4M-vertex graph hold about 87 GB of HBM), so that queries
 // with tables of ~1e6 rows finish in their slot and a batch is one launch.
 constexpr int32_t kRootTab = 1024;        // vertices of a type from which its degrees are counted
+// a root is sparse from a range of kRootTab vertices of which at most one in
+// this many, and no more than a list holds, has the degrees it asks for
+constexpr int32_t kRootSparseDiv = 8;
 constexpr int32_t kHubTypesMax = 4096;    // more vertex types: no hub-row index
 constexpr int64_t kHostOrderRows = 65536;  // final tables from this size are ordered by the host
 constexpr int64_t kBatchSlabPerVertex = 40;
@@ -1720,8 +1724,8 @@ int32_t root_passing(const sgm_graph *g, int32_t label, int32_t qout, int32_t qi
 
 // Pack one validated query and its plan; false if it exceeds the packed
 // descriptor's capacity (the query then runs on the multi-kernel path).
-bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, NQuery *nq,
-                Plan *pl_out) {
+bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, int32_t lcap,
+                NQuery *nq, Plan *pl_out) {
     Program pr;
     build_program(qi, pl, g->opts.low_conn_degree, g->opts.refine_reversed, &pr);
     if ((int)(pr.init.size() + pr.refine.size()) > kNMaxSteps || (int)pr.nbr.size() > kNMaxNbr)
@@ -1746,6 +1750,12 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, N
     } else {
         nq->root_lo = lab < g->n_types ? g->type_off[lab] : 0;
         nq->root_hi = lab < g->n_types ? g->type_off[lab + 1] : 0;
+    }
+    if (nq->root_lo >= 0) {
+        const int32_t u = nq->root, range = nq->root_hi - nq->root_lo;
+        const int32_t pass = root_passing(g, lab, qi.qout[u], qi.qin[u]);
+        if (pass == 0) nq->root_hi = nq->root_lo;
+        nq->root_sparse = range >= kRootTab && pass <= range / kRootSparseDiv && pass <= lcap;
     }
     nq->n_init = (int)pr.init.size();
     nq->n_ref = (int)pr.refine.size();
@@ -1851,7 +1861,8 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     parallel_for(no, 128, [&](int lo, int hi) {
         for (int k = lo; k < hi; ++k) {
             const int i = order[k];
-            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], flags, &nw.h_q[k], &pls[k]);
+            packed_ok[k] = pack_query(g, qis[which[i]], plans[i], flags, nw.lcap, &nw.h_q[k],
+                                      &pls[k]);
         }
     });
     int np = 0;
@@ -2451,13 +2462,16 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             std::vector<int32_t> at(g->type_off.begin(), g->type_off.end() - 1);
             std::vector<int32_t> tv((size_t)n_vertices);
             std::vector<int4> tr((size_t)n_vertices);
+            std::vector<uint16_t> td(((size_t)n_vertices + 7) & ~(size_t)7);
             for (int32_t v = 0; v < n_vertices; ++v) {
                 const int32_t p = at[type[v]]++;
                 tv[p] = v;
                 tr[p] = vr[v];
+                td[p] = (uint16_t)(std::min(vi[v].y & 255, 127) | std::min(vi[v].y >> 8, 127) << 8);
             }
             g->d_tverts = dev_upload(tv);
             g->d_trow = dev_upload(tr);
+            g->d_tdeg = dev_upload(td);
         }
         if (g->n_types <= kHubTypesMax) {
             HubIndex hx;
@@ -2491,6 +2505,7 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
         g->dg.vrow = g->d_vrow;
         g->dg.tverts = g->d_tverts;
         g->dg.trow = g->d_trow;
+        g->dg.tdeg = g->d_tdeg;
         g->dg.out_ta = g->d_out_ta;
         g->dg.out_tb = g->d_out_tb;
         g->dg.in_ta = g->d_in_ta;
@@ -3596,7 +3611,7 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
     if (make_plan(qi, g->V, g->type_freq.data(), g->n_types, &pl) != SGM_OK) return SGM_EINVAL;
     NQuery nq;
     Plan pl_out;
-    if (!pack_query(g, qi, pl, flags, &nq, &pl_out)) {
+    if (!pack_query(g, qi, pl, flags, L.lcap, &nq, &pl_out)) {
         g_last_error = "query plan exceeds the packed descriptor";
         return SGM_EUNSUPPORTED;
     }

@@ -44,6 +44,9 @@ struct DevGraph {
     // extents in the same order
     const int32_t *tverts;
     const int4 *trow;
+    // vinfo's degrees in type order, up to 127 each and in whole groups of
+    // eight, for roots that few vertices reach
+    const uint16_t *tdeg;
     // An adjacency entry's second word is its relation (y & rel_mask) and,
     // with typed_adj, the type of the entry's vertex above it (y >> 16), so
     // that a test against a typed query vertex reads no memory for the

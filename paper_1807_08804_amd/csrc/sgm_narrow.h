@@ -51,6 +51,7 @@ struct NQuery {
     // the root's range in DevGraph::tverts (its type's vertices, or all of
     // them for an untyped root); root_lo = -1 if the root is pinned
     int32_t root_lo, root_hi;
+    int32_t root_sparse;    // 1: its degree bounds admit few of the range
     int32_t n_init, n_ref;  // explore steps, then refine steps (one round)
     int32_t refine_rounds;  // -1: until nothing is removed
     uint32_t proj;          // projected columns (bit u = query vertex u kept; 0: all)
@@ -158,7 +159,8 @@ struct HelpJob {
     int32_t chunk, done, q, kind;  // kind 0: chunks of the candidate list; 1: row segments;
                                    // 2: parent rows of a join level; 3: keys of an
                                    // edge-candidate table; 4: rows above wg_rows of a
-                                   // prune-only step, one per chunk
+                                   // prune-only step, one per chunk; 5: the
+                                   // range of a sparse root
     int32_t n_items, G, ncount;
     int32_t nodrop;       // 1: the items stay candidates whatever the tests say
     int32_t defer, ndef;  // kind 4: survivors' pushes go to the deferred list

@@ -227,6 +227,7 @@ __device__ __forceinline__ NArgs own_args() {
     in_memory(g.vrow);
     in_memory(g.tverts);
     in_memory(g.trow);
+    in_memory(g.tdeg);
     in_memory(g.vinfo);
     in_memory(g.out_ta);
     in_memory(g.out_tb);
@@ -1237,6 +1238,72 @@ __device__ __forceinline__ void filter_items(Ctx &c, const K &k, int u, int32_t 
     }
 }
 
+// A root that few vertices of its range reach (root_sparse): the vertices of
+// ul[i0, i1) that have the degrees it asks for, into u's list and bitmap. The
+// bounds alone cost two bytes a vertex here, eight vertices to a load and two
+// to a comparison, the next round's loads under way; in a root step each 64
+// vertices cost a wave's turn, 8 ns a vertex alone. (500,000 vertices of which
+// none has 12 out-edges: 213 -> 115 us a call, 4.0 -> 0.4 ms in a served
+// query's one workgroup.)
+constexpr int kSparseLoads = 4;
+constexpr int32_t kSparseRound = kSparseLoads * 512;  // vertices a wave takes at once
+constexpr int32_t kSparseShare = 1 << 16;  // range from which the scan is shared
+template <class K>
+__device__ __forceinline__ void sparse_scan(Ctx &c, const K &k, int u, int32_t root,
+                                            const int32_t *ul, int32_t i0, int32_t i1,
+                                            uint64_t &fb) {
+    const int lane = threadIdx.x & 63;
+    // place i of the range is entry i + shift of deg, which starts at a
+    // multiple of eight vertices in type order
+    const int64_t p0 = ul - c.g.tverts;
+    const int32_t shift = (int32_t)(p0 & 7), end = i1 + shift;
+    const uint4 *deg = (const uint4 *)(c.g.tdeg + (p0 - shift));
+    const uint32_t top = 0x80808080u, least = (uint32_t)(root & 0xffff) * 0x10001u;
+    uint4 next[kSparseLoads];
+    auto load = [&](int32_t at) {
+#pragma unroll
+        for (int q = 0; q < kSparseLoads; ++q) {
+            const int32_t e = at + (q * 64 + lane) * 8;
+            next[q] = e < end ? deg[e >> 3] : make_uint4(0, 0, 0, 0);
+        }
+    };
+    int32_t at = ((i0 + shift) & ~7) + (int32_t)(threadIdx.x >> 6) * kSparseRound;
+    load(at);
+    for (; at < end; at += NW * kSparseRound) {
+        // both bytes of a vertex's word at least the bounds: bit 7 of each
+        uint32_t hit[kSparseLoads * 4], any = 0;
+#pragma unroll
+        for (int q = 0; q < kSparseLoads * 4; ++q) {
+            const uint4 x = next[q >> 2];
+            const uint32_t w = (q & 3) == 0 ? x.x : (q & 3) == 1 ? x.y : (q & 3) == 2 ? x.z : x.w;
+            const uint32_t ge = ((w | top) - least) & top;
+            hit[q] = ge & (ge >> 8) & 0x00800080u;
+            any |= hit[q];
+        }
+        load(at + NW * kSparseRound);
+        if (lane == 0) fb += 2ull * min(kSparseRound, end - at);
+        if (__ballot(any != 0) == 0ull) continue;
+        uint32_t ok = 0;  // bit 8 q + r: entry r of load q
+#pragma unroll
+        for (int q = 0; q < kSparseLoads * 4; ++q) {
+            const int32_t i = at + ((q >> 2) * 64 + lane) * 8 + (q & 3) * 2 - shift;
+            ok |= (uint32_t)((hit[q] & 0x80u) && i >= i0 && i < i1) << (2 * q);
+            ok |= (uint32_t)((hit[q] >> 16) && i + 1 >= i0 && i + 1 < i1) << (2 * q + 1);
+        }
+        const int32_t n = __popc(ok), inc = wave_incl_scan32(n, lane);
+        int32_t p = 0;
+        if (lane == 63) p = atomicAdd(k.cnt(u), inc);
+        p = __builtin_amdgcn_readlane(p, 63) + inc - n;
+        for (; ok; ok &= ok - 1u) {
+            const int b = __builtin_ctz(ok);
+            const int32_t v = ul[at + ((b >> 3) * 64 + lane) * 8 + (b & 7) - shift];
+            if (p < c.lcap) c.L(u)[p++] = v;
+            else *k.abort_() = kWhyList;
+            atomicOr((unsigned long long *)&c.B(u)[v >> 6], 1ull << (v & 63));
+        }
+    }
+}
+
 // Empty polls in a row before a helper leaves (helping is optional, so
 // leaving early only costs speed; about a second of polling). The owner of
 // a shared step polls its completion count at most NArgs::help_wait times
@@ -1333,12 +1400,12 @@ __device__ __forceinline__ void ec_chunk(Ctx &c, const EcJob &E, HelpJob *j, int
 // nch chunks that the owner and its helpers claim (kind 0: K candidates of
 // u's list, G lanes each; kind 1: one row segment each), and the owner waits
 // for the chunks its helpers claimed before taking the counters back.
-__device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, const NTest *nb,
+template <class W>
+__device__ __forceinline__ void shared_run(Ctx &c, int kind, const NStep &st, const NTest *nb,
                                            int ncount, const int32_t *ul, uint64_t *ub,
                                            int32_t n_items, int32_t K, int G, int32_t nch,
-                                           const int4 *seg, uint64_t &fb,
-                                           const EcJob *ecj = nullptr, bool nodefer = false,
-                                           int32_t root = -1, int32_t *def = nullptr) {
+                                           const int4 *seg, const EcJob *ecj, bool nodefer,
+                                           int32_t root, const int32_t *def, W work) {
     HelpJob *j = c.job;
     if (threadIdx.x == 0) {
         for (int v = 0; v < SGM_MAX_QV; ++v) j->cnt[v] = g_s.cnt[v];
@@ -1395,15 +1462,7 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
         const int32_t ch = g_s.hch;
         __syncthreads();
         if (ch < 0) break;
-        if (kind == 0)
-            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, nb, ncount, ul, ub, ch * K,
-                         min(n_items, ch * K + K), fb, nodefer);
-        else if (kind == 3)
-            ec_chunk(c, *ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
-        else if (kind == 4)
-            item_wg_k(c, BoardCtr{j}, st, nb, ncount, ul[ch], ub, fb, def);
-        else
-            push_segment(c, BoardCtr{j}, nb, seg[ch], fb);
+        work(j, ch);
         ++own;
     }
     __syncthreads();
@@ -1443,6 +1502,26 @@ __device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, co
     __syncthreads();
 }
 
+__device__ __forceinline__ void shared_job(Ctx &c, int kind, const NStep &st, const NTest *nb,
+                                           int ncount, const int32_t *ul, uint64_t *ub,
+                                           int32_t n_items, int32_t K, int G, int32_t nch,
+                                           const int4 *seg, uint64_t &fb,
+                                           const EcJob *ecj = nullptr, bool nodefer = false,
+                                           int32_t root = -1, int32_t *def = nullptr) {
+    shared_run(c, kind, st, nb, ncount, ul, ub, n_items, K, G, nch, seg, ecj, nodefer, root, def,
+               [&](HelpJob *j, int32_t ch) {
+        if (kind == 0)
+            filter_items(c, BoardCtr{j}, st.u, root, st.push != 0, nb, ncount, ul, ub, ch * K,
+                         min(n_items, ch * K + K), fb, nodefer);
+        else if (kind == 3)
+            ec_chunk(c, *ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
+        else if (kind == 4)
+            item_wg_k(c, BoardCtr{j}, st, nb, ncount, ul[ch], ub, fb, def);
+        else
+            push_segment(c, BoardCtr{j}, nb, seg[ch], fb);
+    });
+}
+
 // Workgroups that can help this slot now: the launch's extra ones and the
 // slot workgroups whose queue ran dry (uniform).
 __device__ __forceinline__ int32_t helpers_now(Ctx &c) {
@@ -1456,6 +1535,29 @@ __device__ __forceinline__ int32_t helpers_now(Ctx &c) {
     const int32_t h = g_s.hch;
     __syncthreads();
     return h;
+}
+
+// The candidates of a sparse root (uniform), shared from kSparseShare vertices.
+__device__ __attribute__((noinline)) void sparse_root() {
+    SGM_OWN_CTX(c);
+    const int u = uniform(c.Q->root);
+    const int32_t root = uniform(c.Q->pred[u].qout) | uniform(c.Q->pred[u].qin) << 8;
+    const int32_t *ul = c.g.tverts + uniform(c.Q->root_lo);
+    const int32_t n = uniform(c.Q->root_hi) - uniform(c.Q->root_lo);
+    uint64_t fb = 0;
+    if (c.help_items > 0 && c.job && n >= kSparseShare) {
+        const int32_t K = chunk_items(n, helpers_now(c), NW * kSparseRound, 1 << 16);
+        NStep st{};
+        st.u = (int8_t)u;
+        shared_run(c, 5, st, nullptr, 0, ul, nullptr, n, K, 64, chunk_count(n, K), nullptr, nullptr,
+                   false, root, nullptr, [&](HelpJob *j, int32_t ch) {
+            sparse_scan(c, BoardCtr{j}, u, root, ul, ch * K, min(n, ch * K + K), fb);
+        });
+    } else {
+        sparse_scan(c, LdsCtr{}, u, root, ul, 0, n, fb);
+    }
+    add_bytes_wave(c, fb);
+    __syncthreads();
 }
 
 // Where the wave and workgroup tiers of a pushing step list the candidates
@@ -3093,7 +3195,8 @@ __device__ __attribute__((noinline)) void filter_phase() {
     const int n = uniform(Q.n);
     // root candidates
     const int root = Q.root;
-    const int32_t rootq = Q.root_lo < 0 ? -1
+    // (a sparse root's are listed already: its step is one over a list)
+    const int32_t rootq = Q.root_lo < 0 || Q.root_sparse ? -1
                                         : Q.pred[root].qout | Q.pred[root].qin << 8 | (Q.homo ? 1 << 16 : 0);
     if (rootq < 0) {
         if (threadIdx.x == 0) {
@@ -3744,6 +3847,7 @@ __device__ __forceinline__ void run_query(Ctx &c) {
     __syncthreads();
     mark(c, 0);
     ev(c, SGM_EV_START);
+    if (Q.root_sparse) sparse_root();
     filter_phase();
     __syncthreads();
     mark(c, 1);
@@ -3823,6 +3927,8 @@ __device__ __forceinline__ void help_step(const NArgs &a, int e, int32_t ch) {
             ec_chunk(c, j->ecj, j, ch * K, min(n_items, ch * K + K), G, fb);
         } else if (kind == 4) {
             item_wg_k(c, BoardCtr{j}, st, s.nbl, ncount, hul[ch], nodrop ? nullptr : c.B(st.u), fb, def);
+        } else if (kind == 5) {
+            sparse_scan(c, BoardCtr{j}, st.u, root, hul, ch * K, min(n_items, ch * K + K), fb);
         } else {
             join_chunk(c, s.jl, ch, &j->jrows, &j->abort_, fb);
         }

@@ -253,3 +253,34 @@ def test_marks_kept_word_by_word_and_one_by_one(k, back):
             (rn, sn), (rw, sw) = [g.match_query(q, with_stats=True) for g in gs]
             assert len(rn) == k and np.array_equal(rn, rw) and np.array_equal(rn, og.match_query(q))
             assert sn["cand"] == sw["cand"] and sn["ec"] == sw["ec"]
+
+
+@pytest.mark.parametrize("helpers,help_items", [(64, 64), (512, 1024), (0, 0)])
+@pytest.mark.parametrize("V,every", [(1024, 8), (1024, 7), (4096, 64), (4097, 9), (9000, 300),
+                                     (70000, 8), (70000, 33), (300001, 999)])
+def test_roots_that_few_vertices_reach(V, every, helpers, help_items):
+    """Roots whose degree bounds admit few of their range (one vertex in eight
+    and fewer; just more than that; none), looked up by degrees alone: ranges
+    of one round and many, one type and any, served and not."""
+    hub = np.arange(0, V, every)
+    k = 1 + np.arange(len(hub)) % 3  # spokes beyond the four they need
+    src = np.concatenate([np.repeat(hub, 3 + k), np.arange(1, V)])
+    dst = np.concatenate([np.arange(int((3 + k).sum())) * 7 % V, np.zeros(V - 1)])
+    rel = np.concatenate([np.arange(int((3 + k).sum())) % 5, np.full(V - 1, 5)])
+    vt = (np.arange(V) % 50 == 49).astype(np.int32)
+    mg = MicroGraph(V, src, dst, rel, vt)
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rl, typ = mg.csr()
+    g = P.Graph(rp, col, rl, typ)
+    g.set_tuning(help_items=help_items, helpers=helpers)
+    star = lambda l, w: MicroQuery(w + 1, [l] + [-1] * w, [-1] * (w + 1), [0] * w,
+                                   range(1, w + 1), [0, 1, 2, 3, 4, 0, 1, 2][:w])
+    qs = [star(0, 4), star(-1, 4), star(1, 4), star(0, 5), star(-1, 8)]
+    srv = P.Server(g)
+    for i, q in enumerate(qs):
+        print("case: query", i, flush=True)
+        want = og.match_query(q)
+        assert np.array_equal(g.match_query(q), want)
+        assert np.array_equal(srv.wait(srv.submit(q), q.n)[1], want)
+    srv.close()
+    g.close()
