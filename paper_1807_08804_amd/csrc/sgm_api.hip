@@ -1937,7 +1937,7 @@ bool narrow_launch(sgm_graph *g, NarrowCtx &nw, const std::vector<QInfo> &qis, c
     }
     {
         Prof p(g, SGM_K_PERSIST, 0.0, profiled);
-        launch_narrow(st, a, grid);
+        HIPX(launch_narrow(st, a, grid));
     }
     if (job.traced)
         HIPX(hipMemcpyAsync(nw.h_trace, nw.d_trace, sizeof(int64_t) * SGM_TRACE_CAP * np,
@@ -3662,8 +3662,7 @@ int sgm_match_query_noalloc(sgm_graph *g, const sgm_query *q, uint32_t flags, in
         a.help_wait = g->tune.help_wait > 0 ? g->tune.help_wait : kHelpWaitDefault;
         const int grid = a.help_items > 0 ? std::min(kNarrowMaxSlots, std::max(1, g->tune.helpers)) : 1;
         a.ngrid = grid;
-        launch_narrow(st, a, grid);
-        HIPX(hipGetLastError());
+        HIPX(launch_narrow(st, a, grid));
         HIPX(hipMemcpyAsync(&r, base + L.res, sizeof(NResult), hipMemcpyDeviceToHost, st));
         HIPX(hipStreamSynchronize(st));
         // the kernel left the slot bitmaps zero, unless its owner gave up on

@@ -228,6 +228,8 @@ struct NArgs {
 };
 
 void launch_reset(hipStream_t s, unsigned long long *ctr);
-void launch_narrow(hipStream_t s, const NArgs &a, int grid);
+// The launch's own status: results are read from the memory that the kernel
+// writes, where an earlier launch's would still stand.
+hipError_t launch_narrow(hipStream_t s, const NArgs &a, int grid);
 
 }  // namespace sgm

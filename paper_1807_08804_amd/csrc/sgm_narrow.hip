@@ -4164,8 +4164,10 @@ __global__ void k_reset(unsigned long long *ctr) {
 
 }  // namespace
 
-void launch_narrow(hipStream_t s, const NArgs &a, int grid) {
-    hipLaunchKernelGGL(k_narrow, dim3(grid), dim3(NT), 0, s, a);
+hipError_t launch_narrow(hipStream_t s, const NArgs &a, int grid) {
+    NArgs arg = a;
+    void *args[] = {&arg};
+    return hipLaunchKernel((const void *)k_narrow, dim3(grid), dim3(NT), args, 0, s);
 }
 
 void launch_reset(hipStream_t s, unsigned long long *ctr) {

@@ -1,0 +1,104 @@
+"""A launch that the runtime refuses, on the CPU: the library over a stand-in
+for the HIP runtime (device memory is host memory, kernels do not run) whose
+launches fail on request."""
+import os
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RUNTIME = r"""
+#include <stdint.h>
+#include <stdlib.h>
+#include <string.h>
+struct dim3 { uint32_t x, y, z; };
+static int fail = 0, launches = 0;
+static thread_local int sticky = 0;
+static struct { dim3 g, b; size_t m; void *s; } cfg;
+extern "C" {
+void fake_fail(int on) { fail = on; }
+int fake_launches() { return launches; }
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, void *s) { cfg.g = g; cfg.b = b; cfg.m = m; cfg.s = s; return 0; }
+int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, void **s) { *g = cfg.g; *b = cfg.b; *m = cfg.m; *s = cfg.s; return 0; }
+int hipLaunchKernel(const void *, dim3, dim3, void **, size_t, void *) {
+    ++launches;
+    if (fail) sticky = 9;  // hipErrorInvalidConfiguration
+    return fail ? 9 : 0;
+}
+int hipGetLastError() { int e = sticky; sticky = 0; return e; }
+const char *hipGetErrorString(int) { return "refused"; }
+int hipDeviceGetAttribute(int *v, int, int) { *v = 100000; return 0; }
+int hipDeviceSynchronize() { return 0; }
+int hipSetDevice(int) { return 0; }
+int hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
+int hipFree(void *p) { free(p); return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+int hipHostFree(void *p) { free(p); return 0; }
+int hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return 0; }
+int hipGetSymbolAddress(void **p, const void *) { static void *a = calloc(1, 64 << 20); *p = a; return 0; }
+int hipMemcpy(void *d, const void *s, size_t n, int) { memcpy(d, s, n); return 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) { memcpy(d, s, n); return 0; }
+int hipMemsetAsync(void *d, int v, size_t n, void *) { if (v) memset(d, v, n); return 0; }
+int hipStreamCreateWithFlags(void **s, unsigned) { *s = malloc(1); return 0; }
+int hipStreamDestroy(void *s) { free(s); return 0; }
+int hipStreamSynchronize(void *) { return 0; }
+int hipStreamWaitEvent(void *, void *, unsigned) { return 0; }
+int hipEventCreate(void **e) { *e = malloc(1); return 0; }
+int hipEventCreateWithFlags(void **e, unsigned) { return hipEventCreate(e); }
+int hipEventDestroy(void *e) { free(e); return 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipEventSynchronize(void *) { return 0; }
+int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1; return 0; }
+}
+"""
+
+SCRIPT = r"""
+import ctypes, sys
+rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import numpy as np
+import paper_1807_08804_amd as P
+from tests.micro import MicroQuery
+
+a = np.arange(20, dtype=np.int32)
+g = P.Graph(np.arange(21, dtype=np.int32), (a + 1) % 20, a * 0, a * 0)
+q = MicroQuery(2, [-1, 0], [-1, -1], [0], [1], [0])
+assert rt.fake_launches() == 0
+
+
+def status(f):
+    try:
+        f()
+        return P.SGM_OK
+    except P.SGMError as e:
+        return e.code
+
+
+calls = [lambda: g.match_query(q), lambda: g.match_batch([q, q]),
+         lambda: g.match_query_noalloc(q, 16)]
+# kernels that do not run leave zeroed results: no rows
+assert [status(f) for f in calls] == [P.SGM_OK] * 3 and rt.fake_launches() >= 3
+rt.fake_fail(1)
+print("refused:", [status(f) for f in calls])
+assert [status(f) for f in calls] == [P.SGM_EDEVICE] * 3
+srv = P.Server(g)
+assert srv.wait(srv.submit(q), q.n)[0] == P.SGM_EDEVICE
+rt.fake_fail(0)
+assert srv.wait(srv.submit(q), q.n)[0] == P.SGM_OK
+srv.close()
+print("again:", [status(f) for f in calls])
+assert [status(f) for f in calls] == [P.SGM_OK] * 3
+g.close()
+print("ok")
+"""
+
+
+def test_a_refused_launch_is_an_error(tmp_path):
+    """Results are read from the memory that the kernel writes: a launch that
+    the runtime refuses ends the call with a device error (a batch, a served
+    query and one without allocation too), and the next call is answered."""
+    src, lib = tmp_path / "fakehip.cpp", tmp_path / "libfakehip.so"
+    src.write_text(RUNTIME)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    out = subprocess.run([sys.executable, "-c", SCRIPT, str(lib)], cwd=ROOT, capture_output=True,
+                         text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout + out.stderr
