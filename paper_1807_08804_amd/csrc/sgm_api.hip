@@ -1646,7 +1646,7 @@ T *host_ptr(T *h) {
     return (T *)d;
 }
 
-void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
+void narrow_grow(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     if (nw.lcap == 0) {
         nw.lcap = std::min<int32_t>(g->V, nw.lcap_want ? nw.lcap_want : kNarrowListCap);
         nw.slab_bytes = nw.slab_want ? nw.slab_want : narrow_slab_bytes(g, nw.serve);
@@ -1720,6 +1720,17 @@ int32_t root_passing(const sgm_graph *g, int32_t label, int32_t qout, int32_t qi
         c = &g->root_tab[(size_t)g->root_tab_of[label] * 256];
     }
     return c[std::min(qout, 15) * 16 + std::min(qin, 15)];
+}
+
+// A context that could not be built whole is given up: the next call starts
+// from nothing, not from the buffers that were left out.
+void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
+    try {
+        narrow_grow(g, nw, slots, nq);
+    } catch (...) {
+        narrow_free(nw);
+        throw;
+    }
 }
 
 // Pack one validated query and its plan; false if it exceeds the packed

@@ -1,6 +1,6 @@
-"""A launch that the runtime refuses, on the CPU: the library over a stand-in
-for the HIP runtime (device memory is host memory, kernels do not run) whose
-launches fail on request."""
+"""Launches and allocations that the runtime refuses, on the CPU: the library
+over a stand-in for the HIP runtime (device memory is host memory, kernels do
+not run) in which they fail on request."""
 import os
 import subprocess
 import sys
@@ -13,10 +13,12 @@ RUNTIME = r"""
 #include <string.h>
 struct dim3 { uint32_t x, y, z; };
 static int fail = 0, launches = 0;
+static size_t most = ~(size_t)0;
 static thread_local int sticky = 0;
 static struct { dim3 g, b; size_t m; void *s; } cfg;
 extern "C" {
 void fake_fail(int on) { fail = on; }
+void fake_most(size_t bytes) { most = bytes; }
 int fake_launches() { return launches; }
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, void *s) { cfg.g = g; cfg.b = b; cfg.m = m; cfg.s = s; return 0; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, void **s) { *g = cfg.g; *b = cfg.b; *m = cfg.m; *s = cfg.s; return 0; }
@@ -30,7 +32,7 @@ const char *hipGetErrorString(int) { return "refused"; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 100000; return 0; }
 int hipDeviceSynchronize() { return 0; }
 int hipSetDevice(int) { return 0; }
-int hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
+int hipMalloc(void **p, size_t n) { *p = n > most ? 0 : calloc(1, n ? n : 1); return *p ? 0 : 2; }
 int hipFree(void *p) { free(p); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
 int hipHostFree(void *p) { free(p); return 0; }
@@ -52,7 +54,7 @@ int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1; return 0; }
 }
 """
 
-SCRIPT = r"""
+SETUP = r"""
 import ctypes, sys
 rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 import numpy as np
@@ -73,6 +75,9 @@ def status(f):
         return e.code
 
 
+"""
+
+LAUNCHES = SETUP + r"""
 calls = [lambda: g.match_query(q), lambda: g.match_batch([q, q]),
          lambda: g.match_query_noalloc(q, 16)]
 # kernels that do not run leave zeroed results: no rows
@@ -92,13 +97,38 @@ print("ok")
 """
 
 
+ALLOCATIONS = SETUP + r"""
+for most in (1 << 29, 1 << 19, 4000):  # the output arena, slot memory, small buffers
+    rt.fake_most(ctypes.c_size_t(most))
+    for calls in range(3):
+        assert status(lambda: g.match_query(q)) == P.SGM_EDEVICE
+        assert status(lambda: g.match_batch([q, q])) == P.SGM_EDEVICE
+    rt.fake_most(ctypes.c_size_t(1 << 62))
+    assert status(lambda: g.match_query(q)) == P.SGM_OK
+    g.close()
+    g = P.Graph(np.arange(21, dtype=np.int32), (a + 1) % 20, a * 0, a * 0)
+g.close()
+print("ok")
+"""
+
+
+def run(tmp_path, script):
+    src, lib = tmp_path / "fakehip.cpp", tmp_path / "libfakehip.so"
+    src.write_text(RUNTIME)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
+    out = subprocess.run([sys.executable, "-c", script, str(lib)], cwd=ROOT, capture_output=True,
+                         text=True, timeout=120)
+    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout + out.stderr
+
+
+def test_a_refused_allocation_stays_an_error(tmp_path):
+    """A context whose buffers could not all be had is not used: every call
+    reports it, until there is memory again."""
+    run(tmp_path, ALLOCATIONS)
+
+
 def test_a_refused_launch_is_an_error(tmp_path):
     """Results are read from the memory that the kernel writes: a launch that
     the runtime refuses ends the call with a device error (a batch, a served
     query and one without allocation too), and the next call is answered."""
-    src, lib = tmp_path / "fakehip.cpp", tmp_path / "libfakehip.so"
-    src.write_text(RUNTIME)
-    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(src), "-o", str(lib)], check=True)
-    out = subprocess.run([sys.executable, "-c", SCRIPT, str(lib)], cwd=ROOT, capture_output=True,
-                         text=True, timeout=120)
-    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout + out.stderr
+    run(tmp_path, LAUNCHES)
