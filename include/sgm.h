@@ -332,12 +332,12 @@ int sgm_get_tuning(const sgm_graph *g, sgm_tuning *t);
  * server of the graph runs or another match call is in flight. */
 int sgm_set_tuning(sgm_graph *g, const sgm_tuning *t);
 /*
- * Autotuner: runs the n sample queries as persistent-kernel batches (count
- * only, reps times each) under every tuning of a small grid (slots 256/512,
+ * Autotuner: runs the n sample queries as persistent-kernel batches (whole
+ * tables, joined, ordered and written on the device but not copied to the
+ * host; reps times each) under every tuning of a small grid (slots 256/512,
  * group_lanes 16/64, wg_rows 2048/8192/32768, join_policy 0/1, help_items
- * 0/1024; helpers as set), keeps the
- * one with the lowest median batch time, sets it on the graph and returns it
- * in *best (may be NULL). Every tuning must give the same per-query row
+ * 0/1024; helpers as set), keeps the one with the lowest median batch time,
+ * sets it on the graph and returns it in *best (may be NULL). Every tuning must give the same per-query row
  * counts; otherwise the previous tuning is restored and SGM_EDEVICE
  * returned. Same threading rule as sgm_set_tuning.
  */

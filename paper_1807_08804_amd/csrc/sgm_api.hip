@@ -1733,6 +1733,10 @@ void narrow_reserve(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     }
 }
 
+// With SGM_COUNT_ONLY, inside the library: the kernel joins, orders and writes
+// the rows all the same, and only their copy to the host is left out.
+constexpr uint32_t kDeviceRows = 1u << 31;
+
 // Pack one validated query and its plan; false if it exceeds the packed
 // descriptor's capacity (the query then runs on the multi-kernel path).
 bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, int32_t lcap,
@@ -1774,7 +1778,7 @@ bool pack_query(sgm_graph *g, const QInfo &qi, const Plan &pl, uint32_t flags, i
     nq->proj = qi.proj;
     nq->homo = g->homomorphic ? 1 : 0;
     // a projection's count needs its distinct rows
-    nq->count_only = (flags & SGM_COUNT_ONLY) && !qi.proj;
+    nq->count_only = (flags & SGM_COUNT_ONLY) && !(flags & kDeviceRows) && !qi.proj;
     int k = 0;
     auto put = [&](const PStep &s) {
         NStep &t = nq->steps[k++];
@@ -2845,7 +2849,7 @@ int sgm_autotune(sgm_graph *g, const sgm_query *qs, int32_t n, int32_t reps, sgm
                 for (sgm_result &x : store) x = sgm_result{};
                 std::vector<int> wide;
                 const int64_t t0 = now_ns();
-                narrow_batch(g, qis, valid, SGM_COUNT_ONLY, res, wide);
+                narrow_batch(g, qis, valid, SGM_COUNT_ONLY | kDeviceRows, res, wide);
                 const double el = (double)(now_ns() - t0);
                 if (r > 0) ts.push_back(el);
                 std::vector<int64_t> rows((size_t)n, -1);
