@@ -389,7 +389,7 @@ def bench_large(args, P, kggen):
     # per-phase algorithmic bytes and device time of the persistent kernel
     # (filter = root candidates, explore and refine; collect = candidate
     # edges; join; finish = ordering and output), summed over the batch
-    _, bstats = g.match_batch(queries, count_only=True, with_stats=True)
+    _, bstats = g.match_batch(queries, with_stats=True)
     phases = phase_rates(bstats, P, resident=min(tuned["slots"], len(queries)))
 
     gp.match_batch(queries)
