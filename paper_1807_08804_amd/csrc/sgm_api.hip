@@ -2464,8 +2464,8 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             vi[v] = make_int2(type[v], std::min(od, 255) | std::min(id, 255) << 8);
         }
         g->d_vinfo = dev_upload(vi);
-        count_root_degrees(g, vi);
-        {
+        if (!g->opts.out_only) {  // (the persistent kernel's alone)
+            count_root_degrees(g, vi);
             std::vector<int4> vr((size_t)n_vertices);
             for (int32_t v = 0; v < n_vertices; ++v)
                 vr[v] = make_int4(off[v], off[v + 1], in_off[v], in_off[v + 1]);

@@ -13,13 +13,14 @@ RUNTIME = r"""
 #include <string.h>
 struct dim3 { uint32_t x, y, z; };
 static int fail = 0, launches = 0;
-static size_t most = ~(size_t)0;
+static size_t most = ~(size_t)0, bytes = 0;
 static thread_local int sticky = 0;
 static struct { dim3 g, b; size_t m; void *s; } cfg;
 extern "C" {
 void fake_fail(int on) { fail = on; }
 void fake_most(size_t bytes) { most = bytes; }
 int fake_launches() { return launches; }
+size_t fake_bytes() { return bytes; }
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, void *s) { cfg.g = g; cfg.b = b; cfg.m = m; cfg.s = s; return 0; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, void **s) { *g = cfg.g; *b = cfg.b; *m = cfg.m; *s = cfg.s; return 0; }
 int hipLaunchKernel(const void *, dim3, dim3, void **, size_t, void *) {
@@ -32,7 +33,7 @@ const char *hipGetErrorString(int) { return "refused"; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 100000; return 0; }
 int hipDeviceSynchronize() { return 0; }
 int hipSetDevice(int) { return 0; }
-int hipMalloc(void **p, size_t n) { *p = n > most ? 0 : calloc(1, n ? n : 1); return *p ? 0 : 2; }
+int hipMalloc(void **p, size_t n) { bytes += n; *p = n > most ? 0 : calloc(1, n ? n : 1); return *p ? 0 : 2; }
 int hipFree(void *p) { free(p); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
 int hipHostFree(void *p) { free(p); return 0; }
@@ -110,6 +111,26 @@ for most in (1 << 29, 1 << 19, 4000):  # the output arena, slot memory, small bu
 g.close()
 print("ok")
 """
+
+
+MEMORY = SETUP + r"""
+rt.fake_bytes.restype = ctypes.c_size_t
+V = 100000
+at, size = np.zeros(V + 1, np.int32), {}
+for out_only in (0, 1):
+    b = rt.fake_bytes()
+    P.Graph(at, a[:0], a[:0], np.zeros(V, np.int32), out_only=out_only).close()
+    size[out_only] = rt.fake_bytes() - b
+print(size)
+assert size[1] + 36 * V <= size[0]
+print("ok")
+"""
+
+
+def test_outgoing_graph_alone_holds_its_own_arrays(tmp_path):
+    """The row extents and type order that the persistent kernel reads (36
+    bytes a vertex and more) are not kept for a graph that never runs it."""
+    run(tmp_path, MEMORY)
 
 
 def run(tmp_path, script):
