@@ -880,10 +880,13 @@ __device__ __forceinline__ int lanes_for(int32_t n, int gmax) {
 // one. pre: where each segment starts; adr: what turns a position into an
 // index of the adjacency array.
 // Longer rows go to a wider tier: many candidates share a wave's scan, and
-// its few long rows would hold the others back while other waves idle (dense
-// graph, 59 queries: 16.8 ms a call at 512, 14.7 at 96); a wave with one
+// its few long rows would hold the others back while other waves idle (rows
+// of about 300, 28 queries one at a time: 3.4 ms at 512, 2.7 at 256). A tier
+// more costs 10 us a step, so it begins where the rows pay for it: 300,000
+// vertices with rows of 20 to 200, 28 queries one at a time 2.64 ms at 96,
+// 2.36 at 256; a dense graph's 59 queries 8.9 ms at either. A wave with one
 // candidate takes more.
-constexpr int kFlatRow = 96;
+constexpr int kFlatRow = 256;
 constexpr int kFlatRowOne = 512;
 struct FlatLds {
     int32_t pre[64], adr[64];

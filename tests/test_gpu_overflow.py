@@ -55,7 +55,9 @@ def test_root_survivors_past_the_list(overflow, help_items):
     for r, w in zip(g.match_batch(big + small), want):
         assert np.array_equal(r, w)
     # the fixed area's one slot: refused past its list, whole again after
-    if keep + 40 > LCAP:
+    # (how many of the long rows are listed until a later tier drops them
+    # depends on the tiers, so a root of just a list's length may do either)
+    if keep > LCAP:
         with pytest.raises(P.SGMError):
             g.match_query_noalloc(big[0], 1 << 17)
     for q, w in zip(small, want[2:]):

@@ -284,3 +284,27 @@ def test_roots_that_few_vertices_reach(V, every, helpers, help_items):
         assert np.array_equal(srv.wait(srv.submit(q), q.n)[1], want)
     srv.close()
     g.close()
+
+
+@pytest.mark.parametrize("row", [95, 96, 97, 255, 256, 257, 511, 512, 513])
+@pytest.mark.parametrize("cands", [6, 40, 700])
+def test_rows_at_the_flat_window(cands, row):
+    """Candidates whose rows are just as long as a wave's flat scan takes, one
+    less and one more, alone in their wave and with others; shared or not."""
+    T = 3000
+    rng = np.random.default_rng(row + cands)
+    dst = cands + np.concatenate([rng.permutation(T)[:row] for _ in range(cands)])
+    src = np.repeat(np.arange(cands), row)
+    mg = MicroGraph(cands + T, src, dst, rng.integers(0, 40, len(src)),
+                    np.concatenate([np.zeros(cands), 1 + rng.integers(0, 30, T)]))
+    og = oracle.Graph(mg.V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    qs = [MicroQuery(3, [0, 1, 2], [-1, -1, -1], [0, 0], [1, 2], [3, -1]),
+          MicroQuery(3, [1, 0, 0], [-1, -1, -1], [1, 2], [0, 0], [5, 7])]
+    g = P.Graph(rp, col, rel, typ)
+    for tune in (dict(help_items=64), dict(help_items=0)):
+        g.set_tuning(**tune)
+        for i, q in enumerate(qs):
+            print("case: query", i, tune, flush=True)
+            assert np.array_equal(g.match_query(q), og.match_query(q))
+    g.close()
