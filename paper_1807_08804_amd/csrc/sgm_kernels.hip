@@ -194,7 +194,9 @@ __global__ __launch_bounds__(kBlock) void k_filter_small(FilterArgs a) {
 
 // Rounds of the workgroups that take a long row whole: 1024 threads, eight
 // entries each in flight (a row of 340,000 entries: 42 rounds and their
-// barriers instead of 1,300 of one entry for each of 256 threads).
+// barriers instead of 1,300 of one entry for each of 256 threads). Places count
+// from the row's start: the last round's, past the row's end, could not be
+// told from the array's first ones where 2^31 edges end.
 constexpr int kBigBlock = 1024;
 constexpr int kBigItems = 8;
 
@@ -210,16 +212,16 @@ __global__ __launch_bounds__(kBigBlock) void k_filter_big(FilterArgs a) {
         bool alive = true;
         for (int j = 0; j < a.n_nbr && alive; ++j) {
             const NbrDesc d = a.nbr[j];
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
-            const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            const int32_t i0 = beg + threadIdx.x;
-            bool found = __syncthreads_or(i0 < end && nbr_ok(g, d, adj[i0]));
-            for (int32_t base = beg + kBigBlock; base < end && !found; base += kBigBlock * kBigItems) {
+            const int2 *row = (d.dir ? g.in_adj : g.out_adj) + (d.dir ? ib : ob);
+            const int32_t len = d.dir ? ie - ib : oe - ob;
+            const int32_t i0 = threadIdx.x;
+            bool found = __syncthreads_or(i0 < len && nbr_ok(g, d, row[i0]));
+            for (int32_t base = kBigBlock; base < len && !found; base += kBigBlock * kBigItems) {
                 bool hit = false;
 #pragma unroll
                 for (int q = 0; q < kBigItems; ++q) {
                     const int32_t i = base + q * kBigBlock + (int32_t)threadIdx.x;
-                    if (i < end) hit |= nbr_ok(g, d, adj[i]);
+                    if (i < len) hit |= nbr_ok(g, d, row[i]);
                 }
                 found = __syncthreads_or(hit);
             }
@@ -236,18 +238,18 @@ __global__ __launch_bounds__(kBigBlock) void k_filter_big(FilterArgs a) {
         for (int j = 0; j < a.n_nbr; ++j) {
             const NbrDesc d = a.nbr[j];
             if (!d.push) continue;
-            const int2 *adj = d.dir ? g.in_adj : g.out_adj;
-            const int32_t beg = d.dir ? ib : ob, end = d.dir ? ie : oe;
-            for (int32_t base = beg; base < end; base += kBigBlock * kBigItems) {
+            const int2 *row = (d.dir ? g.in_adj : g.out_adj) + (d.dir ? ib : ob);
+            const int32_t len = d.dir ? ie - ib : oe - ob;
+            for (int32_t base = 0; base < len; base += kBigBlock * kBigItems) {
                 int2 e[kBigItems];
 #pragma unroll
                 for (int q = 0; q < kBigItems; ++q) {
                     const int32_t i = base + q * kBigBlock + (int32_t)threadIdx.x;
-                    e[q] = adj[i < end ? i : beg];
+                    e[q] = row[i < len ? i : 0];
                 }
 #pragma unroll
                 for (int q = 0; q < kBigItems; ++q)
-                    if (base + q * kBigBlock + (int32_t)threadIdx.x < end && nbr_ok(g, d, e[q]))
+                    if (base + q * kBigBlock + (int32_t)threadIdx.x < len && nbr_ok(g, d, e[q]))
                         bit_set_atomic(d.push_bits, e[q].x);
             }
         }
@@ -330,10 +332,11 @@ __global__ __launch_bounds__(kBigBlock) void k_ec_big(DevGraph g, ECDesc d) {
     for (int32_t bi = blockIdx.x; bi < n; bi += gridDim.x) {
         const int32_t it = d.big_items[bi];
         const int32_t key = d.keys[it];
-        const int32_t beg = off[key], end = off[key + 1];
+        const int2 *row = adj + off[key];
+        const int32_t len = off[key + 1] - off[key];
         int32_t c = WRITE ? d.offs[it] : 0;
         int par = 0;  // the counts alternate: one barrier per round
-        for (int32_t base = beg; base < end; base += kBigBlock * kBigItems, par ^= 1) {
+        for (int32_t base = 0; base < len; base += kBigBlock * kBigItems, par ^= 1) {
             uint64_t b[kBigItems];
             int32_t x[kBigItems];
             int32_t mine = 0;
@@ -341,8 +344,8 @@ __global__ __launch_bounds__(kBigBlock) void k_ec_big(DevGraph g, ECDesc d) {
 #pragma unroll
             for (int q = 0; q < kBigItems; ++q) {
                 const int32_t i = at + q * 64;
-                const bool hit = i < end && ec_hit(g, d, adj, beg, i, key);
-                x[q] = WRITE && hit ? adj[i].x : 0;
+                const bool hit = i < len && ec_hit(g, d, row, 0, i, key);
+                x[q] = WRITE && hit ? row[i].x : 0;
                 b[q] = __ballot(hit);
                 mine += __popcll(b[q]);
             }
