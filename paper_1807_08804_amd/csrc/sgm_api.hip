@@ -1689,18 +1689,31 @@ void narrow_grow(sgm_graph *g, NarrowCtx &nw, int slots, int nq) {
     }
 }
 
-// Fills g->root_tab from the vertices' types and clamped degrees (vinfo).
-void count_root_degrees(sgm_graph *g, const std::vector<int2> &vi) {
+// Fills g->root_tab from the vertices' degrees in type order (DevGraph::tdeg).
+void count_root_degrees(sgm_graph *g, const std::vector<uint16_t> &td) {
     g->root_tab_of.assign((size_t)g->n_types, -1);
     int32_t n = 0;
     for (int32_t t = 0; t < g->n_types; ++t)
         if (g->type_freq[t] >= kRootTab) g->root_tab_of[t] = n++;
     g->root_tab.assign((size_t)(n + 1) * 256, 0);
-    for (const int2 &v : vi) {
-        const int32_t at = std::min(v.y & 255, 15) * 16 + std::min(v.y >> 8, 15);
-        if (g->root_tab_of[v.x] >= 0) ++g->root_tab[(size_t)g->root_tab_of[v.x] * 256 + at];
-        ++g->root_tab[(size_t)n * 256 + at];
-    }
+    parallel_for(g->V, 1 << 16, [&](int lo, int hi) {
+        int32_t all[256] = {};
+        const auto first = std::upper_bound(g->type_off.begin(), g->type_off.end(), lo) - 1;
+        for (int32_t t = (int32_t)(first - g->type_off.begin()); lo < hi; ++t) {
+            int32_t h[256] = {};
+            const int32_t end = std::min(hi, g->type_off[t + 1]);
+            int32_t *const c = g->root_tab_of[t] < 0 ? all : h;
+            for (; lo < end; ++lo) ++c[std::min(td[lo] & 255, 15) * 16 + std::min(td[lo] >> 8, 15)];
+            for (int k = 0; c == h && k < 256; ++k)
+                if (h[k]) {
+                    __atomic_fetch_add(&g->root_tab[(size_t)g->root_tab_of[t] * 256 + k], h[k],
+                                       __ATOMIC_RELAXED);
+                    all[k] += h[k];
+                }
+        }
+        for (int k = 0; k < 256; ++k)
+            if (all[k]) __atomic_fetch_add(&g->root_tab[(size_t)n * 256 + k], all[k], __ATOMIC_RELAXED);
+    });
     for (int32_t i = 0; i <= n; ++i) {
         int32_t *c = &g->root_tab[(size_t)i * 256];
         for (int a = 15; a >= 0; --a)
@@ -2465,7 +2478,6 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
         }
         g->d_vinfo = dev_upload(vi);
         if (!g->opts.out_only) {  // (the persistent kernel's alone)
-            count_root_degrees(g, vi);
             std::vector<int4> vr((size_t)n_vertices);
             for (int32_t v = 0; v < n_vertices; ++v)
                 vr[v] = make_int4(off[v], off[v + 1], in_off[v], in_off[v + 1]);
@@ -2487,6 +2499,7 @@ static int load_graph_impl(int32_t n_vertices, int32_t n_edges, const int32_t *r
             g->d_tverts = dev_upload(tv);
             g->d_trow = dev_upload(tr);
             g->d_tdeg = dev_upload(td);
+            count_root_degrees(g, td);
         }
         if (g->n_types <= kHubTypesMax) {
             HubIndex hx;
