@@ -274,7 +274,7 @@ const char *sgm_last_error(void);
 #define SGM_EV_EXPLORE 3   /* one kernel_explore step along the spanning tree */
 #define SGM_EV_REFINE 4    /* one refinement step */
 #define SGM_EV_LISTS 5     /* candidate lists sorted */
-#define SGM_EV_EDGES 6     /* one candidate-edge table built */
+#define SGM_EV_EDGES 6     /* a candidate-edge table built, or those of few keys together */
 #define SGM_EV_ORDER 7     /* join order chosen */
 #define SGM_EV_LEVEL 8     /* one join level written */
 #define SGM_EV_SORT 9      /* final rows ordered */
@@ -290,7 +290,9 @@ int sgm_trace_events(sgm_graph *g, int32_t i, int64_t *out, int32_t cap, double 
  * help_wait 0.
  *   slots        workgroups of one persistent launch that take queries
  *                (1..512; two per CU fit)
- *   group_lanes  most lanes working on one candidate's rows (1, 2, 4, ..., 64)
+ *   group_lanes  most lanes working on one key's row of a candidate-edge table
+ *                (1, 2, 4, ..., 64; filter steps deal rows to lanes end to
+ *                end and take no share of it)
  *   wg_rows      rows longer than this are scanned by the whole workgroup
  *                (>= 64; shorter long rows get one wave)
  *   join_policy  0: bind the vertex of the cheapest candidate-edge table

@@ -17,9 +17,6 @@ constexpr int kBlock = 256;
 constexpr int kBigDegree = 256;
 constexpr int kMaxNbr = SGM_MAX_QE;
 
-// Read-only view of the device-resident data graph. Each adjacency entry is
-// {neighbour id, relation}; out-rows are sorted by (dst, rel), in-rows by
-// (src, rel), exact duplicate triples removed.
 // a or b by value: a conditional on the members themselves picks an address,
 // and a copy of the struct then has to live in scratch memory. (In a function
 // that is not inlined the generated choice between the two scratch addresses
@@ -29,6 +26,10 @@ __host__ __device__ inline T pick(int second, T a, T b) {
     return second ? b : a;
 }
 
+// Read-only view of the device-resident data graph. Each adjacency entry is
+// {neighbour id, relation and, with typed_adj, the neighbour's type above it
+// (see rel_mask)}; out-rows are sorted by (dst, rel), in-rows by
+// (src, rel), exact duplicate triples removed.
 struct DevGraph {
     int32_t V;
     int32_t nwords;  // ceil(V / 64): words of one candidate bitmap

@@ -209,7 +209,7 @@ struct NArgs {
     int64_t *trace;           // [nq][SGM_TRACE_CAP] step events, or null
     // work-division and schedule knobs (sgm_tuning); results do not depend
     // on them
-    int32_t group_lanes;      // most lanes per candidate group (power of two, 1..64)
+    int32_t group_lanes;      // most lanes per key of an edge table (power of two, 1..64)
     int32_t wg_rows;          // rows longer than this get the whole workgroup
     int32_t join_policy;      // 0: cheapest edge first; 1: most-constrained vertex first
     // shared filter steps: workgroups [0, nslot) own slots and take queries;

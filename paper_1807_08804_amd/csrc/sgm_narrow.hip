@@ -133,9 +133,12 @@ static_assert(8 * 256 * sizeof(int32_t) <= kStageOff, "radix counts");
 // The workgroup's LDS, at file scope: a query's phases and the shared tiers
 // are functions that are not inlined, each with registers of its own, and
 // reach it as LDS too; they rebuild their context from the launch's arguments
-// kept here. In one body the small steps paid for the large tiers' spills: an
-// explore step of one candidate took 9 us, now 6 (a pinned 12-vertex chain
-// 162 -> 126 us), and the kernel's code is a seventh of the former 750 KB.
+// kept here. In one body, 750 KB of code, the small steps paid for the large
+// tiers' spills; the split leaves a seventh of the code and shortens the
+// large steps (six cyclic queries on 4M vertices 96 -> 73 ms, with the shared
+// giant rows and reverse tests by marks that it made room for; queries of a
+// few candidates within 2 %). A call into a large tier saves registers to
+// scratch memory, most of what a launch of small queries writes.
 __shared__ Smem g_s;
 __shared__ NArgs g_args;
 __shared__ __align__(16) unsigned char g_dyn[kDynLds];
@@ -158,7 +161,7 @@ struct Ctx {
     int32_t *lists;     // slot lists [SGM_MAX_QV * lcap]
     char *slab;
     int64_t *trace;     // this query's step events, or null
-    int32_t gmax;       // most lanes per candidate group
+    int32_t gmax;       // most lanes per key of an edge table
     int32_t wg_rows;    // rows longer than this get the whole workgroup
     int32_t join_policy;
     int32_t *marks;     // pushes into the scratch bitmap, while filtering (slab)
@@ -866,8 +869,8 @@ __device__ __forceinline__ int32_t max_row(const DevGraph &g, const NTest *nb, i
     return m;
 }
 
-// lanes per candidate for n items: the whole workgroup for a handful,
-// otherwise a power of two in [1, 64] so that all lanes hold an item
+// lanes per key of an edge table for n keys: a power of two in [1, gmax], the
+// most that leaves no lane without a key
 __device__ __forceinline__ int lanes_for(int32_t n, int gmax) {
     int G = gmax;
     while (G > 1 && (int64_t)G * n > NT) G >>= 1;
@@ -1401,7 +1404,7 @@ __device__ __forceinline__ void ec_chunk(Ctx &c, const EcJob &E, HelpJob *j, int
 // A filter step shared with the launch's idle workgroups through this
 // slot's board entry: the counters move to the entry, the work is cut into
 // nch chunks that the owner and its helpers claim (kind 0: K candidates of
-// u's list, G lanes each; kind 1: one row segment each), and the owner waits
+// u's list; kind 1: one row segment each; see HelpJob), and the owner waits
 // for the chunks its helpers claimed before taking the counters back.
 template <class W>
 __device__ __forceinline__ void shared_run(Ctx &c, int kind, const NStep &st, const NTest *nb,
