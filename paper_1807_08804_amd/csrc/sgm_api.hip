@@ -3305,13 +3305,20 @@ void serve_rerun(sgm_server *S) {
         }
         {
             std::lock_guard<std::mutex> gl(g->mu);
+            // the queries that were not left for the multi-kernel path
+            auto failed = [&](int32_t code) {
+                for (size_t i = 0; i < take.size(); ++i)
+                    if (std::find(wide.begin(), wide.end(), (int)i) == wide.end()) res[i]->status = code;
+            };
             try {
                 narrow_retry_large(g, qis, flags, res, wide);
             } catch (const DeviceError &e) {
                 (void)hipStreamSynchronize(g->stream);
                 (void)hipGetLastError();
                 g->pending.clear();
+                failed(e.code);
             } catch (const std::bad_alloc &) {
+                failed(SGM_ENOMEM);
             }
             for (int i : wide) {
                 const int32_t why = res[i]->stats.fallback;

@@ -113,6 +113,30 @@ print("ok")
 """
 
 
+RERUNS = SETUP + r"""
+# a root of more vertices than a regular list: served by the rerun thread
+V = 70000
+b = np.arange(V, dtype=np.int32)
+g = P.Graph(np.arange(V + 1, dtype=np.int32), (b + 1) % V, b * 0, b * 0)
+srv = P.Server(g)
+q = MicroQuery(2, [-1, -1], [-1, -1], [0], [1], [0])
+assert srv.wait(srv.submit(q), q.n)[0] == P.SGM_OK
+rt.fake_fail(1)
+assert srv.wait(srv.submit(q), q.n)[0] == P.SGM_EDEVICE
+rt.fake_fail(0)
+assert srv.wait(srv.submit(q), q.n)[0] == P.SGM_OK
+srv.close()
+g.close()
+print("ok")
+"""
+
+
+def test_a_refused_rerun_is_an_error(tmp_path):
+    """A served query whose rerun in a larger slot fails is reported, not
+    answered with no rows."""
+    run(tmp_path, RERUNS)
+
+
 MEMORY = SETUP + r"""
 rt.fake_bytes.restype = ctypes.c_size_t
 V = 100000
