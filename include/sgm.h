@@ -143,7 +143,9 @@ typedef struct {
                                       times are ns_filter .. ns_finish) */
     int32_t path;                  /* SGM_PATH_WIDE or SGM_PATH_NARROW: where it ran */
     int32_t fallback;              /* why a query outgrew a regular persistent-kernel
-                                      slot: 1 candidate list capacity, 2 slot
+                                      slot: 1 candidate list capacity (without
+                                      helpers also a root with more candidates
+                                      than that, before it ran), 2 slot
                                       memory, 4 ordering key > 64 bits, 8 output
                                       arena full, 16 plan descriptor size, 32 a
                                       shared filter step not finished by its
