@@ -308,3 +308,31 @@ def test_rows_at_the_flat_window(cands, row):
             print("case: query", i, tune, flush=True)
             assert np.array_equal(g.match_query(q), og.match_query(q))
     g.close()
+
+
+def test_sparse_roots_of_a_compressed_graph():
+    """Roots that few vertices reach, by a compressed graph's degree bounds
+    instead of its row lengths."""
+    V = 6000
+    rng = np.random.default_rng(17)
+    hub = rng.permutation(V)[:60]
+    src = np.concatenate([rng.integers(0, V, V), np.repeat(hub, 7)])
+    dst = np.concatenate([rng.integers(0, V, V), rng.integers(0, V, 60 * 7)])
+    mg = MicroGraph(V, src, dst, rng.integers(0, 4, len(src)), rng.integers(0, 2, V))
+    og = oracle.Graph(V, mg.src, mg.dst, mg.rel, mg.vtype)
+    rp, col, rel, typ = mg.csr()
+    g = P.Graph(rp, col, rel, typ)
+    cg = P.CompressedGraph(g, P.Compressed(rp, col, rel, typ))
+    rows = 0
+    for w in (4, 5):
+        for label in (-1, 0, 1):
+            q = MicroQuery(w + 1, [label] + [-1] * w, [-1] * (w + 1), [0] * w, range(1, w + 1),
+                           [0, 1, 2, 3, -1][:w])
+            print("case: star of", w, "label", label, flush=True)
+            want = og.match_query(q)
+            rows += len(want)
+            assert np.array_equal(g.match_query(q), want)
+            assert np.array_equal(cg.match_query(q), want)
+    assert rows > 0
+    cg.close()
+    g.close()
